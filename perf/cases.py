@@ -390,3 +390,135 @@ def run(s):
         return layer.Y
     layer.backward(g, s.X, s.dY)
     return [layer.Y, *layer.gradients()]
+
+
+# ---- the same path in 64 bits, in plain torch ----------------------------------------------------------
+SLOPE = 0.2                           # LeakyReLU of the attention logits (the plan's default)
+
+
+def _entries64(case, seed):
+    """(row, col) of A + I in row order, from the same draws as the inputs' graph."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(int(seed))
+    n = case["n"]
+    rowptr, col = _pattern(case, gen, directed=case["kind"] in ("sage", "gat", "gat2", "setup"))
+    row = torch.repeat_interleave(torch.arange(n, device="cuda"), (rowptr[1:] - rowptr[:-1]).long())
+    loops = torch.arange(n, device="cuda")             # the pattern has no diagonal
+    key = torch.cat([row * n + col.long(), loops * (n + 1)]).sort().values
+    row = torch.div(key, n, rounding_mode="floor")
+    return row, key - row * n
+
+
+def _propagate64(to, frm, val, X, n):
+    """out[to] += val * X[frm], in pieces that fit beside the operands; val [q] or [q, heads], X [n, ...]."""
+    out = torch.zeros((n,) + X.shape[1:], dtype=torch.float64, device="cuda")
+    piece = max(1 << 16, (1 << 28) // X[0].numel())
+    for lo in range(0, to.numel(), piece):
+        hi = min(lo + piece, to.numel())
+        v = val[lo:hi]
+        out.index_add_(0, to[lo:hi], X[frm[lo:hi]] * v.reshape(v.shape + (1,) * (X.dim() - v.dim())))
+    return out
+
+
+def _gat64(layer, row, col, n, X):
+    """Forward of one attention layer; returns what backward needs."""
+    h, k = layer.a[0].shape
+    M = (X @ layer.W.double()).view(n, h, k)
+    a_src, a_dst = (t.double() for t in layer.a)
+    y = (M * a_src).sum(2)[row] + (M * a_dst).sum(2)[col]
+    w = torch.where(y > 0, y, SLOPE * y)
+    top = torch.full((n, h), -math.inf, dtype=torch.float64, device="cuda").index_reduce_(0, row, w, "amax")
+    alpha = torch.exp(w - top[row])
+    alpha = alpha / torch.zeros(n, h, dtype=torch.float64, device="cuda").index_add_(0, row, alpha)[row]
+    Y = _propagate64(row, col, alpha, M, n).reshape(n, h * k)
+    return M, y, alpha, Y + layer.b.double() if layer.b is not None else Y
+
+
+def _gat64_backward(layer, row, col, n, X, saved, G):
+    M, y, alpha = saved
+    h, k = layer.a[0].shape
+    a_src, a_dst = (t.double() for t in layer.a)
+    Gh = G.view(n, h, k)
+    ga = torch.empty_like(alpha)
+    piece = max(1 << 16, (1 << 28) // (h * k))
+    for lo in range(0, row.numel(), piece):
+        ga[lo:lo + piece] = (Gh[row[lo:lo + piece]] * M[col[lo:lo + piece]]).sum(2)
+    zero = lambda: torch.zeros(n, h, dtype=torch.float64, device="cuda")  # noqa: E731
+    gy = alpha * (ga - zero().index_add_(0, row, alpha * ga)[row]) * torch.where(y > 0, 1.0, SLOPE)
+    ds, dd = zero().index_add_(0, row, gy), zero().index_add_(0, col, gy)
+    dM = _propagate64(col, row, alpha, Gh, n) + ds[:, :, None] * a_src + dd[:, :, None] * a_dst
+    out = [X.t() @ dM.view(n, h * k), (ds[:, :, None] * M).sum(0), (dd[:, :, None] * M).sum(0)]
+    return out + ([G.sum(0)] if layer.b is not None else []), dM.view(n, h * k) @ layer.W.double().t()
+
+
+def _elu(Z):
+    return torch.where(Z > 0, Z, torch.expm1(Z))
+
+
+def exact(case, seed):
+    """What `run` returns, in 64 bits; None in the place of whole numbers."""
+    kind, n = case["kind"], case["n"]
+    row, col = _entries64(case, seed)
+    deg = torch.bincount(row, minlength=n).double()
+    sym = 1.0 / torch.sqrt(deg[row] * deg[col])
+    if kind == "setup":
+        order = torch.sort(col, stable=True).indices
+        return [None, None, None, sym, None, None, None, None, sym[order], None]
+    s = prepare(case, seed)
+    X = s.X.double()
+    if kind == "spmm":
+        return _propagate64(row, col, sym, X, n)
+    if kind == "gcn2":
+        W1, W2 = (l.W.double() for l in s.layers)
+        P = _propagate64(row, col, sym, X, n)
+        H = torch.relu(P @ W1)
+        Z = _propagate64(row, col, sym, H @ W2, n)
+        at = torch.arange(n, device="cuda"), s.labels.long()
+        loss = (torch.logsumexp(Z, 1) - Z[at]).sum().reshape(1)
+        dZ = torch.softmax(Z, 1)
+        dZ[at] -= 1.0
+        D = _propagate64(row, col, sym, dZ, n)         # the operator is symmetric
+        dH = D @ W2.t()
+        return [loss, Z, H.t() @ D, dH, P.t() @ (dH * (H > 0))]
+    if kind == "gat2":
+        first, second = s.layers
+        *saved1, Z1 = _gat64(first, row, col, n, X)
+        H = _elu(Z1)
+        *saved2, Z = _gat64(second, row, col, n, H)
+        dZ = Z - s.target.double()
+        g2, dH = _gat64_backward(second, row, col, n, H, saved2, dZ)
+        g1, _ = _gat64_backward(first, row, col, n, X, saved1, dH * torch.where(H > 0, 1.0, H + 1.0))
+        return [0.5 * (dZ * dZ).sum().reshape(1), Z, *g2, dH, *g1]
+    layer = s.layers[0]
+    if kind == "gat":
+        *saved, Z = _gat64(layer, row, col, n, X)
+        Y = _elu(Z) if case["elu"] else Z
+        if not s.step:
+            return Y
+        G = s.dY.double()
+        if case["elu"]:
+            G = G * torch.where(Y > 0, 1.0, Y + 1.0)
+        grads, dX = _gat64_backward(layer, row, col, n, X, saved, G)
+        return [Y, *grads, dX]
+    val = sym if kind == "gcn" else 1.0 / deg[row]
+    W = layer.W.double()
+    Wn = W if kind == "gcn" else layer.W2.double()     # the weight behind the operator
+    P = _propagate64(row, col, val, X, n)
+    Y = P @ Wn
+    if kind == "sage":
+        Y += X @ W
+    if layer.b is not None:
+        Y += layer.b.double()
+    if case["relu"]:
+        Y = torch.relu(Y)
+    if not s.step:
+        return Y
+    G = s.dY.double()
+    if case["relu"]:
+        G = G * (Y > 0)
+    dX = _propagate64(col, row, val, G @ Wn.t(), n)
+    grads = [P.t() @ G]
+    if kind == "sage":
+        grads.insert(0, X.t() @ G)
+        dX += G @ W.t()
+    return [Y, *grads, *([G.sum(0)] if layer.b is not None else []), dX]
