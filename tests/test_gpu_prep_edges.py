@@ -1,0 +1,56 @@
+"""Preprocessing at the edges of its tiles (4096 entries; 8192 in the sort) and digits, bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2308_12093_amd import binding as B
+from paper_2308_12093_amd import graphs as G
+from tests._util import assert_close, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+def pattern(n, nnz, hub, seed):
+    """Sorted rows without duplicates: `hub` of the entries in row n // 2, the others spread; empty rows at both ends."""
+    rng = np.random.default_rng(seed)
+    keys = set((n // 2) * n + rng.choice(n, min(hub, n), replace=False).astype(np.int64))
+    lo, hi = (n // 4, n - n // 4) if n > 8 else (0, n)
+    while len(keys) < nnz:
+        r, c = rng.integers(lo, hi, nnz), rng.integers(0, n, nnz)
+        for k in r * n + c:
+            keys.add(int(k))
+            if len(keys) == nnz:
+                break
+    keys = np.sort(np.fromiter(keys, np.int64, len(keys)))
+    rowptr = np.zeros(n + 1, np.int32)
+    np.cumsum(np.bincount(keys // n, minlength=n), out=rowptr[1:])
+    return rowptr, (keys % n).astype(np.int32)
+
+
+@pytest.mark.parametrize("n,nnz,hub", [
+    (1, 1, 0), (2, 1, 0), (257, 4095, 257), (300, 4096, 0), (300, 4097, 0), (256, 8192, 256), (70000, 8191, 8000),
+    (20000, 8193, 8193), (65536, 40960, 20000), (65537, 3, 0), (128, 4096, 0), (300, 12288, 0),
+])
+def test_tile_and_digit_edges(n, nnz, hub):
+    rowptr, col = pattern(n, nnz, hub, seed=n + nnz)
+    rp_o, c_o, deg_o = oracle.add_self_loops_degree(rowptr, col)
+    rp, c, deg = G.add_self_loops(n, dev(rowptr), dev(col))
+    for got, ref in ((rp, rp_o), (c, c_o), (deg, deg_o)):
+        np.testing.assert_array_equal(host(got), ref)
+    val = torch.empty(c.numel(), device="cuda")
+    B.gnn_gcn_normalize(n, rp, c, deg, val)
+    assert_close(host(val), oracle.gcn_normalize(rp_o, c_o, deg_o), "val", tol=1e-6)
+    for ptr, idx in ((rowptr, col), (rp_o, c_o)):          # with empty rows, and with none
+        np.testing.assert_array_equal(host(G.expand(n, dev(ptr), idx.size)), np.repeat(np.arange(n), np.diff(ptr)))
+        for got, ref in zip(G.transpose(n, dev(ptr), dev(idx)), oracle.csr_transpose(ptr, idx)):
+            np.testing.assert_array_equal(host(got), ref)
+
+
+@pytest.mark.parametrize("count", [1, 4095, 4096, 4097, 1 << 20, (1 << 20) + 1])
+def test_scan_tiles(count):
+    """Row pointers after the insertion of the diagonal into an empty pattern: the scan of `count` ones and a zero."""
+    rp, c, deg = G.add_self_loops(count, dev(np.zeros(count + 1, np.int32)), dev(np.zeros(0, np.int32)))
+    np.testing.assert_array_equal(host(rp), np.arange(count + 1))
+    np.testing.assert_array_equal(host(c), np.arange(count))
+    assert int(deg.min()) == int(deg.max()) == 1
