@@ -424,8 +424,8 @@ size_t gnn_gat_aggregate_workspace_bytes(int32_t nnz, int32_t heads, int32_t f);
  *   relu is a flag word: GNN_GEMM_RELU (1) applies max(., 0); GNN_GEMM_ACCUMULATE (4) adds the
  *   product (and bias) to what C holds before the ReLU, trans_a == 0 only (GNN_ERR_UNSUPPORTED
  *   otherwise); any other bit is GNN_ERR_INVALID_ARG.
- *   workspace: gnn_gemm_workspace_bytes(trans_a, trans_b, M, N, K); required for (0,0) (holds B^T)
- *   and (1,0) (holds the partial products); (0,1) needs none.
+ *   workspace: gnn_gemm_workspace_bytes(trans_a, trans_b, M, N, K); required for (0,0) (holds B in the
+ *   form the product reads) and (1,0) (holds the partial products); (0,1) runs without, faster with.
  */
 enum { GNN_GEMM_RELU = 1, GNN_GEMM_ACCUMULATE = 4 };
 gnn_status_t gnn_gemm(int32_t trans_a, int32_t trans_b, int64_t M, int64_t N, int64_t K,

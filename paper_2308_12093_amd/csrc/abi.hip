@@ -363,10 +363,11 @@ gnn_status_t gnn_gemm(int32_t trans_a, int32_t trans_b, int64_t M, int64_t N, in
     if (relu & ~(GNN_GEMM_RELU | GNN_GEMM_ACCUMULATE)) return GNN_ERR_INVALID_ARG;
     if (trans_a && (relu & GNN_GEMM_ACCUMULATE)) return GNN_ERR_UNSUPPORTED;
     const size_t need = gnn_gemm_workspace_bytes(trans_a, trans_b, M, N, K);
-    if (trans_a || !trans_b) {                          // only the A B^T form needs no scratch
+    if (trans_a || !trans_b) {                          // the A B^T form takes scratch if it is given enough
         if (!workspace || bad_align(workspace)) return GNN_ERR_INVALID_ARG;
         if (workspace_bytes < need) return GNN_ERR_BUFFER_TOO_SMALL;
     }
+    if (!trans_a && (bad_align(workspace) || workspace_bytes < need)) workspace = nullptr;
     return gemm_launch(trans_a ? 1 : 0, trans_b ? 1 : 0, M, N, K, A, B, C, bias, relu, workspace,
                        as_stream(hip_stream));
 }

@@ -14,10 +14,12 @@ constexpr size_t kAlign = 256;       // alignment of every carved workspace / ca
 
 // activation codes of the fused epilogues (the `relu` argument of the launchers: 0, 1 = the public values)
 constexpr int kActNone = 0, kActRelu = 1, kActElu = 2;
-// fp32 GEMM only, or-ed into its `relu` argument: add the product to what C already holds (before the activation)
+// plain products only, or-ed into its `relu` argument: add the product to what C already holds (before the activation)
 constexpr int kActAccumulate = 4;
 // set by the GEMM launcher itself for outputs beyond kStreamBytes: non-temporal stores
 constexpr int kActStream = 8;
+// plain products: an activation or a LeakyReLU further down decides on the sign of the result
+constexpr int kActSigns = 16;
 constexpr size_t kStreamBytes = (size_t)64 << 20;
 
 static inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a; }
@@ -73,11 +75,18 @@ size_t gemm_workspace_bytes(int ta, int tb, int64_t M, int64_t N, int64_t K);
 // b_mask_act (kActRelu, kActElu) taken from its output b_mask, an array of B's shape.
 // ldc (plain products only): rows of C are ldc >= N floats apart, the columns in between written as zeros.
 // A2, B2 (plain products only; shapes of A and B): C = op(A) op(B) + op(A2) op(B2) in one pass, one rounding
-// chain; the untransposed-B form then needs a workspace of 2 x gemm_workspace_bytes.
+// chain; needs a workspace of 2 x gemm_workspace_bytes.
+// workspace: gemm_workspace_bytes; the A B^T form also runs without one (NULL).
 gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B,
                          float *C, const float *bias, int relu, void *workspace, hipStream_t st,
                          const float *b_mask = nullptr, int b_mask_act = 0, int64_t ldc = 0,
                          const float *A2 = nullptr, const float *B2 = nullptr);
+
+// the plain products (gemm_split.hip): see there
+size_t gemm_split_workspace_bytes(int64_t N, int64_t K);
+gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B, float *C,
+                               int64_t ldc, const float *bias, int act, void *workspace, hipStream_t st,
+                               const float *A2, const float *B2);
 
 // ---- element-wise and reductions (elementwise.hip) ---------------------------------
 // out = G * [Y > 0]

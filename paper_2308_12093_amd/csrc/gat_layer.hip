@@ -42,7 +42,7 @@ gnn_status_t gat_forward(Plan &p, const gnn_graph_t &g, const float *X, const fl
     const Buffers B = pick_buffers(L, cache, workspace);
 
     // M = X Theta; s, d per node and head (App. B)
-    GNN_TRY(gemm_launch(0, 0, n, f, m, X, W, B.M, nullptr, 0, at<char>(workspace, L.w_gemm_nn), st));
+    GNN_TRY(gemm_launch(0, 0, n, f, m, X, W, B.M, nullptr, kActSigns, at<char>(workspace, L.w_gemm_nn), st));
     GNN_TRY(gat_node_attention_launch(n, h, k, B.M, a_src, a_dst, B.s, B.d, st));
     const float *bias = d.has_bias ? b : nullptr;
     const int act = d.fuse_elu ? kActElu : kActNone;
@@ -77,7 +77,7 @@ gnn_status_t gat_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
 
     // rebuild what the variant did not keep
     if (variant == GNN_CACHE_NONE)
-        GNN_TRY(gemm_launch(0, 0, n, f, m, X, W, B.M, nullptr, 0, at<char>(workspace, L.w_gemm_nn), st));
+        GNN_TRY(gemm_launch(0, 0, n, f, m, X, W, B.M, nullptr, kActSigns, at<char>(workspace, L.w_gemm_nn), st));
     if (variant == GNN_CACHE_NONE || variant == GNN_CACHE_GAT_FEAT)
         GNN_TRY(gat_node_attention_launch(n, h, k, B.M, a_src, a_dst, B.s, B.d, st));
     const bool fused = gat_fused_shape(n, q, h, k) && aligned16(dY_in) && aligned16(a_src) && aligned16(a_dst);
@@ -123,7 +123,7 @@ gnn_status_t gat_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
     GNN_TRY(gat_attention_grad2_launch(n, h, k, ds, dd, B.M, da_src, da_dst, at<char>(workspace, L.w_red), st));
     // dTheta = X^T dM, dX = dM Theta^T
     GNN_TRY(gemm_launch(1, 0, m, f, n, X, dM, dW, nullptr, 0, at<char>(workspace, L.w_gemm_tn), st));
-    if (d.need_input_grad) GNN_TRY(gemm_launch(0, 1, n, m, f, dM, W, dX, nullptr, 0, nullptr, st));
+    if (d.need_input_grad) GNN_TRY(gemm_launch(0, 1, n, m, f, dM, W, dX, nullptr, 0, at<char>(workspace, L.w_gemm_tn), st));
     return GNN_OK;
 }
 

@@ -47,7 +47,7 @@ gnn_status_t gcn_forward(Plan &p, const gnn_graph_t &g, const float *X, const fl
         // a width that the SpMM runs on a padded operand: the GEMM writes T in that layout, where the SpMM looks for it
         int ldt = k;
         if (float *Tp = spmm_padded_operand(sp, g.csr_erow, n, d.nnz, k, &ldt)) T = Tp;
-        GNN_TRY(gemm_launch(0, 0, n, k, m, X, W, T, nullptr, 0, wt, st, nullptr, 0, ldt));
+        GNN_TRY(gemm_launch(0, 0, n, k, m, X, W, T, nullptr, d.fuse_relu ? kActSigns : 0, wt, st, nullptr, 0, ldt));
         GNN_TRY(spmm(g, forward_view(g, k), T, k, Y, bias, d.fuse_relu, sp, st));
     } else {
         // P = A' X (kept in the cache slot when the plan caches it), then Y = P W (+ b, ReLU)
@@ -87,7 +87,7 @@ gnn_status_t gcn_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
         void *red = ws.take<char>(colsum_workspace_bytes(n, k));
         GNN_TRY(colsum_launch(n, k, G, db, red, st, mask_y, kActRelu));
     }
-    void *gemm_ws = ws.take<char>(gemm_workspace_bytes(1, 0, m, k, n));
+    void *gemm_ws = ws.take<char>(backward_gemm_bytes(n, m, k, dx, 1));   // one product at a time
 
     if (p.info.bwd == GNN_BWD_FUSED_PROPAGATE) {
         // H = A'^T G once; dW = X^T H; dX = H W^T
@@ -95,7 +95,7 @@ gnn_status_t gcn_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
         void *sp = ws.take<char>(spmm_workspace_bytes(n, d.nnz, k));
         GNN_TRY(spmm(g, transposed_view(g, k), G, k, H, nullptr, 0, sp, st));
         GNN_TRY(gemm_launch(1, 0, m, k, n, X, H, dW, nullptr, 0, gemm_ws, st));
-        if (dx) GNN_TRY(gemm_launch(0, 1, n, m, k, H, W, dX, nullptr, 0, nullptr, st));
+        if (dx) GNN_TRY(gemm_launch(0, 1, n, m, k, H, W, dX, nullptr, 0, gemm_ws, st));
     } else {
         // dW = (A'X)^T G with A'X from the cache or recomputed; dX = A'^T (G W^T)
         const bool cached = p.info.cache == GNN_CACHE_AX;
@@ -112,7 +112,7 @@ gnn_status_t gcn_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
             const SparseView tv = transposed_view(g, m);
             int ldu = m;                                    // as in the forward pass: U written where the SpMM pads
             if (float *Up = spmm_padded_operand(sp, tv.eidx, n, d.nnz, m, &ldu)) U = Up;
-            GNN_TRY(gemm_launch(0, 1, n, m, k, G, W, U, nullptr, 0, nullptr, st, nullptr, 0, ldu));
+            GNN_TRY(gemm_launch(0, 1, n, m, k, G, W, U, nullptr, 0, gemm_ws, st, nullptr, 0, ldu));
             GNN_TRY(spmm(g, tv, U, m, dX, nullptr, 0, sp, st));
         }
     }
@@ -134,7 +134,7 @@ gnn_status_t sage_forward(Plan &p, const gnn_graph_t &g, const float *X, const f
         void *wt = ws.take<char>(2 * gemm_workspace_bytes(0, 0, n, k, m));
         int ldt = k;
         if (float *Tp = spmm_padded_operand(sp, g.csr_erow, n, d.nnz, k, &ldt)) T = Tp;
-        GNN_TRY(gemm_launch(0, 0, n, k, m, X, Wn, T, nullptr, 0, wt, st, nullptr, 0, ldt));
+        GNN_TRY(gemm_launch(0, 0, n, k, m, X, Wn, T, nullptr, d.fuse_relu ? kActSigns : 0, wt, st, nullptr, 0, ldt));
         GNN_TRY(spmm(g, forward_view(g, k), T, k, Y, nullptr, 0, sp, st));
         GNN_TRY(gemm_launch(0, 0, n, k, m, X, Ws, Y, bias, last, wt, st));
     } else {
@@ -172,7 +172,7 @@ gnn_status_t sage_backward(Plan &p, const gnn_graph_t &g, const float *X, const 
         void *red = ws.take<char>(colsum_workspace_bytes(n, k));
         GNN_TRY(colsum_launch(n, k, G, db, red, st, mask_y, kActRelu));
     }
-    void *gemm_ws = ws.take<char>(gemm_workspace_bytes(1, 0, m, k, n));
+    void *gemm_ws = ws.take<char>(backward_gemm_bytes(n, m, k, dx, 2));
     GNN_TRY(gemm_launch(1, 0, m, k, n, X, G, dWs, nullptr, 0, gemm_ws, st, mask_y, kActRelu));     // dWs = X^T G
 
     if (p.info.bwd == GNN_BWD_FUSED_PROPAGATE) {
@@ -182,7 +182,7 @@ gnn_status_t sage_backward(Plan &p, const gnn_graph_t &g, const float *X, const 
         GNN_TRY(spmm(g, transposed_view(g, k), G, k, H, nullptr, 0, sp, st));
         GNN_TRY(gemm_launch(1, 0, m, k, n, X, H, dWn, nullptr, 0, gemm_ws, st));
         if (dx) {
-            GNN_TRY(gemm_launch(0, 1, n, m, k, G, Ws, dX, nullptr, 0, nullptr, st, nullptr, 0, 0, H, Wn));
+            GNN_TRY(gemm_launch(0, 1, n, m, k, G, Ws, dX, nullptr, 0, gemm_ws, st, nullptr, 0, 0, H, Wn));
         }
     } else {
         // dWn = (A'X)^T G with A'X from the cache or recomputed; dX = A'^T (G Wn^T) + G Ws^T
@@ -200,9 +200,9 @@ gnn_status_t sage_backward(Plan &p, const gnn_graph_t &g, const float *X, const 
             const SparseView tv = transposed_view(g, m);
             int ldu = m;
             if (float *Up = spmm_padded_operand(sp, tv.eidx, n, d.nnz, m, &ldu)) U = Up;
-            GNN_TRY(gemm_launch(0, 1, n, m, k, G, Wn, U, nullptr, 0, nullptr, st, nullptr, 0, ldu));
+            GNN_TRY(gemm_launch(0, 1, n, m, k, G, Wn, U, nullptr, 0, gemm_ws, st, nullptr, 0, ldu));
             GNN_TRY(spmm(g, tv, U, m, dX, nullptr, 0, sp, st));
-            GNN_TRY(gemm_launch(0, 1, n, m, k, G, Ws, dX, nullptr, kActAccumulate, nullptr, st));
+            GNN_TRY(gemm_launch(0, 1, n, m, k, G, Ws, dX, nullptr, kActAccumulate, gemm_ws, st));
         }
     }
     return GNN_OK;

@@ -1,5 +1,5 @@
 // Dense products of the GCN / GAT layers on the gfx950 matrix cores:
-//   X Theta,  G Theta^T   rows = nodes, a few hundred columns at most   (fp32 MFMA)
+//   X Theta,  G Theta^T   rows = nodes, a few hundred columns at most   (fp32 MFMA here; bf16 MFMA in gemm_split.hip)
 //   X^T H                 a small output reduced over all nodes          (fp64 MFMA)
 //
 // One block = 256 threads = 4 wavefronts arranged WM x WN; each wavefront owns
@@ -27,6 +27,7 @@ namespace {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));   // a native vector: loads and stores stay typed
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));   // ... at a 4-byte aligned address
 
 constexpr int kGemmGeneral = 0, kGemmInterior = 1, kGemmEdge = 2;
 
@@ -519,6 +520,73 @@ gemm_f32_kernel(int M, int N, int K, const float *__restrict__ A, const float *_
     }
 }
 
+// The same product for few rows, bit for bit: one wavefront per 32 x 32 tile, operands straight from memory into
+// registers in the order the instruction takes them (the lower lane half k = 0..15 of a step of 32, the upper 16..31),
+// three steps ahead.  Latency bound: the 256 instructions of a 512-long reduction take 7 us by themselves.  No LDS, no
+// transposed copy of B.  2048 x 512 by 512 x 16 took 20.4 us through the kernel above (16 blocks, one barrier per
+// step, and the copy), 16.3 now; 3001 x 203 by 203 x 7 24.4 and 9.8.
+__global__ void __launch_bounds__(64)
+gemm_few_kernel(int M, int N, int K, const float *__restrict__ A, const float *__restrict__ B,
+                const float *__restrict__ A2, const float *__restrict__ B2, long sk, long sn, float *__restrict__ C,
+                int ldc, const float *__restrict__ bias, int relu, int tiles_n) {
+    constexpr int AHEAD = 3;
+    const int lane = threadIdx.x, l32 = lane % 32, half = lane / 32;
+    const int m0 = (int)(blockIdx.x / tiles_n) * 32, n = (int)(blockIdx.x % tiles_n) * 32 + l32;
+    const int kt1 = (K + BK - 1) / BK, total = A2 ? 2 * kt1 : kt1;
+    const size_t ro = (size_t)min(m0 + l32, M - 1) * K;    // rows and columns past the end re-read the last one
+    const long co = min(n, N - 1) * sn;
+    float x[AHEAD][16], y[AHEAD][16];
+    auto load = [&](int step, float (&xs)[16], float (&ys)[16]) __attribute__((always_inline)) {
+        const bool second = step >= kt1;
+        const float *a = (second ? A2 : A) + ro, *b = (second ? B2 : B) + co;
+        const int k0 = (second ? step - kt1 : step) * BK + 16 * half;
+        if (k0 + 16 <= K) {                                // 16 consecutive floats at a 4-byte aligned address
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const floatx4u v = *reinterpret_cast<const floatx4u *>(a + k0 + 4 * i);
+                xs[4 * i] = v.x; xs[4 * i + 1] = v.y; xs[4 * i + 2] = v.z; xs[4 * i + 3] = v.w;
+            }
+#pragma unroll
+            for (int j = 0; j < 16; ++j) ys[j] = b[(k0 + j) * sk];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                xs[j] = k0 + j < K ? a[k0 + j] : 0.f;
+                ys[j] = k0 + j < K ? b[(k0 + j) * sk] : 0.f;
+            }
+        }
+    };
+    floatx16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+        if (u < total) load(u, x[u], y[u]);
+    for (int step = 0; step < total; step += AHEAD) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            if (step + u < total) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u][j], y[u][j], acc, 0, 0, 0);
+                if (step + u + AHEAD < total) load(step + u + AHEAD, x[u], y[u]);
+            }
+        }
+    }
+    const float bj = bias && n < N ? bias[n] : 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int m = m0 + 8 * (v / 4) + 4 * half + v % 4;
+        if (m < M && n < N) {
+            float o = acc[v] + bj;
+            if (relu & kActAccumulate) o += C[(size_t)m * ldc + n];
+            if (relu & kActRelu) o = fmaxf(o, 0.f);
+            C[(size_t)m * ldc + n] = o;
+        } else if (m < M && n < ldc) {
+            C[(size_t)m * ldc + n] = 0.f;                  // padding columns of a wider row stride
+        }
+    }
+}
+
 // out[c][r] = in[r][c] for a small weight matrix (rows x cols), through a 32 x 33 LDS tile.
 __global__ void __launch_bounds__(256)
 transpose_kernel(int rows, int cols, const float *__restrict__ in, float *__restrict__ out) {
@@ -599,10 +667,20 @@ int pick_splits(int ta, int64_t M, int64_t N, int64_t K) {
     return (int)s;
 }
 
+// One wavefront per 32 x 32 tile while two per SIMD hold them all; beyond, the kernels that share operands through LDS.
+// Both sides of the line (fp32 kernel / one wavefront per tile): 4096 x 256 x 256, 1024 tiles, 26.9 / 14.3 us;
+// 32768 x 64 x 64, 2048, 13.9 / 9.4; 50021 x 96 x 64, 3128, 17.8 / 18.6; 16384 x 256 x 256, 4096, 31.0 / 47.5.
+bool few_rows(int64_t M, int64_t N) { return ceil_div(M, 32) * ceil_div(N, 32) <= 2048; }
+
 }  // namespace
 
 size_t gemm_workspace_bytes(int ta, int tb, int64_t M, int64_t N, int64_t K) {
-    if (!ta) return tb ? kAlign : align_up((size_t)(N > 0 ? N : 1) * (K > 0 ? K : 1) * sizeof(float));   // B^T
+    if (!ta) {                                             // B^T for the one kernel, the parts of B for the other
+        if (M <= 0 || N <= 0 || K <= 0 || few_rows(M, N)) return kAlign;
+        const size_t parts = gemm_split_workspace_bytes(N, K);
+        const size_t bt = tb ? kAlign : align_up((size_t)N * K * sizeof(float));
+        return parts > bt ? parts : bt;
+    }
     return align_up((size_t)pick_splits(ta, M, N, K) * M * N * sizeof(double));
 }
 
@@ -665,6 +743,19 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
         // the kernel wants B with the reduction index contiguous: B[N][K]; transpose a [K][N] weight first
         const float *Bt = B, *Bt2 = B2;
         if (K <= 0) A2 = Bt2 = nullptr;                    // an empty reduction: nothing to add
+        const bool signs = (relu & (kActRelu | kActSigns)) != 0;
+        relu &= kActRelu | kActAccumulate;
+        if (few_rows(M, N)) {
+            const long tn = ceil_div(N, 32), total = ceil_div(M, 32) * tn;
+            hipLaunchKernelGGL(gemm_few_kernel, dim3((unsigned)total), dim3(64), 0, st, (int)M, (int)N, (int)K, A, B, A2,
+                               Bt2, tb ? 1L : (long)N, tb ? (long)K : 1L, C, (int)ldc, bias, relu, (int)tn);
+            return launch_status();
+        }
+        const bool stream = (size_t)M * N * sizeof(float) > kStreamBytes && !(relu & kActAccumulate);
+        // A product whose result decides signs (an activation in its own epilogue, or kActSigns) keeps the sums of
+        // the fp32 instruction: a pre-activation within rounding of zero changes a gradient entry by its full size.
+        if (!signs && workspace && K >= 4)
+            return gemm_split_launch(tb, M, N, K, A, B, C, ldc, bias, stream ? relu | kActStream : relu, workspace, st, A2, B2);
         if (!tb && K > 0) {
             float *wt = static_cast<float *>(workspace);
             hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)ceil_div(N, 32), (unsigned)ceil_div(K, 32)), dim3(256),
@@ -681,8 +772,7 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
         }
         const int vec_a = aligned16(A) && (!A2 || aligned16(A2)) && K % 4 == 0;
         const int vec_b = aligned16(Bt) && (!Bt2 || aligned16(Bt2)) && K % 4 == 0;
-        relu &= kActRelu | kActAccumulate;
-        if ((size_t)M * N * sizeof(float) > kStreamBytes && !(relu & kActAccumulate)) relu |= kActStream;
+        if (stream) relu |= kActStream;
         // persistent blocks: 64 per XCD (2 per CU), each owning a contiguous range of tiles
         const long total = (long)tiles_m * tiles_n;
         if (total > INT32_MAX / 4 || total * ceil_div(K > 0 ? K : 1, 32) > INT32_MAX / 4) return GNN_ERR_UNSUPPORTED;

@@ -1,0 +1,396 @@
+// C = A op(B) (+ A2 op(B2)) (+ what C holds) + bias, ReLU, for rows = nodes and a few hundred columns, with fp32
+// operands, sums and results, on the bf16 matrix instruction.
+//
+// A float is the exact sum of three bf16 numbers (8 + 8 + 8 bits: round, subtract, round, subtract), and a product of
+// two bf16 numbers is exact in float.  Six of the nine products of the parts are formed, the three below 2^-26 of the
+// whole (a1 b2, a2 b1, a2 b2) are not, and everything is added in float by v_mfma_f32_32x32x16_bf16, six instructions
+// for 16 reduction indices where v_mfma_f32_32x32x2_f32 takes eight of four times the cost per index: the matrix cores
+// offer 2.5 PFLOP/s / 6 = 420 against 157 TFLOP/s.  The five small products of a step are summed from zero and join the
+// sum at its end, so the sum is rounded three times per 32 indices instead of 16 times.  Relative 2-norm error of the
+// products of a layer against 64 bits, fp32 instruction and parts: 2.0e-7 and
+// 0.7e-7 (K = 128), 2.9e-7 and 1.0e-7 (256), 4.1e-7 and 1.4e-7 (512); of positive operands 1.7e-7 and 0.7e-7 (128).
+//
+// What the parts cannot hold is recomputed: a wavefront whose result is not finite (operands that are, or that the
+// rounding to bf16 or a partial sum carries over the edge) or whose operands are so small that their third part falls
+// below the bf16 range (a row of A or a column of B that is nowhere above 2^-100 and not zero) forms its tile again
+// with the fp32 instruction.
+#include "common.h"
+
+namespace gnn {
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes at a 4-byte aligned address
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+
+constexpr int KB = 32;                 // reduction indices of a step: lane half h takes 16 h .. 16 h + 15
+constexpr float kTiny = 0x1p-100f;
+constexpr int kFragBytes = 64 * 16;    // eight bf16 per lane: one operand of one instruction
+constexpr int kStepBytes = 2 * 3 * kFragBytes;   // [instruction][part] for 32 columns and KB indices
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2){a, b}, bf16x2));
+}
+__device__ __forceinline__ float low(unsigned u) { return __uint_as_float(u << 16); }
+__device__ __forceinline__ float high(unsigned u) { return __uint_as_float(u & 0xffff0000u); }
+
+// three parts of eight floats; `top` collects the largest magnitude
+__device__ __forceinline__ void split8(const floatx4 &x, const floatx4 &y, bf16x8 (&part)[3], float &top) {
+    uintx4 u[3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = i < 2 ? x[2 * i] : y[2 * i - 4], b = i < 2 ? x[2 * i + 1] : y[2 * i - 3];
+        top = fmaxf(top, fmaxf(fabsf(a), fabsf(b)));
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const unsigned h = pack_bf16(a, b);
+            u[p][i] = h;
+            if (p < 2) { a -= low(h); b -= high(h); }
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p) part[p] = __builtin_bit_cast(bf16x8, u[p]);
+}
+
+// the kept products, smallest first; the last, of the leading parts, goes to the sum itself
+constexpr int kProducts = 6;
+__device__ constexpr int kPartA[kProducts] = {1, 0, 2, 1, 0, 0}, kPartB[kProducts] = {1, 2, 0, 0, 1, 0};
+
+__device__ __forceinline__ bool tiny(float top) { return top > 0.f && top < kTiny; }
+
+// columns of B as the kernels read it: element (k, n) at k * sk + n * sn
+struct Operand {
+    const float *p;
+    long sk, sn;
+};
+
+// ---- parts of B, in the order in which the product kernel's lanes take them ----------------------------
+// out: [32-column tile][KB step][instruction][part][lane][8]; lane (half, l): column 32 tile + l, indices
+// KB step + 16 half + 8 instruction + 0..7; zeros past N and K.  tiny_out[tile]: some column of the tile is tiny.
+// One block per tile, 1024 threads: eight steps at a time.
+__global__ void __launch_bounds__(1024)
+split_weights_kernel(int N, int K, int steps, Operand b0, Operand b1, char *__restrict__ out0, char *__restrict__ out1,
+                     int32_t *__restrict__ tiny0, int32_t *__restrict__ tiny1) {
+    __shared__ unsigned top[32];
+    const Operand b = blockIdx.y ? b1 : b0;
+    char *out = (blockIdx.y ? out1 : out0) + (size_t)blockIdx.x * steps * kStepBytes;
+    const int lane = threadIdx.x % 64, ins = (threadIdx.x / 64) % 2, sub = threadIdx.x / 128;
+    const int l = lane % 32, half = lane / 32;
+    const int n = blockIdx.x * 32 + l;
+    if (threadIdx.x < 32) top[threadIdx.x] = 0;
+    __syncthreads();
+    float t = 0.f;
+    for (int s = sub; s < steps; s += 8) {
+        const int k0 = s * KB + 16 * half + 8 * ins;
+        floatx4 x[2];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j / 4][j % 4] = n < N && k0 + j < K ? b.p[(k0 + j) * b.sk + n * b.sn] : 0.f;
+        bf16x8 part[3];
+        split8(x[0], x[1], part, t);
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            *reinterpret_cast<bf16x8 *>(out + (size_t)s * kStepBytes + (ins * 3 + p) * kFragBytes + lane * 16) = part[p];
+    }
+    atomicMax(&top[l], __float_as_uint(t));                 // magnitudes order like their bits
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const bool any = __any(threadIdx.x < 32 && tiny(__uint_as_float(top[threadIdx.x % 32])));
+        if (threadIdx.x == 0) (blockIdx.y ? tiny1 : tiny0)[blockIdx.x] = any;
+    }
+}
+
+struct Product {
+    int M, N, K, steps;                // steps: KB steps of one operand pair
+    const float *A, *A2;               // A2: NULL without a second pair
+    Operand B, B2;
+    const char *parts, *parts2;
+    const int32_t *tiny, *tiny2;
+    float *C;
+    int ldc;
+    const float *bias;
+    int act;
+    int tiles_m, tiles_n;
+};
+
+// logical tile of a block: each XCD (ids are dealt round-robin to eight) takes a contiguous range, the column tiles of
+// the same rows side by side, so that they share an L2
+__device__ __forceinline__ long xcd_tile(long total) {
+    const long per = (total + 7) / 8;
+    const long id = (long)(blockIdx.x % 8) * per + blockIdx.x / 8;
+    return blockIdx.x / 8 < per ? id : total;
+}
+
+// a lane's 4 of the 16 indices of its half: A[row][k .. k + 3], zeros past K
+__device__ __forceinline__ floatx4 load_row4(const float *row, int k, int K) {
+    if (k + 4 <= K) return *reinterpret_cast<const float4u *>(row + k);
+    floatx4 v = {0.f, 0.f, 0.f, 0.f};
+    if (k < K) v.x = row[k];
+    if (k + 1 < K) v.y = row[k + 1];
+    if (k + 2 < K) v.z = row[k + 2];
+    return v;
+}
+
+__device__ __forceinline__ void put(const Product &g, float *at, float o, float bias) {
+    o += bias;
+    if (g.act & kActAccumulate) o += *at;
+    if (g.act & kActRelu) o = fmaxf(o, 0.f);
+    if (g.act & kActStream) __builtin_nontemporal_store(o, at);
+    else *at = o;
+}
+
+// ---- the product ------------------------------------------------------------------------------------------
+// A block of four wavefronts owns 4 x 32 RT rows and 32 NT columns.  A lane reads its 16 consecutive floats of a row
+// straight into registers (the two lane halves take a row's whole 128-byte line, in one go, one step ahead) and splits
+// them there: a row is split once per column tile and never passes through LDS.  The parts of B, split beforehand, are
+// shared by the block: copied to LDS without touching registers, 6 NT KB per step, double-buffered, one barrier per
+// step.  RT = 1 leaves three to four wavefronts per SIMD: loads, splitting, matrix instructions and stores of a block
+// hardly overlap, those of different blocks do (RT = 2, two wavefronts: the same within 5 %, 24 % slower at 65536 rows
+// and 64 columns).  At 2^17 rows, against the fp32 instruction (K -> N): 128 -> 512 201 -> 167 us,
+// 512 -> 128 159 -> 137, 256 -> 256 158 -> 119, 128 -> 128 51 -> 43, 256 -> 64 47 -> 39 (4.3 TB/s); at 2^20 rows
+// 100 -> 256 773 -> 564, 47 -> 256 594 -> 328, 256 -> 47 414 -> 313; at 2^22 64 -> 256 1551 -> 1424, 256 -> 64 1378 ->
+// 1226 (4.4 TB/s: what a copy reaches).  Matrix instructions, stores and loads still add up more than they overlap:
+// without the stores 128 -> 512 takes 115 us, with a sixth of the matrix instructions 117.
+template <int RT, int NT>
+__global__ void __launch_bounds__(256, NT == 4 ? 3 : 4)
+gemm_split_kernel(Product g) {
+    extern __shared__ __align__(16) char lds[];
+    constexpr int STAGE = NT * kStepBytes;
+    const long tile = xcd_tile((long)g.tiles_m * g.tiles_n);
+    if (tile >= (long)g.tiles_m * g.tiles_n) return;
+    const int t = threadIdx.x, lane = t % 64, wave = __builtin_amdgcn_readfirstlane(t / 64);
+    const int l = lane % 32, half = lane / 32;
+    const int row0 = (int)(tile / g.tiles_n) * (128 * RT) + wave * (32 * RT);
+    const int ct0 = (int)(tile % g.tiles_n) * NT;           // first 32-column tile
+    const int total = g.A2 ? 2 * g.steps : g.steps;
+
+    size_t ro[RT];                                           // rows past the end re-read the last one
+#pragma unroll
+    for (int r = 0; r < RT; ++r) ro[r] = (size_t)min(row0 + 32 * r + l, g.M - 1) * g.K;
+
+    // Four indices at a time, at any 4-byte aligned address; the ones that would run over the row's end are read from
+    // its last four floats instead (K >= 4) and put in place by `settle`, so no load stands behind a branch.
+    floatx4 raw[RT][4];
+    auto load = [&](int step) __attribute__((always_inline)) {
+        const bool second = step >= g.steps;
+        const float *A = second ? g.A2 : g.A;
+        const int k = (second ? step - g.steps : step) * KB + 16 * half;
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) raw[r][i] = *reinterpret_cast<const float4u *>(A + ro[r] + min(k + 4 * i, g.K - 4));
+    };
+    auto settle = [&](int step) __attribute__((always_inline)) {
+        const int k0 = (step >= g.steps ? step - g.steps : step) * KB;
+        if (k0 + KB <= g.K) return;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // floats past the end: 0 none .. 4 all; a shift by one, by two and by four places
+            const int over = min(max(k0 + 16 * half + 4 * i + 4 - g.K, 0), 4);
+            const bool one = over & 1, two = over & 2, all = over & 4;
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                floatx4 v = raw[r][i];
+                v = floatx4{one ? v.y : v.x, one ? v.z : v.y, one ? v.w : v.z, one ? 0.f : v.w};
+                v = floatx4{two ? v.z : v.x, two ? v.w : v.y, two ? 0.f : v.z, two ? 0.f : v.w};
+                raw[r][i] = floatx4{all ? 0.f : v.x, all ? 0.f : v.y, all ? 0.f : v.z, all ? 0.f : v.w};
+            }
+        }
+    };
+    // global -> LDS, 1 KB per wavefront and instruction: the 6 NT fragments of a step are dealt to the four wavefronts
+    auto stage = [&](int step, int buf) __attribute__((always_inline)) {
+        const bool second = step >= g.steps;
+        const char *src = (second ? g.parts2 : g.parts) + (size_t)(second ? step - g.steps : step) * kStepBytes;
+#pragma unroll
+        for (int i = 0; i < (6 * NT + 3) / 4; ++i) {
+            const int f = wave + 4 * i;                      // uniform
+            if (6 * NT % 4 == 0 || f < 6 * NT) {
+                const char *from = src + (size_t)(ct0 + f / 6) * g.steps * kStepBytes + (f % 6) * kFragBytes + lane * 16;
+                char *to = lds + buf * STAGE + f * kFragBytes;
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)from,
+                                                 (__attribute__((address_space(3))) void *)to, 16, 0, 0);
+            }
+        }
+    };
+
+    floatx16 acc[RT][NT];
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int c = 0; c < NT; ++c)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.f;
+    };
+    clear();
+    float top[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) top[r] = 0.f;
+
+    stage(0, 0);
+    load(0);
+    for (int step = 0; step < total; ++step) {
+        // this wavefront's copies of the step have arrived; after the barrier everyone's have, and the other buffer,
+        // read in the step before, is free
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const int buf = step & 1;
+        const bool more = step + 1 < total;
+        if (more) stage(step + 1, buf ^ 1);
+        bf16x8 a[2][RT][3];
+        settle(step);
+#pragma unroll
+        for (int ins = 0; ins < 2; ++ins)
+#pragma unroll
+            for (int r = 0; r < RT; ++r) split8(raw[r][2 * ins], raw[r][2 * ins + 1], a[ins][r], top[r]);
+        load(min(step + 1, total - 1));                    // the last step again after the last: no branch, no use
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+            bf16x8 b[2][3];
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+                b[i / 3][i % 3] = *reinterpret_cast<const bf16x8 *>(lds + buf * STAGE + c * kStepBytes + i * kFragBytes + lane * 16);
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                floatx16 small;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) small[v] = 0.f;
+#pragma unroll
+                for (int i = 0; i < kProducts - 1; ++i)
+#pragma unroll
+                    for (int ins = 0; ins < 2; ++ins)
+                        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ins][r][kPartA[i]], b[ins][kPartB[i]], small, 0, 0, 0);
+#pragma unroll
+                for (int ins = 0; ins < 2; ++ins)
+                    acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ins][r][0], b[ins][0], acc[r][c], 0, 0, 0);
+                acc[r][c] += small;
+            }
+        }
+    }
+
+    // what the parts cannot hold: see the top of the file.  A row of A may be tiny over both pairs only together.
+    bool bad = false;
+    float finite = 0.f;
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        bad |= tiny(fmaxf(top[r], __shfl_xor(top[r], 32, 64)));
+#pragma unroll
+        for (int c = 0; c < NT; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) finite = fmaf(acc[r][c][v], 0.f, finite);
+    }
+    bad |= finite != 0.f;                                    // 0 x (inf or NaN) is NaN
+#pragma unroll
+    for (int c = 0; c < NT; ++c) {
+        bad |= g.tiny[ct0 + c] != 0;
+        if (g.A2) bad |= g.tiny2[ct0 + c] != 0;
+    }
+    if (__any(bad)) {
+        clear();
+        for (int step = 0; step < total; ++step) {
+            load(step);
+            settle(step);
+            const bool second = step >= g.steps;
+            const Operand b = second ? g.B2 : g.B;
+            const int k0 = (second ? step - g.steps : step) * KB + 16 * half;
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+#pragma unroll
+                for (int c = 0; c < NT; ++c) {
+                    const int n = (ct0 + c) * 32 + l;
+                    const float bv = k0 + j < g.K && n < g.N ? b.p[(k0 + j) * b.sk + n * b.sn] : 0.f;
+#pragma unroll
+                    for (int r = 0; r < RT; ++r)
+                        acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(raw[r][j / 4][j % 4], bv, acc[r][c], 0, 0, 0);
+                }
+        }
+    }
+
+    // accumulator register v of lane (half, l): row 8 (v / 4) + 4 half + v % 4, column l of its 32 x 32 tile
+#pragma unroll
+    for (int c = 0; c < NT; ++c) {
+        const int n = (ct0 + c) * 32 + l;
+        const float bias = g.bias && n < g.N ? g.bias[n] : 0.f;
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            const int m0 = row0 + 32 * r + 4 * half;
+            float *at = g.C + (size_t)m0 * g.ldc + n;
+            if (row0 + 32 * r + 32 <= g.M && n < g.N) {
+                if (g.act & kActAccumulate) {                // a tile's worth of loads before the first store
+                    float held[16];
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) held[v] = at[(size_t)(8 * (v / 4) + v % 4) * g.ldc];
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const float o = acc[r][c][v] + bias + held[v];
+                        at[(size_t)(8 * (v / 4) + v % 4) * g.ldc] = (g.act & kActRelu) ? fmaxf(o, 0.f) : o;
+                    }
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) put(g, at + (size_t)(8 * (v / 4) + v % 4) * g.ldc, acc[r][c][v], bias);
+                }
+            } else if (n < g.ldc) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int dm = 8 * (v / 4) + v % 4;
+                    if (m0 + dm < g.M) {
+                        if (n < g.N) put(g, at + (size_t)dm * g.ldc, acc[r][c][v], bias);
+                        else at[(size_t)dm * g.ldc] = 0.f;   // padding columns of a wider row stride
+                    }
+                }
+            }
+        }
+    }
+}
+
+// 32-column tiles per block: as wide as the output allows (a row of A is split once per tile)
+int tiles_wide(int64_t N) { return N <= 32 ? 1 : N <= 64 ? 2 : 4; }
+
+size_t parts_bytes(int64_t N, int64_t K) {
+    const int64_t w = tiles_wide(N);
+    return align_up((size_t)(ceil_div(N, 32 * w) * w) * ceil_div(K, KB) * kStepBytes);
+}
+
+}  // namespace
+
+// scratch of one operand pair: the parts of B, then a word per 32 columns
+size_t gemm_split_workspace_bytes(int64_t N, int64_t K) {
+    return parts_bytes(N, K) + align_up((size_t)(ceil_div(N, 32) + 3) * sizeof(int32_t));
+}
+
+// C [M][N], rows ldc apart = A [M][K] op(B) (+ A2 op(B2)), K >= 4; tb: B is [N][K], else [K][N].  workspace:
+// gemm_split_workspace_bytes per operand pair.
+gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B, float *C,
+                               int64_t ldc, const float *bias, int act, void *workspace, hipStream_t st,
+                               const float *A2, const float *B2) {
+    Product g{};
+    g.M = (int)M; g.N = (int)N; g.K = (int)K;
+    g.steps = (int)ceil_div(K, KB);
+    g.A = A; g.A2 = A2;
+    g.B = Operand{B, tb ? 1 : (long)N, tb ? (long)K : 1};
+    g.B2 = Operand{B2, g.B.sk, g.B.sn};
+    g.C = C; g.ldc = (int)ldc; g.bias = bias; g.act = act;
+    const int w = tiles_wide(N);
+    g.tiles_m = (int)ceil_div(M, 128); g.tiles_n = (int)ceil_div(N, 32 * w);
+    const size_t one = gemm_split_workspace_bytes(N, K), words = parts_bytes(N, K);
+    char *ws = static_cast<char *>(workspace), *ws2 = ws + one;
+    g.parts = ws; g.parts2 = ws2;
+    g.tiny = reinterpret_cast<int32_t *>(ws + words); g.tiny2 = reinterpret_cast<int32_t *>(ws2 + words);
+    hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)(g.tiles_n * w), A2 ? 2 : 1), dim3(1024), 0, st, (int)N,
+                       (int)K, g.steps, g.B, g.B2, ws, ws2, reinterpret_cast<int32_t *>(ws + words),
+                       reinterpret_cast<int32_t *>(ws2 + words));
+    GNN_TRY(launch_status());
+    const long total = (long)g.tiles_m * g.tiles_n;
+    if (total > INT32_MAX / 2) return GNN_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)(8 * ceil_div(total, 8)));
+    const size_t lds = (size_t)2 * w * kStepBytes;
+    if (w == 1) hipLaunchKernelGGL((gemm_split_kernel<1, 1>), grid, dim3(256), lds, st, g);
+    else if (w == 2) hipLaunchKernelGGL((gemm_split_kernel<1, 2>), grid, dim3(256), lds, st, g);
+    else hipLaunchKernelGGL((gemm_split_kernel<1, 4>), grid, dim3(256), lds, st, g);
+    return launch_status();
+}
+
+}  // namespace gnn

@@ -24,6 +24,8 @@ struct GatLayout {
     size_t workspace_bytes;
 };
 
+// scratch of the products of a backward pass, one at a time: X^T H, and (dx) up to `pairs` pairs of G W^T
+size_t backward_gemm_bytes(int64_t n, int64_t m, int64_t k, bool dx, int pairs);
 GatLayout gat_layout(const Plan &p);
 gnn_status_t plan_create(const gnn_plan_desc_t *desc, Plan **out);
 

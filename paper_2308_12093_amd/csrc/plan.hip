@@ -78,7 +78,7 @@ void size_gcn(Plan &p) {
 
     // forward
     size_t fwd = gemm_workspace_bytes(0, 0, n, k, m);
-    if (d.layer == GNN_LAYER_SAGE) fwd *= 2;               // both weights transposed for the one product that uses both
+    if (d.layer == GNN_LAYER_SAGE) fwd *= 2;               // both weights, for the one product that uses both
     if (tf) {
         fwd += align_up((size_t)n * k * fl) + spmm_workspace_bytes(n, q, (int)k);
         p.info.transient_fwd = n * k;
@@ -93,7 +93,7 @@ void size_gcn(Plan &p) {
     size_t bwd = 0;
     if (d.fuse_relu) bwd += align_up((size_t)n * k * fl);
     if (d.has_bias) bwd += colsum_workspace_bytes(n, (int)k);
-    bwd += gemm_workspace_bytes(1, 0, m, k, n);
+    bwd += align_up(backward_gemm_bytes(n, m, k, dx, d.layer == GNN_LAYER_SAGE ? 2 : 1));
     if (fp) {
         bwd += align_up((size_t)n * k * fl) + spmm_workspace_bytes(n, q, (int)k);
         p.info.transient_bwd = n * k;
@@ -144,6 +144,12 @@ double spmm_time_model_us(int64_t n, int64_t nnz, int f) {
     return 12.0 + (double)nnz * per_entry_ps * 1e-6;
 }
 
+size_t backward_gemm_bytes(int64_t n, int64_t m, int64_t k, bool dx, int pairs) {
+    const size_t tn = gemm_workspace_bytes(1, 0, m, k, n);
+    const size_t nt = dx ? pairs * gemm_workspace_bytes(0, 1, n, m, k) : 0;
+    return tn > nt ? tn : nt;
+}
+
 GatLayout gat_layout(const Plan &p) {
     const gnn_plan_desc_t &d = p.desc;
     const size_t n = d.n, q = d.nnz, h = d.heads, k = d.f_out, f = h * k, m = d.f_in, fl = sizeof(float);
@@ -174,7 +180,7 @@ GatLayout gat_layout(const Plan &p) {
     L.w_spmm_h = take(spmm_workspace_bytes(0, q, (int)h));        // its dense operand has q rows: never padded
     L.w_dM = take(n * f * fl);
     L.w_red = take(2 * colsum_workspace_bytes(n, (int)f));
-    L.w_gemm_tn = take(gemm_workspace_bytes(1, 0, m, f, n));
+    L.w_gemm_tn = take(backward_gemm_bytes(n, m, f, d.need_input_grad != 0, 1));
     L.w_G = d.fuse_elu ? take(n * f * fl) : (size_t)-1;
     L.w_fused = take(gat_fused_workspace_bytes(q, (int)h, (int)k));
     L.w_node = take(n * h * 4 * fl);
