@@ -26,6 +26,22 @@ static inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Four entries of an index or weight array, at any 4-byte aligned address
+typedef int32_t int4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// The four consecutive entries p[x .. x + 3] of an array of nnz entries; `fill` past the end.
+__device__ __forceinline__ int4 load_entries(const int32_t *__restrict__ p, long x, long nnz, int32_t fill) {
+    if (x + 4 <= nnz) {
+        const int4u v = *reinterpret_cast<const int4u *>(p + x);
+        return make_int4(v.x, v.y, v.z, v.w);
+    }
+    int4 v = make_int4(fill, fill, fill, fill);
+    if (x < nnz) v.x = p[x];
+    if (x + 1 < nnz) v.y = p[x + 1];
+    if (x + 2 < nnz) v.z = p[x + 2];
+    return v;
+}
+
 // Carves consecutive aligned blocks out of one caller buffer.
 struct Carver {
     char *base;

@@ -405,12 +405,17 @@ seg_walk_kernel(int nnz, int seg, long nseg, const int32_t *__restrict__ rowidx,
     float *s_tail = s_head + 256 * W;
     WalkInfo *s_info = reinterpret_cast<WalkInfo *>(s_tail + 256 * W);
     const long blk_first = (long)blockIdx.x * span;
-    for (int i = threadIdx.x; i < span; i += 256) {
+    // past the end: entry 0 of row / column 0, loaded but never folded
+#pragma unroll 2
+    for (int i = 4 * threadIdx.x; i < span; i += 1024) {
         const long x = blk_first + i;
-        const bool in = x < nnz;                           // past the end: entry 0 of row / column 0, loaded but never folded
-        s_row[i] = in ? rowidx[x] : 0;
-        s_col[i] = in ? colidx[x] : 0;
-        s_slot[i] = in ? (slotidx ? slotidx[x] : (int)x) : 0;
+        const int4 r = load_entries(rowidx, x, nnz, 0), c = load_entries(colidx, x, nnz, 0);
+        const int4 sl = slotidx ? load_entries(slotidx, x, nnz, 0)
+                                : make_int4(x < nnz ? (int)x : 0, x + 1 < nnz ? (int)x + 1 : 0,
+                                            x + 2 < nnz ? (int)x + 2 : 0, x + 3 < nnz ? (int)x + 3 : 0);
+        *reinterpret_cast<int4 *>(s_row + i) = r;
+        *reinterpret_cast<int4 *>(s_col + i) = c;
+        *reinterpret_cast<int4 *>(s_slot + i) = sl;
     }
     __syncthreads();
     const int l = threadIdx.x % LPE, gl = threadIdx.x / LPE;

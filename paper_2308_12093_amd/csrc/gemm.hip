@@ -522,7 +522,7 @@ gemm_f32_kernel(int M, int N, int K, const float *__restrict__ A, const float *_
 
 // The same product for few rows, bit for bit: one wavefront per 32 x 32 tile, operands straight from memory into
 // registers in the order the instruction takes them (the lower lane half k = 0..15 of a step of 32, the upper 16..31),
-// three steps ahead.  Latency bound: the 256 instructions of a 512-long reduction take 7 us by themselves.  No LDS, no
+// three steps ahead (six: the same there, 32768 x 128 x 64 12 -> 16 us).  Latency bound: the 256 instructions of a 512-long reduction take 7 us by themselves.  No LDS, no
 // transposed copy of B.  2048 x 512 by 512 x 16 took 20.4 us through the kernel above (16 blocks, one barrier per
 // step, and the copy), 16.3 now; 3001 x 203 by 203 x 7 24.4 and 9.8.
 __global__ void __launch_bounds__(64)
@@ -667,10 +667,10 @@ int pick_splits(int ta, int64_t M, int64_t N, int64_t K) {
     return (int)s;
 }
 
-// One wavefront per 32 x 32 tile while two per SIMD hold them all; beyond, the kernels that share operands through LDS.
+// One wavefront per 32 x 32 tile while there are few; beyond, the kernels that share operands through LDS.
 // Both sides of the line (fp32 kernel / one wavefront per tile): 4096 x 256 x 256, 1024 tiles, 26.9 / 14.3 us;
-// 32768 x 64 x 64, 2048, 13.9 / 9.4; 50021 x 96 x 64, 3128, 17.8 / 18.6; 16384 x 256 x 256, 4096, 31.0 / 47.5.
-bool few_rows(int64_t M, int64_t N) { return ceil_div(M, 32) * ceil_div(N, 32) <= 2048; }
+// 16384 x 256 x 64, 1024, 18.0 / 14.2; 49152 x 128 x 32, 1536, 12.7 / 13.4; 65536 x 512 x 16, 2048, 34.2 / 36.6; 50021 x 96 x 64, 3128, 17.8 / 18.6; 16384 x 256 x 256, 4096, 31.0 / 47.5.
+bool few_rows(int64_t M, int64_t N) { return ceil_div(M, 32) * ceil_div(N, 32) <= 1024; }
 
 }  // namespace
 

@@ -31,11 +31,15 @@
 namespace gnn {
 namespace {
 
-__device__ __forceinline__ float epilogue(float x, const float *bias, int c, int act) {
-    if (bias) x += bias[c];
+__device__ __forceinline__ float activate(float x, int act) {
     if (act == kActRelu) x = fmaxf(x, 0.f);
     else if (act == kActElu) x = x > 0.f ? x : expm1f(x);
     return x;
+}
+
+__device__ __forceinline__ float epilogue(float x, const float *bias, int c, int act) {
+    if (bias) x += bias[c];
+    return activate(x, act);
 }
 
 // four floats at a 4-byte aligned address: global dwordx4 accesses need no more than that
@@ -82,15 +86,26 @@ spmm_seg_kernel(int nnz, int f, int ldb, int seg, long nseg, const int32_t *__re
     SegInfo *s_info = reinterpret_cast<SegInfo *>(s_tail + GPB * FT);    // [GPB]
 
     const long blk_first = (long)blockIdx.x * span;
-    for (int i = threadIdx.x; i < span; i += 256) {
+    // four entries per thread and array, at most two rounds, all loads in flight at once; entry by entry they were up to
+    // eight rounds one after the other (2^17 nodes, f = 47: 75.1 -> 71.2 us)
+#pragma unroll 2
+    for (int i = 4 * threadIdx.x; i < span; i += 1024) {
         const long x = blk_first + i;
-        if (x < nnz) {
-            s_row[i] = erow[x];
-            s_col[i] = col[x];
-            const int slot = w.perm ? w.perm[x] : (int)x;
-            if constexpr (HEADS) s_w[i] = slot;
-            else s_w[i] = __float_as_int(w.val ? w.val[slot] : 1.f);
+        if (x >= nnz) break;
+        const int4 r = load_entries(erow, x, nnz, 0), c = load_entries(col, x, nnz, 0);
+        int4 v;
+        if (w.perm) v = load_entries(w.perm, x, nnz, 0);
+        else if (HEADS || !w.val) v = make_int4((int)x, (int)x + 1, (int)x + 2, (int)x + 3);
+        else v = load_entries(reinterpret_cast<const int32_t *>(w.val), x, nnz, 0);
+        if constexpr (!HEADS) {
+            if (!w.val) v = make_int4(__float_as_int(1.f), __float_as_int(1.f), __float_as_int(1.f), __float_as_int(1.f));
+            else if (w.perm)                               // past the end: slot 0, read and never used
+                v = make_int4(__float_as_int(w.val[v.x]), __float_as_int(w.val[v.y]), __float_as_int(w.val[v.z]),
+                              __float_as_int(w.val[v.w]));
         }
+        *reinterpret_cast<int4 *>(s_row + i) = r;
+        *reinterpret_cast<int4 *>(s_col + i) = c;
+        *reinterpret_cast<int4 *>(s_w + i) = v;
     }
     __syncthreads();
 
@@ -137,6 +152,13 @@ spmm_seg_kernel(int nnz, int f, int ldb, int seg, long nseg, const int32_t *__re
             for (int i = 0; i < VEC; ++i) acc[t][i] = overwrite ? q[i] : acc[t][i] + q[i];
         }
     };
+    // the bias of the lane's features, read once: loaded at every row's end it was a wait per row, behind the
+    // row's stores (3001 nodes, f = 7, bias and ReLU: 18.7 -> 10.6 us)
+    float bv[NT][VEC];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) bv[t][i] = bias && foff[t] + i < f ? bias[foff[t] + i] : 0.f;
     auto store_global = [&](float *dst, bool with_epilogue) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
@@ -144,26 +166,26 @@ spmm_seg_kernel(int nnz, int f, int ldb, int seg, long nseg, const int32_t *__re
             if constexpr (VEC == 4 && UA) {
                 if (foff[t] + 4 <= f) {
                     float4u o;
-                    o.x = with_epilogue ? epilogue(acc[t][0], bias, foff[t] + 0, relu) : acc[t][0];
-                    o.y = with_epilogue ? epilogue(acc[t][1], bias, foff[t] + 1, relu) : acc[t][1];
-                    o.z = with_epilogue ? epilogue(acc[t][2], bias, foff[t] + 2, relu) : acc[t][2];
-                    o.w = with_epilogue ? epilogue(acc[t][3], bias, foff[t] + 3, relu) : acc[t][3];
+                    o.x = with_epilogue ? activate(acc[t][0] + bv[t][0], relu) : acc[t][0];
+                    o.y = with_epilogue ? activate(acc[t][1] + bv[t][1], relu) : acc[t][1];
+                    o.z = with_epilogue ? activate(acc[t][2] + bv[t][2], relu) : acc[t][2];
+                    o.w = with_epilogue ? activate(acc[t][3] + bv[t][3], relu) : acc[t][3];
                     *reinterpret_cast<float4u *>(dst + foff[t]) = o;
                 } else {
 #pragma unroll
                     for (int i = 0; i < 3; ++i)
                         if (foff[t] + i < f)
-                            dst[foff[t] + i] = with_epilogue ? epilogue(acc[t][i], bias, foff[t] + i, relu) : acc[t][i];
+                            dst[foff[t] + i] = with_epilogue ? activate(acc[t][i] + bv[t][i], relu) : acc[t][i];
                 }
             } else if constexpr (VEC == 4) {
                 float4 o;
-                o.x = with_epilogue ? epilogue(acc[t][0], bias, foff[t] + 0, relu) : acc[t][0];
-                o.y = with_epilogue ? epilogue(acc[t][1], bias, foff[t] + 1, relu) : acc[t][1];
-                o.z = with_epilogue ? epilogue(acc[t][2], bias, foff[t] + 2, relu) : acc[t][2];
-                o.w = with_epilogue ? epilogue(acc[t][3], bias, foff[t] + 3, relu) : acc[t][3];
+                o.x = with_epilogue ? activate(acc[t][0] + bv[t][0], relu) : acc[t][0];
+                o.y = with_epilogue ? activate(acc[t][1] + bv[t][1], relu) : acc[t][1];
+                o.z = with_epilogue ? activate(acc[t][2] + bv[t][2], relu) : acc[t][2];
+                o.w = with_epilogue ? activate(acc[t][3] + bv[t][3], relu) : acc[t][3];
                 *reinterpret_cast<float4 *>(dst + foff[t]) = o;
             } else {
-                dst[foff[t]] = with_epilogue ? epilogue(acc[t][0], bias, foff[t], relu) : acc[t][0];
+                dst[foff[t]] = with_epilogue ? activate(acc[t][0] + bv[t][0], relu) : acc[t][0];
             }
         }
     };

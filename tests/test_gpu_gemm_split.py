@@ -8,10 +8,10 @@ from paper_2308_12093_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K): below and above the size (2048 tiles of 32 x 32) up to which a tile has a wavefront of its own, edges of the
+# (M, N, K): below and above the size (1024 tiles of 32 x 32) up to which a tile has a wavefront of its own, edges of the
 # 128-row, 32/64/128-column tiles and 32-index steps, widths that are no multiple of 4
-SHAPES = [(1, 1, 1), (33, 31, 3), (64, 32, 32), (2048, 16, 512), (3001, 7, 203), (65537, 16, 128), (65600, 32, 3),
-          (66000, 33, 31), (65281, 64, 47), (40000, 200, 5), (65281, 65, 33), (33000, 129, 36), (32769, 256, 64),
+SHAPES = [(1, 1, 1), (33, 31, 3), (64, 32, 32), (2048, 16, 512), (3001, 7, 203), (32768, 16, 128), (32769, 16, 128), (65600, 32, 3),
+          (66000, 33, 31), (65281, 64, 47), (32000, 200, 5), (65281, 65, 33), (33000, 129, 36), (32769, 256, 64),
           (65536, 128, 16), (66001, 100, 101), (65664, 32, 4)]
 
 
