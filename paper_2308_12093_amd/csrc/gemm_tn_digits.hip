@@ -205,18 +205,27 @@ gemm_tn_digits_kernel(int M, int N, long K, const float *__restrict__ A, const f
         asm volatile("" : "+v"(zero));                      // keeps the addresses below out of the step loop's registers
         const int nl = wn * 32 + l + zero, n = n0 + nl;
         const double sn = s_scale[BT + nl] * 65536.0;
+        // eight outputs at a time: what memory holds of them is on its way while their digits are put together
 #pragma unroll
         for (int x = 0; x < 2; ++x)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int ml = wm * 64 + x * 32 + 8 * (v / 4) + 4 * half + v % 4 + zero, m = m0 + ml;
-                double s = (double)acc[x][0][v];
+            for (int v0 = 0; v0 < 16; v0 += 8) {
+                const int mr = wm * 64 + x * 32 + v0 * 2 + 4 * half + zero;         // rows 8 (v / 4) + v % 4 from here
+                double held[8];
 #pragma unroll
-                for (int c = 1; c < DIGITS; ++c) s = s * 256.0 + (double)acc[x][c][v];
-                s *= s_scale[ml] * sn;
-                if (m < M && n < N) {
-                    double *at = out + (size_t)m * N + n;
-                    *at = folded ? *at + s : s;
+                for (int u = 0; u < 8; ++u) {
+                    const int m = m0 + mr + 8 * (u / 4) + u % 4;
+                    held[u] = folded && m < M && n < N ? out[(size_t)m * N + n] : 0.0;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int ml = mr + 8 * (u / 4) + u % 4, m = m0 + ml, v = v0 + u;
+                    double s = (double)acc[x][0][v];
+#pragma unroll
+                    for (int c = 1; c < DIGITS; ++c) s = s * 256.0 + (double)acc[x][c][v];
+                    s = s * (s_scale[ml] * sn) + held[u];
+                    if (m < M && n < N) out[(size_t)m * N + n] = s;
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
