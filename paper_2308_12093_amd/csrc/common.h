@@ -115,10 +115,11 @@ gnn_status_t gemm_tn_digits_launch(int64_t M, int64_t N, int64_t K, const float 
 // out = G * act'(x) with the derivative taken from the activation's output Y (kActRelu or kActElu)
 gnn_status_t activation_grad_launch(int64_t count, const float *G, const float *Y, float *out, int act, hipStream_t st);
 // out[c] = sum_i G[i][c], deterministic two-stage; workspace colsum_workspace_bytes(n, f).
-// With mask_y: the sum of G .* act'(mask_y) (mask_act: kActRelu or kActElu), as in activation_grad_launch.
+// With mask_y: the sum of G .* act'(mask_y) (mask_act: kActRelu or kActElu), as in activation_grad_launch; that product
+// is written to `masked` unless it is NULL.
 size_t colsum_workspace_bytes(int64_t n, int f);
 gnn_status_t colsum_launch(int64_t n, int f, const float *G, float *out, void *workspace, hipStream_t st,
-                           const float *mask_y = nullptr, int mask_act = 0);
+                           const float *mask_y = nullptr, int mask_act = 0, float *masked = nullptr);
 gnn_status_t squared_error_launch(int64_t count, const float *Z, const float *T, float *dZ, float *loss,
                                   void *workspace, hipStream_t st);
 gnn_status_t softmax_xent_launch(int n, int c, const float *Z, const int32_t *labels, float *dZ, float *loss,

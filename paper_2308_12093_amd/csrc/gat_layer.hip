@@ -90,14 +90,17 @@ gnn_status_t gat_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
     const float *dY = dY_in;
     if (d.fuse_elu) {
         float *G = at<float>(workspace, L.w_G);
-        GNN_TRY(activation_grad_launch((int64_t)n * f, dY_in, Y, G, kActElu, st));
+        if (d.has_bias)                                     // with the bias gradient, in one pass
+            GNN_TRY(colsum_launch(n, f, dY_in, db, at<char>(workspace, L.w_red), st, Y, kActElu, G));
+        else
+            GNN_TRY(activation_grad_launch((int64_t)n * f, dY_in, Y, G, kActElu, st));
         dY = G;
     }
 
     float *gy = at<float>(workspace, L.w_gy), *sums = at<float>(workspace, L.w_sums);
     float *ds = at<float>(workspace, L.w_ds), *dd = at<float>(workspace, L.w_dd), *dM = at<float>(workspace, L.w_dM);
 
-    if (d.has_bias) GNN_TRY(colsum_launch(n, f, dY, db, at<char>(workspace, L.w_red), st));
+    if (d.has_bias && !d.fuse_elu) GNN_TRY(colsum_launch(n, f, dY, db, at<char>(workspace, L.w_red), st));
     if (fused) {
         // row pass: SDDMM folded into the row sums (ds, t); column pass: dd and dM = A^T G + ds a_src + dd a_dst
         const bool cached = variant == GNN_CACHE_GAT_FEAT_EDGE;

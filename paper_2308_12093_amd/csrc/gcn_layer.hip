@@ -79,14 +79,14 @@ gnn_status_t gcn_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
     const float *mask_y = mask_in_consumers ? Y : nullptr;
     const float *G = dY;
     float *Gm = d.fuse_relu ? ws.take<float>((size_t)n * k) : nullptr;   // carved either way: the layout is the plan's
-    if (d.fuse_relu && !mask_in_consumers) {
-        GNN_TRY(activation_grad_launch((int64_t)n * k, dY, Y, Gm, kActRelu, st));
-        G = Gm;
-    }
-    if (d.has_bias) {                               // db = G^T 1
+    const bool make_g = d.fuse_relu && !mask_in_consumers;
+    if (d.has_bias) {                               // db = G^T 1; G is made in the same pass
         void *red = ws.take<char>(colsum_workspace_bytes(n, k));
-        GNN_TRY(colsum_launch(n, k, G, db, red, st, mask_y, kActRelu));
+        GNN_TRY(colsum_launch(n, k, dY, db, red, st, d.fuse_relu ? Y : nullptr, kActRelu, make_g ? Gm : nullptr));
+    } else if (make_g) {
+        GNN_TRY(activation_grad_launch((int64_t)n * k, dY, Y, Gm, kActRelu, st));
     }
+    if (make_g) G = Gm;
     void *gemm_ws = ws.take<char>(backward_gemm_bytes(n, m, k, dx, 1));   // one product at a time
 
     if (p.info.bwd == GNN_BWD_FUSED_PROPAGATE) {
@@ -164,14 +164,14 @@ gnn_status_t sage_backward(Plan &p, const gnn_graph_t &g, const float *X, const 
     const float *mask_y = mask_in_consumers ? Y : nullptr;
     const float *G = dY;
     float *Gm = d.fuse_relu ? ws.take<float>((size_t)n * k) : nullptr;
-    if (d.fuse_relu && !mask_in_consumers) {
-        GNN_TRY(activation_grad_launch((int64_t)n * k, dY, Y, Gm, kActRelu, st));
-        G = Gm;
-    }
-    if (d.has_bias) {
+    const bool make_g = d.fuse_relu && !mask_in_consumers;
+    if (d.has_bias) {                               // db = G^T 1; G is made in the same pass
         void *red = ws.take<char>(colsum_workspace_bytes(n, k));
-        GNN_TRY(colsum_launch(n, k, G, db, red, st, mask_y, kActRelu));
+        GNN_TRY(colsum_launch(n, k, dY, db, red, st, d.fuse_relu ? Y : nullptr, kActRelu, make_g ? Gm : nullptr));
+    } else if (make_g) {
+        GNN_TRY(activation_grad_launch((int64_t)n * k, dY, Y, Gm, kActRelu, st));
     }
+    if (make_g) G = Gm;
     void *gemm_ws = ws.take<char>(backward_gemm_bytes(n, m, k, dx, 2));
     GNN_TRY(gemm_launch(1, 0, m, k, n, X, G, dWs, nullptr, 0, gemm_ws, st, mask_y, kActRelu));     // dWs = X^T G
 

@@ -8,7 +8,7 @@
 // and the product of two operands is the sum of fifteen digit products d_i d'_j with i + j <= 6, collected by i + j in five
 // int32 accumulators.  What is left out is below 2^-46 of the columns' largest magnitudes per product, the rounding of
 // the fifth digit below 2^-39: on normal, positive and one-sided operands the float result is as far from the 64-bit
-// one as the rounding to float makes it (ERRS).
+// one as the rounding to float makes it (relative 2-norm 2.5e-8 on normal operands of 2^13 .. 2^22 rows, both ways).
 //
 // The exponent of a column starts three bits above the largest magnitude of its first non-zero step of 32 rows.  When a
 // larger value arrives, the block folds its integers into the double partials, in memory, and goes on with the new
@@ -58,7 +58,7 @@ __device__ __forceinline__ void digits4(float x0, float x1, float x2, float x3, 
 // owns column tile w of eight (four of X, four of H): lane (half, l) takes 16 consecutive rows of column l, read as lines
 // of 128 bytes, makes their digits and writes them where the instruction's lane (half, l) reads them.  One block per CU,
 // 147 KB of LDS, one barrier per step.  Half of the wavefronts stage step s + 1 before they multiply step s, the others
-// after.  A step takes some 4900 cycles, of which a wavefront multiplies 1200 (its 30 instructions cannot take less than
+// after.  A step takes some 4900 cycles, of which a wavefront multiplies 1200 (its 30 instructions take no less than
 // 960) and stages 3000 - 3400: 1100 for the digits, 500 for the exponent, up to 1200 behind its loads.  Loads into
 // registers a step ahead, __shfl, matrix and vector instructions interleaved by hand or by the compiler: all within 3 %.
 template <bool MASK>
