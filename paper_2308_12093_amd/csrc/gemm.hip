@@ -664,7 +664,7 @@ int pick_splits(int ta, int64_t M, int64_t N, int64_t K) {
     // equal blocks spread evenly over the 256 CUs only if their number is a multiple of 256: round down to one
     // (640 blocks leave half the CUs with three and half with two)
     if (tiles * s > 256) s = (tiles * s / 256 * 256) / tiles;
-    return (int)s;
+    return s < 1 ? 1 : (int)s;                             // more than 256 tiles in one chunk each: no multiple to round to
 }
 
 // One wavefront per 32 x 32 tile while there are few; beyond, the kernels that share operands through LDS.

@@ -258,6 +258,12 @@ def test_operator_calls_check_sizes():
     assert aggregate(100, 1000, 2, 8, ws_bytes=B.gnn_gat_aggregate_workspace_bytes(1000, 2, 8) - 1) == B.GNN_ERR_BUFFER_TOO_SMALL
 
 
+@pytest.mark.parametrize("M,N,K", [(2100, 2050, 100), (2100, 2050, 8200), (1100, 1100, 3000), (5000, 300, 64), (64, 40000, 512)])
+def test_transposed_product_has_room_for_a_chunk_of_every_shape(M, N, K):
+    """Outputs of more than 256 tiles whose reduction is not cut: at least one partial product of doubles."""
+    assert B.gnn_gemm_workspace_bytes(1, 0, M, N, K) >= 8 * M * N
+
+
 # ---- calibrated selection and constant inputs (host logic) --------------------------------
 def model_us(n, nnz, f):
     """The documented time model, evaluated here from the text of the header."""
