@@ -104,12 +104,6 @@ gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const fl
                                int64_t ldc, const float *bias, int act, void *workspace, hipStream_t st,
                                const float *A2, const float *B2);
 
-// the transposed-A product of long reductions (gemm_tn_digits.hip): see there
-bool gemm_tn_digits_shape(int64_t M, int64_t N, int64_t K);
-size_t gemm_tn_digits_workspace_bytes(int64_t M, int64_t N, int64_t K);
-gnn_status_t gemm_tn_digits_launch(int64_t M, int64_t N, int64_t K, const float *A, const float *B, const float *relu_y,
-                                   void *workspace, int *splits, hipStream_t st);
-
 // ---- element-wise and reductions (elementwise.hip) ---------------------------------
 // out = G * [Y > 0]
 // out = G * act'(x) with the derivative taken from the activation's output Y (kActRelu or kActElu)

@@ -681,11 +681,6 @@ size_t gemm_workspace_bytes(int ta, int tb, int64_t M, int64_t N, int64_t K) {
         const size_t bt = tb ? kAlign : align_up((size_t)N * K * sizeof(float));
         return parts > bt ? parts : bt;
     }
-    if (gemm_tn_digits_shape(M, N, K)) {
-        const size_t digits = gemm_tn_digits_workspace_bytes(M, N, K);
-        const size_t f64 = align_up((size_t)pick_splits(ta, M, N, K) * M * N * sizeof(double));   // a gradient masked by an ELU
-        return digits > f64 ? digits : f64;
-    }
     return align_up((size_t)pick_splits(ta, M, N, K) * M * N * sizeof(double));
 }
 
@@ -790,14 +785,6 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
         if (!launched) return GNN_ERR_UNSUPPORTED;
         return launch_status();
     }
-    const long count = (long)M * N;
-    if (gemm_tn_digits_shape(M, N, K) && (!b_mask || b_mask_act == kActRelu)) {
-        int parts;
-        GNN_TRY(gemm_tn_digits_launch(M, N, K, A, B, b_mask, workspace, &parts, st));
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)ceil_div(count, 16)), dim3(256), 0, st, count, parts,
-                           static_cast<const double *>(workspace), C);
-        return launch_status();
-    }
     int splits = pick_splits(ta, M, N, K);
     const long k_chunk = ceil_div(ceil_div(K > 0 ? K : 1, splits), BK) * BK;
     splits = (int)ceil_div(K > 0 ? K : 1, k_chunk);
@@ -809,6 +796,7 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
     GEMM_F64_CASE(4, 1, 1, 1) GEMM_F64_CASE(4, 1, 1, 2) GEMM_F64_CASE(2, 2, 2, 2) GEMM_F64_CASE(2, 2, 4, 4)
     if (!launched) return GNN_ERR_UNSUPPORTED;
     GNN_TRY(launch_status());
+    const long count = (long)M * N;
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)ceil_div(count, 16)), dim3(256), 0, st, count, splits,
                        static_cast<const double *>(workspace), C);
     return launch_status();
