@@ -10,10 +10,10 @@
 // products of a layer against 64 bits, fp32 instruction and parts: 2.0e-7 and
 // 0.7e-7 (K = 128), 2.9e-7 and 1.0e-7 (256), 4.1e-7 and 1.4e-7 (512); of positive operands 1.7e-7 and 0.7e-7 (128).
 //
-// What the parts cannot hold is recomputed: a wavefront whose result is not finite (operands that are, or that the
-// rounding to bf16 or a partial sum carries over the edge) or whose operands are so small that their third part falls
-// below the bf16 range (a row of A or a column of B that is nowhere above 2^-100 and not zero) forms its tile again
-// with the fp32 instruction.
+// What the parts cannot hold is recomputed with the fp32 instruction, wavefront by wavefront: a tile with results that
+// are not finite (operands that are not, or that the rounding to bf16 or a partial sum carries over the edge), and a tile
+// with operands whose third part falls below the bf16 range (magnitudes below 2^-110: they lose up to 2^-134) where that
+// loss may show in a result.
 #include "common.h"
 
 namespace gnn {
@@ -28,7 +28,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr int KB = 32;                 // reduction indices of a step: lane half h takes 16 h .. 16 h + 15
-constexpr float kTiny = 0x1p-100f;
+constexpr unsigned kTinyCode = 2 * ((127u - 110) << 23) - 1;   // magnitude_code(2^-110)
 constexpr int kFragBytes = 64 * 16;    // eight bf16 per lane: one operand of one instruction
 constexpr int kStepBytes = 2 * 3 * kFragBytes;   // [instruction][part] for 32 columns and KB indices
 
@@ -38,13 +38,16 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
 __device__ __forceinline__ float low(unsigned u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float high(unsigned u) { return __uint_as_float(u & 0xffff0000u); }
 
-// three parts of eight floats; `top` collects the largest magnitude
-__device__ __forceinline__ void split8(const floatx4 &x, const floatx4 &y, bf16x8 (&part)[3], float &top) {
+// orders like the magnitude, except that zero comes last
+__device__ __forceinline__ unsigned magnitude_code(float a) { return 2 * __float_as_uint(a) - 1; }
+
+// three parts of eight floats; `least` collects the smallest magnitude code
+__device__ __forceinline__ void split8(const floatx4 &x, const floatx4 &y, bf16x8 (&part)[3], unsigned &least) {
     uintx4 u[3];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         float a = i < 2 ? x[2 * i] : y[2 * i - 4], b = i < 2 ? x[2 * i + 1] : y[2 * i - 3];
-        top = fmaxf(top, fmaxf(fabsf(a), fabsf(b)));
+        least = min(least, min(magnitude_code(a), magnitude_code(b)));
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
             const unsigned h = pack_bf16(a, b);
@@ -60,8 +63,6 @@ __device__ __forceinline__ void split8(const floatx4 &x, const floatx4 &y, bf16x
 constexpr int kProducts = 6;
 __device__ constexpr int kPartA[kProducts] = {1, 0, 2, 1, 0, 0}, kPartB[kProducts] = {1, 2, 0, 0, 1, 0};
 
-__device__ __forceinline__ bool tiny(float top) { return top > 0.f && top < kTiny; }
-
 // columns of B as the kernels read it: element (k, n) at k * sk + n * sn
 struct Operand {
     const float *p;
@@ -70,37 +71,47 @@ struct Operand {
 
 // ---- parts of B, in the order in which the product kernel's lanes take them ----------------------------
 // out: [32-column tile][KB step][instruction][part][lane][8]; lane (half, l): column 32 tile + l, indices
-// KB step + 16 half + 8 instruction + 0..7; zeros past N and K.  tiny_out[tile]: some column of the tile is tiny.
-// One block per tile, 1024 threads: eight steps at a time.
+// KB step + 16 half + 8 instruction + 0..7; zeros past N and K.  range[tile]: the tile's smallest magnitude code and its
+// largest magnitude.  One block per tile, 1024 threads: eight steps at a time.
+struct Range {
+    unsigned least;
+    float top;
+};
+
 __global__ void __launch_bounds__(1024)
 split_weights_kernel(int N, int K, int steps, Operand b0, Operand b1, char *__restrict__ out0, char *__restrict__ out1,
-                     int32_t *__restrict__ tiny0, int32_t *__restrict__ tiny1) {
-    __shared__ unsigned top[32];
+                     Range *__restrict__ range0, Range *__restrict__ range1) {
+    __shared__ unsigned s_least, s_top;
     const Operand b = blockIdx.y ? b1 : b0;
     char *out = (blockIdx.y ? out1 : out0) + (size_t)blockIdx.x * steps * kStepBytes;
     const int lane = threadIdx.x % 64, ins = (threadIdx.x / 64) % 2, sub = threadIdx.x / 128;
     const int l = lane % 32, half = lane / 32;
     const int n = blockIdx.x * 32 + l;
-    if (threadIdx.x < 32) top[threadIdx.x] = 0;
+    if (threadIdx.x == 0) { s_least = ~0u; s_top = 0; }
     __syncthreads();
-    float t = 0.f;
+    unsigned least = ~0u, top = 0;                          // magnitudes order like their bits, NaN last
     for (int s = sub; s < steps; s += 8) {
         const int k0 = s * KB + 16 * half + 8 * ins;
         floatx4 x[2];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j / 4][j % 4] = n < N && k0 + j < K ? b.p[(k0 + j) * b.sk + n * b.sn] : 0.f;
+        for (int j = 0; j < 8; ++j) {
+            x[j / 4][j % 4] = n < N && k0 + j < K ? b.p[(k0 + j) * b.sk + n * b.sn] : 0.f;
+            top = max(top, __float_as_uint(x[j / 4][j % 4]) & 0x7fffffffu);
+        }
         bf16x8 part[3];
-        split8(x[0], x[1], part, t);
+        split8(x[0], x[1], part, least);
 #pragma unroll
         for (int p = 0; p < 3; ++p)
             *reinterpret_cast<bf16x8 *>(out + (size_t)s * kStepBytes + (ins * 3 + p) * kFragBytes + lane * 16) = part[p];
     }
-    atomicMax(&top[l], __float_as_uint(t));                 // magnitudes order like their bits
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        const bool any = __any(threadIdx.x < 32 && tiny(__uint_as_float(top[threadIdx.x % 32])));
-        if (threadIdx.x == 0) (blockIdx.y ? tiny1 : tiny0)[blockIdx.x] = any;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        least = min(least, (unsigned)__shfl_xor((int)least, d, 64));
+        top = max(top, (unsigned)__shfl_xor((int)top, d, 64));
     }
+    if (lane == 0) { atomicMin(&s_least, least); atomicMax(&s_top, top); }
+    __syncthreads();
+    if (threadIdx.x == 0) (blockIdx.y ? range1 : range0)[blockIdx.x] = Range{s_least, __uint_as_float(s_top)};
 }
 
 struct Product {
@@ -108,7 +119,7 @@ struct Product {
     const float *A, *A2;               // A2: NULL without a second pair
     Operand B, B2;
     const char *parts, *parts2;
-    const int32_t *tiny, *tiny2;
+    const Range *range, *range2;
     float *C;
     int ldc;
     const float *bias;
@@ -226,9 +237,9 @@ gemm_split_kernel(Product g) {
                 for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.f;
     };
     clear();
-    float top[RT];
+    unsigned least[RT];                                      // of this lane's half of the row
 #pragma unroll
-    for (int r = 0; r < RT; ++r) top[r] = 0.f;
+    for (int r = 0; r < RT; ++r) least[r] = ~0u;
 
     stage(0, 0);
     load(0);
@@ -245,7 +256,7 @@ gemm_split_kernel(Product g) {
 #pragma unroll
         for (int ins = 0; ins < 2; ++ins)
 #pragma unroll
-            for (int r = 0; r < RT; ++r) split8(raw[r][2 * ins], raw[r][2 * ins + 1], a[ins][r], top[r]);
+            for (int r = 0; r < RT; ++r) split8(raw[r][2 * ins], raw[r][2 * ins + 1], a[ins][r], least[r]);
         load(min(step + 1, total - 1));                    // the last step again after the last: no branch, no use
 #pragma unroll
         for (int c = 0; c < NT; ++c) {
@@ -271,22 +282,65 @@ gemm_split_kernel(Product g) {
         }
     }
 
-    // what the parts cannot hold: see the top of the file.  A row of A may be tiny over both pairs only together.
-    bool bad = false;
+    // what the parts cannot hold: see the top of the file
     float finite = 0.f;
+    unsigned small_a = ~0u, small_b = ~0u;
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
-        bad |= tiny(fmaxf(top[r], __shfl_xor(top[r], 32, 64)));
+        small_a = min(small_a, least[r]);
 #pragma unroll
         for (int c = 0; c < NT; ++c)
 #pragma unroll
             for (int v = 0; v < 16; ++v) finite = fmaf(acc[r][c][v], 0.f, finite);
     }
-    bad |= finite != 0.f;                                    // 0 x (inf or NaN) is NaN
 #pragma unroll
     for (int c = 0; c < NT; ++c) {
-        bad |= g.tiny[ct0 + c] != 0;
-        if (g.A2) bad |= g.tiny2[ct0 + c] != 0;
+        small_b = min(small_b, g.range[ct0 + c].least);
+        if (g.A2) small_b = min(small_b, g.range2[ct0 + c].least);
+    }
+    bool bad = finite != 0.f;                                // 0 x (inf or NaN) is NaN
+    if (!__any(bad) && __any(min(small_a, small_b) < kTinyCode)) {
+        // Some operand lost up to 2^-134: a result is off by at most K 2^-134 times the largest magnitude it met (the
+        // rows' for a tiny B, the column tile's for a tiny row).  Where that is below the rounding of the result nothing
+        // is lost: rows that hold a saturated probability beside ordinary values, weights that have decayed.
+        float top[RT];                                       // of the row, read once more
+#pragma unroll
+        for (int r = 0; r < RT; ++r) top[r] = 0.f;
+#pragma unroll 1
+        for (int step = 0; step < total; ++step) {
+            load(step);
+            settle(step);
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) top[r] = fmaxf(top[r], fabsf(raw[r][j / 4][j % 4]));
+        }
+        const float lost = 0x1p-110f * (float)(g.A2 ? 2L * g.K : (long)g.K);   // 2^24 times what a unit magnitude loses
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            // a bit per row, from both halves of it
+            unsigned long long row_tiny = __ballot(least[r] < kTinyCode), row_zero = __ballot(top[r] == 0.f);
+            row_tiny |= row_tiny >> 32;
+            row_zero &= row_zero >> 32;
+            const unsigned tiny = (unsigned)row_tiny >> (4 * half), zero = (unsigned)row_zero >> (4 * half);
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) top[r] = fmaxf(top[r], __shfl_xor(top[r], d, 64));
+#pragma unroll
+            for (int c = 0; c < NT; ++c) {
+                Range b = g.range[ct0 + c];
+                if (g.A2) {
+                    const Range b2 = g.range2[ct0 + c];
+                    b = Range{min(b.least, b2.least), fmaxf(b.top, b2.top)};
+                }
+                const float of_b = lost * b.top, of_a = b.least < kTinyCode ? lost * top[r] : 0.f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = 8 * (v / 4) + v % 4;     // of this register, behind the shift by 4 half
+                    const float most = ((tiny >> row) & 1 ? of_b : 0.f) + ((zero >> row) & 1 ? 0.f : of_a);
+                    bad |= (ct0 + c) * 32 + l < g.N && !(fabsf(acc[r][c][v]) >= most);
+                }
+            }
+        }
     }
     if (__any(bad)) {
         clear();
@@ -356,9 +410,9 @@ size_t parts_bytes(int64_t N, int64_t K) {
 
 }  // namespace
 
-// scratch of one operand pair: the parts of B, then a word per 32 columns
+// scratch of one operand pair: the parts of B, then a Range per 32 columns
 size_t gemm_split_workspace_bytes(int64_t N, int64_t K) {
-    return parts_bytes(N, K) + align_up((size_t)(ceil_div(N, 32) + 3) * sizeof(int32_t));
+    return parts_bytes(N, K) + align_up((size_t)(ceil_div(N, 32) + 3) * sizeof(Range));
 }
 
 // C [M][N], rows ldc apart = A [M][K] op(B) (+ A2 op(B2)), K >= 4; tb: B is [N][K], else [K][N].  workspace:
@@ -378,10 +432,10 @@ gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const fl
     const size_t one = gemm_split_workspace_bytes(N, K), words = parts_bytes(N, K);
     char *ws = static_cast<char *>(workspace), *ws2 = ws + one;
     g.parts = ws; g.parts2 = ws2;
-    g.tiny = reinterpret_cast<int32_t *>(ws + words); g.tiny2 = reinterpret_cast<int32_t *>(ws2 + words);
+    Range *range = reinterpret_cast<Range *>(ws + words), *range2 = reinterpret_cast<Range *>(ws2 + words);
+    g.range = range; g.range2 = range2;
     hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)(g.tiles_n * w), A2 ? 2 : 1), dim3(1024), 0, st, (int)N,
-                       (int)K, g.steps, g.B, g.B2, ws, ws2, reinterpret_cast<int32_t *>(ws + words),
-                       reinterpret_cast<int32_t *>(ws2 + words));
+                       (int)K, g.steps, g.B, g.B2, ws, ws2, range, range2);
     GNN_TRY(launch_status());
     const long total = (long)g.tiles_m * g.tiles_n;
     if (total > INT32_MAX / 2) return GNN_ERR_UNSUPPORTED;

@@ -64,3 +64,36 @@ def test_values_the_parts_cannot_hold(M):
     fits = keep[:, None] & (ref.abs() < 3.4e38)
     assert bool(((got.double() - ref).abs() <= bound)[fits].all())
     assert bool(torch.isinf(got[40][ref[40] > 3.5e38]).all())
+
+
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("side", ["A", "B"])
+@pytest.mark.parametrize("N,K", [(40, 70), (128, 33)])
+def test_small_operands_beside_large_ones(side, tb, N, K):
+    """Rows and columns whose sum hangs on an element of 2^-100 .. 2^-149 (its third part is below the bf16 range from 2^-110
+    on): what is larger in its row or column meets zero."""
+    M = 70000
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    small = torch.empty(M if side == "A" else N, device="cuda").uniform_(1, 2, generator=gen)
+    small *= 2.0 ** -(100.0 + torch.arange(small.numel(), device="cuda") % 46)
+    A, Bm = torch.zeros(M, K, device="cuda"), torch.zeros(K, N, device="cuda")
+    if side == "A":
+        A[:, 0], A[:, 3], Bm[3] = 1.0, small, torch.empty(N, device="cuda").uniform_(1, 2, generator=gen) * 2.0 ** 112
+        A[5], A[6, 3] = 0.0, 0.0
+    else:
+        Bm[0], Bm[3], A[:, 3] = 1.0, small, torch.empty(M, device="cuda").uniform_(1, 2, generator=gen) * 2.0 ** 112
+        Bm[:, 7] = 0.0
+    ref = A.double() @ Bm.double()
+    # one product a result: its rounding; the parts' dropped products 3 2^-26 and the roundings of three sums
+    assert bool(((product(M, N, K, A, Bm, tb).double() - ref).abs() <= 2.0 ** -22 * ref.abs()).all())
+
+
+def test_small_operands_that_do_not_matter():
+    """Saturated probabilities beside ordinary gradients, and decayed weights: the results stay those of the parts."""
+    M, N, K = 66000, 64, 48
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    A, Bm = torch.randn(M, K, generator=gen, device="cuda"), torch.randn(K, N, generator=gen, device="cuda")
+    A[::3, 5], A[1::3], Bm[11] = 1e-36, 0.0, 3e-39
+    A0, B0 = A.clone(), Bm.clone()
+    A0[::3, 5], B0[11] = 0.0, 0.0
+    assert bool((product(M, N, K, A, Bm, 0) == product(M, N, K, A0, B0, 0)).all())
