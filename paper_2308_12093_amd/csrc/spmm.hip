@@ -158,7 +158,7 @@ spmm_seg_kernel(int nnz, int f, int ldb, int seg, long nseg, const int32_t *__re
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) bv[t][i] = bias && foff[t] + i < f ? bias[foff[t] + i] : 0.f;
+        for (int i = 0; i < VEC; ++i) bv[t][i] = bias && foff[t] + i < f ? bias[foff[t] + i] : -0.f;   // x + -0 is x
     auto store_global = [&](float *dst, bool with_epilogue) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) {

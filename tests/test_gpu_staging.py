@@ -36,3 +36,16 @@ def test_spmm(nnz, f):
         B.gnn_spmm_csr(n, nnz, rp, shifted(dev(col), by), shifted(dev(val), by), shifted(G.expand(n, rp, nnz), by), dev(X),
                        f, C, workspace=B.alloc(B.gnn_spmm_workspace_bytes(n, nnz, f)))
         assert_close(host(C), ref, f"shift {by}", tol=2e-6)
+
+
+@pytest.mark.parametrize("f", [1, 7, 8, 47, 64, 300])
+def test_spmm_without_a_bias_keeps_the_sign_of_zero(f):
+    """One entry a row: the product, which underflows to -0 in every other row."""
+    n = 1000
+    ids = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+    val = torch.full((n,), 1e-30, device="cuda")
+    X = torch.full((n, f), 1e-30, device="cuda")
+    X[::2] = -1e-30
+    C = torch.empty(n, f, device="cuda")
+    B.gnn_spmm_csr(n, n, ids, ids[:n].clone(), val, ids[:n].clone(), X, f, C, workspace=B.alloc(B.gnn_spmm_workspace_bytes(n, n, f)))
+    assert bool((C == 0).all()) and bool(torch.signbit(C[::2]).all()) and not bool(torch.signbit(C[1::2]).any())
