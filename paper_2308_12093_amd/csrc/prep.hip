@@ -480,10 +480,12 @@ gnn_status_t normalize_launch(int n, const int32_t *rowptr, const int32_t *col, 
 }
 
 gnn_status_t expand_ptr_launch(int n, int nnz, const int32_t *ptr, int32_t *out, hipStream_t st) {
-    if (n <= 0 || nnz <= 0) return GNN_OK;
+    if (n <= 0) return GNN_OK;
+    // nnz sets the number of blocks alone: what is written is what ptr says
     const bool small = nnz < ROW_SMALL;
-    hipLaunchKernelGGL(small ? expand_ptr_kernel<ROW_TILE_SMALL> : expand_ptr_kernel<ROW_TILE>,
-                       dim3((unsigned)ceil_div(nnz, small ? ROW_TILE_SMALL : ROW_TILE)), dim3(ROW_THREADS), 0, st, n, ptr, out);
+    const long tiles = ceil_div(nnz > 0 ? nnz : 1, small ? ROW_TILE_SMALL : ROW_TILE);
+    hipLaunchKernelGGL(small ? expand_ptr_kernel<ROW_TILE_SMALL> : expand_ptr_kernel<ROW_TILE>, dim3((unsigned)tiles),
+                       dim3(ROW_THREADS), 0, st, n, ptr, out);
     return launch_status();
 }
 

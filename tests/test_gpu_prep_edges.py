@@ -54,3 +54,12 @@ def test_scan_tiles(count):
     np.testing.assert_array_equal(host(rp), np.arange(count + 1))
     np.testing.assert_array_equal(host(c), np.arange(count))
     assert int(deg.min()) == int(deg.max()) == 1
+
+
+@pytest.mark.parametrize("said", [0, 1, 5000])
+def test_expand_writes_what_the_pointers_say(said):
+    """The entry count that goes with the call only sizes the launch."""
+    rowptr, _ = pattern(3000, 9001, 2000, seed=1)
+    out = torch.full((9001,), -1, dtype=torch.int32, device="cuda")
+    B.gnn_expand_ptr(3000, said, dev(rowptr), out)
+    np.testing.assert_array_equal(host(out), np.repeat(np.arange(3000), np.diff(rowptr)))
