@@ -63,3 +63,60 @@ def test_expand_writes_what_the_pointers_say(said):
     out = torch.full((9001,), -1, dtype=torch.int32, device="cuda")
     B.gnn_expand_ptr(3000, said, dev(rowptr), out)
     np.testing.assert_array_equal(host(out), np.repeat(np.arange(3000), np.diff(rowptr)))
+
+
+def check_setup(n, rowptr, col):
+    """Every preprocessing step of a pattern, bit for bit."""
+    rp_o, c_o, deg_o = oracle.add_self_loops_degree(rowptr, col)
+    rp, c, deg = G.add_self_loops(n, dev(rowptr), dev(col))
+    for got, ref in ((rp, rp_o), (c, c_o), (deg, deg_o)):
+        np.testing.assert_array_equal(host(got), ref)
+    for got, ref in zip(G.transpose(n, dev(rowptr), dev(col)), oracle.csr_transpose(rowptr, col)):
+        np.testing.assert_array_equal(host(got), ref)
+    rows = np.repeat(np.arange(n), np.diff(rowptr))
+    np.testing.assert_array_equal(host(G.expand(n, dev(rowptr), col.size)), rows)
+    val, ones = torch.empty(col.size, device="cuda"), torch.arange(1, n + 1, dtype=torch.int32, device="cuda")
+    B.gnn_aggregator_weights(B.GNN_AGG_MEAN, 0.0, n, dev(rowptr), dev(col), ones, val)
+    np.testing.assert_array_equal(host(val), np.float32(1) / (rows + 1).astype(np.float32))
+
+
+def stretched(nnz, gaps, seed):
+    """Rows of one to nine entries, with `gaps` (place among them, number) of empty rows in between."""
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(1, 10, nnz // 4)
+    lens = lens[np.cumsum(lens) < nnz]
+    lens = np.append(lens, nnz - lens.sum())
+    lens = np.insert(lens, np.repeat([int(at * lens.size) for at, _ in gaps], [k for _, k in gaps]), 0)
+    n = lens.size
+    rowptr = np.zeros(n + 1, np.int32)
+    np.cumsum(lens, out=rowptr[1:])
+    j = np.arange(nnz) - np.repeat(rowptr[:-1], lens)       # ascending: a random start and a step that fits
+    step = n // (int(lens.max()) + 1)
+    col = np.repeat(rng.integers(0, step, n), lens) + j * step
+    return n, rowptr, col.astype(np.int32)
+
+
+# a long run of empty rows inside one tile (of 1024, of 4096 and of 8192 entries): in front, between, at the end; a few beside it
+@pytest.mark.parametrize("nnz", [700, 8200, (1 << 20) + 4100])
+@pytest.mark.parametrize("gaps", [[(0, 40000)], [(0.5, 40000)], [(1, 40000)], [(0.3, 5), (0.31, 33000), (0.6, 70000), (1, 1)]])
+def test_long_runs_of_empty_rows(nnz, gaps):
+    check_setup(*stretched(nnz, gaps, seed=nnz))
+
+
+def test_empty_rows_cost_no_more_than_others():
+    """2^21 nodes without an edge against as many with one each."""
+    n = 1 << 21
+    cases = [(torch.zeros(n + 1, dtype=torch.int32, device="cuda"), torch.empty(0, dtype=torch.int32, device="cuda")),
+             (torch.arange(n + 1, dtype=torch.int32, device="cuda"), torch.arange(n, dtype=torch.int32, device="cuda").flip(0).contiguous())]
+    times = []
+    for rowptr, col in cases:
+        best = float("inf")
+        for _ in range(4):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            G.add_self_loops(n, rowptr, col)
+            end.record()
+            end.synchronize()
+            best = min(best, start.elapsed_time(end))
+        times.append(best)
+    assert times[0] < 3 * times[1], times
