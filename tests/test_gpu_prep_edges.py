@@ -1,4 +1,5 @@
-"""Preprocessing at the edges of its tiles (4096 entries; 8192 in the sort) and digits, bit for bit against the oracle."""
+"""Preprocessing at the edges of its tiles (1024 entries in lists below 2^20, 4096 in longer ones; 8192 in the sort) and
+digits, bit for bit against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -120,3 +121,38 @@ def test_empty_rows_cost_no_more_than_others():
             best = min(best, start.elapsed_time(end))
         times.append(best)
     assert times[0] < 3 * times[1], times
+
+
+# lists of 2^20 entries and more, in tiles of 4096: around the line, whole tiles, one entry more and less; empty rows here and there
+@pytest.mark.parametrize("nnz", [(1 << 20) - 1, 1 << 20, (1 << 20) + 1, (1 << 20) + 4095, (1 << 20) + 4097])
+def test_edges_of_long_lists(nnz):
+    check_setup(*stretched(nnz, [(0, 3), (0.25, 1), (0.5, 5000), (1, 2)], seed=nnz))
+
+
+def test_hub_rows_of_long_lists():
+    """Rows that fill several tiles of 4096 entries, and one that ends with one."""
+    lens = np.zeros(100000, np.int64)
+    lens[::7] = 70
+    lens[[0, 5, 50001, 99999]] = 40000, 8192, 12289, 4096
+    rowptr = np.zeros(lens.size + 1, np.int32)
+    np.cumsum(lens, out=rowptr[1:])
+    col = np.concatenate([np.arange(k) + i % (lens.size - k + 1) for i, k in enumerate(lens) if k]).astype(np.int32)
+    assert col.size > 1 << 20
+    check_setup(lens.size, rowptr, col)
+
+
+@pytest.mark.parametrize("count", [(1 << 24) - 1, 1 << 24, (1 << 24) + 4097])
+def test_scans_of_many_tiles(count):
+    """4096 tiles of 4096 elements, up to which the second kernel sums the tile totals, and more, where they are scanned: `count`
+    row lengths and a zero, an entry in every third row."""
+    entries = torch.arange(0, count, 3, device="cuda")
+    rowptr = (torch.arange(count + 1, device="cuda") + 2).div(3, rounding_mode="floor").int()
+    rp, c, deg = G.add_self_loops(count, rowptr, (entries == 0).int())
+    # row 3 i holds column 0 (row 0: column 1): a diagonal and an entry there, a diagonal elsewhere
+    at = torch.arange(count + 1, device="cuda")
+    assert bool((rp == at + (at + 2).div(3, rounding_mode="floor")).all())
+    has = at[:-1] % 3 == 0
+    assert bool((deg == 1 + has.int()).all()) and c.numel() == count + entries.numel()
+    first = c[rp[:-1].long()]
+    assert bool((first == torch.where(has, 0, at[:-1])).all())
+    assert bool((c[rp[:-1][has].long() + 1] == torch.where(at[:-1][has] == 0, 1, at[:-1][has])).all())
