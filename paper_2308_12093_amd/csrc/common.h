@@ -99,6 +99,7 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
                          const float *A2 = nullptr, const float *B2 = nullptr);
 
 // the plain products (gemm_split.hip): see there
+bool gemm_split_fits(int64_t M, int64_t N);
 size_t gemm_split_workspace_bytes(int64_t N, int64_t K);
 gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B, float *C,
                                int64_t ldc, const float *bias, int act, void *workspace, hipStream_t st,

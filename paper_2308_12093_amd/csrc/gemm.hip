@@ -740,21 +740,24 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
     const int tiles_m = (int)ceil_div(M, tile_m(f64, tl)), tiles_n = (int)ceil_div(N, tile_n(f64, tl));
     bool launched = false;
     if (!f64) {
+        // 32-bit counts of tiles and of steps; checked before the first launch, whichever kernel takes the product
+        const long total = (long)tiles_m * tiles_n;
+        if (total > INT32_MAX / 4 || total * ceil_div(K > 0 ? K : 1, 32) > INT32_MAX / 4) return GNN_ERR_UNSUPPORTED;
         // the kernel wants B with the reduction index contiguous: B[N][K]; transpose a [K][N] weight first
         const float *Bt = B, *Bt2 = B2;
         if (K <= 0) A2 = Bt2 = nullptr;                    // an empty reduction: nothing to add
         const bool signs = (relu & (kActRelu | kActSigns)) != 0;
         relu &= kActRelu | kActAccumulate;
         if (few_rows(M, N)) {
-            const long tn = ceil_div(N, 32), total = ceil_div(M, 32) * tn;
-            hipLaunchKernelGGL(gemm_few_kernel, dim3((unsigned)total), dim3(64), 0, st, (int)M, (int)N, (int)K, A, B, A2,
+            const long tn = ceil_div(N, 32);
+            hipLaunchKernelGGL(gemm_few_kernel, dim3((unsigned)(ceil_div(M, 32) * tn)), dim3(64), 0, st, (int)M, (int)N, (int)K, A, B, A2,
                                Bt2, tb ? 1L : (long)N, tb ? (long)K : 1L, C, (int)ldc, bias, relu, (int)tn);
             return launch_status();
         }
         const bool stream = (size_t)M * N * sizeof(float) > kStreamBytes && !(relu & kActAccumulate);
         // A product whose result decides signs (an activation in its own epilogue, or kActSigns) keeps the sums of
         // the fp32 instruction: a pre-activation within rounding of zero changes a gradient entry by its full size.
-        if (!signs && workspace && K >= 4)
+        if (!signs && workspace && K >= 4 && gemm_split_fits(M, N))
             return gemm_split_launch(tb, M, N, K, A, B, C, ldc, bias, stream ? relu | kActStream : relu, workspace, st, A2, B2);
         if (!tb && K > 0) {
             float *wt = static_cast<float *>(workspace);
@@ -774,8 +777,6 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
         const int vec_b = aligned16(Bt) && (!Bt2 || aligned16(Bt2)) && K % 4 == 0;
         if (stream) relu |= kActStream;
         // persistent blocks: 64 per XCD (2 per CU), each owning a contiguous range of tiles
-        const long total = (long)tiles_m * tiles_n;
-        if (total > INT32_MAX / 4 || total * ceil_div(K > 0 ? K : 1, 32) > INT32_MAX / 4) return GNN_ERR_UNSUPPORTED;
         const long per_xcd = ceil_div(total, 8);
         const int blocks_per_xcd = (int)(per_xcd < 64 ? per_xcd : 64);
         const int tiles_per_block = (int)ceil_div(per_xcd, blocks_per_xcd);

@@ -408,15 +408,20 @@ size_t parts_bytes(int64_t N, int64_t K) {
     return align_up((size_t)(ceil_div(N, 32 * w) * w) * ceil_div(K, KB) * kStepBytes);
 }
 
+int64_t split_blocks(int64_t M, int64_t N) { return 8 * ceil_div(ceil_div(M, 128) * ceil_div(N, 32 * tiles_wide(N)), 8); }
+
 }  // namespace
+
+// a grid has less than 2^32 threads
+bool gemm_split_fits(int64_t M, int64_t N) { return split_blocks(M, N) < (int64_t)1 << 24; }
 
 // scratch of one operand pair: the parts of B, then a Range per 32 columns
 size_t gemm_split_workspace_bytes(int64_t N, int64_t K) {
     return parts_bytes(N, K) + align_up((size_t)(ceil_div(N, 32) + 3) * sizeof(Range));
 }
 
-// C [M][N], rows ldc apart = A [M][K] op(B) (+ A2 op(B2)), K >= 4; tb: B is [N][K], else [K][N].  workspace:
-// gemm_split_workspace_bytes per operand pair.
+// C [M][N], rows ldc apart = A [M][K] op(B) (+ A2 op(B2)), K >= 4 and gemm_split_fits; tb: B is [N][K], else
+// [K][N].  workspace: gemm_split_workspace_bytes per operand pair.
 gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B, float *C,
                                int64_t ldc, const float *bias, int act, void *workspace, hipStream_t st,
                                const float *A2, const float *B2) {
@@ -437,9 +442,7 @@ gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const fl
     hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)(g.tiles_n * w), A2 ? 2 : 1), dim3(1024), 0, st, (int)N,
                        (int)K, g.steps, g.B, g.B2, ws, ws2, range, range2);
     GNN_TRY(launch_status());
-    const long total = (long)g.tiles_m * g.tiles_n;
-    if (total > INT32_MAX / 2) return GNN_ERR_UNSUPPORTED;
-    const dim3 grid((unsigned)(8 * ceil_div(total, 8)));
+    const dim3 grid((unsigned)split_blocks(M, N));
     const size_t lds = (size_t)2 * w * kStepBytes;
     if (w == 1) hipLaunchKernelGGL((gemm_split_kernel<1, 1>), grid, dim3(256), lds, st, g);
     else if (w == 2) hipLaunchKernelGGL((gemm_split_kernel<1, 2>), grid, dim3(256), lds, st, g);

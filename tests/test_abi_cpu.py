@@ -264,6 +264,13 @@ def test_transposed_product_has_room_for_a_chunk_of_every_shape(M, N, K):
     assert B.gnn_gemm_workspace_bytes(1, 0, M, N, K) >= 8 * M * N
 
 
+@pytest.mark.parametrize("trans_b,relu", [(0, 0), (1, 0), (0, 1), (1, 1)])
+def test_products_beyond_the_step_count_are_refused_before_any_launch(trans_b, relu):
+    """More than 2^29 steps of 128 x 128 x 32, whichever kernel the product would take."""
+    one, m = ctypes.c_void_p(256), 65664
+    assert B.lib.gnn_gemm(0, trans_b, m, m, m, one, one, one, None, relu, one, 1 << 40, None) == B.GNN_ERR_UNSUPPORTED
+
+
 # ---- calibrated selection and constant inputs (host logic) --------------------------------
 def model_us(n, nnz, f):
     """The documented time model, evaluated here from the text of the header."""
