@@ -522,19 +522,21 @@ gemm_f32_kernel(int M, int N, int K, const float *__restrict__ A, const float *_
 
 // The same product for few rows, bit for bit: one wavefront per 32 x 32 tile, operands straight from memory into
 // registers in the order the instruction takes them (the lower lane half k = 0..15 of a step of 32, the upper 16..31),
-// three steps ahead (six: the same there, 32768 x 128 x 64 12 -> 16 us).  Latency bound: the 256 instructions of a 512-long reduction take 7 us by themselves.  No LDS, no
-// transposed copy of B.  2048 x 512 by 512 x 16 took 20.4 us through the kernel above (16 blocks, one barrier per
-// step, and the copy), 16.3 now; 3001 x 203 by 203 x 7 24.4 and 9.8.
+// three steps ahead (six: the same there, 32768 x 128 x 64 12 -> 16 us).  Latency bound: the 256 instructions of a
+// 512-long reduction take 7 us by themselves.  No LDS, no transposed copy of B.  2048 x 512 by 512 x 16 took 20.4 us
+// through the kernel above (16 blocks, one barrier per step, and the copy), 16.3 now; 3001 x 203 by 203 x 7 24.4 and 9.8.
+// TB: B is [N][K], a lane's column read like a row of A; else [K][N].
+template <bool TB>
 __global__ void __launch_bounds__(64)
 gemm_few_kernel(int M, int N, int K, const float *__restrict__ A, const float *__restrict__ B,
-                const float *__restrict__ A2, const float *__restrict__ B2, long sk, long sn, float *__restrict__ C,
-                int ldc, const float *__restrict__ bias, int relu, int tiles_n) {
+                const float *__restrict__ A2, const float *__restrict__ B2, float *__restrict__ C, int ldc,
+                const float *__restrict__ bias, int relu, int tiles_n) {
     constexpr int AHEAD = 3;
     const int lane = threadIdx.x, l32 = lane % 32, half = lane / 32;
     const int m0 = (int)(blockIdx.x / tiles_n) * 32, n = (int)(blockIdx.x % tiles_n) * 32 + l32;
     const int kt1 = (K + BK - 1) / BK, total = A2 ? 2 * kt1 : kt1;
     const size_t ro = (size_t)min(m0 + l32, M - 1) * K;    // rows and columns past the end re-read the last one
-    const long co = min(n, N - 1) * sn;
+    const size_t sk = TB ? 1 : N, co = (size_t)min(n, N - 1) * (TB ? K : 1);
     float x[AHEAD][16], y[AHEAD][16];
     auto load = [&](int step, float (&xs)[16], float (&ys)[16]) __attribute__((always_inline)) {
         const bool second = step >= kt1;
@@ -545,9 +547,15 @@ gemm_few_kernel(int M, int N, int K, const float *__restrict__ A, const float *_
             for (int i = 0; i < 4; ++i) {
                 const floatx4u v = *reinterpret_cast<const floatx4u *>(a + k0 + 4 * i);
                 xs[4 * i] = v.x; xs[4 * i + 1] = v.y; xs[4 * i + 2] = v.z; xs[4 * i + 3] = v.w;
+                if constexpr (TB) {
+                    const floatx4u w = *reinterpret_cast<const floatx4u *>(b + k0 + 4 * i);
+                    ys[4 * i] = w.x; ys[4 * i + 1] = w.y; ys[4 * i + 2] = w.z; ys[4 * i + 3] = w.w;
+                }
             }
+            if constexpr (!TB) {
 #pragma unroll
-            for (int j = 0; j < 16; ++j) ys[j] = b[(k0 + j) * sk];
+                for (int j = 0; j < 16; ++j) ys[j] = b[(k0 + j) * sk];
+            }
         } else {
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
@@ -667,16 +675,41 @@ int pick_splits(int ta, int64_t M, int64_t N, int64_t K) {
     return s < 1 ? 1 : (int)s;                             // more than 256 tiles in one chunk each: no multiple to round to
 }
 
-// One wavefront per 32 x 32 tile while there are few; beyond, the kernels that share operands through LDS.
-// Both sides of the line (fp32 kernel / one wavefront per tile): 4096 x 256 x 256, 1024 tiles, 26.9 / 14.3 us;
-// 16384 x 256 x 64, 1024, 18.0 / 14.2; 49152 x 128 x 32, 1536, 12.7 / 13.4; 65536 x 512 x 16, 2048, 34.2 / 36.6; 50021 x 96 x 64, 3128, 17.8 / 18.6; 16384 x 256 x 256, 4096, 31.0 / 47.5.
-bool few_rows(int64_t M, int64_t N) { return ceil_div(M, 32) * ceil_div(N, 32) <= 1024; }
+// One wavefront per 32 x 32 tile while there are few; beyond, the kernels that share operands through LDS.  Both sides of
+// the line (fp32 kernel / one wavefront per tile, us): 4096 x 256 x 256, 1024 tiles, 26 / 14; 16384 x 256 x 64, 4096, 18 / 14
+// and 16384 x 256 x 256 31 / 48; 49152 x 128 x 32 12.7 / 13.4; 65536 x 512 x 16 34 / 37; 50021 x 96 x 64 17.8 / 18.6.
+bool few_tiles(int64_t M, int64_t N) { return ceil_div(M, 32) * ceil_div(N, 32) <= 1024; }
+
+// One column tile and a chip full of rows is what the LDS kernels are made for as well: they read whole lines, which tells
+// in long reductions.  32768 x 32, B transposed: K = 64 7.5 / 7.5, 128 7.9 / 10, 512 18 / 22; B as it is, behind its
+// transposed copy: 256 14.5 / 14.9, 512 22 / 25; up to 16 columns 32768 x 7 x 256 equal, 512 20 / 21.
+bool few_rows(int tb, int64_t M, int64_t N, int64_t K) {
+    return few_tiles(M, N) && !(N <= 32 && M > 8192 && K % 4 == 0 && K >= (tb && N > 16 ? 128 : 384));
+}
+
+// Where the fp32 instruction is faster than split parts all the same (K: indices of all operand pairs; aligned rows).  fp32 /
+// parts in us, tb where B is [N][K] and the fp32 kernel needs no launch before it:
+//   32 columns, a whole tile: tb always (65536 x 32 10.2 / 14.4 at K = 128, 2^20 138 / 149); else A from 64 MB on (2^18 x 64
+//     23 / 26, 2^20 x 100 134 / 147, 2^20 x 300 314 / 373; below, 131072 x 64 15.5 / 15.0);
+//   fewer: tb and few rows (40000 x 16 x 4 7.8 / 9.2, 65536 x 16 x 128 12.1 / 13.5; 131072 x 16 x 64 15 / 13), and long
+//     reductions over a large A (2^20 x 8 x 300 295 / 362, 2^19 x 16 x 160 89 / 92; but 2^20 x 16 x 64 94 / 73);
+//   64: tb, few rows, short reductions (65536 x 64 x 32 10 / 11.2, x 64 11 / 13; 131072 x 64 x 16 14 / 14);
+//   whole tiles of 128 columns: short reductions into outputs of 1 GB (2^21 x 128 x 4 236 / 278, 2^20 x 256 x 16 243 / 267,
+//     3 000 000 x 256 x 24 696 / 738; but 2^20 x 256 x 48 392 / 333, 2^21 x 128 x 32 298 / 262, 2^19 x 256 x 16 148 / 136);
+//   and what few_rows leaves to it (15000 x 30 x 448 20 / 23, 30000 x 10 x 1000 36 / 47).
+bool fp32_pays(int tb, int64_t M, int64_t N, int64_t K) {
+    if (few_tiles(M, N)) return true;
+    if (N == 32) return tb || (K >= 64 && M * K >= 1 << 24);
+    if (N < 32) return (tb && M <= 65536) || (K >= 160 && M * K >= 1 << 26);
+    if (N == 64) return tb && M <= 65536 && K <= 128;
+    return N % 128 == 0 && K <= (N > 128 ? 32 : 16) && M * N >= 1 << 28;
+}
 
 }  // namespace
 
 size_t gemm_workspace_bytes(int ta, int tb, int64_t M, int64_t N, int64_t K) {
     if (!ta) {                                             // B^T for the one kernel, the parts of B for the other
-        if (M <= 0 || N <= 0 || K <= 0 || few_rows(M, N)) return kAlign;
+        if (M <= 0 || N <= 0 || K <= 0 || few_rows(tb, M, N, K)) return kAlign;
         const size_t parts = gemm_split_workspace_bytes(N, K);
         const size_t bt = tb ? kAlign : align_up((size_t)N * K * sizeof(float));
         return parts > bt ? parts : bt;
@@ -748,16 +781,17 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
         if (K <= 0) A2 = Bt2 = nullptr;                    // an empty reduction: nothing to add
         const bool signs = (relu & (kActRelu | kActSigns)) != 0;
         relu &= kActRelu | kActAccumulate;
-        if (few_rows(M, N)) {
+        if (few_rows(tb, M, N, K)) {
             const long tn = ceil_div(N, 32);
-            hipLaunchKernelGGL(gemm_few_kernel, dim3((unsigned)(ceil_div(M, 32) * tn)), dim3(64), 0, st, (int)M, (int)N, (int)K, A, B, A2,
-                               Bt2, tb ? 1L : (long)N, tb ? (long)K : 1L, C, (int)ldc, bias, relu, (int)tn);
+            hipLaunchKernelGGL(tb ? gemm_few_kernel<true> : gemm_few_kernel<false>, dim3((unsigned)(ceil_div(M, 32) * tn)),
+                               dim3(64), 0, st, (int)M, (int)N, (int)K, A, B, A2, Bt2, C, (int)ldc, bias, relu, (int)tn);
             return launch_status();
         }
         const bool stream = (size_t)M * N * sizeof(float) > kStreamBytes && !(relu & kActAccumulate);
         // A product whose result decides signs (an activation in its own epilogue, or kActSigns) keeps the sums of
         // the fp32 instruction: a pre-activation within rounding of zero changes a gradient entry by its full size.
-        if (!signs && workspace && K >= 4 && gemm_split_fits(M, N))
+        const bool rows16 = K % 4 == 0 && aligned16(A) && (!A2 || aligned16(A2)) && (!tb || (aligned16(B) && (!B2 || aligned16(B2))));
+        if (!signs && workspace && K >= 4 && gemm_split_fits(M, N) && !(rows16 && fp32_pays(tb, M, N, A2 ? 2 * K : K)))
             return gemm_split_launch(tb, M, N, K, A, B, C, ldc, bias, stream ? relu | kActStream : relu, workspace, st, A2, B2);
         if (!tb && K > 0) {
             float *wt = static_cast<float *>(workspace);

@@ -97,3 +97,15 @@ def test_small_operands_that_do_not_matter():
     A0, B0 = A.clone(), Bm.clone()
     A0[::3, 5], B0[11] = 0.0, 0.0
     assert bool((product(M, N, K, A, Bm, 0) == product(M, N, K, A0, B0, 0)).all())
+
+
+# long reductions of a narrow output; 32 columns; fewer, few rows or a large first operand; 64 columns and few rows
+@pytest.mark.parametrize("tb,M,N,K", [(1, 12288, 32, 128), (0, 9000, 24, 384), (0, 8225, 7, 1000), (1, 40000, 32, 4), (0, 262144, 32, 64),
+                                      (1, 40001, 16, 64), (1, 33000, 1, 4), (0, 420000, 20, 160), (1, 50000, 64, 128)])
+def test_fp32_instruction_where_it_is_faster(tb, M, N, K):
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, Bm = torch.randn(M, K, generator=gen, device="cuda"), torch.randn(K, N, generator=gen, device="cuda")
+    C = product(M, N, K, A, Bm, tb)
+    assert bool((torch.relu(C) == product(M, N, K, A, Bm, tb, relu=1)).all())      # the same sums as before an activation
+    bound = (K + 4) * 2.0 ** -24 * (A.abs().double() @ Bm.abs().double())
+    assert bool(((C.double() - A.double() @ Bm.double()).abs() <= bound).all())
