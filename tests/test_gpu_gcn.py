@@ -278,3 +278,22 @@ def test_layer_calls_can_be_captured_in_a_hip_graph_and_replayed(B, G):
             torch.cuda.synchronize()
             for got, ref, name in zip((Y, dW, dX), eager, ("Y", "dW", "dX")):
                 assert np.array_equal(host(got), ref), f"{scheme} replay {replay}: {name}"
+
+
+# the masked gradient and the bias gradient in two passes (few rows and wide ones; odd ones from 64 MB on) and in one
+@pytest.mark.parametrize("n,k", [(500, 260), (16383, 260), (16384, 260), (2000, 257), (360000, 47), (350000, 47), (4000, 1000)])
+def test_bias_gradient_with_the_mask(B, n, k):
+    m, gen = 8, torch.Generator(device="cuda").manual_seed(n + k)
+    ids = torch.arange(n + 1, dtype=torch.int32, device="cuda")       # A' is the identity
+    g = B.Graph(n, ids, ids[:n].clone(), torch.ones(n, device="cuda"), ids[:n].clone(), symmetric=True)
+    plan = B.Plan(B.GNN_LAYER_GCN, n, n, m, k, need_input_grad=True, has_bias=True, fuse_relu=True)
+    X, W, Y, dY = (torch.randn(*s, generator=gen, device="cuda") for s in ((n, m), (m, k), (n, k), (n, k)))
+    dW, db, dX = torch.empty(m, k, device="cuda"), torch.empty(k, device="cuda"), torch.empty(n, m, device="cuda")
+    cache, ws = B.alloc(plan.info.cache_bytes), B.alloc(plan.info.workspace_bytes)
+    B.gcn_layer_fwd(plan, g, X, W, torch.zeros(k, device="cuda"), torch.empty(n, k, device="cuda"), cache, ws)
+    B.gcn_layer_bwd(plan, g, X, W, Y, dY, dW, db, dX, cache, ws)
+    G_ = (dY * (Y > 0)).double()
+    for got, ref, size in ((db, G_.sum(0), G_.abs().sum(0)), (dW, X.double().t() @ G_, X.double().abs().t() @ G_.abs())):
+        assert bool(((got.double() - ref).abs() <= 2.0 ** -24 * ref.abs() + 2 * n * 2.0 ** -53 * size).all())     # sums in double
+    bound = (8 * ((k + 15) // 16) + 4) * 2.0 ** -24 * (G_.abs() @ W.double().abs().t())      # eight roundings per 16 indices
+    assert bool(((dX.double() - G_ @ W.double().t()).abs() <= bound).all())
