@@ -211,6 +211,30 @@ gemm_split_kernel(Product g) {
             }
         }
     };
+    // Rows that begin with tiny values (a saturated node's gradient) are taken times a power of two and their results
+    // back, in a wavefront that has one.  Formed again, one such row in 32 costs four times the product: 128 -> 512 over
+    // 2^17 rows 606 us, 512 -> 128 717, with the power of two 152 and 136 (without such rows 152 and 133).
+    float scale[RT];
+    bool scaled = false;                                     // uniform
+    auto fit = [&]() __attribute__((always_inline)) {       // from the first step, once it is settled
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            float top = 0.f;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) top = fmaxf(top, fabsf(raw[r][j / 4][j % 4]));
+            top = fmaxf(top, __shfl_xor(top, 32, 64));
+            const bool low = top > 0.f && top < 0x1p-90f;
+            scale[r] = low ? ldexpf(1.f, min(-ilogbf(top), 126)) : 1.f;
+            scaled |= __any(low) != 0;
+        }
+    };
+    auto apply = [&]() __attribute__((always_inline)) {
+        if (!scaled) return;
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) raw[r][i] *= scale[r];
+    };
     // global -> LDS, 1 KB per wavefront and instruction: the 6 NT fragments of a step are dealt to the four wavefronts
     auto stage = [&](int step, int buf) __attribute__((always_inline)) {
         const bool second = step >= g.steps;
@@ -253,6 +277,8 @@ gemm_split_kernel(Product g) {
         if (more) stage(step + 1, buf ^ 1);
         bf16x8 a[2][RT][3];
         settle(step);
+        if (step == 0) fit();
+        apply();
 #pragma unroll
         for (int ins = 0; ins < 2; ++ins)
 #pragma unroll
@@ -303,13 +329,14 @@ gemm_split_kernel(Product g) {
         // Some operand lost up to 2^-134: a result is off by at most K 2^-134 times the largest magnitude it met (the
         // rows' for a tiny B, the column tile's for a tiny row).  Where that is below the rounding of the result nothing
         // is lost: rows that hold a saturated probability beside ordinary values, weights that have decayed.
-        float top[RT];                                       // of the row, read once more
+        float top[RT];                                       // of the row, read once more for a tiny B
 #pragma unroll
         for (int r = 0; r < RT; ++r) top[r] = 0.f;
 #pragma unroll 1
-        for (int step = 0; step < total; ++step) {
+        for (int step = 0; step < total && small_b < kTinyCode; ++step) {
             load(step);
             settle(step);
+            apply();
 #pragma unroll
             for (int r = 0; r < RT; ++r)
 #pragma unroll
@@ -344,6 +371,7 @@ gemm_split_kernel(Product g) {
     }
     if (__any(bad)) {
         clear();
+        scaled = false;
         for (int step = 0; step < total; ++step) {
             load(step);
             settle(step);
@@ -364,6 +392,16 @@ gemm_split_kernel(Product g) {
     }
 
     // accumulator register v of lane (half, l): row 8 (v / 4) + 4 half + v % 4, column l of its 32 x 32 tile
+    if (scaled) {
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float back = 1.f / __shfl(scale[r], 8 * (v / 4) + 4 * half + v % 4, 64);
+#pragma unroll
+                for (int c = 0; c < NT; ++c) acc[r][c][v] *= back;
+            }
+    }
 #pragma unroll
     for (int c = 0; c < NT; ++c) {
         const int n = (ct0 + c) * 32 + l;

@@ -109,3 +109,22 @@ def test_fp32_instruction_where_it_is_faster(tb, M, N, K):
     assert bool((torch.relu(C) == product(M, N, K, A, Bm, tb, relu=1)).all())      # the same sums as before an activation
     bound = (K + 4) * 2.0 ** -24 * (A.abs().double() @ Bm.abs().double())
     assert bool(((C.double() - A.double() @ Bm.double()).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("N,K", [(70, 40), (256, 33), (33, 200)])
+def test_rows_of_tiny_values(N, K, tb):
+    """Rows of 2^-85 .. 2^-149, some with larger values later on, beside ordinary rows and rows of zeros."""
+    M = 70000
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    A, Bm = torch.randn(M, K, generator=gen, device="cuda"), torch.randn(K, N, generator=gen, device="cuda")
+    A[::3] *= 2.0 ** -(85.0 + torch.arange(A[::3].shape[0], device="cuda") % 65)[:, None]
+    A[1::21] = 0.0
+    A[2::33, :32] *= 2.0 ** -100                            # tiny in the first 32 places only
+    A[4::33, :32] *= 2.0 ** -140
+    A[5::1000, 0], A[6::1000, K - 1] = float("inf"), 1e38
+    C, ref = product(M, N, K, A, Bm, tb).double(), A.double() @ Bm.double()
+    bound = (8 * ((K + 15) // 16) + 4) * 2.0 ** -24 * (A.abs().double() @ Bm.abs().double()) + K * 2.0 ** -149
+    fine = torch.isfinite(ref) & (ref.abs() < 3e38)
+    assert bool(((C - ref).abs() <= bound)[fine].all())
+    assert bool((torch.isinf(C) | torch.isnan(C))[5::1000].all())
