@@ -135,16 +135,6 @@ __device__ __forceinline__ long xcd_tile(long total) {
     return blockIdx.x / 8 < per ? id : total;
 }
 
-// a lane's 4 of the 16 indices of its half: A[row][k .. k + 3], zeros past K
-__device__ __forceinline__ floatx4 load_row4(const float *row, int k, int K) {
-    if (k + 4 <= K) return *reinterpret_cast<const float4u *>(row + k);
-    floatx4 v = {0.f, 0.f, 0.f, 0.f};
-    if (k < K) v.x = row[k];
-    if (k + 1 < K) v.y = row[k + 1];
-    if (k + 2 < K) v.z = row[k + 2];
-    return v;
-}
-
 __device__ __forceinline__ void put(const Product &g, float *at, float o, float bias) {
     o += bias;
     if (g.act & kActAccumulate) o += *at;
@@ -154,18 +144,18 @@ __device__ __forceinline__ void put(const Product &g, float *at, float o, float 
 }
 
 // ---- the product ------------------------------------------------------------------------------------------
-// A block of four wavefronts owns 4 x 32 RT rows and 32 NT columns.  A lane reads its 16 consecutive floats of a row
+// A block of four wavefronts owns 4 x 32 rows and 32 NT columns.  A lane reads its 16 consecutive floats of a row
 // straight into registers (the two lane halves take a row's whole 128-byte line, in one go, one step ahead) and splits
 // them there: a row is split once per column tile and never passes through LDS.  The parts of B, split beforehand, are
 // shared by the block: copied to LDS without touching registers, 6 NT KB per step, double-buffered, one barrier per
-// step.  RT = 1 leaves three to four wavefronts per SIMD: loads, splitting, matrix instructions and stores of a block
-// hardly overlap, those of different blocks do (RT = 2, two wavefronts: the same within 5 %, 24 % slower at 65536 rows
+// step.  Three to four wavefronts fit a SIMD: loads, splitting, matrix instructions and stores of a block hardly overlap,
+// those of different blocks do (64 rows a wavefront, two of them a SIMD: the same within 5 %, 24 % slower at 65536 rows
 // and 64 columns).  At 2^17 rows, against the fp32 instruction (K -> N): 128 -> 512 201 -> 167 us,
 // 512 -> 128 159 -> 137, 256 -> 256 158 -> 119, 128 -> 128 51 -> 43, 256 -> 64 47 -> 39 (4.3 TB/s); at 2^20 rows
 // 100 -> 256 773 -> 564, 47 -> 256 594 -> 328, 256 -> 47 414 -> 313; at 2^22 64 -> 256 1551 -> 1424, 256 -> 64 1378 ->
 // 1226 (4.4 TB/s: what a copy reaches).  Matrix instructions, stores and loads still add up more than they overlap:
 // without the stores 128 -> 512 takes 115 us, with a sixth of the matrix instructions 117.
-template <int RT, int NT>
+template <int NT>
 __global__ void __launch_bounds__(256, NT == 4 ? 3 : 4)
 gemm_split_kernel(Product g) {
     extern __shared__ __align__(16) char lds[];
@@ -174,25 +164,21 @@ gemm_split_kernel(Product g) {
     if (tile >= (long)g.tiles_m * g.tiles_n) return;
     const int t = threadIdx.x, lane = t % 64, wave = __builtin_amdgcn_readfirstlane(t / 64);
     const int l = lane % 32, half = lane / 32;
-    const int row0 = (int)(tile / g.tiles_n) * (128 * RT) + wave * (32 * RT);
+    const int row0 = (int)(tile / g.tiles_n) * 128 + wave * 32;
     const int ct0 = (int)(tile % g.tiles_n) * NT;           // first 32-column tile
     const int total = g.A2 ? 2 * g.steps : g.steps;
 
-    size_t ro[RT];                                           // rows past the end re-read the last one
-#pragma unroll
-    for (int r = 0; r < RT; ++r) ro[r] = (size_t)min(row0 + 32 * r + l, g.M - 1) * g.K;
+    const size_t ro = (size_t)min(row0 + l, g.M - 1) * g.K;   // rows past the end re-read the last one
 
     // Four indices at a time, at any 4-byte aligned address; the ones that would run over the row's end are read from
     // its last four floats instead (K >= 4) and put in place by `settle`, so no load stands behind a branch.
-    floatx4 raw[RT][4];
+    floatx4 raw[4];
     auto load = [&](int step) __attribute__((always_inline)) {
         const bool second = step >= g.steps;
         const float *A = second ? g.A2 : g.A;
         const int k = (second ? step - g.steps : step) * KB + 16 * half;
 #pragma unroll
-        for (int r = 0; r < RT; ++r)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) raw[r][i] = *reinterpret_cast<const float4u *>(A + ro[r] + min(k + 4 * i, g.K - 4));
+        for (int i = 0; i < 4; ++i) raw[i] = *reinterpret_cast<const float4u *>(A + ro + min(k + 4 * i, g.K - 4));
     };
     auto settle = [&](int step) __attribute__((always_inline)) {
         const int k0 = (step >= g.steps ? step - g.steps : step) * KB;
@@ -202,38 +188,32 @@ gemm_split_kernel(Product g) {
             // floats past the end: 0 none .. 4 all; a shift by one, by two and by four places
             const int over = min(max(k0 + 16 * half + 4 * i + 4 - g.K, 0), 4);
             const bool one = over & 1, two = over & 2, all = over & 4;
-#pragma unroll
-            for (int r = 0; r < RT; ++r) {
-                floatx4 v = raw[r][i];
-                v = floatx4{one ? v.y : v.x, one ? v.z : v.y, one ? v.w : v.z, one ? 0.f : v.w};
-                v = floatx4{two ? v.z : v.x, two ? v.w : v.y, two ? 0.f : v.z, two ? 0.f : v.w};
-                raw[r][i] = floatx4{all ? 0.f : v.x, all ? 0.f : v.y, all ? 0.f : v.z, all ? 0.f : v.w};
-            }
+            floatx4 v = raw[i];
+            v = floatx4{one ? v.y : v.x, one ? v.z : v.y, one ? v.w : v.z, one ? 0.f : v.w};
+            v = floatx4{two ? v.z : v.x, two ? v.w : v.y, two ? 0.f : v.z, two ? 0.f : v.w};
+            raw[i] = floatx4{all ? 0.f : v.x, all ? 0.f : v.y, all ? 0.f : v.z, all ? 0.f : v.w};
         }
     };
     // Rows that begin with tiny values (a saturated node's gradient) are taken times a power of two and their results
     // back, in a wavefront that has one.  Formed again, one such row in 32 costs four times the product: 128 -> 512 over
     // 2^17 rows 606 us, 512 -> 128 717, with the power of two 152 and 136 (without such rows 152 and 133).
-    float scale[RT];
+    __shared__ float s_scale[128];                           // of the block's rows; a wavefront reads its own alone
+    float *scale = s_scale + wave * 32;
     bool scaled = false;                                     // uniform
     auto fit = [&]() __attribute__((always_inline)) {       // from the first step, once it is settled
+        float top = 0.f;
 #pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            float top = 0.f;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) top = fmaxf(top, fabsf(raw[r][j / 4][j % 4]));
-            top = fmaxf(top, __shfl_xor(top, 32, 64));
-            const bool low = top > 0.f && top < 0x1p-90f;
-            scale[r] = low ? ldexpf(1.f, min(-ilogbf(top), 126)) : 1.f;
-            scaled |= __any(low) != 0;
-        }
+        for (int j = 0; j < 16; ++j) top = fmaxf(top, fabsf(raw[j / 4][j % 4]));
+        top = fmaxf(top, __shfl_xor(top, 32, 64));
+        const bool low = top > 0.f && top < 0x1p-90f;
+        scaled = __any(low);
+        if (scaled) scale[l] = low ? ldexpf(1.f, min(-ilogbf(top), 126)) : 1.f;     // both halves of a row the same
     };
     auto apply = [&]() __attribute__((always_inline)) {
         if (!scaled) return;
+        const float by = scale[l];
 #pragma unroll
-        for (int r = 0; r < RT; ++r)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) raw[r][i] *= scale[r];
+        for (int i = 0; i < 4; ++i) raw[i] *= by;
     };
     // global -> LDS, 1 KB per wavefront and instruction: the 6 NT fragments of a step are dealt to the four wavefronts
     auto stage = [&](int step, int buf) __attribute__((always_inline)) {
@@ -251,19 +231,15 @@ gemm_split_kernel(Product g) {
         }
     };
 
-    floatx16 acc[RT][NT];
+    floatx16 acc[NT];
     auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < RT; ++r)
+        for (int c = 0; c < NT; ++c)
 #pragma unroll
-            for (int c = 0; c < NT; ++c)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
     };
     clear();
-    unsigned least[RT];                                      // of this lane's half of the row
-#pragma unroll
-    for (int r = 0; r < RT; ++r) least[r] = ~0u;
+    unsigned least = ~0u;                                   // of this lane's half of the row
 
     stage(0, 0);
     load(0);
@@ -275,14 +251,12 @@ gemm_split_kernel(Product g) {
         const int buf = step & 1;
         const bool more = step + 1 < total;
         if (more) stage(step + 1, buf ^ 1);
-        bf16x8 a[2][RT][3];
+        bf16x8 a[2][3];
         settle(step);
         if (step == 0) fit();
         apply();
 #pragma unroll
-        for (int ins = 0; ins < 2; ++ins)
-#pragma unroll
-            for (int r = 0; r < RT; ++r) split8(raw[r][2 * ins], raw[r][2 * ins + 1], a[ins][r], least[r]);
+        for (int ins = 0; ins < 2; ++ins) split8(raw[2 * ins], raw[2 * ins + 1], a[ins], least);
         load(min(step + 1, total - 1));                    // the last step again after the last: no branch, no use
 #pragma unroll
         for (int c = 0; c < NT; ++c) {
@@ -290,82 +264,68 @@ gemm_split_kernel(Product g) {
 #pragma unroll
             for (int i = 0; i < 6; ++i)
                 b[i / 3][i % 3] = *reinterpret_cast<const bf16x8 *>(lds + buf * STAGE + c * kStepBytes + i * kFragBytes + lane * 16);
+            floatx16 small;
 #pragma unroll
-            for (int r = 0; r < RT; ++r) {
-                floatx16 small;
+            for (int v = 0; v < 16; ++v) small[v] = 0.f;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) small[v] = 0.f;
-#pragma unroll
-                for (int i = 0; i < kProducts - 1; ++i)
-#pragma unroll
-                    for (int ins = 0; ins < 2; ++ins)
-                        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ins][r][kPartA[i]], b[ins][kPartB[i]], small, 0, 0, 0);
+            for (int i = 0; i < kProducts - 1; ++i)
 #pragma unroll
                 for (int ins = 0; ins < 2; ++ins)
-                    acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ins][r][0], b[ins][0], acc[r][c], 0, 0, 0);
-                acc[r][c] += small;
-            }
+                    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ins][kPartA[i]], b[ins][kPartB[i]], small, 0, 0, 0);
+#pragma unroll
+            for (int ins = 0; ins < 2; ++ins)
+                acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ins][0], b[ins][0], acc[c], 0, 0, 0);
+            acc[c] += small;
         }
     }
 
     // what the parts cannot hold: see the top of the file
     float finite = 0.f;
-    unsigned small_a = ~0u, small_b = ~0u;
+    unsigned least_b = ~0u;
 #pragma unroll
-    for (int r = 0; r < RT; ++r) {
-        small_a = min(small_a, least[r]);
+    for (int c = 0; c < NT; ++c)
 #pragma unroll
-        for (int c = 0; c < NT; ++c)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) finite = fmaf(acc[r][c][v], 0.f, finite);
-    }
+        for (int v = 0; v < 16; ++v) finite = fmaf(acc[c][v], 0.f, finite);
 #pragma unroll
     for (int c = 0; c < NT; ++c) {
-        small_b = min(small_b, g.range[ct0 + c].least);
-        if (g.A2) small_b = min(small_b, g.range2[ct0 + c].least);
+        least_b = min(least_b, g.range[ct0 + c].least);
+        if (g.A2) least_b = min(least_b, g.range2[ct0 + c].least);
     }
     bool bad = finite != 0.f;                                // 0 x (inf or NaN) is NaN
-    if (!__any(bad) && __any(min(small_a, small_b) < kTinyCode)) {
+    if (!__any(bad) && __any(min(least, least_b) < kTinyCode)) {
         // Some operand lost up to 2^-134: a result is off by at most K 2^-134 times the largest magnitude it met (the
         // rows' for a tiny B, the column tile's for a tiny row).  Where that is below the rounding of the result nothing
         // is lost: rows that hold a saturated probability beside ordinary values, weights that have decayed.
-        float top[RT];                                       // of the row, read once more for a tiny B
-#pragma unroll
-        for (int r = 0; r < RT; ++r) top[r] = 0.f;
+        float top = 0.f;                                     // of the row, read once more for a tiny B
 #pragma unroll 1
-        for (int step = 0; step < total && small_b < kTinyCode; ++step) {
+        for (int step = 0; step < total && least_b < kTinyCode; ++step) {
             load(step);
             settle(step);
             apply();
 #pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) top[r] = fmaxf(top[r], fabsf(raw[r][j / 4][j % 4]));
+            for (int j = 0; j < 16; ++j) top = fmaxf(top, fabsf(raw[j / 4][j % 4]));
         }
         const float lost = 0x1p-110f * (float)(g.A2 ? 2L * g.K : (long)g.K);   // 2^24 times what a unit magnitude loses
+        // a bit per row, from both halves of it
+        unsigned long long row_tiny = __ballot(least < kTinyCode), row_zero = __ballot(top == 0.f);
+        row_tiny |= row_tiny >> 32;
+        row_zero &= row_zero >> 32;
+        const unsigned tiny = (unsigned)row_tiny >> (4 * half), zero = (unsigned)row_zero >> (4 * half);
 #pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            // a bit per row, from both halves of it
-            unsigned long long row_tiny = __ballot(least[r] < kTinyCode), row_zero = __ballot(top[r] == 0.f);
-            row_tiny |= row_tiny >> 32;
-            row_zero &= row_zero >> 32;
-            const unsigned tiny = (unsigned)row_tiny >> (4 * half), zero = (unsigned)row_zero >> (4 * half);
+        for (int d = 32; d >= 1; d >>= 1) top = fmaxf(top, __shfl_xor(top, d, 64));
 #pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) top[r] = fmaxf(top[r], __shfl_xor(top[r], d, 64));
+        for (int c = 0; c < NT; ++c) {
+            Range b = g.range[ct0 + c];
+            if (g.A2) {
+                const Range b2 = g.range2[ct0 + c];
+                b = Range{min(b.least, b2.least), fmaxf(b.top, b2.top)};
+            }
+            const float of_b = lost * b.top, of_a = b.least < kTinyCode ? lost * top : 0.f;
 #pragma unroll
-            for (int c = 0; c < NT; ++c) {
-                Range b = g.range[ct0 + c];
-                if (g.A2) {
-                    const Range b2 = g.range2[ct0 + c];
-                    b = Range{min(b.least, b2.least), fmaxf(b.top, b2.top)};
-                }
-                const float of_b = lost * b.top, of_a = b.least < kTinyCode ? lost * top[r] : 0.f;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = 8 * (v / 4) + v % 4;     // of this register, behind the shift by 4 half
-                    const float most = ((tiny >> row) & 1 ? of_b : 0.f) + ((zero >> row) & 1 ? 0.f : of_a);
-                    bad |= (ct0 + c) * 32 + l < g.N && !(fabsf(acc[r][c][v]) >= most);
-                }
+            for (int v = 0; v < 16; ++v) {
+                const int row = 8 * (v / 4) + v % 4;         // of this register, behind the shift by 4 half
+                const float most = ((tiny >> row) & 1 ? of_b : 0.f) + ((zero >> row) & 1 ? 0.f : of_a);
+                bad |= (ct0 + c) * 32 + l < g.N && !(fabsf(acc[c][v]) >= most);
             }
         }
     }
@@ -384,9 +344,7 @@ gemm_split_kernel(Product g) {
                 for (int c = 0; c < NT; ++c) {
                     const int n = (ct0 + c) * 32 + l;
                     const float bv = k0 + j < g.K && n < g.N ? b.p[(k0 + j) * b.sk + n * b.sn] : 0.f;
-#pragma unroll
-                    for (int r = 0; r < RT; ++r)
-                        acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(raw[r][j / 4][j % 4], bv, acc[r][c], 0, 0, 0);
+                    acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(raw[j / 4][j % 4], bv, acc[c], 0, 0, 0);
                 }
         }
     }
@@ -394,44 +352,39 @@ gemm_split_kernel(Product g) {
     // accumulator register v of lane (half, l): row 8 (v / 4) + 4 half + v % 4, column l of its 32 x 32 tile
     if (scaled) {
 #pragma unroll
-        for (int r = 0; r < RT; ++r)
+        for (int v = 0; v < 16; ++v) {
+            const float back = 1.f / scale[8 * (v / 4) + 4 * half + v % 4];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float back = 1.f / __shfl(scale[r], 8 * (v / 4) + 4 * half + v % 4, 64);
-#pragma unroll
-                for (int c = 0; c < NT; ++c) acc[r][c][v] *= back;
-            }
+            for (int c = 0; c < NT; ++c) acc[c][v] *= back;
+        }
     }
 #pragma unroll
     for (int c = 0; c < NT; ++c) {
         const int n = (ct0 + c) * 32 + l;
         const float bias = g.bias && n < g.N ? g.bias[n] : 0.f;
+        const int m0 = row0 + 4 * half;
+        float *at = g.C + (size_t)m0 * g.ldc + n;
+        if (row0 + 32 <= g.M && n < g.N) {
+            if (g.act & kActAccumulate) {                    // a tile's worth of loads before the first store
+                float held[16];
 #pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            const int m0 = row0 + 32 * r + 4 * half;
-            float *at = g.C + (size_t)m0 * g.ldc + n;
-            if (row0 + 32 * r + 32 <= g.M && n < g.N) {
-                if (g.act & kActAccumulate) {                // a tile's worth of loads before the first store
-                    float held[16];
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) held[v] = at[(size_t)(8 * (v / 4) + v % 4) * g.ldc];
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const float o = acc[r][c][v] + bias + held[v];
-                        at[(size_t)(8 * (v / 4) + v % 4) * g.ldc] = (g.act & kActRelu) ? fmaxf(o, 0.f) : o;
-                    }
-                } else {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) put(g, at + (size_t)(8 * (v / 4) + v % 4) * g.ldc, acc[r][c][v], bias);
-                }
-            } else if (n < g.ldc) {
+                for (int v = 0; v < 16; ++v) held[v] = at[(size_t)(8 * (v / 4) + v % 4) * g.ldc];
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const int dm = 8 * (v / 4) + v % 4;
-                    if (m0 + dm < g.M) {
-                        if (n < g.N) put(g, at + (size_t)dm * g.ldc, acc[r][c][v], bias);
-                        else at[(size_t)dm * g.ldc] = 0.f;   // padding columns of a wider row stride
-                    }
+                    const float o = acc[c][v] + bias + held[v];
+                    at[(size_t)(8 * (v / 4) + v % 4) * g.ldc] = (g.act & kActRelu) ? fmaxf(o, 0.f) : o;
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) put(g, at + (size_t)(8 * (v / 4) + v % 4) * g.ldc, acc[c][v], bias);
+            }
+        } else if (n < g.ldc) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int dm = 8 * (v / 4) + v % 4;
+                if (m0 + dm < g.M) {
+                    if (n < g.N) put(g, at + (size_t)dm * g.ldc, acc[c][v], bias);
+                    else at[(size_t)dm * g.ldc] = 0.f;       // padding columns of a wider row stride
                 }
             }
         }
@@ -482,9 +435,9 @@ gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const fl
     GNN_TRY(launch_status());
     const dim3 grid((unsigned)split_blocks(M, N));
     const size_t lds = (size_t)2 * w * kStepBytes;
-    if (w == 1) hipLaunchKernelGGL((gemm_split_kernel<1, 1>), grid, dim3(256), lds, st, g);
-    else if (w == 2) hipLaunchKernelGGL((gemm_split_kernel<1, 2>), grid, dim3(256), lds, st, g);
-    else hipLaunchKernelGGL((gemm_split_kernel<1, 4>), grid, dim3(256), lds, st, g);
+    if (w == 1) hipLaunchKernelGGL(gemm_split_kernel<1>, grid, dim3(256), lds, st, g);
+    else if (w == 2) hipLaunchKernelGGL(gemm_split_kernel<2>, grid, dim3(256), lds, st, g);
+    else hipLaunchKernelGGL(gemm_split_kernel<4>, grid, dim3(256), lds, st, g);
     return launch_status();
 }
 
