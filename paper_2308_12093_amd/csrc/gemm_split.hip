@@ -150,11 +150,12 @@ __device__ __forceinline__ void put(const Product &g, float *at, float o, float 
 // shared by the block: copied to LDS without touching registers, 6 NT KB per step, double-buffered, one barrier per
 // step.  Three to four wavefronts fit a SIMD: loads, splitting, matrix instructions and stores of a block hardly overlap,
 // those of different blocks do (64 rows a wavefront, two of them a SIMD: the same within 5 %, 24 % slower at 65536 rows
-// and 64 columns).  At 2^17 rows, against the fp32 instruction (K -> N): 128 -> 512 201 -> 167 us,
-// 512 -> 128 159 -> 137, 256 -> 256 158 -> 119, 128 -> 128 51 -> 43, 256 -> 64 47 -> 39 (4.3 TB/s); at 2^20 rows
-// 100 -> 256 773 -> 564, 47 -> 256 594 -> 328, 256 -> 47 414 -> 313; at 2^22 64 -> 256 1551 -> 1424, 256 -> 64 1378 ->
-// 1226 (4.4 TB/s: what a copy reaches).  Matrix instructions, stores and loads still add up more than they overlap:
-// without the stores 128 -> 512 takes 115 us, with a sixth of the matrix instructions 117.
+// and 64 columns).  At 2^17 rows, against the fp32 instruction, B transposed (K -> N): 128 -> 512 165 -> 148 us,
+// 512 -> 128 142 -> 133, 256 -> 256 150 -> 115, 128 -> 128 48 -> 43, 256 -> 64 43 -> 39 (4.3 TB/s); at 2^20 rows
+// 100 -> 256 662 -> 543, 47 -> 256 571 -> 318, 256 -> 47 378 -> 296; at 2^22 64 -> 256 1460 -> 1420, 256 -> 64 1308 ->
+// 1162 (4.6 TB/s: what a copy reaches).  Matrix cores busy 27 % (512 -> 128, 128 -> 128) and 34 % (128 -> 512): matrix
+// instructions, stores and loads add up more than they overlap; without the stores 128 -> 512 took 115 of then 167 us,
+// with a sixth of the matrix instructions 117.
 template <int NT>
 __global__ void __launch_bounds__(256, NT == 4 ? 3 : 4)
 gemm_split_kernel(Product g) {
