@@ -292,9 +292,10 @@ static gnn_status_t colsum_weighted(int64_t n, int f, const float *G, const floa
 
 gnn_status_t colsum_launch(int64_t n, int f, const float *G, float *out, void *workspace, hipStream_t st,
                            const float *mask_y, int mask_act, float *masked) {
-    // Writing the masked gradient along the way does not pay where a row is wide and the 64-row blocks are few (two passes /
-    // one, whole backward calls: 4000 x 1000 83 / 95 us, 2000 x 512 58.6 / 61.0; 2000 x 256 equal, 16384 x 512 80 / 76), nor
-    // where rows that are no multiple of four words go through memory one word at a time (2^20 x 47 429 / 491; 2^17 x 47 equal).
+    // Writing the masked gradient along the way does not pay where a row is wide and the 64-row blocks are few (two
+    // passes / one, whole backward calls: 4000 x 1000 83 / 95 us, 2000 x 512 58.6 / 61.0; 2000 x 256 equal, 16384 x 512
+    // 80 / 76), nor where rows that are no multiple of four words go through memory one word at a time (2^20 x 47
+    // 429 / 491; 2^17 x 47 equal).
     if (masked && ((n < 16384 && f > 256) || (f % 4 != 0 && (size_t)n * f * sizeof(float) > kStreamBytes))) {
         GNN_TRY(activation_grad_launch(n * f, G, mask_y, masked, mask_act, st));
         return colsum_weighted(n, f, masked, nullptr, nullptr, 1, f, out, nullptr, workspace, st);

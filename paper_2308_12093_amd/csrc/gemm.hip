@@ -790,7 +790,8 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
         const bool stream = (size_t)M * N * sizeof(float) > kStreamBytes && !(relu & kActAccumulate);
         // A product whose result decides signs (an activation in its own epilogue, or kActSigns) keeps the sums of
         // the fp32 instruction: a pre-activation within rounding of zero changes a gradient entry by its full size.
-        const bool rows16 = K % 4 == 0 && aligned16(A) && (!A2 || aligned16(A2)) && (!tb || (aligned16(B) && (!B2 || aligned16(B2))));
+        const bool rows16 = K % 4 == 0 && aligned16(A) && (!A2 || aligned16(A2)) &&
+                            (!tb || (aligned16(B) && (!B2 || aligned16(B2))));
         if (!signs && workspace && K >= 4 && gemm_split_fits(M, N) && !(rows16 && fp32_pays(tb, M, N, A2 ? 2 * K : K)))
             return gemm_split_launch(tb, M, N, K, A, B, C, ldc, bias, stream ? relu | kActStream : relu, workspace, st, A2, B2);
         if (!tb && K > 0) {

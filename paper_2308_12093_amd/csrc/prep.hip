@@ -479,7 +479,7 @@ gnn_status_t add_self_loops_launch(int n, int nnz, const int32_t *rowptr, const 
     if (n > 0) {
         const bool small = nnz < ROW_SMALL;
         const long tiles = ceil_div(nnz, small ? ROW_TILE_SMALL : ROW_TILE);
-        const long rows = ceil_div(n, ROW_THREADS), blocks = rows < kRowBlocks ? rows : kRowBlocks;   // at least, for the empty rows
+        const long rows = ceil_div(n, ROW_THREADS), blocks = rows < kRowBlocks ? rows : kRowBlocks;   // for the empty rows
         hipLaunchKernelGGL(small ? selfloop_fill_kernel<ROW_TILE_SMALL> : selfloop_fill_kernel<ROW_TILE>,
                            dim3((unsigned)(tiles > blocks ? tiles : blocks)), dim3(ROW_THREADS), 0, st, n, rowptr, col,
                            rowptr_out, col_out);
@@ -492,8 +492,9 @@ gnn_status_t normalize_launch(int n, const int32_t *rowptr, const int32_t *col, 
                               int kind, float eps, hipStream_t st) {
     if (n <= 0) return GNN_OK;
     // the number of entries stands in rowptr[n]: taken as some 16 per row here
-    hipLaunchKernelGGL(n < ROW_SMALL / 16 ? normalize_kernel<ROW_TILE_SMALL> : normalize_kernel<ROW_TILE>, dim3(kRowBlocks), dim3(ROW_THREADS), 0, st, n, rowptr, col, deg, val, kind,
-                       eps);
+    const bool small = n < ROW_SMALL / 16;
+    hipLaunchKernelGGL(small ? normalize_kernel<ROW_TILE_SMALL> : normalize_kernel<ROW_TILE>, dim3(kRowBlocks),
+                       dim3(ROW_THREADS), 0, st, n, rowptr, col, deg, val, kind, eps);
     return launch_status();
 }
 

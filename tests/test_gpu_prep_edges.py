@@ -107,8 +107,8 @@ def test_long_runs_of_empty_rows(nnz, gaps):
 def test_empty_rows_cost_no_more_than_others():
     """2^21 nodes without an edge against as many with one each."""
     n = 1 << 21
-    cases = [(torch.zeros(n + 1, dtype=torch.int32, device="cuda"), torch.empty(0, dtype=torch.int32, device="cuda")),
-             (torch.arange(n + 1, dtype=torch.int32, device="cuda"), torch.arange(n, dtype=torch.int32, device="cuda").flip(0).contiguous())]
+    ids = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+    cases = [(torch.zeros_like(ids), ids[:0]), (ids, ids[:n].flip(0).contiguous())]
     times = []
     for rowptr, col in cases:
         best = float("inf")
