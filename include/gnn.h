@@ -319,7 +319,8 @@ gnn_status_t gnn_gather_f32(int64_t count, const float *in, const int32_t *perm,
  *   erow: optional expanded row index (see gnn_graph_t); selects the entry-balanced kernel.
  *   bias [f] or NULL, relu (0 or 1; anything else is GNN_ERR_INVALID_ARG): fused epilogue C = relu(A B + 1 b^T).
  *   workspace: gnn_spmm_workspace_bytes(n, nnz, f) bytes (only used with erow): partial rows of the
- *   blocks and, when f is not a multiple of 4, a copy of B with rows padded to the next multiple of 4.
+ *   blocks, when f is not a multiple of 4 a copy of B with rows padded to the next multiple of 4, and for
+ *   products of 2e9 multiplications and more the lists and partial rows of long rows computed in pieces.
  *   B and C may start at any 4-byte aligned address; 16-byte aligned rows take the fastest kernel.
  */
 gnn_status_t gnn_spmm_csr(int32_t n, int32_t nnz, const int32_t *rowptr, const int32_t *col, const float *val,
@@ -334,8 +335,9 @@ size_t gnn_spmm_workspace_bytes(int32_t n, int32_t nnz, int32_t f);
  * arguments, kernels and results as gnn_spmm_csr; the scratch (partial rows, padded operand) is a device
  * array of GNN_STATIC_SCRATCH_BYTES bytes inside the library, one copy per GPU, held until the process ends.
  * The call allocates nothing and frees nothing.
- *   Errors: as gnn_spmm_csr; GNN_ERR_BUFFER_TOO_SMALL when gnn_spmm_workspace_bytes(n, nnz, f) exceeds
- *   GNN_STATIC_SCRATCH_BYTES (then use gnn_spmm_csr with a workspace of that size).
+ *   Errors: as gnn_spmm_csr; GNN_ERR_BUFFER_TOO_SMALL when those two exceed GNN_STATIC_SCRATCH_BYTES (then use
+ *   gnn_spmm_csr with a workspace).  Large products whose long rows gnn_spmm_csr computes in pieces, with a workspace for
+ *   those, are computed without pieces here: results equal to rounding.
  *   The first call on a device looks up the array's address there (make it outside a graph capture).
  *   All calls on one GPU share that GPU's array: calls that may overlap in time on one GPU (different
  *   streams, or several host threads) race; calls on one stream are ordered and safe.  Nothing in the

@@ -259,10 +259,10 @@ gnn_status_t gnn_spmm_csr(int32_t n, int32_t nnz, const int32_t *rowptr, const i
     if (nnz > 0 && (!col || !B)) return GNN_ERR_INVALID_ARG;
     if (erow && nnz > 0) {
         if (!workspace || bad_align(workspace)) return GNN_ERR_INVALID_ARG;
-        if (workspace_bytes < spmm_workspace_bytes(n, nnz, f)) return GNN_ERR_BUFFER_TOO_SMALL;
+        if (workspace_bytes < spmm_segments_bytes(n, nnz, f)) return GNN_ERR_BUFFER_TOO_SMALL;
     }
     return spmm_launch(n, nnz, rowptr, col, erow, EdgeWeights{val, nullptr, 1, f}, B, n, f, C, bias, relu, workspace,
-                       as_stream(hip_stream));
+                       as_stream(hip_stream), workspace_bytes >= spmm_workspace_bytes(n, nnz, f));
 }
 
 gnn_status_t gnn_sddmm_csr(int32_t n, int32_t nnz, const int32_t *erow, const int32_t *col, const float *val,

@@ -75,11 +75,14 @@ struct EdgeWeights {
 
 int spmm_segment_len(int64_t nnz, int f);
 size_t spmm_workspace_bytes(int64_t n, int64_t nnz, int f);
+// the part of it that a call without `pieces` uses
+size_t spmm_segments_bytes(int64_t n, int64_t nnz, int f);
 // b_rows: rows of B (n when the column indices are node numbers), or 0 = unknown: then a width that is
-// not a multiple of 4 is not run on a padded copy of B.  workspace: spmm_workspace_bytes(b_rows, nnz, f)
+// not a multiple of 4 is not run on a padded copy of B.  workspace: spmm_segments_bytes(b_rows, nnz, f).
+// pieces: long rows of a large product may be summed in another order (spmm_hub.hip); workspace: spmm_workspace_bytes
 gnn_status_t spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_t *col, const int32_t *erow,
                          EdgeWeights w, const float *B, long b_rows, int f, float *C, const float *bias, int relu,
-                         void *workspace, hipStream_t st);
+                         void *workspace, hipStream_t st, bool pieces = false);
 // The place inside `workspace` where such a call (one weight per entry) keeps its padded copy of B, rows *ld
 // floats apart, or NULL when it makes none.  A caller that produces B itself may write it there in that layout
 // (padding columns included, any finite value) and pass that address as B: the call then copies nothing.

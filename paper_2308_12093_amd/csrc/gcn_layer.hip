@@ -27,9 +27,13 @@ SparseView transposed_view(const gnn_graph_t &g, int f) {
 }
 
 gnn_status_t spmm(const gnn_graph_t &g, const SparseView &v, const float *B, int f, float *C, const float *bias,
-                  int relu, void *ws, hipStream_t st) {
-    return spmm_launch(g.n, g.nnz, v.ptr, v.idx, v.eidx, v.w, B, g.n, f, C, bias, relu, ws, st);
+                  int relu, void *ws, hipStream_t st, bool pieces = true) {
+    return spmm_launch(g.n, g.nnz, v.ptr, v.idx, v.eidx, v.w, B, g.n, f, C, bias, relu, ws, st, pieces);
 }
+
+// A pre-activation within rounding of zero changes a row of dX by its full size: the sums before it stay as they are
+// whatever the size of the graph.  Without dX such an entry is one of n in the sums of dW.
+bool sums_decide_signs(const gnn_plan_desc_t &d) { return d.fuse_relu && d.need_input_grad; }
 
 }  // namespace
 
@@ -38,6 +42,7 @@ gnn_status_t gcn_forward(Plan &p, const gnn_graph_t &g, const float *X, const fl
     const gnn_plan_desc_t &d = p.desc;
     const int n = d.n, m = d.f_in, k = d.f_out;
     const float *bias = d.has_bias ? b : nullptr;
+    const bool signs = sums_decide_signs(d);
     Carver ws(workspace);
     if (p.info.order == GNN_ORDER_TRANSFORM_FIRST) {
         // T = X W, then Y = A' T (+ b, ReLU) fused into the SpMM write
@@ -48,7 +53,7 @@ gnn_status_t gcn_forward(Plan &p, const gnn_graph_t &g, const float *X, const fl
         int ldt = k;
         if (float *Tp = spmm_padded_operand(sp, g.csr_erow, n, d.nnz, k, &ldt)) T = Tp;
         GNN_TRY(gemm_launch(0, 0, n, k, m, X, W, T, nullptr, d.fuse_relu ? kActSigns : 0, wt, st, nullptr, 0, ldt));
-        GNN_TRY(spmm(g, forward_view(g, k), T, k, Y, bias, d.fuse_relu, sp, st));
+        GNN_TRY(spmm(g, forward_view(g, k), T, k, Y, bias, d.fuse_relu, sp, st, !signs));
     } else {
         // P = A' X (kept in the cache slot when the plan caches it), then Y = P W (+ b, ReLU)
         const bool cached = p.info.cache == GNN_CACHE_AX;
@@ -57,7 +62,7 @@ gnn_status_t gcn_forward(Plan &p, const gnn_graph_t &g, const float *X, const fl
         void *wt = ws.take<char>(gemm_workspace_bytes(0, 0, n, k, m));
         // a constant input (promised by the caller) needs its A'X only once
         if (!(cached && d.constant_input && p.cache_filled))
-            GNN_TRY(spmm(g, forward_view(g, m), X, m, P, nullptr, 0, sp, st));
+            GNN_TRY(spmm(g, forward_view(g, m), X, m, P, nullptr, 0, sp, st, !signs));
         GNN_TRY(gemm_launch(0, 0, n, k, m, P, W, Y, bias, d.fuse_relu, wt, st));
         if (cached) p.cache_filled = true;
     }
@@ -126,6 +131,7 @@ gnn_status_t sage_forward(Plan &p, const gnn_graph_t &g, const float *X, const f
     const gnn_plan_desc_t &d = p.desc;
     const int n = d.n, m = d.f_in, k = d.f_out;
     const float *bias = d.has_bias ? b : nullptr;
+    const bool signs = sums_decide_signs(d);
     const int last = kActAccumulate | (d.fuse_relu ? kActRelu : 0);
     Carver ws(workspace);
     if (p.info.order == GNN_ORDER_TRANSFORM_FIRST) {
@@ -135,7 +141,7 @@ gnn_status_t sage_forward(Plan &p, const gnn_graph_t &g, const float *X, const f
         int ldt = k;
         if (float *Tp = spmm_padded_operand(sp, g.csr_erow, n, d.nnz, k, &ldt)) T = Tp;
         GNN_TRY(gemm_launch(0, 0, n, k, m, X, Wn, T, nullptr, d.fuse_relu ? kActSigns : 0, wt, st, nullptr, 0, ldt));
-        GNN_TRY(spmm(g, forward_view(g, k), T, k, Y, nullptr, 0, sp, st));
+        GNN_TRY(spmm(g, forward_view(g, k), T, k, Y, nullptr, 0, sp, st, !signs));
         GNN_TRY(gemm_launch(0, 0, n, k, m, X, Ws, Y, bias, last, wt, st));
     } else {
         const bool cached = p.info.cache == GNN_CACHE_AX;
@@ -143,7 +149,7 @@ gnn_status_t sage_forward(Plan &p, const gnn_graph_t &g, const float *X, const f
         void *sp = ws.take<char>(spmm_workspace_bytes(n, d.nnz, m));
         void *wt = ws.take<char>(2 * gemm_workspace_bytes(0, 0, n, k, m));
         if (!(cached && d.constant_input && p.cache_filled))
-            GNN_TRY(spmm(g, forward_view(g, m), X, m, P, nullptr, 0, sp, st));
+            GNN_TRY(spmm(g, forward_view(g, m), X, m, P, nullptr, 0, sp, st, !signs));
         GNN_TRY(gemm_launch(0, 0, n, k, m, X, Ws, Y, bias, d.fuse_relu, wt, st, nullptr, 0, 0, P, Wn));
         if (cached) p.cache_filled = true;
     }

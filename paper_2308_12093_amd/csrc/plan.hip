@@ -171,13 +171,13 @@ GatLayout gat_layout(const Plan &p) {
     if (L.c_alpha == (size_t)-1) L.w_alpha = take(q * h * fl);
     L.w_stat = take(n * h * 2 * fl);
     L.w_walk = take(gat_walker_workspace_bytes(q, (int)h));
-    L.w_spmm = take(spmm_workspace_bytes(n, q, (int)f));
+    L.w_spmm = take(spmm_segments_bytes(n, q, (int)f));
     L.w_gemm_nn = take(gemm_workspace_bytes(0, 0, n, f, m));
     L.w_gy = take(q * h * fl);
     L.w_sums = take(n * h * 3 * fl);
     L.w_ds = take(n * h * fl);
     L.w_dd = take(n * h * fl);
-    L.w_spmm_h = take(spmm_workspace_bytes(0, q, (int)h));        // its dense operand has q rows: never padded
+    L.w_spmm_h = take(spmm_segments_bytes(0, q, (int)h));        // its dense operand has q rows: never padded
     L.w_dM = take(n * f * fl);
     L.w_red = take(2 * colsum_workspace_bytes(n, (int)f));
     L.w_gemm_tn = take(backward_gemm_bytes(n, m, f, d.need_input_grad != 0, 1));

@@ -25,25 +25,18 @@
 //      tail partial per block, added in block order by spmm_fixup_kernel.
 //   Every sum has a fixed association, so results are reproducible.
 //
+// Large products with many long rows go to spmm_hub.hip instead.
+//
 // Row kernel (no `erow`): one wavefront per row; same results, no balancing.
-#include "common.h"
+#include "spmm_hub.h"
 
 namespace gnn {
 namespace {
-
-__device__ __forceinline__ float activate(float x, int act) {
-    if (act == kActRelu) x = fmaxf(x, 0.f);
-    else if (act == kActElu) x = x > 0.f ? x : expm1f(x);
-    return x;
-}
 
 __device__ __forceinline__ float epilogue(float x, const float *bias, int c, int act) {
     if (bias) x += bias[c];
     return activate(x, act);
 }
-
-// four floats at a 4-byte aligned address: global dwordx4 accesses need no more than that
-typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int N> struct IntVec;
 template <> struct IntVec<8> { int4 a, b; __device__ int get(int i) const { const int4 &q = i < 4 ? a : b; i &= 3; return i == 0 ? q.x : i == 1 ? q.y : i == 2 ? q.z : q.w; } };
@@ -75,8 +68,10 @@ template <int VEC, int LPE, int NT, int U, bool HEADS, bool UA = false>
 __global__ void __launch_bounds__(256)
 spmm_seg_kernel(int nnz, int f, int ldb, int seg, long nseg, const int32_t *__restrict__ erow,
                 const int32_t *__restrict__ col, EdgeWeights w, const float *__restrict__ B,
-                float *__restrict__ C, float *__restrict__ part, const float *__restrict__ bias, int relu) {
+                float *__restrict__ C, float *__restrict__ part, const float *__restrict__ bias, int relu,
+                const int32_t *__restrict__ done) {
     extern __shared__ __align__(16) int32_t smem[];
+    if (done && *done) return;
     constexpr int GPB = 256 / LPE;
     constexpr int FT = LPE * VEC * NT;                     // features handled by one block (blockIdx.y picks the tile)
     const int span = GPB * seg;
@@ -316,11 +311,16 @@ spmm_seg_kernel(int nnz, int f, int ldb, int seg, long nseg, const int32_t *__re
 //      are then combined by a fixed shuffle tree: a hub row that spans hundreds of
 //      blocks is summed in parallel, and always in the same order.
 //  (2) lane i of wavefront w gives row 64 w + i the epilogue of zero if it is empty.
-template <int VEC, bool RAGGED>                           // RAGGED: f is not a multiple of VEC
+//  HUBS: where the long rows were computed in pieces, what is left of that instead (hub_reduce).
+template <int VEC, bool RAGGED, bool HUBS>                // RAGGED: f is not a multiple of VEC
 __global__ void __launch_bounds__(256)
 spmm_fixup_kernel(int n, int nnz, int f, int span, long nspan, int lpf, const int32_t *__restrict__ erow,
                   const int32_t *__restrict__ rowptr, const float *__restrict__ part, float *__restrict__ C,
-                  const float *__restrict__ bias, int relu) {
+                  const float *__restrict__ bias, int relu, HubReduce hubs) {
+    if (HUBS && *hubs.use) {
+        hub_reduce(hubs, f, C, bias, relu);
+        return;
+    }
     const int lane = threadIdx.x % kWave;
     const long g = (long)blockIdx.x * 4 + threadIdx.x / kWave;
 
@@ -465,10 +465,23 @@ static size_t partials_bytes(int64_t nnz, int f) {
 }
 
 // ... followed, for a ragged width, by the padded copy of the dense operand
-size_t spmm_workspace_bytes(int64_t n, int64_t nnz, int f) {
+size_t spmm_segments_bytes(int64_t n, int64_t nnz, int f) {
     size_t bytes = partials_bytes(nnz, f);
     if (padded_operand(f) && nnz > 0 && n > 0) bytes += align_up((size_t)n * ((f + 3) / 4 * 4) * sizeof(float));
     return bytes;
+}
+
+// Products whose long rows, where there are many, are computed in pieces (spmm_hub.hip): from 2e9 multiplications on, about
+// a millisecond.  Below, its longer way through lists and queues (100 us) eats the gain: R-MAT, 2^20 nodes, 53 M entries,
+// f = 16 (0.9e9): 587 -> 662 us; 2^18, 5.5 M, f = 200 (1.1e9): 559 -> 561; above, 2^20, f = 47 (2.5e9): 1410 -> 1280;
+// 2^19, 16 M, f = 200 (3.3e9): 1613 -> 1408; 2^22, 138 M, f = 64 (8.9e9): 4307 -> 3630.  A graph without long rows pays
+// five launches: uniform, 2^20 nodes, 22 M entries, f = 128 (2.8e9): 1637 -> 1657.
+constexpr int64_t kHubWork = 2000000000;
+static bool hubs_pay(int64_t n, int64_t nnz, int f) { return n > 0 && f > 8 && nnz >= kHubRow && nnz * f >= kHubWork; }
+
+// ... and by what these need
+size_t spmm_workspace_bytes(int64_t n, int64_t nnz, int f) {
+    return spmm_segments_bytes(n, nnz, f) + (hubs_pay(n, nnz, f) ? hub_workspace_bytes(n, nnz, (f + 3) / 4 * 4) : 0);
 }
 
 // Where spmm_launch puts the padded copy of B for this call, or NULL if the call makes none.
@@ -486,19 +499,19 @@ float *spmm_padded_operand(void *workspace, const int32_t *erow, int64_t b_rows,
                            (size_t)2 * GPB_ * (LPE_ * VEC_ * NT_) * sizeof(float) + GPB_ * sizeof(SegInfo);  \
         if (heads)                                                                                           \
             hipLaunchKernelGGL((spmm_seg_kernel<VEC_, LPE_, NT_, U_, true>), grid, dim3(256), lds, st, nnz,  \
-                               f, f, seg, nseg, erow, col, w, B, C, part, bias, relu);                       \
+                               f, f, seg, nseg, erow, col, w, B, C, part, bias, relu, hubs.use);                 \
         else if (VEC_ == 4 && ragged)                                                                        \
             hipLaunchKernelGGL((spmm_seg_kernel<VEC_, LPE_, NT_, U_, false, VEC_ == 4>), grid, dim3(256),    \
-                               lds, st, nnz, f, fp, seg, nseg, erow, col, w, Bp, C, part, bias, relu);       \
+                               lds, st, nnz, f, fp, seg, nseg, erow, col, w, Bp, C, part, bias, relu, hubs.use); \
         else                                                                                                 \
             hipLaunchKernelGGL((spmm_seg_kernel<VEC_, LPE_, NT_, U_, false>), grid, dim3(256), lds, st, nnz, \
-                               f, f, seg, nseg, erow, col, w, B, C, part, bias, relu);                       \
+                               f, f, seg, nseg, erow, col, w, B, C, part, bias, relu, hubs.use);                 \
         launched = true;                                                                                     \
     }
 
 gnn_status_t spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_t *col, const int32_t *erow,
                          EdgeWeights w, const float *B, long b_rows, int f, float *C, const float *bias, int relu,
-                         void *workspace, hipStream_t st) {
+                         void *workspace, hipStream_t st, bool pieces) {
     if (n <= 0 || f <= 0) return GNN_OK;
     if (w.heads < 1) w.heads = 1;
     if (w.heads == 1) w.head_dim = f;
@@ -527,6 +540,10 @@ gnn_status_t spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_t *c
             GNN_TRY(launch_status());
         }
     }
+    HubReduce hubs{};                                      // hubs.use: spmm_hub.hip did it, but for the last step
+    if (pieces && vec4 && !heads && b_rows == n && hubs_pay(n, nnz, f))
+        GNN_TRY(hub_spmm_launch(n, nnz, rowptr, col, w, ragged ? Bp : B, f, fp, C, bias, relu,
+                                static_cast<char *>(workspace) + spmm_segments_bytes(n, nnz, f), st, &hubs));
     const int seg = spmm_segment_len(nnz, f);
     const long nseg = ceil_div(nnz, seg);
 
@@ -544,15 +561,13 @@ gnn_status_t spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_t *c
     int lpf = pow2_at_least((f + sh.vec - 1) / sh.vec);    // lanes per slot: one per VEC-wide chunk of a row
     if (lpf > kWave) lpf = kWave;
     const long waves = nspan > ceil_div(n, kWave) ? nspan : ceil_div(n, kWave);
-    if (sh.vec == 4 && ragged)
-        hipLaunchKernelGGL((spmm_fixup_kernel<4, true>), dim3((unsigned)ceil_div(waves, 4)), dim3(256), 0, st, n, nnz, f,
-                           span, nspan, lpf, erow, rowptr, part, C, bias, relu);
-    else if (sh.vec == 4)
-        hipLaunchKernelGGL((spmm_fixup_kernel<4, false>), dim3((unsigned)ceil_div(waves, 4)), dim3(256), 0, st, n, nnz, f,
-                           span, nspan, lpf, erow, rowptr, part, C, bias, relu);
-    else
-        hipLaunchKernelGGL((spmm_fixup_kernel<1, false>), dim3((unsigned)ceil_div(waves, 4)), dim3(256), 0, st, n, nnz, f,
-                           span, nspan, lpf, erow, rowptr, part, C, bias, relu);
+#define FIXUP_CASE(VEC_, RAGGED_, HUBS_)                                                                     \
+    if (sh.vec == VEC_ && ragged == RAGGED_ && (hubs.use != nullptr) == HUBS_)                               \
+        hipLaunchKernelGGL((spmm_fixup_kernel<VEC_, RAGGED_, HUBS_>), dim3((unsigned)ceil_div(waves, 4)),    \
+                           dim3(256), 0, st, n, nnz, f, span, nspan, lpf, erow, rowptr, part, C, bias, relu, \
+                           hubs);
+    FIXUP_CASE(4, true, true) FIXUP_CASE(4, true, false) FIXUP_CASE(4, false, true) FIXUP_CASE(4, false, false)
+    FIXUP_CASE(1, false, false)
     return launch_status();
 }
 

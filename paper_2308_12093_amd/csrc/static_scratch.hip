@@ -45,7 +45,7 @@ extern "C" gnn_status_t gnn_spmm_csr_static(int32_t n, int32_t nnz, const int32_
     void *ws = nullptr;
     if (erow && nnz > 0) {
         // the same bytes gnn_spmm_csr asks its caller for
-        if (gnn::spmm_workspace_bytes(n, nnz, f) > kStaticScratchBytes) return GNN_ERR_BUFFER_TOO_SMALL;
+        if (gnn::spmm_segments_bytes(n, nnz, f) > kStaticScratchBytes) return GNN_ERR_BUFFER_TOO_SMALL;
         GNN_TRY(scratch_of_current_device(&ws));
     }
     return gnn::spmm_launch(n, nnz, rowptr, col, erow, gnn::EdgeWeights{val, nullptr, 1, f}, B, n, f, C, bias, relu,
