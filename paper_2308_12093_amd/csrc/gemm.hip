@@ -526,15 +526,18 @@ gemm_f32_kernel(int M, int N, int K, const float *__restrict__ A, const float *_
 // 512-long reduction take 7 us by themselves.  No LDS, no transposed copy of B.  2048 x 512 by 512 x 16 took 20.4 us
 // through the kernel above (16 blocks, one barrier per step, and the copy), 16.3 now; 3001 x 203 by 203 x 7 24.4 and 9.8.
 // TB: B is [N][K], a lane's column read like a row of A; else [K][N].
-template <bool TB>
-__global__ void __launch_bounds__(64)
+// WAVES = 4: four wavefronts share a tile, each with a quarter of the reduction, and add their sums in LDS, each a quarter of
+// the rows.  For products that decide no signs: the order of the sums is another, and the chains are a quarter as long.
+template <bool TB, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES)
 gemm_few_kernel(int M, int N, int K, const float *__restrict__ A, const float *__restrict__ B,
                 const float *__restrict__ A2, const float *__restrict__ B2, float *__restrict__ C, int ldc,
                 const float *__restrict__ bias, int relu, int tiles_n) {
     constexpr int AHEAD = 3;
-    const int lane = threadIdx.x, l32 = lane % 32, half = lane / 32;
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64, l32 = lane % 32, half = lane / 32;
     const int m0 = (int)(blockIdx.x / tiles_n) * 32, n = (int)(blockIdx.x % tiles_n) * 32 + l32;
-    const int kt1 = (K + BK - 1) / BK, total = A2 ? 2 * kt1 : kt1;
+    const int kt1 = (K + BK - 1) / BK, all = A2 ? 2 * kt1 : kt1;
+    const int first = WAVES == 1 ? 0 : all * wave / WAVES, total = WAVES == 1 ? all : all * (wave + 1) / WAVES;
     const size_t ro = (size_t)min(m0 + l32, M - 1) * K;    // rows and columns past the end re-read the last one
     const size_t sk = TB ? 1 : N, co = (size_t)min(n, N - 1) * (TB ? K : 1);
     float x[AHEAD][16], y[AHEAD][16];
@@ -569,8 +572,8 @@ gemm_few_kernel(int M, int N, int K, const float *__restrict__ A, const float *_
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
     for (int u = 0; u < AHEAD; ++u)
-        if (u < total) load(u, x[u], y[u]);
-    for (int step = 0; step < total; step += AHEAD) {
+        if (first + u < total) load(first + u, x[u], y[u]);
+    for (int step = first; step < total; step += AHEAD) {
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) {
             if (step + u < total) {
@@ -581,9 +584,18 @@ gemm_few_kernel(int M, int N, int K, const float *__restrict__ A, const float *_
         }
     }
     const float bj = bias && n < N ? bias[n] : 0.f;
+    if constexpr (WAVES > 1) {
+        __shared__ floatx4 sums[WAVES][4][64];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int m = m0 + 8 * (v / 4) + 4 * half + v % 4;
+        for (int j = 0; j < 4; ++j)
+            sums[wave][j][lane] = floatx4{acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]};
+        __syncthreads();
+        const floatx4 s = (sums[0][wave][lane] + sums[1][wave][lane]) + (sums[2][wave][lane] + sums[3][wave][lane]);
+        acc[0] = s.x; acc[1] = s.y; acc[2] = s.z; acc[3] = s.w;
+    }
+#pragma unroll
+    for (int v = 0; v < 16 / WAVES; ++v) {
+        const int m = m0 + 8 * (WAVES == 1 ? v / 4 : wave) + 4 * half + v % 4;
         if (m < M && n < N) {
             float o = acc[v] + bj;
             if (relu & kActAccumulate) o += C[(size_t)m * ldc + n];
@@ -687,6 +699,11 @@ bool few_rows(int tb, int64_t M, int64_t N, int64_t K) {
     return few_tiles(M, N) && !(N <= 32 && M > 8192 && K % 4 == 0 && K >= (tb && N > 16 ? 128 : 384));
 }
 
+// Four wavefronts a tile where tiles alone leave most of the chip idle (one wavefront / four, us): 2048 x 16, K = 64 5.6 / 4.8,
+// 128 7.0 / 4.8, 512 15.6 / 6.5; 2048 x 128 x 256, B transposed 9.7 / 5.6; 512 tiles: 8192 x 64 x 128 7.5 / 5.4, 16384 x 32 x 64
+// 5.7 / 4.9; more: 8192 x 128 x 256 equal, 3000 x 300 x 300 15.3 / 19.2; shorter: 2048 x 512 x 16 6.0 / 6.6.
+bool few_share(int64_t M, int64_t N, int64_t K) { return K >= 64 && ceil_div(M, 32) * ceil_div(N, 32) <= 512; }
+
 // Where the fp32 instruction is faster than split parts all the same (K: indices of all operand pairs; aligned rows).  fp32 /
 // parts in us, tb where B is [N][K] and the fp32 kernel needs no launch before it:
 //   32 columns, a whole tile: tb always (65536 x 32 10.2 / 14.4 at K = 128, 2^20 138 / 149); else A from 64 MB on (2^18 x 64
@@ -783,8 +800,11 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
         relu &= kActRelu | kActAccumulate;
         if (few_rows(tb, M, N, K)) {
             const long tn = ceil_div(N, 32);
-            hipLaunchKernelGGL(tb ? gemm_few_kernel<true> : gemm_few_kernel<false>, dim3((unsigned)(ceil_div(M, 32) * tn)),
-                               dim3(64), 0, st, (int)M, (int)N, (int)K, A, B, A2, Bt2, C, (int)ldc, bias, relu, (int)tn);
+            const bool share = !signs && few_share(M, N, A2 ? 2 * K : K);
+            auto kernel = share ? (tb ? gemm_few_kernel<true, 4> : gemm_few_kernel<false, 4>)
+                                : (tb ? gemm_few_kernel<true, 1> : gemm_few_kernel<false, 1>);
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(ceil_div(M, 32) * tn)), dim3(share ? 256 : 64), 0, st, (int)M, (int)N,
+                               (int)K, A, B, A2, Bt2, C, (int)ldc, bias, relu, (int)tn);
             return launch_status();
         }
         const bool stream = (size_t)M * N * sizeof(float) > kStreamBytes && !(relu & kActAccumulate);
