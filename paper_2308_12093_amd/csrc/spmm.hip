@@ -64,14 +64,15 @@ struct SegInfo {
 // copy padded to ldb = f rounded up (16-byte aligned rows, zeros in the padding), while the rows of C and
 // `part` keep the stride f: whole groups of four go out as one 4-byte aligned 16-byte store, the lane that
 // holds the ragged end of a row stores its one to three values one by one.
-template <int VEC, int LPE, int NT, int U, bool HEADS, bool UA = false>
+// HUBS: *done says that spmm_hub.hip has computed the product.
+template <int VEC, int LPE, int NT, int U, bool HEADS, bool UA = false, bool HUBS = false>
 __global__ void __launch_bounds__(256)
 spmm_seg_kernel(int nnz, int f, int ldb, int seg, long nseg, const int32_t *__restrict__ erow,
                 const int32_t *__restrict__ col, EdgeWeights w, const float *__restrict__ B,
                 float *__restrict__ C, float *__restrict__ part, const float *__restrict__ bias, int relu,
                 const int32_t *__restrict__ done) {
     extern __shared__ __align__(16) int32_t smem[];
-    if (done && *done) return;
+    if (HUBS && *done) return;
     constexpr int GPB = 256 / LPE;
     constexpr int FT = LPE * VEC * NT;                     // features handled by one block (blockIdx.y picks the tile)
     const int span = GPB * seg;
@@ -497,15 +498,23 @@ float *spmm_padded_operand(void *workspace, const int32_t *erow, int64_t b_rows,
         dim3 grid((unsigned)ceil_div(nseg, GPB_), (unsigned)sh.tiles_y);                                     \
         const size_t lds = (size_t)3 * GPB_ * seg * sizeof(int32_t) +                                        \
                            (size_t)2 * GPB_ * (LPE_ * VEC_ * NT_) * sizeof(float) + GPB_ * sizeof(SegInfo);  \
+        constexpr bool HUB_ = VEC_ == 4 && LPE_ > 2;                                                         \
         if (heads)                                                                                           \
             hipLaunchKernelGGL((spmm_seg_kernel<VEC_, LPE_, NT_, U_, true>), grid, dim3(256), lds, st, nnz,  \
-                               f, f, seg, nseg, erow, col, w, B, C, part, bias, relu, hubs.use);                 \
+                               f, f, seg, nseg, erow, col, w, B, C, part, bias, relu, nullptr);              \
+        else if (HUB_ && hubs.use && ragged)                                                                 \
+            hipLaunchKernelGGL((spmm_seg_kernel<VEC_, LPE_, NT_, U_, false, HUB_, HUB_>), grid, dim3(256),   \
+                               lds, st, nnz, f, fp, seg, nseg, erow, col, w, Bp, C, part, bias, relu,        \
+                               hubs.use);                                                                    \
+        else if (HUB_ && hubs.use)                                                                           \
+            hipLaunchKernelGGL((spmm_seg_kernel<VEC_, LPE_, NT_, U_, false, false, HUB_>), grid, dim3(256),  \
+                               lds, st, nnz, f, f, seg, nseg, erow, col, w, B, C, part, bias, relu, hubs.use); \
         else if (VEC_ == 4 && ragged)                                                                        \
             hipLaunchKernelGGL((spmm_seg_kernel<VEC_, LPE_, NT_, U_, false, VEC_ == 4>), grid, dim3(256),    \
-                               lds, st, nnz, f, fp, seg, nseg, erow, col, w, Bp, C, part, bias, relu, hubs.use); \
+                               lds, st, nnz, f, fp, seg, nseg, erow, col, w, Bp, C, part, bias, relu, nullptr); \
         else                                                                                                 \
             hipLaunchKernelGGL((spmm_seg_kernel<VEC_, LPE_, NT_, U_, false>), grid, dim3(256), lds, st, nnz, \
-                               f, f, seg, nseg, erow, col, w, B, C, part, bias, relu, hubs.use);                 \
+                               f, f, seg, nseg, erow, col, w, B, C, part, bias, relu, nullptr);              \
         launched = true;                                                                                     \
     }
 
