@@ -47,16 +47,18 @@ constexpr int BK = 32;
 // MASK: B is used as B .* act'(Ymask), the derivative of a fused activation taken from the layer's output
 // Ymask (same shape as B): ReLU 1 / 0, ELU 1 / y + 1.  The gradient through the activation then needs no
 // pass of its own: the second operand stream costs nothing while the matrix cores are the bound.
+// words per LDS row of `cols` columns: the lanes of one k-row read 16 * T consecutive words.  T odd: word by word, the 16
+// lanes of a row T banks apart, four rows in 64 banks at a row length of 16 mod 64; T = 2: two rows per pass, 32 mod 64;
+// T = 4: one row per pass
+constexpr int tn_row_words(int cols, int T) { return cols + (T % 2 ? (80 - cols % 64) % 64 : T == 2 ? (96 - cols % 64) % 64 : 4); }
+
 template <int WM, int WN, int TM, int TN, bool MASK>
 __global__ void __launch_bounds__(256)
 gemm_tn_f64_kernel(int M, int N, long K, const float *__restrict__ A, const float *__restrict__ B,
                    const float *__restrict__ Ymask, int mask_act,
                    double *__restrict__ P, long k_chunk, int tiles_m, int tiles_n, int splits, int vec_a, int vec_b) {
     constexpr int BM = WM * TM * 16, BN = WN * TN * 16, KSTEP = 4;
-    // words per LDS row: the lanes of one k-row read 16 * T consecutive words; T = 1: four rows fill the 64
-    // banks at a row length of 16 mod 64; T = 2: two rows per pass, 32 mod 64; T = 4: one row per pass
-    constexpr int LA = BM + (TM == 1 ? (80 - BM % 64) % 64 : TM == 2 ? (96 - BM % 64) % 64 : 4);
-    constexpr int LB = BN + (TN == 1 ? (80 - BN % 64) % 64 : TN == 2 ? (96 - BN % 64) % 64 : 4);
+    constexpr int LA = tn_row_words(BM, TM), LB = tn_row_words(BN, TN);
     constexpr int NA = BM * BK / 4, NB = BN * BK / 4;   // 16-byte granules per tile
     constexpr int GA = (NA + 255) / 256, GB = (NB + 255) / 256;
     extern __shared__ __align__(16) float lds[];
@@ -139,10 +141,14 @@ gemm_tn_f64_kernel(int M, int N, long K, const float *__restrict__ A, const floa
         const float *pb = &Bs[buf][kk + lk][(wn * 16 + lu) * TN];
         if constexpr (TM == 4) { const floatx4 q = *reinterpret_cast<const floatx4 *>(pa); av[0] = q.x; av[1] = q.y; av[2] = q.z; av[3] = q.w; }
         else if constexpr (TM == 2) { const float2 q = *reinterpret_cast<const float2 *>(pa); av[0] = q.x; av[1] = q.y; }
-        else av[0] = *pa;
+        else
+#pragma unroll
+            for (int x = 0; x < TM; ++x) av[x] = pa[x];
         if constexpr (TN == 4) { const floatx4 q = *reinterpret_cast<const floatx4 *>(pb); bv[0] = q.x; bv[1] = q.y; bv[2] = q.z; bv[3] = q.w; }
         else if constexpr (TN == 2) { const float2 q = *reinterpret_cast<const float2 *>(pb); bv[0] = q.x; bv[1] = q.y; }
-        else bv[0] = *pb;
+        else
+#pragma unroll
+            for (int y = 0; y < TN; ++y) bv[y] = pb[y];
     };
     auto mma = [&](const float (&av)[TM], const float (&bv)[TN]) __attribute__((always_inline)) {
 #pragma unroll
@@ -655,36 +661,66 @@ struct Tiling {
 int tile_m(bool f64, const Tiling &t) { return t.wm * t.tm * (f64 ? 16 : 32); }
 int tile_n(bool f64, const Tiling &t) { return t.wn * t.tn * (f64 ? 16 : 32); }
 
-Tiling pick_tiling(bool f64, int64_t M, int64_t N) {
-    if (f64) {
-        if (N <= 16) return Tiling{4, 1, 1, 1};            // 64 x 16
-        if (N <= 32) return Tiling{4, 1, 1, 2};            // 64 x 32
-        if (M >= 256 && N >= 256) return Tiling{2, 2, 4, 4};   // 128 x 128
-        return Tiling{2, 2, 2, 2};                         // 64 x 64
-    }
+Tiling pick_tiling(int64_t M, int64_t N) {
     if (M <= 64) return N <= 64 ? Tiling{2, 2, 1, 1} : Tiling{2, 2, 1, 2};
     if (N <= 32) return Tiling{4, 1, 1, 1};
     if (N <= 64) return Tiling{4, 1, 1, 2};
     return Tiling{2, 2, 2, 2};
 }
 
-// Number of chunks the reduction of a transposed-A product is cut into: enough blocks
-// to fill the chip, as long as the double partials (written and read once each) stay
-// within a quarter of the operand bytes.
-int pick_splits(int ta, int64_t M, int64_t N, int64_t K) {
-    if (!ta) return 1;
-    const Tiling tl = pick_tiling(true, M, N);
-    const int64_t tiles = ceil_div(M, tile_m(true, tl)) * ceil_div(N, tile_n(true, tl));
-    int64_t s = ceil_div(2048, tiles);
-    const int64_t by_k = K / (4 * BK);
-    const int64_t by_traffic = K * (M + N) / (16 * M * N);
-    if (s > by_k) s = by_k;
-    if (s > by_traffic) s = by_traffic;
-    if (s < 1) s = 1;
-    // equal blocks spread evenly over the 256 CUs only if their number is a multiple of 256: round down to one
-    // (640 blocks leave half the CUs with three and half with two)
-    if (tiles * s > 256) s = (tiles * s / 256 * 256) / tiles;
-    return s < 1 ? 1 : (int)s;                             // more than 256 tiles in one chunk each: no multiple to round to
+// Tile and number of chunks of the reduction of a transposed-A product, by the time they should take.  A block on its own
+// waits for its barriers and LDS, up to `resident` blocks of a CU hide that for one another.  Padding counts as work; the
+// double partials are written and read once.  Rates are measured, at 2^17 to 2^22 rows, old tile and chunks / new, us:
+// 512 x 512 over 2048 290 / 38, 128 x 128 over 2048 49 / 9, over 16384 50 / 22, over 2^17 93 / 92; 300 x 300 over 8192
+// 411 / 46; 256 x 256 over 20000 315 / 61, over 2^17 322 / 302; 70 x 75 over 2^18 195 / 105; 96 x 64 over 50021 36 / 27;
+// 256 x 47 over 2^20 665 / 490, 100 x 256 1150 / 1094; 64 x 256 over 2^22 2230 / 2240.  Outputs of a few tiles fill the
+// chip only with many short chunks, whatever their partials come to beside the operands.
+struct TnTile {
+    Tiling tile;
+    int resident;                                          // blocks on a CU, by registers and LDS
+    double rate;                                           // us for 64 x 64 outputs and 32 indices on a busy CU, measured
+};
+
+constexpr TnTile kTnTiles[] = {{{4, 1, 1, 1}, 6, 1.7}, {{4, 1, 1, 2}, 5, 1.5}, {{4, 1, 2, 3}, 3, 1.15}, {{2, 2, 2, 2}, 3, 1.08},
+                               {{2, 2, 3, 3}, 2, 1.13}, {{4, 1, 2, 5}, 2, 1.12}, {{4, 1, 2, 7}, 2, 1.1}, {{2, 2, 4, 4}, 2, 1.03}};
+constexpr double kTnWait = 0.4, kTnTurn = 0.15;            // us a k-tile: a block on its own, any number of them
+
+struct TnPlan {
+    Tiling tile;
+    int splits;
+};
+
+TnPlan pick_tn(int64_t M, int64_t N, int64_t K) {
+    TnPlan best{kTnTiles[0].tile, 1};
+    double least = 1e300;
+    const int64_t ktiles = ceil_div(K > 0 ? K : 1, BK);
+    for (const TnTile &c : kTnTiles) {
+        const int bm = tile_m(true, c.tile), bn = tile_n(true, c.tile);
+        const int64_t tiles = ceil_div(M, bm) * ceil_div(N, bn);
+        const double step = c.rate / 4096 * bm * bn;
+        int64_t before = 0;
+        for (int want = -7; want <= 8; ++want) {           // blocks a CU; below one, fractions of the chip
+            int64_t splits = (want > 0 ? 256 * want : 256 >> -want) / tiles;
+            if (splits > ktiles / 3) splits = ktiles / 3;
+            if (splits < 1) splits = 1;
+            if (splits == before) continue;
+            before = splits;
+            const int64_t per_cu = ceil_div(tiles * splits, 256), rest = per_cu % c.resident;
+            auto turn = [&](int64_t blocks) {              // one k-tile of each of `blocks` on a CU
+                const double busy = blocks * step + kTnTurn, alone = step + kTnWait;
+                return blocks == 0 ? 0.0 : busy > alone ? busy : alone;
+            };
+            const double chunk = (double)ceil_div(ktiles, splits), last = turn(per_cu < c.resident ? per_cu : c.resident);
+            // blocks do not end together: a few hundredths of the time of the last
+            const double t = ((double)(per_cu / c.resident) * turn(c.resident) + turn(rest) + 0.03 * last) * chunk +
+                             0.4 * per_cu + (double)(splits * M * N) * (16 / 4.5e6);
+            if (t < least) {
+                least = t;
+                best = TnPlan{c.tile, (int)splits};
+            }
+        }
+    }
+    return best;
 }
 
 // One wavefront per 32 x 32 tile while there are few; beyond, the kernels that share operands through LDS.  Both sides of
@@ -731,7 +767,7 @@ size_t gemm_workspace_bytes(int ta, int tb, int64_t M, int64_t N, int64_t K) {
         const size_t bt = tb ? kAlign : align_up((size_t)N * K * sizeof(float));
         return parts > bt ? parts : bt;
     }
-    return align_up((size_t)pick_splits(ta, M, N, K) * M * N * sizeof(double));
+    return align_up((size_t)pick_tn(M, N, K).splits * M * N * sizeof(double));
 }
 
 #define GEMM_F32_CASE(WM_, WN_, TM_, TN_)                                                                   \
@@ -759,8 +795,7 @@ size_t gemm_workspace_bytes(int ta, int tb, int64_t M, int64_t N, int64_t K) {
 #define GEMM_F64_CASE(WM_, WN_, TM_, TN_)                                                                        \
     if (tl.wm == WM_ && tl.wn == WN_ && tl.tm == TM_ && tl.tn == TN_) {                                          \
         constexpr int BM_ = WM_ * TM_ * 16, BN_ = WN_ * TN_ * 16;                                                \
-        constexpr int LA_ = BM_ + (TM_ == 1 ? (80 - BM_ % 64) % 64 : TM_ == 2 ? (96 - BM_ % 64) % 64 : 4);       \
-        constexpr int LB_ = BN_ + (TN_ == 1 ? (80 - BN_ % 64) % 64 : TN_ == 2 ? (96 - BN_ % 64) % 64 : 4);       \
+        constexpr int LA_ = tn_row_words(BM_, TM_), LB_ = tn_row_words(BN_, TN_);                                \
         const size_t lds = (size_t)2 * BK * (LA_ + LB_) * sizeof(float);                                         \
         if (b_mask)                                                                                              \
             hipLaunchKernelGGL((gemm_tn_f64_kernel<WM_, WN_, TM_, TN_, true>), grid, dim3(256), lds, st, (int)M,  \
@@ -786,7 +821,8 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
     if (b_mask && !ta) return GNN_ERR_UNSUPPORTED;         // only the transposed-A product masks its second operand
     if (M > INT32_MAX / 2 || N > INT32_MAX / 2 || (!ta && K > INT32_MAX / 2)) return GNN_ERR_UNSUPPORTED;
     const bool f64 = ta != 0;
-    const Tiling tl = pick_tiling(f64, M, N);
+    const TnPlan plan = f64 ? pick_tn(M, N, K) : TnPlan{pick_tiling(M, N), 1};
+    const Tiling tl = plan.tile;
     const int tiles_m = (int)ceil_div(M, tile_m(f64, tl)), tiles_n = (int)ceil_div(N, tile_n(f64, tl));
     bool launched = false;
     if (!f64) {
@@ -841,7 +877,7 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
         if (!launched) return GNN_ERR_UNSUPPORTED;
         return launch_status();
     }
-    int splits = pick_splits(ta, M, N, K);
+    int splits = plan.splits;
     const long k_chunk = ceil_div(ceil_div(K > 0 ? K : 1, splits), BK) * BK;
     splits = (int)ceil_div(K > 0 ? K : 1, k_chunk);
     // a float4 may be read only if every granule start is 16-byte aligned
@@ -849,7 +885,8 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
     const int vec_b = aligned16(B) && N % 4 == 0 && (!b_mask || aligned16(b_mask));
     const long total = (long)tiles_m * tiles_n * splits;
     dim3 grid((unsigned)(8 * ceil_div(total, 8)));
-    GEMM_F64_CASE(4, 1, 1, 1) GEMM_F64_CASE(4, 1, 1, 2) GEMM_F64_CASE(2, 2, 2, 2) GEMM_F64_CASE(2, 2, 4, 4)
+    GEMM_F64_CASE(4, 1, 1, 1) GEMM_F64_CASE(4, 1, 1, 2) GEMM_F64_CASE(4, 1, 2, 3) GEMM_F64_CASE(2, 2, 2, 2)
+    GEMM_F64_CASE(2, 2, 3, 3) GEMM_F64_CASE(4, 1, 2, 5) GEMM_F64_CASE(4, 1, 2, 7) GEMM_F64_CASE(2, 2, 4, 4)
     if (!launched) return GNN_ERR_UNSUPPORTED;
     GNN_TRY(launch_status());
     const long count = (long)M * N;
