@@ -96,17 +96,26 @@ size_t gemm_workspace_bytes(int ta, int tb, int64_t M, int64_t N, int64_t K);
 // A2, B2 (plain products only; shapes of A and B): C = op(A) op(B) + op(A2) op(B2) in one pass, one rounding
 // chain; needs a workspace of 2 x gemm_workspace_bytes.
 // workspace: gemm_workspace_bytes; the A B^T form also runs without one (NULL).
+// extras: what a product does on the side, or a mask it takes (see GemmExtras).
+struct GemmExtras {
+    float *sums;            // transposed-A form: the column sums of B as used, or NULL
+    void *workspace;        //   gemm_sums_bytes(M, N, K) of scratch for them
+    uint16_t *bits;         //   and which elements of it are not zero, or NULL: [K][ceil(N / 16)], 16 columns to a word
+    const uint16_t *a_bits; // plain products that gemm_takes_bits: such words for A [M][ceil(K / 16)], zero = used as 0
+};
+size_t gemm_sums_bytes(int64_t M, int64_t N, int64_t K);
+bool gemm_takes_bits(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B);
 gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B,
                          float *C, const float *bias, int relu, void *workspace, hipStream_t st,
                          const float *b_mask = nullptr, int b_mask_act = 0, int64_t ldc = 0,
-                         const float *A2 = nullptr, const float *B2 = nullptr);
+                         const float *A2 = nullptr, const float *B2 = nullptr, const GemmExtras *extras = nullptr);
 
 // the plain products (gemm_split.hip): see there
 bool gemm_split_fits(int64_t M, int64_t N);
 size_t gemm_split_workspace_bytes(int64_t N, int64_t K);
 gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B, float *C,
                                int64_t ldc, const float *bias, int act, void *workspace, hipStream_t st,
-                               const float *A2, const float *B2);
+                               const float *A2, const float *B2, const uint16_t *a_bits);
 
 // ---- element-wise and reductions (elementwise.hip) ---------------------------------
 // out = G * [Y > 0]

@@ -125,6 +125,8 @@ struct Product {
     const float *bias;
     int act;
     int tiles_m, tiles_n;
+    const uint16_t *a_bits;            // see GemmExtras
+    int bit_words, bit_stride;         // of a row, in memory and in LDS (an odd number of banks)
 };
 
 // logical tile of a block: each XCD (ids are dealt round-robin to eight) takes a contiguous range, the column tiles of
@@ -156,8 +158,10 @@ __device__ __forceinline__ void put(const Product &g, float *at, float o, float 
 // 1162 (4.6 TB/s: what a copy reaches).  Matrix cores busy 27 % (512 -> 128, 128 -> 128) and 34 % (128 -> 512): matrix
 // instructions, stores and loads add up more than they overlap; without the stores 128 -> 512 took 115 of then 167 us,
 // with a sixth of the matrix instructions 117.
-template <int NT>
-__global__ void __launch_bounds__(256, NT == 4 ? 3 : 4)
+// BITS: A is used where its bit is set; a lane's 16 floats have one word, from the block's copy in LDS (held in registers a
+// step ahead it spills).
+template <int NT, bool BITS>
+__global__ void __launch_bounds__(256, (NT == 4 ? 3 : 4) - (BITS && NT > 1))
 gemm_split_kernel(Product g) {
     extern __shared__ __align__(16) char lds[];
     constexpr int STAGE = NT * kStepBytes;
@@ -174,6 +178,11 @@ gemm_split_kernel(Product g) {
     // Four indices at a time, at any 4-byte aligned address; the ones that would run over the row's end are read from
     // its last four floats instead (K >= 4) and put in place by `settle`, so no load stands behind a branch.
     floatx4 raw[4];
+    uint16_t *bits = reinterpret_cast<uint16_t *>(lds + 2 * STAGE);
+    if constexpr (BITS) {                                  // the block's words; the first step's barrier covers them
+        const size_t from = (size_t)min(row0 - wave * 32 + t / 2, g.M - 1) * g.bit_words;
+        for (int i = t % 2; i < g.bit_words; i += 2) bits[t / 2 * g.bit_stride + i] = g.a_bits[from + i];
+    }
     auto load = [&](int step) __attribute__((always_inline)) {
         const bool second = step >= g.steps;
         const float *A = second ? g.A2 : g.A;
@@ -183,7 +192,15 @@ gemm_split_kernel(Product g) {
     };
     auto settle = [&](int step) __attribute__((always_inline)) {
         const int k0 = (step >= g.steps ? step - g.steps : step) * KB;
-        if (k0 + KB <= g.K) return;
+        auto use = [&]() __attribute__((always_inline)) {
+            if constexpr (BITS) {
+                const int mask = bits[(wave * 32 + l) * g.bit_stride + min(2 * step + half, g.bit_words - 1)];
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    raw[j / 4][j % 4] = __int_as_float(__float_as_int(raw[j / 4][j % 4]) & __builtin_amdgcn_sbfe(mask, j, 1));
+            }
+        };
+        if (k0 + KB <= g.K) return use();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             // floats past the end: 0 none .. 4 all; a shift by one, by two and by four places
@@ -194,6 +211,7 @@ gemm_split_kernel(Product g) {
             v = floatx4{two ? v.z : v.x, two ? v.w : v.y, two ? 0.f : v.z, two ? 0.f : v.w};
             raw[i] = floatx4{all ? 0.f : v.x, all ? 0.f : v.y, all ? 0.f : v.z, all ? 0.f : v.w};
         }
+        use();
     };
     // Rows that begin with tiny values (a saturated node's gradient) are taken times a power of two and their results
     // back, in a wavefront that has one.  Formed again, one such row in 32 costs four times the product: 128 -> 512 over
@@ -416,7 +434,7 @@ size_t gemm_split_workspace_bytes(int64_t N, int64_t K) {
 // [K][N].  workspace: gemm_split_workspace_bytes per operand pair.
 gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B, float *C,
                                int64_t ldc, const float *bias, int act, void *workspace, hipStream_t st,
-                               const float *A2, const float *B2) {
+                               const float *A2, const float *B2, const uint16_t *a_bits) {
     Product g{};
     g.M = (int)M; g.N = (int)N; g.K = (int)K;
     g.steps = (int)ceil_div(K, KB);
@@ -424,6 +442,7 @@ gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const fl
     g.B = Operand{B, tb ? 1 : (long)N, tb ? (long)K : 1};
     g.B2 = Operand{B2, g.B.sk, g.B.sn};
     g.C = C; g.ldc = (int)ldc; g.bias = bias; g.act = act;
+    g.a_bits = a_bits; g.bit_words = (int)ceil_div(K, 16); g.bit_stride = 2 * ((g.bit_words + 1) / 2 | 1);
     const int w = tiles_wide(N);
     g.tiles_m = (int)ceil_div(M, 128); g.tiles_n = (int)ceil_div(N, 32 * w);
     const size_t one = gemm_split_workspace_bytes(N, K), words = parts_bytes(N, K);
@@ -435,10 +454,11 @@ gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const fl
                        (int)K, g.steps, g.B, g.B2, ws, ws2, range, range2);
     GNN_TRY(launch_status());
     const dim3 grid((unsigned)split_blocks(M, N));
-    const size_t lds = (size_t)2 * w * kStepBytes;
-    if (w == 1) hipLaunchKernelGGL(gemm_split_kernel<1>, grid, dim3(256), lds, st, g);
-    else if (w == 2) hipLaunchKernelGGL(gemm_split_kernel<2>, grid, dim3(256), lds, st, g);
-    else hipLaunchKernelGGL(gemm_split_kernel<4>, grid, dim3(256), lds, st, g);
+    const size_t lds = (size_t)2 * w * kStepBytes + (a_bits ? (size_t)128 * g.bit_stride * sizeof(uint16_t) : 0);
+    auto kernel = w == 1   ? (a_bits ? gemm_split_kernel<1, true> : gemm_split_kernel<1, false>)
+                  : w == 2 ? (a_bits ? gemm_split_kernel<2, true> : gemm_split_kernel<2, false>)
+                           : (a_bits ? gemm_split_kernel<4, true> : gemm_split_kernel<4, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), lds, st, g);
     return launch_status();
 }
 

@@ -26,6 +26,8 @@ struct GatLayout {
 
 // scratch of the products of a backward pass, one at a time: X^T H, and (dx) up to `pairs` pairs of G W^T
 size_t backward_gemm_bytes(int64_t n, int64_t m, int64_t k, bool dx, int pairs);
+// scratch of the bias gradient, in a pass of its own or beside X^T H
+size_t bias_gradient_bytes(int64_t n, int64_t m, int64_t k);
 GatLayout gat_layout(const Plan &p);
 gnn_status_t plan_create(const gnn_plan_desc_t *desc, Plan **out);
 

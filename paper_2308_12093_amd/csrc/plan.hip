@@ -92,7 +92,7 @@ void size_gcn(Plan &p) {
     // backward
     size_t bwd = 0;
     if (d.fuse_relu) bwd += align_up((size_t)n * k * fl);
-    if (d.has_bias) bwd += colsum_workspace_bytes(n, (int)k);
+    if (d.has_bias) bwd += bias_gradient_bytes(n, m, k);
     bwd += align_up(backward_gemm_bytes(n, m, k, dx, d.layer == GNN_LAYER_SAGE ? 2 : 1));
     if (fp) {
         bwd += align_up((size_t)n * k * fl) + spmm_workspace_bytes(n, q, (int)k);

@@ -1,0 +1,53 @@
+"""Backward of layers with bias and ReLU in the split-propagate scheme: bias gradient and mask formed beside X^T G, the mask
+taken by the products with the weights.  A' is the identity, so that every gradient is a dense product."""
+import pytest
+import torch
+
+from paper_2308_12093_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def normal(gen, *shape):
+    return torch.randn(*shape, generator=gen, device="cuda")
+
+
+def close(got, want, most):
+    assert bool(((got.double() - want).abs() <= most).all())
+
+
+# widths at the edges of tiles and of 16-column words; 2100 columns and few rows take the mask no product's way
+@pytest.mark.parametrize("sage", [False, True])
+@pytest.mark.parametrize("relu,dx", [(True, True), (True, False), (False, True)])
+@pytest.mark.parametrize("n,m,k", [(40007, 64, 64), (33000, 100, 33), (40000, 130, 47), (36000, 70, 200), (65536, 128, 512),
+                                   (35001, 96, 80), (34000, 300, 17), (3000, 40, 50), (40000, 40, 2100), (70001, 16, 5)])
+def test_gradients(n, m, k, relu, dx, sage):
+    gen = torch.Generator(device="cuda").manual_seed(n + m + k)
+    ids = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+    g = B.Graph(n, ids, ids[:n].clone(), torch.ones(n, device="cuda"), ids[:n].clone(), symmetric=True)
+    plan = B.Plan(B.GNN_LAYER_SAGE if sage else B.GNN_LAYER_GCN, n, n, m, k, need_input_grad=dx, has_bias=True, fuse_relu=relu,
+                  order=B.GNN_ORDER_PROPAGATE_FIRST, bwd=B.GNN_BWD_SPLIT_PROPAGATE)
+    X, Ws, Wn, b, dY = normal(gen, n, m), normal(gen, m, k) * 0.1, normal(gen, m, k) * 0.1, normal(gen, k), normal(gen, n, k)
+    dY[normal(gen, n, k) > 1.5] = 0.0
+    Y, dWs, dWn = torch.empty(n, k, device="cuda"), torch.empty(m, k, device="cuda"), torch.empty(m, k, device="cuda")
+    db, dX = torch.empty(k, device="cuda"), torch.empty(n, m, device="cuda") if dx else None
+    cache, ws = B.alloc(plan.info.cache_bytes), B.alloc(plan.info.workspace_bytes)
+    for _ in range(2):                                      # the second over what the first left
+        if sage:
+            B.sage_layer_fwd(plan, g, X, Ws, Wn, b, Y, cache, ws)
+            B.sage_layer_bwd(plan, g, X, Ws, Wn, Y, dY, dWs, dWn, db, dX, cache, ws)
+        else:
+            B.gcn_layer_fwd(plan, g, X, Wn, b, Y, cache, ws)
+            B.gcn_layer_bwd(plan, g, X, Wn, Y, dY, dWn, db, dX, cache, ws)
+    G = dY.double() * (Y > 0) if relu else dY.double()
+    # sums in double, and the rounding to float
+    double = lambda ref, mag, terms: 2.0 ** -24 * ref.abs() + 2 * terms * 2.0 ** -53 * mag  # noqa: E731
+    Xd = X.double()
+    ref, mag = Xd.t() @ G, Xd.abs().t() @ G.abs()
+    for d in (dWs, dWn) if sage else (dWn,):
+        close(d, ref, double(ref, mag, n))
+    close(db, G.sum(0), double(G.sum(0), G.abs().sum(0), n))
+    if dx:
+        # sums in float: at most eight roundings per 16 indices, and those of the two products and the aggregation
+        W, Wabs = (Ws.double() + Wn.double(), Ws.abs().double() + Wn.abs().double()) if sage else (Wn.double(), Wn.abs().double())
+        close(dX, G @ W.t(), (8 * ((k + 15) // 16) + 8) * 2.0 ** -24 * (G.abs() @ Wabs.t()))
