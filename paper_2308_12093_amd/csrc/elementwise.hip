@@ -30,11 +30,11 @@ activation_grad_kernel(long count4, long count, const float *__restrict__ G, con
 // min(f / VEC, 256)); each block owns `rows_per_block` consecutive rows and writes one partial
 // row of f sums.  Four rows are in flight per thread (rotating accumulators, added in a
 // fixed order).  VEC = 4 needs f and head_dim to be multiples of 4 and 16-byte aligned rows.
-// With a second weight array wgt2 the kernel forms two sums in one launch: output columns [0, f) use wgt,
-// columns [f, 2f) use wgt2 on the same G (the second read of a row comes from the cache); fo = 2f then.
+// DUAL: two sums of the same G in one pass, columns [0, fo / 2) with wgt and the others with wgt2 (2^17 x 256: 80 -> 53 us
+// against a second read of every row for the second sum); fo = 2f then.
 // masked: the masked gradient is written as well, where others read it later: one pass over G and Y instead of two
 // over G (2^17 x 512: 131 + 66 -> 178 us).
-template <int VEC>
+template <int VEC, bool DUAL>
 __global__ void __launch_bounds__(256)
 colsum_partial_kernel(long n, int f, int fo, int fp, long rows_per_block, const float *__restrict__ G,
                       const float *__restrict__ wgt, const float *__restrict__ wgt2, int heads, int head_dim,
@@ -44,57 +44,70 @@ colsum_partial_kernel(long n, int f, int fo, int fp, long rows_per_block, const 
     const int c0 = threadIdx.x % fp, rl = threadIdx.x / fp, lanes = 256 / fp;
     const long r0 = (long)blockIdx.x * rows_per_block;
     const long r1 = min(n, r0 + rows_per_block);
-    const int groups = (fo + VEC - 1) / VEC;
+    const int groups = (f + VEC - 1) / VEC;
+    constexpr int SETS = DUAL ? 2 : 1;
     for (int cb = 0; cb < groups; cb += fp) {
         const int c = (cb + c0) * VEC;
-        double a[4][VEC];
+        double a[SETS][4 / SETS][VEC];                     // rotating
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int d = 0; d < SETS; ++d)
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) a[j][v] = 0.0;
-        if (c < fo) {
-            const int cg = c < f ? c : c - f;                         // column of G
-            const float *wsel = c < f ? wgt : wgt2;
-            const int hd = wsel ? cg / head_dim : 0;
-            auto row = [&](long i, double (&acc)[VEC]) {
-                const double w = wsel ? (double)wsel[(size_t)i * heads + hd] : 1.0;
+            for (int j = 0; j < 4 / SETS; ++j)
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) a[d][j][v] = 0.0;
+        if (c < f) {
+            const int hd = wgt ? c / head_dim : 0;
+            auto row = [&](long i, int j) __attribute__((always_inline)) {
                 // with mask_y: G times the derivative of the fused activation, taken from its output
                 auto dact = [mask_act](float g, float y) { return y > 0.f ? g : (mask_act == kActElu ? g * (y + 1.f) : 0.f); };
+                float g[VEC];
                 if constexpr (VEC == 4) {
-                    float4 g = *reinterpret_cast<const float4 *>(G + (size_t)i * f + cg);
+                    float4 q = *reinterpret_cast<const float4 *>(G + (size_t)i * f + c);
                     if (mask_y) {
-                        const float4 y = *reinterpret_cast<const float4 *>(mask_y + (size_t)i * f + cg);
-                        g = make_float4(dact(g.x, y.x), dact(g.y, y.y), dact(g.z, y.z), dact(g.w, y.w));
-                        if (masked) *reinterpret_cast<float4 *>(masked + (size_t)i * f + cg) = g;
+                        const float4 y = *reinterpret_cast<const float4 *>(mask_y + (size_t)i * f + c);
+                        q = make_float4(dact(q.x, y.x), dact(q.y, y.y), dact(q.z, y.z), dact(q.w, y.w));
+                        if (masked) *reinterpret_cast<float4 *>(masked + (size_t)i * f + c) = q;
                     }
-                    acc[0] += w * g.x; acc[1] += w * g.y; acc[2] += w * g.z; acc[3] += w * g.w;
+                    g[0] = q.x; g[1] = q.y; g[2] = q.z; g[3] = q.w;
                 } else {
-                    float g = G[(size_t)i * f + cg];
+                    g[0] = G[(size_t)i * f + c];
                     if (mask_y) {
-                        g = dact(g, mask_y[(size_t)i * f + cg]);
-                        if (masked) masked[(size_t)i * f + cg] = g;
+                        g[0] = dact(g[0], mask_y[(size_t)i * f + c]);
+                        if (masked) masked[(size_t)i * f + c] = g[0];
                     }
-                    acc[0] += w * (double)g;
+                }
+                const double w = wgt ? (double)wgt[(size_t)i * heads + hd] : 1.0;
+                const double w2 = DUAL ? (double)wgt2[(size_t)i * heads + hd] : 0.0;
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    a[0][j % (4 / SETS)][v] += w * g[v];
+                    if constexpr (DUAL) a[SETS - 1][j % (4 / SETS)][v] += w2 * g[v];
                 }
             };
             long i = r0 + rl;
             for (; i + 3L * lanes < r1; i += 4L * lanes) {
-                row(i, a[0]); row(i + lanes, a[1]); row(i + 2L * lanes, a[2]); row(i + 3L * lanes, a[3]);
+                row(i, 0); row(i + lanes, 1); row(i + 2L * lanes, 2); row(i + 3L * lanes, 3);
             }
-            for (; i < r1; i += lanes) row(i, a[0]);
+            for (; i < r1; i += lanes) row(i, 0);
         }
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) red[threadIdx.x][v] = (a[0][v] + a[1][v]) + (a[2][v] + a[3][v]);
-        __syncthreads();
-        if (rl == 0 && c < fo) {
+        for (int d = 0; d < SETS; ++d) {
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
-                double s = 0.0;
-                for (int k = 0; k < lanes; ++k) s += red[k * fp + c0][v];
-                part[(size_t)blockIdx.x * fo + c + v] = s;
+                if constexpr (DUAL) red[threadIdx.x][v] = a[d][0][v] + a[d][1][v];
+                else red[threadIdx.x][v] = (a[d][0][v] + a[d][1][v]) + (a[d][2][v] + a[d][3][v]);
             }
+            __syncthreads();
+            if (rl == 0 && c < f) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    double s = 0.0;
+                    for (int k = 0; k < lanes; ++k) s += red[k * fp + c0][v];
+                    part[(size_t)blockIdx.x * fo + d * f + c + v] = s;
+                }
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
@@ -161,11 +174,13 @@ constexpr int kXentLdsFloats = 12288;          // 48 KB tile of logits
 
 // The same per 256-node block, tiled through LDS: a pass copies R = 256 / G whole rows (contiguous in
 // memory, so the copy is coalesced), G = 2^g lanes share a row (elements lane, lane + G, ...; maximum and
-// sum by a fixed xor tree), the gradients replace the logits in LDS and go out coalesced again.
+// sum by a fixed xor tree), the gradients replace the logits in LDS and go out coalesced again.  A tile takes what R rows
+// need: the loads of one block hide behind the others of its CU (2^20 x 47: 244 -> 78 us with that, with four words a
+// lane where tiles are 16-byte aligned, and with one exponential per element instead of two).
 __global__ void __launch_bounds__(256)
 softmax_xent_tiled_kernel(int n, int c, int G, const float *__restrict__ Z, const int32_t *__restrict__ labels,
-                          float *__restrict__ dZ, float *__restrict__ block_loss) {
-    __shared__ float tile[kXentLdsFloats];
+                          float *__restrict__ dZ, float *__restrict__ block_loss, int aligned) {
+    extern __shared__ __align__(16) float tile[];
     __shared__ float red[256];
     const int R = 256 / G;
     const int r = threadIdx.x / G, g = threadIdx.x % G;
@@ -175,7 +190,12 @@ softmax_xent_tiled_kernel(int n, int c, int G, const float *__restrict__ Z, cons
         const int rows = min(R, n - first - p0);
         const size_t base = (size_t)(first + p0) * c;
         const int count = rows * c;
-        for (int i = threadIdx.x; i < count; i += 256) tile[i] = Z[base + i];
+        const bool vec = base % 4 == 0 && count % 4 == 0 && aligned;       // uniform
+        if (vec)
+            for (int i = 4 * threadIdx.x; i < count; i += 1024)
+                *reinterpret_cast<float4 *>(tile + i) = *reinterpret_cast<const float4 *>(Z + base + i);
+        else
+            for (int i = threadIdx.x; i < count; i += 256) tile[i] = Z[base + i];
         __syncthreads();
         float mx = -INFINITY, sum = 0.f, zl = 0.f;
         int lab = -1;
@@ -183,19 +203,27 @@ softmax_xent_tiled_kernel(int n, int c, int G, const float *__restrict__ Z, cons
         if (r < rows) {
             for (int t = g; t < c; t += G) mx = fmaxf(mx, z[t]);
             for (int o = G >> 1; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-            for (int t = g; t < c; t += G) sum += expf(z[t] - mx);
-            for (int o = G >> 1; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
             lab = labels[first + p0 + r];
             zl = z[lab];
         }
         __syncthreads();                                   // every read of the logits precedes the overwrite
-        if (r < rows) {
+        if (r < rows) {                                    // a lane's elements are its own from here on
+            for (int t = g; t < c; t += G) {
+                const float e = expf(z[t] - mx);
+                z[t] = e;
+                sum += e;
+            }
+            for (int o = G >> 1; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
             if (g == 0) loss += logf(sum) + mx - zl;
             const float inv = 1.f / sum;
-            for (int t = g; t < c; t += G) z[t] = expf(z[t] - mx) * inv - (t == lab ? 1.f : 0.f);
+            for (int t = g; t < c; t += G) z[t] = z[t] * inv - (t == lab ? 1.f : 0.f);
         }
         __syncthreads();
-        for (int i = threadIdx.x; i < count; i += 256) dZ[base + i] = tile[i];
+        if (vec)
+            for (int i = 4 * threadIdx.x; i < count; i += 1024)
+                *reinterpret_cast<float4 *>(dZ + base + i) = *reinterpret_cast<const float4 *>(tile + i);
+        else
+            for (int i = threadIdx.x; i < count; i += 256) dZ[base + i] = tile[i];
         __syncthreads();
     }
     red[threadIdx.x] = loss;
@@ -274,16 +302,14 @@ static gnn_status_t colsum_weighted(int64_t n, int f, const float *G, const floa
     const bool vec = f % 4 == 0 && head_dim % 4 == 0 && aligned16(G) && (!mask_y || aligned16(mask_y)) &&
                      (!masked || aligned16(masked));
     const int fo = wgt2 ? 2 * f : f;
-    const int groups = vec ? fo / 4 : fo;
+    const int groups = vec ? f / 4 : f;
     int fp = 1;
     while (fp < groups && fp < 256) fp <<= 1;
     double *part = static_cast<double *>(workspace);
-    if (vec)
-        hipLaunchKernelGGL(colsum_partial_kernel<4>, dim3(blocks), dim3(256), 0, st, (long)n, f, fo, fp, rpb, G, wgt, wgt2,
-                           heads, head_dim, mask_y, mask_act, masked, part);
-    else
-        hipLaunchKernelGGL(colsum_partial_kernel<1>, dim3(blocks), dim3(256), 0, st, (long)n, f, fo, fp, rpb, G, wgt, wgt2,
-                           heads, head_dim, mask_y, mask_act, masked, part);
+    auto kernel = vec ? (wgt2 ? colsum_partial_kernel<4, true> : colsum_partial_kernel<4, false>)
+                      : (wgt2 ? colsum_partial_kernel<1, true> : colsum_partial_kernel<1, false>);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, (long)n, f, fo, fp, rpb, G, wgt, wgt2, heads, head_dim, mask_y,
+                       mask_act, masked, part);
     GNN_TRY(launch_status());
     hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)ceil_div(fo, 16)), dim3(256), 0, st, fo, f, blocks, part, out,
                        out2);
@@ -321,7 +347,8 @@ gnn_status_t softmax_xent_launch(int n, int c, const float *Z, const int32_t *la
     int G = 1;                                             // lanes per row: about 16 elements each
     while (G < 64 && G * 16 < c) G <<= 1;
     if ((long)(256 / G) * c <= kXentLdsFloats)
-        hipLaunchKernelGGL(softmax_xent_tiled_kernel, dim3(blocks), dim3(256), 0, st, n, c, G, Z, labels, dZ, part);
+        hipLaunchKernelGGL(softmax_xent_tiled_kernel, dim3(blocks), dim3(256), (size_t)(256 / G) * c * sizeof(float), st, n, c,
+                           G, Z, labels, dZ, part, aligned16(Z) && aligned16(dZ));
     else
         hipLaunchKernelGGL(softmax_xent_rows_kernel, dim3(blocks), dim3(256), 0, st, n, c, Z, labels, dZ, part);
     GNN_TRY(launch_status());
