@@ -20,6 +20,8 @@ constexpr int kActAccumulate = 4;
 constexpr int kActStream = 8;
 // plain products: an activation or a LeakyReLU further down decides on the sign of the result
 constexpr int kActSigns = 16;
+// plain products with kActRelu: a result within rounding of zero may fall on either side of it
+constexpr int kActAnySign = 32;
 constexpr size_t kStreamBytes = (size_t)64 << 20;
 
 static inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a; }

@@ -904,7 +904,7 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
         // the kernel wants B with the reduction index contiguous: B[N][K]; transpose a [K][N] weight first
         const float *Bt = B, *Bt2 = B2;
         if (K <= 0) A2 = Bt2 = nullptr;                    // an empty reduction: nothing to add
-        const bool signs = (relu & (kActRelu | kActSigns)) != 0;
+        const bool signs = (relu & (kActRelu | kActSigns)) != 0 && !(relu & kActAnySign);
         relu &= kActRelu | kActAccumulate;
         if (few_rows(tb, M, N, K)) {
             const long tn = ceil_div(N, 32);
