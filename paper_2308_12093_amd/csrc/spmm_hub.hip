@@ -1,14 +1,14 @@
 // Sparse-dense product of a large graph with hubs: long rows in pieces, ordered by where their columns lie.
 //
 // What bounds the SpMM on a large graph are the lines that miss the L2s: a compute unit has at most 64 lines under way
-// (TCP_TCC_READ_REQ_LATENCY over the cycles, in this kernel and in spmm_seg_kernel), so its rate is 64 lines over their
-// mean latency, and a line from beyond the L2 takes three to four times as long as one in it.  Each of the eight L2s (4 MB)
-// meets the columns of its share of the rows in no order and fetches nearly every gathered row anew (2^20 nodes, f = 100:
-// 19.6 GB of 25 GB requested).  But the columns of a row ascend, and where a graph has hubs most entries lie in long
-// rows (in rows of 128 and more: 78 % of the entries there, 70 % at 2^22 nodes).  So long rows are cut into pieces, and
-// the pieces of all rows are processed in the order of their position inside the row, XCD x the x-th eighth of that order:
-// it gathers from about an eighth of the dense operand, walked once from beginning to end in step with all other long
-// rows.  Lines fetched at f = 100: 19.6 -> 12.7 GB; 2960 -> 2260 us.  f = 64 at 2^22 nodes: 4300 -> 3530 us.
+// (TCP_TCC_READ_REQ_LATENCY over cycles and CUs is 64 in this kernel), so its rate is 64 lines over their mean latency, and
+// a line from beyond the L2 takes three to four times as long as one in it.  Each of the eight L2s (4 MB) meets the columns
+// of its share of the rows in no order and fetches nearly every gathered row anew (2^20 nodes, f = 100: 19.6 GB of 25 GB
+// requested).  But the columns of a row ascend, and where a graph has hubs most entries lie in long rows (in rows of 128
+// and more: 78 % of the entries there, 70 % at 2^22 nodes).  So long rows are cut into pieces, and the pieces of all rows
+// are processed in the order of their position inside the row, XCD x the x-th eighth of that order: it gathers from about
+// an eighth of the dense operand, walked once from beginning to end in step with all other long rows.  Lines fetched at
+// f = 100: 19.6 -> 12.7 GB; 2960 -> 2330 us.  f = 64 at 2^22 nodes: 4300 -> 3630 us.
 // Nothing but the time depends on the order of the columns.
 //
 //   hub_count_kernel    looks at kSamples rows: is a third of the entries in long ones?  If not, all that follow return
@@ -17,11 +17,12 @@
 //   (scan)              counts -> places
 //   hub_scatter_kernel  writes the ordered list of pieces and short rows, and the list of long rows
 //   hub_gather_kernel   one group of lanes per item: a partial row for a piece, a row of C for a short row
-//   hub_reduce          (in spmm_fixup_kernel) one wavefront per long row: its partials in a fixed order, bias, activation
+//   hub_reduce          (in spmm_fixup_kernel) one wavefront per long row: its partials in a fixed order, bias,
+//                       activation
 //
-// Shorter pieces, or pieces cut at columns instead of positions, miss less often (8.9 instead of 12.7 GB) and are no
-// faster: 32 entries a piece 2300 us, cut at columns 2250 - 2310 us.  So are gathers of the next sixteen entries under
-// way while sixteen are folded (2350 us): the lines under way are what is short.
+// Shorter pieces, or pieces cut at columns instead of positions, miss less often (11.4 instead of 12.7 GB) and are no
+// faster, within 2 %; with the gathers of the next sixteen entries under way while sixteen are folded it is 4 % slower: the
+// lines under way are what is short.
 #include "spmm_hub.h"
 
 #include <type_traits>
