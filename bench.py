@@ -171,7 +171,7 @@ def spmm_roofline(torch, B, ev, g, launch_widths, workload, step_ms):
     if parts and all(p[0] is not None for p in parts):
         traffic, src = round(sum(p[0] for p in parts) / len(parts)), parts[0][1]
     widths = sorted(per_width)
-    return {"bound": "hbm", "kernel": "spmm_seg_kernel (+ spmm_fixup_kernel)", "achieved": round(achieved, 1),
+    return {"bound": "hbm", "kernel": "gnn_spmm_csr (spmm_seg_kernel or hub_gather_kernel, + spmm_fixup_kernel)", "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
             "traffic": traffic, "traffic_source": src,
             # the same launches priced by the bytes the L2s exchanged with the fabric (the profile above)
