@@ -224,6 +224,7 @@ gnn_status_t gcn_layer_bwd(gnn_plan_t *plan, const gnn_graph_t *graph, const flo
  *   X [n, f_in], W_self / W_neigh [f_in, f_out], b [f_out] or NULL, Y [n, f_out]
  *   backward: dW_self = X^T G, dW_neigh = (A'X)^T G, db = G^T 1, dX = G W_self^T + A'^T G W_neigh^T
  *   (G = dY, masked by [Y > 0] with fuse_relu).  X is needed by backward in every scheme.
+ *   dX and dY may share memory with fuse_relu only (in gcn_layer_bwd always): without it dY is read after dX is written.
  * cache / workspace sizes: gnn_plan_query.  Errors as gcn_layer_fwd / gcn_layer_bwd.
  */
 gnn_status_t sage_layer_fwd(gnn_plan_t *plan, const gnn_graph_t *graph, const float *X, const float *W_self,

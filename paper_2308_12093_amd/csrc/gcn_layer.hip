@@ -41,25 +41,32 @@ int relu_flags(const gnn_plan_desc_t &d, int with_relu) {
     return !d.fuse_relu ? 0 : sums_decide_signs(d) || d.n < 1 << 16 ? with_relu : with_relu | kActAnySign;
 }
 
+bool overlap(const float *a, size_t count_a, const float *b, size_t count_b) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a && b && x < y + count_b * sizeof(float) && y < x + count_a * sizeof(float);
+}
+
 // Gradient through the fused ReLU, G = dY .* [Y > 0], and through the bias, db = G^T 1.
 // Split-propagate scheme: G is read by the weight-gradient products, which mask dY as they load it and add up db on the
 // side, and with dX by the products with the weights, which take the mask as bits from the first of those: G is never
-// written, nothing but products reads dY or Y (2^17 nodes, 128 -> 512, a step: 930 -> 828 us; GraphSAGE 128 -> 128: 588 -> 568).  Where those products run on a kernel that
-// takes no bits, and in the fused-propagate scheme, whose gather would fetch Y beside dY, one pass makes G and db.
+// written, nothing but products reads dY or Y (2^17 nodes, 128 -> 512, a step: 930 -> 828 us; GraphSAGE 128 -> 128:
+// 588 -> 573).  Where those products run on a kernel that takes no bits, where dY is read again after dX was written and
+// shares memory with it, and in the fused-propagate scheme, whose gather would fetch Y beside dY, one pass makes G and db.
 struct BiasAndMask {
     const float *G = nullptr, *mask_y = nullptr;       // G, or dY and what the products mask it by
     GemmExtras side{}, masked{};                       // for the first weight-gradient product; for those with the weights
 
-    // W, W2: the weights behind G
+    // W, W2: the weights behind G; dX: where the input gradient goes if dY is read once more behind it, or NULL
     gnn_status_t start(const gnn_plan_desc_t &d, gnn_bwd_t bwd, const float *W, const float *W2, const float *Y,
-                       const float *dY, float *db, Carver &ws, hipStream_t st) {
+                       const float *dY, const float *dX, float *db, Carver &ws, hipStream_t st) {
         const int n = d.n, m = d.f_in, k = d.f_out;
         const bool dx = d.need_input_grad != 0, split = bwd == GNN_BWD_SPLIT_PROPAGATE;
         // carved either way: the layout is the plan's
         float *Gm = d.fuse_relu ? ws.take<float>((size_t)n * k) : nullptr;
         void *red = d.has_bias ? ws.take<char>(bias_gradient_bytes(n, m, k)) : nullptr;
-        const bool in_products = split && (!d.fuse_relu || !dx || (gemm_takes_bits(1, n, m, k, dY, W) &&
-                                                                           gemm_takes_bits(1, n, m, k, dY, W2)));
+        const bool in_products = split && (!d.fuse_relu || !dx ||
+                                           (!overlap(dX, (size_t)n * m, dY, (size_t)n * k) &&
+                                            gemm_takes_bits(1, n, m, k, dY, W) && gemm_takes_bits(1, n, m, k, dY, W2)));
         G = dY;
         if (in_products) {
             if (d.has_bias) side = GemmExtras{db, red, nullptr, nullptr};
@@ -129,7 +136,7 @@ gnn_status_t gcn_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
     Carver ws(workspace);
 
     BiasAndMask bm;
-    GNN_TRY(bm.start(d, p.info.bwd, W, W, Y, dY, db, ws, st));
+    GNN_TRY(bm.start(d, p.info.bwd, W, W, Y, dY, nullptr, db, ws, st));
     const float *G = bm.G;
     void *gemm_ws = ws.take<char>(backward_gemm_bytes(n, m, k, dx, 1));   // one product at a time
 
@@ -204,7 +211,7 @@ gnn_status_t sage_backward(Plan &p, const gnn_graph_t &g, const float *X, const 
     Carver ws(workspace);
 
     BiasAndMask bm;
-    GNN_TRY(bm.start(d, p.info.bwd, Ws, Wn, Y, dY, db, ws, st));
+    GNN_TRY(bm.start(d, p.info.bwd, Ws, Wn, Y, dY, dX, db, ws, st));
     const float *G = bm.G;
     void *gemm_ws = ws.take<char>(backward_gemm_bytes(n, m, k, dx, 2));
     GNN_TRY(gemm_launch(1, 0, m, k, n, X, G, dWs, nullptr, 0, gemm_ws, st, bm.mask_y, kActRelu, 0, nullptr, nullptr,

@@ -51,3 +51,37 @@ def test_gradients(n, m, k, relu, dx, sage):
         # sums in float: at most eight roundings per 16 indices, and those of the two products and the aggregation
         W, Wabs = (Ws.double() + Wn.double(), Ws.abs().double() + Wn.abs().double()) if sage else (Wn.double(), Wn.abs().double())
         close(dX, G @ W.t(), (8 * ((k + 15) // 16) + 8) * 2.0 ** -24 * (G.abs() @ Wabs.t()))
+
+
+@pytest.mark.parametrize("sage", [False, True])
+@pytest.mark.parametrize("offset", [0, 128])
+@pytest.mark.parametrize("n,m", [(40007, 64), (33000, 100), (3000, 40)])
+def test_input_gradient_over_the_output_gradient(n, m, offset, sage):
+    """dX in the memory of dY, the same rows or some floats before them."""
+    gen = torch.Generator(device="cuda").manual_seed(n + m)
+    ids = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+    g = B.Graph(n, ids, ids[:n].clone(), torch.ones(n, device="cuda"), ids[:n].clone(), symmetric=True)
+    plan = B.Plan(B.GNN_LAYER_SAGE if sage else B.GNN_LAYER_GCN, n, n, m, m, has_bias=True, fuse_relu=True,
+                  order=B.GNN_ORDER_PROPAGATE_FIRST, bwd=B.GNN_BWD_SPLIT_PROPAGATE)
+    X, Ws, Wn, b = normal(gen, n, m), normal(gen, m, m) * 0.1, normal(gen, m, m) * 0.1, normal(gen, m)
+    memory = normal(gen, n * m + offset)
+    dY, dX = memory[offset:].view(n, m), memory[:n * m].view(n, m)
+    G = dY.double()
+    Y, cache, ws = torch.empty(n, m, device="cuda"), B.alloc(plan.info.cache_bytes), B.alloc(plan.info.workspace_bytes)
+    dWs, dWn, db = torch.empty(m, m, device="cuda"), torch.empty(m, m, device="cuda"), torch.empty(m, device="cuda")
+    if sage:
+        B.sage_layer_fwd(plan, g, X, Ws, Wn, b, Y, cache, ws)
+        B.sage_layer_bwd(plan, g, X, Ws, Wn, Y, dY, dWs, dWn, db, dX, cache, ws)
+    else:
+        B.gcn_layer_fwd(plan, g, X, Wn, b, Y, cache, ws)
+        B.gcn_layer_bwd(plan, g, X, Wn, Y, dY, dWn, db, dX, cache, ws)
+    G *= Y > 0
+    # bounds as above
+    double = lambda ref, mag: 2.0 ** -24 * ref.abs() + 2 * n * 2.0 ** -53 * mag  # noqa: E731
+    Xd = X.double()
+    ref, mag = Xd.t() @ G, Xd.abs().t() @ G.abs()
+    for d in (dWs, dWn) if sage else (dWn,):
+        close(d, ref, double(ref, mag))
+    close(db, G.sum(0), double(G.sum(0), G.abs().sum(0)))
+    W, Wabs = (Ws.double() + Wn.double(), Ws.abs().double() + Wn.abs().double()) if sage else (Wn.double(), Wn.abs().double())
+    close(dX, G @ W.t(), (8 * ((m + 15) // 16) + 8) * 2.0 ** -24 * (G.abs() @ Wabs.t()))
