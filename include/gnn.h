@@ -429,6 +429,7 @@ size_t gnn_gat_aggregate_workspace_bytes(int32_t nnz, int32_t heads, int32_t f);
  *   otherwise); any other bit is GNN_ERR_INVALID_ARG.
  *   workspace: gnn_gemm_workspace_bytes(trans_a, trans_b, M, N, K); required for (0,0) (holds B in the
  *   form the product reads) and (1,0) (holds the partial products); (0,1) runs without, faster with.
+ *   A workspace for K serves every smaller K.
  */
 enum { GNN_GEMM_RELU = 1, GNN_GEMM_ACCUMULATE = 4 };
 gnn_status_t gnn_gemm(int32_t trans_a, int32_t trans_b, int64_t M, int64_t N, int64_t K,

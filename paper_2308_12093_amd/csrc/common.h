@@ -92,12 +92,14 @@ float *spmm_padded_operand(void *workspace, const int32_t *erow, int64_t b_rows,
 
 // ---- dense products (gemm.hip) ----------------------------------------------------
 size_t gemm_workspace_bytes(int ta, int tb, int64_t M, int64_t N, int64_t K);
+// the transposed-A form over exactly K indices: no more than the above
+size_t gemm_tn_workspace_bytes(int64_t M, int64_t N, int64_t K);
 // b_mask (transposed-A form only): B is used as B .* act'(b_mask), the derivative of the activation
 // b_mask_act (kActRelu, kActElu) taken from its output b_mask, an array of B's shape.
 // ldc (plain products only): rows of C are ldc >= N floats apart, the columns in between written as zeros.
 // A2, B2 (plain products only; shapes of A and B): C = op(A) op(B) + op(A2) op(B2) in one pass, one rounding
 // chain; needs a workspace of 2 x gemm_workspace_bytes.
-// workspace: gemm_workspace_bytes; the A B^T form also runs without one (NULL).
+// workspace: gemm_workspace_bytes, never less for a larger K; the A B^T form also runs without one (NULL).
 // extras: what a product does on the side, or a mask it takes (see GemmExtras).
 struct GemmExtras {
     float *sums;            // transposed-A form: the column sums of B as used, or NULL

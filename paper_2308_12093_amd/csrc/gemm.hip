@@ -738,6 +738,7 @@ struct TnTile {
 constexpr TnTile kTnTiles[] = {{{4, 1, 1, 1}, 6, 1.7}, {{4, 1, 1, 2}, 5, 1.5}, {{4, 1, 2, 3}, 3, 1.15}, {{2, 2, 2, 2}, 3, 1.08},
                                {{2, 2, 3, 3}, 2, 1.13}, {{4, 1, 2, 5}, 2, 1.12}, {{4, 1, 2, 7}, 2, 1.1}, {{2, 2, 4, 4}, 2, 1.03}};
 constexpr double kTnWait = 0.4, kTnTurn = 0.15;            // us a k-tile: a block on its own, any number of them
+constexpr int kTnBlocks = 8;                               // blocks a CU at most, over the whole launch
 
 struct TnPlan {
     Tiling tile;
@@ -755,7 +756,7 @@ TnPlan pick_tn(int64_t M, int64_t N, int64_t K, bool side) {
         const int64_t tiles = ceil_div(M, bm) * ceil_div(N, bn);
         const double step = c.rate / 4096 * bm * bn;
         int64_t before = 0;
-        for (int want = -7; want <= 8; ++want) {           // blocks a CU; below one, fractions of the chip
+        for (int want = -7; want <= kTnBlocks; ++want) {   // blocks a CU; below one, fractions of the chip
             int64_t splits = (want > 0 ? 256 * want : 256 >> -want) / tiles;
             if (splits > ktiles / 3) splits = ktiles / 3;
             if (splits < 1) splits = 1;
@@ -777,6 +778,18 @@ TnPlan pick_tn(int64_t M, int64_t N, int64_t K, bool side) {
         }
     }
     return best;
+}
+
+// What pick_tn stays below for K indices and for any smaller number.  Its choice itself does not grow with K: where it goes
+// over to larger tiles, fewer chunks make as many blocks (100 x 256: 512 chunks over 1.6 M indices, 256 over 2.0 M).
+int64_t most_chunks(int64_t M, int64_t N, int64_t K) {
+    int64_t most = 1;
+    for (const TnTile &c : kTnTiles) {
+        const int64_t chunks = 256 * kTnBlocks / (ceil_div(M, tile_m(true, c.tile)) * ceil_div(N, tile_n(true, c.tile)));
+        if (chunks > most) most = chunks;
+    }
+    const int64_t by_k = ceil_div(K > 0 ? K : 1, BK) / 3;
+    return by_k < 1 ? 1 : by_k < most ? by_k : most;
 }
 
 // One wavefront per 32 x 32 tile while there are few; beyond, the kernels that share operands through LDS.  Both sides of
@@ -823,6 +836,11 @@ size_t gemm_workspace_bytes(int ta, int tb, int64_t M, int64_t N, int64_t K) {
         const size_t bt = tb ? kAlign : align_up((size_t)N * K * sizeof(float));
         return parts > bt ? parts : bt;
     }
+    // not what this K takes, but what serves every smaller one as well: a caller sizes its scratch once, for the most rows
+    return align_up((size_t)most_chunks(M, N, K) * M * N * sizeof(double));
+}
+
+size_t gemm_tn_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     const int a = pick_tn(M, N, K, false).splits, b = pick_tn(M, N, K, true).splits;
     return align_up((size_t)(a > b ? a : b) * M * N * sizeof(double));
 }

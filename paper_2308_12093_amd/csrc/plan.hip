@@ -145,7 +145,7 @@ double spmm_time_model_us(int64_t n, int64_t nnz, int f) {
 }
 
 size_t backward_gemm_bytes(int64_t n, int64_t m, int64_t k, bool dx, int pairs) {
-    const size_t tn = gemm_workspace_bytes(1, 0, m, k, n);
+    const size_t tn = gemm_tn_workspace_bytes(m, k, n);
     const size_t nt = dx ? pairs * gemm_workspace_bytes(0, 1, n, m, k) : 0;
     return tn > nt ? tn : nt;
 }
