@@ -976,10 +976,14 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
     const int vec_b = aligned16(B) && N % 4 == 0 && (!b_mask || aligned16(b_mask));
     const long total = (long)tiles_m * tiles_n * splits;
     dim3 grid((unsigned)(8 * ceil_div(total, 8)));
-    GEMM_F64_CASE(4, 1, 1, 1) GEMM_F64_CASE(4, 1, 1, 2) GEMM_F64_CASE(4, 1, 2, 3) GEMM_F64_CASE(2, 2, 2, 2)
-    GEMM_F64_CASE(2, 2, 3, 3) GEMM_F64_CASE(4, 1, 2, 5) GEMM_F64_CASE(4, 1, 2, 7) GEMM_F64_CASE(2, 2, 4, 4)
-    if (!launched) return GNN_ERR_UNSUPPORTED;
-    GNN_TRY(launch_status());
+    if (K <= 0) {
+        splits = 0;                                        // no chunk, no workspace: the sums of none are zero
+    } else {
+        GEMM_F64_CASE(4, 1, 1, 1) GEMM_F64_CASE(4, 1, 1, 2) GEMM_F64_CASE(4, 1, 2, 3) GEMM_F64_CASE(2, 2, 2, 2)
+        GEMM_F64_CASE(2, 2, 3, 3) GEMM_F64_CASE(4, 1, 2, 5) GEMM_F64_CASE(4, 1, 2, 7) GEMM_F64_CASE(2, 2, 4, 4)
+        if (!launched) return GNN_ERR_UNSUPPORTED;
+        GNN_TRY(launch_status());
+    }
     const long count = (long)M * N, count2 = extras && extras->sums ? N : 0;
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)(ceil_div(count, 16) + ceil_div(count2, 16))), dim3(256), 0, st,
                        count, splits, static_cast<const double *>(workspace), C, count2,

@@ -129,3 +129,13 @@ def test_masked_gradient(n):
     B.gcn_layer_fwd(plan, g, X, W, None, Y, cache, ws)
     B.gcn_layer_bwd(plan, g, X, W, Y, dY, dW, None, None, cache, ws)
     check(dW, X, dY * (Y > 0))
+
+
+@pytest.mark.parametrize("M,N", [(1, 1), (5, 7), (16, 3), (300, 500)])
+def test_no_rows_need_no_room(M, N):
+    """Zero rows: zeros, and nothing written behind the workspace that the query asks for."""
+    need = B.gnn_gemm_workspace_bytes(1, 0, M, N, 0)
+    memory = torch.full((need + 16 * M * N + 256,), 7, dtype=torch.uint8, device="cuda")
+    A, H, C = torch.empty(1, M, device="cuda"), torch.empty(1, N, device="cuda"), torch.full((M, N), float("nan"), device="cuda")
+    B.gnn_gemm(1, 0, M, N, 0, A, H, C, None, 0, memory[:need])
+    assert bool((C == 0).all()) and bool((memory[need:] == 7).all())
