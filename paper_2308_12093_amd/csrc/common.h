@@ -105,7 +105,8 @@ struct GemmExtras {
     float *sums;            // transposed-A form: the column sums of B as used, or NULL
     void *workspace;        //   gemm_sums_bytes(M, N, K) of scratch for them
     uint16_t *bits;         //   and which elements of it are not zero, or NULL: [K][ceil(N / 16)], 16 columns to a word
-    const uint16_t *a_bits; // plain products that gemm_takes_bits: such words for A [M][ceil(K / 16)], zero = used as 0
+    const uint16_t *a_bits; // plain products of one operand pair that gemm_takes_bits: such words for A
+                            //   [M][ceil(K / 16)], zero = used as 0
 };
 size_t gemm_sums_bytes(int64_t M, int64_t N, int64_t K);
 bool gemm_takes_bits(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B);

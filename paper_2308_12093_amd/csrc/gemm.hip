@@ -899,7 +899,9 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
                          const float *b_mask, int b_mask_act, int64_t ldc, const float *A2, const float *B2,
                          const GemmExtras *extras) {
     if (M <= 0 || N <= 0) return GNN_OK;
-    if (extras && ((extras->a_bits && (ta || !gemm_takes_bits(tb, M, N, K, A, B))) || ((extras->sums || extras->bits) && !ta)))
+    // bits belong to the first operand pair and would be read past its words for a second one
+    if (extras && ((extras->a_bits && (ta || A2 || !gemm_takes_bits(tb, M, N, K, A, B))) ||
+                   ((extras->sums || extras->bits) && !ta)))
         return GNN_ERR_UNSUPPORTED;
     if (ta && tb) return GNN_ERR_UNSUPPORTED;
     if ((A2 != nullptr) != (B2 != nullptr) || (A2 && ta)) return GNN_ERR_UNSUPPORTED;   // the plain products only

@@ -282,6 +282,19 @@ def test_products_beyond_the_step_count_are_refused_before_any_launch(trans_b, r
     assert B.lib.gnn_gemm(0, trans_b, m, m, m, one, one, one, None, relu, one, 1 << 40, None) == B.GNN_ERR_UNSUPPORTED
 
 
+def test_a_mask_beside_a_second_operand_pair_is_refused():
+    """The words of GemmExtras::a_bits stand for the first pair alone.  No public call joins the two: the library's own."""
+    launch = getattr(B.lib, "_ZN3gnn11gemm_launchEiilllPKfS1_PfS1_iPvP12ihipStream_tS1_ilS1_S1_PKNS_10GemmExtrasE")
+    launch.restype, i64, ptr = ctypes.c_int, ctypes.c_int64, ctypes.c_void_p
+    launch.argtypes = [ctypes.c_int] * 2 + [i64] * 3 + [ptr] * 4 + [ctypes.c_int, ptr, ptr, ptr, ctypes.c_int, i64] + [ptr] * 3
+    extras = (ptr * 4)(None, None, None, 256)              # sums, workspace, bits, a_bits
+    one, (M, N, K) = ptr(256), (200000, 128, 64)
+    call = lambda a2: launch(0, 1, M, N, K, one, one, one, None, 0, one, None, None, 0, 0, a2, a2, extras)  # noqa: E731
+    assert call(one) == B.GNN_ERR_UNSUPPORTED
+    extras[3] = None
+    assert launch(1, 0, M, N, K, one, one, one, None, 0, one, None, None, 0, 0, one, one, extras) == B.GNN_ERR_UNSUPPORTED
+
+
 # ---- calibrated selection and constant inputs (host logic) --------------------------------
 def model_us(n, nnz, f):
     """The documented time model, evaluated here from the text of the header."""
