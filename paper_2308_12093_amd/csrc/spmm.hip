@@ -473,10 +473,12 @@ size_t spmm_segments_bytes(int64_t n, int64_t nnz, int f) {
 }
 
 // Products whose long rows, where there are many, are computed in pieces (spmm_hub.hip): from 2e9 multiplications on, about
-// a millisecond.  Below, its longer way through lists and queues (100 us) eats the gain: R-MAT, 2^20 nodes, 53 M entries,
-// f = 16 (0.9e9): 587 -> 662 us; 2^18, 5.5 M, f = 200 (1.1e9): 559 -> 561; above, 2^20, f = 47 (2.5e9): 1410 -> 1280;
-// 2^19, 16 M, f = 200 (3.3e9): 1613 -> 1408; 2^22, 138 M, f = 64 (8.9e9): 4307 -> 3630.  A graph without long rows pays
-// five launches: uniform, 2^20 nodes, 22 M entries, f = 128 (2.8e9): 1637 -> 1657.
+// a millisecond.  Below, its longer way through lists, queues and partials (60 us) eats the gain where rows are narrow: R-MAT,
+// segments / pieces, us, 2^20 nodes, 53 M entries, f = 16 (0.9e9) 555 / 618, f = 32 (1.7e9) 608 / 670; 2^18, 5.5 M, f = 200
+// (1.1e9) 545 / 554; 2^19, 16 M, f = 100 (1.6e9) 803 / 711; above, 2^18, f = 400 (2.2e9) 1139 / 1037; 2^20, f = 47 (2.5e9)
+// 1316 / 1204; 2^19, f = 200 (3.2e9) 1649 / 1297; 2^22, 136 M, f = 64 (8.7e9) 4839 / 3553.  The host does not know whether a
+// graph has long rows, and one without pays three launches that end at once: uniform, 2^20 nodes, 22 M entries, f = 128
+// (2.8e9) 1630 / 1641, 2^22, 100 M, f = 64 (6.4e9) 4594 / 4631.
 constexpr int64_t kHubWork = 2000000000;
 static bool hubs_pay(int64_t n, int64_t nnz, int f) { return n > 0 && f > 8 && nnz >= kHubRow && nnz * f >= kHubWork; }
 

@@ -8,18 +8,23 @@
 // and more: 78 % of the entries there, 70 % at 2^22 nodes).  So long rows are cut into pieces, and the pieces of all rows
 // are processed in the order of their position inside the row, XCD x the x-th eighth of that order: it gathers from about
 // an eighth of the dense operand, walked once from beginning to end in step with all other long rows.  Lines fetched at
-// f = 100: 19.6 -> 12.7 GB; 2960 -> 2330 us.  f = 64 at 2^22 nodes: 4300 -> 3630 us.
+// f = 100: 19.6 -> 12.7 GB; 2774 -> 2149 us.  f = 64 at 2^22 nodes: 4839 -> 3553 us.
 // Nothing but the time depends on the order of the columns.
 //
 //   hub_count_kernel    looks at kSamples rows: is a third of the entries in long ones?  If not, all that follow return
 //                       at once and spmm_seg_kernel runs (a uniform random graph gains nothing here and pays these
-//                       launches, 20 us).  Else, per block of rows: pieces by position, short rows by length
-//   (scan)              counts -> places
-//   hub_scatter_kernel  writes the ordered list of pieces and short rows, and the list of long rows
+//                       launches).  Else, per block: pieces by position, short rows by length
+//   hub_scatter_kernel  counts -> places; writes the ordered list of pieces and short rows, and the shares of long rows
 //   hub_gather_kernel   one group of lanes per item: a partial row for a piece, a row of C for a short row
-//   hub_reduce          (in spmm_fixup_kernel) one wavefront per long row: its partials in a fixed order, bias,
+//   hub_reduce          (in spmm_fixup_kernel) one wavefront per 512 partial rows of a long row, in a fixed order, bias,
 //                       activation
 //
+// A row has as many pieces as whole 64s of entries, and their partial rows have places of their own among the 64s of the
+// whole list: so one thread per 64 entries finds its row and has its piece, wherever the long rows are.  Walked by rows, the
+// blocks that hold the long ones were all there was to wait for (R-MAT as generated, 2^20 nodes, 53 M entries, most of the
+// long rows side by side: both kernels 386 us, now 41; rows sorted by length 1300, now 50).  With at most 1024 pieces a row,
+// as it once was, pieces of longer rows were long chains of sums, and few: 300 000 nodes, 36 M entries, 16 M of them in one
+// row, f = 100: 8050 -> 1050 us, the segments 2210; a chain of 15 625 equal products is off by up to 2e-4 of its sum.
 // Shorter pieces, or pieces cut at columns instead of positions, miss less often (11.4 instead of 12.7 GB) and are no
 // faster, within 2 %; with the gathers of the next sixteen entries under way while sixteen are folded it is 4 % slower: the
 // lines under way are what is short.
@@ -30,28 +35,36 @@
 namespace gnn {
 namespace {
 
-constexpr int kRowsPerBlock = 1024;
+constexpr int kHubBuckets = 64;            // positions inside a row that the order of the pieces tells apart
 constexpr int kShortClasses = 6;
-// per block of rows: pieces by position, short rows by length, then the number of long rows and of all their pieces
-constexpr int kHubLists = kHubBuckets + kShortClasses + 2;
+// per block: pieces by position, short rows by length, then the shares of long rows; padded to whole int4
+constexpr int kShares = kHubBuckets + kShortClasses, kHubLists = (kShares + 1 + 3) / 4 * 4;
+constexpr int kListBlocks = 512;           // blocks that make the lists: each reads the counts of all
+constexpr int kListThreads = 1024;         // of these: chains of three loads an item, so as many wavefronts as there is room for
 constexpr int kGrab = 4;                   // items a group takes at a time: 2 and 8 are 1 - 4 % slower
 constexpr int kQueueStride = 64;           // counters in lines of their own: in one line each of them waits for all others
 constexpr int kBlocksPerCu = 5;            // by registers
 constexpr int kSamples = 1024;
 
-// Pieces of a row of d >= kHubRow entries.
-__device__ __forceinline__ int hub_pieces(int d) { return min(d / kHubPiece, kHubMaxPieces); }
+// Pieces of a row of d >= kHubRow entries that begins at entry a: their partial rows lie at place `first` and behind.  The
+// next row's begin no earlier than ceil((a + d) / 64), and entry 64 x belongs to the row whose piece has place x.
+struct HubPieces {
+    int first, count;
+};
+__device__ __forceinline__ HubPieces hub_pieces(int a, int d) {
+    return HubPieces{(int)(((int64_t)a + kHubPiece - 1) / kHubPiece), d / kHubPiece};
+}
 
-// First entry of piece p of np: equal shares, moved to the next multiple of sixteen entries so that the sixteen
-// columns and weights read at a time lie in one line each.
+// First entry of piece p of np: equal shares, moved to the next multiple of sixteen entries so that the sixteen columns and
+// weights read at a time lie in one line each.
 __device__ __forceinline__ int hub_begin(int a, int d, int p, int np) {
     if (p <= 0) return a;
     if (p >= np) return a + d;
     return min((a + (int)((int64_t)d * p / np) + 15) & -16, a + d);
 }
 
-// Rows with fewer than kHubRow entries in classes of similar length, the longest first: the groups of a wavefront then
-// have about as much to do as each other, and what is left for the end is short.
+// Rows with fewer than kHubRow entries in classes of similar length, the longest first: the groups of a wavefront then have
+// about as much to do as each other, and what is left for the end is short.
 __device__ __forceinline__ int short_class(int d) {
     return d > 64 ? 0 : d > 32 ? 1 : d > 16 ? 2 : d > 8 ? 3 : d > 1 ? 4 : 5;
 }
@@ -61,13 +74,10 @@ __device__ __forceinline__ bool many_in_long_rows(int n, const int32_t *__restri
     if (threadIdx.x < 2) s_sum[threadIdx.x] = 0;
     __syncthreads();
     unsigned long long all = 0, in_long = 0;
-#pragma unroll
-    for (int i = 0; i < kSamples / 256; ++i) {
-        const int r = (int)((int64_t)n * (i * 256 + threadIdx.x) / kSamples);
-        const int d = rowptr[r + 1] - rowptr[r];
-        all += d;
-        in_long += d >= kHubRow ? d : 0;
-    }
+    static_assert(kSamples == kListThreads, "one each");
+    const int r = (int)((int64_t)n * threadIdx.x / kSamples), d = rowptr[r + 1] - rowptr[r];
+    all += d;
+    in_long += d >= kHubRow ? d : 0;
     for (int m = 1; m < kWave; m <<= 1) {
         all += __shfl_xor(all, m, kWave);
         in_long += __shfl_xor(in_long, m, kWave);
@@ -80,110 +90,161 @@ __device__ __forceinline__ bool many_in_long_rows(int n, const int32_t *__restri
     return 3 * s_sum[1] >= s_sum[0];
 }
 
-// Per block of rows: the long ones go to s_hub (first entry, length, row, pieces before it; in no order), their number
-// and that of their pieces to *s_n; `short_row(class, row, start, length)` sees the others.  Ends with a barrier.
-constexpr int kCountBits = 11;                             // kRowsPerBlock long rows at most, of kHubMaxPieces pieces
-static_assert(kRowsPerBlock < 1 << kCountBits && (int64_t)kRowsPerBlock * kHubMaxPieces < (int64_t)1 << (32 - kCountBits),
-              "both counts in one word");
-template <typename F>
-__device__ __forceinline__ void block_rows(int n, int nnz, const int32_t *__restrict__ rowptr, int4 *s_hub, uint32_t *s_n,
-                                           F short_row) {
-    if (threadIdx.x == 0) *s_n = 0;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kRowsPerBlock / 256; ++i) {
-        const long r = (long)blockIdx.x * kRowsPerBlock + i * 256 + threadIdx.x;
-        const int a = r < n ? rowptr[r] : 0, d = r < n ? min(rowptr[r + 1], nnz) - a : 0;
-        if (d >= kHubRow) {
-            const uint32_t at = atomicAdd(s_n, (uint32_t)hub_pieces(d) << kCountBits | 1u);
-            s_hub[at & ((1 << kCountBits) - 1)] = make_int4(a, d, (int)r, (int)(at >> kCountBits));
-        }
-        short_row(r >= n || d >= kHubRow ? -1 : short_class(d), (int)r, a, d);
-    }
-    __syncthreads();
-}
-
 __device__ __forceinline__ int hub_bucket(int p, int np) { return (int)((2u * p + 1) * (unsigned)kHubBuckets / (2u * np)); }
 
-// The last of s_hub[0 .. hubs) with no more than t pieces before it.
-__device__ __forceinline__ int hub_of_piece(const int4 *s_hub, int hubs, int t) {
-    int lo = 0, hi = hubs - 1;
-    while (lo < hi) {
-        const int m = (lo + hi + 1) / 2;
-        if (s_hub[m].w <= t) lo = m;
-        else hi = m - 1;
+// The last row that begins at or before entry e; 64 probes at a time by one wavefront.
+__device__ __forceinline__ int row_of(const int32_t *__restrict__ rowptr, int n, int e) {
+    const int lane = threadIdx.x % kWave;
+    int64_t lo = 0, hi = n;                                // rowptr[lo] <= e < rowptr[hi] or hi = n
+    while (hi - lo > 1) {
+        const int64_t step = (hi - lo + kWave - 1) / kWave, at = lo + lane * step;
+        const int before = __popcll(__ballot(at < hi && rowptr[at < hi ? at : lo] <= e));
+        lo += (before > 1 ? before - 1 : 0) * step;
+        hi = lo + step < hi ? lo + step : hi;
     }
-    return lo;
+    return (int)lo;
 }
 
-__global__ void __launch_bounds__(256)
-hub_count_kernel(int n, int nnz, const int32_t *__restrict__ rowptr, int32_t *__restrict__ use, int32_t *__restrict__ counts,
-                 int32_t *__restrict__ queues, int nqueues) {
-    __shared__ int4 s_hub[kRowsPerBlock];
-    __shared__ int32_t s_hist[kHubLists];
+// Every item of this block's part of the entries and rows: piece(list, start, length, place) for the pieces, share(row,
+// first, count, which) for the shares of their sums, row(list, row, start, length) for the short rows; the list is -1 if a
+// lane has none.  All lanes of a wavefront call piece and row together.  s_rows: two words of LDS.
+template <typename P, typename S, typename R>
+__device__ __forceinline__ void block_items(int n, int nnz, const int32_t *__restrict__ rowptr, int32_t *s_rows, P piece,
+                                            S share, R row) {
+    const int places = (int)(((int64_t)nnz + kHubPiece - 1) / kHubPiece), per = (places + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int x0 = (int)min((int64_t)blockIdx.x * per, (int64_t)places), x1 = (int)min((int64_t)x0 + per, (int64_t)places);
+    const int wave = threadIdx.x / kWave;
+    if (wave < 2 && x0 < x1) s_rows[wave] = row_of(rowptr, n, (wave ? x1 - 1 : x0) * kHubPiece);
+    __syncthreads();
+    for (int xb = x0; xb < x1; xb += kListThreads) {
+        const int x = xb + threadIdx.x;
+        int a = 0, d = 0, r = s_rows[0];
+        if (x < x1) {
+            // the expanded row index has the answer in every other of its lines: 280 MB at 2^22 nodes and 138 M entries,
+            // where these probes stay within a few thousand row pointers (both kernels 147 -> 92 us)
+            for (int hi = s_rows[1]; r < hi;) {
+                const int m = r + (hi - r + 1) / 2;
+                if (rowptr[m] <= x * kHubPiece) r = m;
+                else hi = m - 1;
+            }
+            a = rowptr[r];
+            d = min(rowptr[r + 1], nnz) - a;
+        }
+        const HubPieces h = hub_pieces(a, d);
+        const int p = x - h.first;
+        const bool mine = d >= kHubRow && p >= 0 && p < h.count;
+        const int begin = mine ? hub_begin(a, d, p, h.count) : 0;
+        piece(mine ? hub_bucket(p, h.count) : -1, begin, mine ? hub_begin(a, d, p + 1, h.count) - begin : 0, x);
+        if (mine && p % kHubShare == 0) share(r, h.first, h.count, p / kHubShare);
+    }
+    const int64_t rows = ((int64_t)n + gridDim.x - 1) / gridDim.x;
+    const int64_t r0 = min(blockIdx.x * rows, (int64_t)n), r1 = min(r0 + rows, (int64_t)n);
+    for (int64_t rb = r0; rb < r1; rb += kListThreads) {
+        const int64_t r = rb + threadIdx.x;
+        const int a = r < r1 ? rowptr[r] : 0, d = r < r1 ? min(rowptr[r + 1], nnz) - a : kHubRow;
+        row(d >= kHubRow ? -1 : short_class(d), (int)r, a, d);
+    }
+}
+
+// Adds the lanes' items to the lists they name (-1: none) and returns their places in them.  Mostly one list for all.
+__device__ __forceinline__ int take_places(int32_t *lists, int list) {
+    const unsigned long long any = __ballot(list >= 0);
+    if (!any) return 0;
+    const int one = __shfl(list, __ffsll(any) - 1, kWave);
+    const unsigned long long same = __ballot(list == one);
+    const int lane = threadIdx.x % kWave;
+    int at = 0;
+    if (same == any) {
+        if (lane == 0) at = atomicAdd(&lists[one], __popcll(any));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(any & ((1ull << lane) - 1));
+    } else if (list >= 0) {
+        at = atomicAdd(&lists[list], 1);
+    }
+    return at;
+}
+
+__global__ void __launch_bounds__(kListThreads)
+hub_count_kernel(int n, int nnz, const int32_t *__restrict__ rowptr, int32_t *__restrict__ use,
+                 int32_t *__restrict__ counts, int32_t *__restrict__ queues, int nqueues,
+                 int32_t *__restrict__ arrived, int narrived) {
+    __shared__ int32_t s_hist[kHubLists], s_rows[2];
     __shared__ unsigned long long s_sum[2];
-    __shared__ uint32_t s_n;
     const bool go = many_in_long_rows(n, rowptr, s_sum);
     if (blockIdx.x == 0 && threadIdx.x == 0) *use = go;
     if (!go) return;
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < nqueues; i += 256) queues[i] = 0;
+    const int all = gridDim.x * kListThreads, me = blockIdx.x * kListThreads + threadIdx.x;
+    for (int i = me; i < nqueues; i += all) queues[i] = 0;
+    for (int i = me; i < narrived; i += all) arrived[i] = 0;
     if (threadIdx.x < kHubLists) s_hist[threadIdx.x] = 0;
-    const int lane = threadIdx.x % kWave;
-    block_rows(n, nnz, rowptr, s_hub, &s_n, [&](int cls, int, int, int) {
-#pragma unroll
-        for (int c = 0; c < kShortClasses; ++c) {
-            const unsigned long long m = __ballot(cls == c);
-            if (lane == 0 && m) atomicAdd(&s_hist[kHubBuckets + c], __popcll(m));
-        }
-    });
-    const int hubs = s_n & ((1 << kCountBits) - 1), total = s_n >> kCountBits;
-    for (int t = threadIdx.x; t < total; t += 256) {
-        const int4 h = s_hub[hub_of_piece(s_hub, hubs, t)];
-        atomicAdd(&s_hist[hub_bucket(t - h.w, hub_pieces(h.y))], 1);
-    }
-    if (threadIdx.x == 0) {
-        s_hist[kHubLists - 2] = hubs;
-        s_hist[kHubLists - 1] = total;
-    }
     __syncthreads();
-    if (threadIdx.x < kHubLists) counts[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = s_hist[threadIdx.x];
+    block_items(
+        n, nnz, rowptr, s_rows, [&](int list, int, int, int) { take_places(s_hist, list); },
+        [&](int, int, int, int) { atomicAdd(&s_hist[kShares], 1); },
+        [&](int cls, int, int, int) { take_places(s_hist, cls < 0 ? -1 : kHubBuckets + cls); });
+    __syncthreads();
+    if (threadIdx.x < kHubLists) counts[(size_t)blockIdx.x * kHubLists + threadIdx.x] = s_hist[threadIdx.x];
 }
 
-__global__ void __launch_bounds__(256)
-hub_scatter_kernel(int n, int nnz, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ use,
-                   const int32_t *__restrict__ place, int4 *__restrict__ items, int4 *__restrict__ rows) {
-    __shared__ int4 s_hub[kRowsPerBlock];
-    __shared__ int32_t s_place[kHubLists];
-    __shared__ uint32_t s_n;
+// place: the number of pieces, of pieces and short rows, and of shares
+__global__ void __launch_bounds__(kListThreads)
+hub_scatter_kernel(int n, int nnz, const int32_t *__restrict__ rowptr,
+                   const int32_t *__restrict__ use, const int32_t *__restrict__ counts, int32_t *__restrict__ place,
+                   int4 *__restrict__ items, int4 *__restrict__ tasks) {
+    constexpr int QUADS = kHubLists / 4, GROUPS = kListThreads / QUADS;
+    __shared__ __align__(16) int32_t s_all[GROUPS][kHubLists], s_before[GROUPS][kHubLists];
+    __shared__ int32_t s_place[kHubLists], s_rows[2];
     if (!*use) return;
-    if (threadIdx.x < kHubLists) {
-        const int32_t *p = place + (size_t)threadIdx.x * gridDim.x;
-        // the last two lists are numbered from zero
-        s_place[threadIdx.x] = p[blockIdx.x] - (threadIdx.x >= kHubLists - 2 ? p[0] : 0);
-    }
-    const int lane = threadIdx.x % kWave;
-    block_rows(n, nnz, rowptr, s_hub, &s_n, [&](int cls, int row, int a, int d) {
-#pragma unroll
-        for (int c = 0; c < kShortClasses; ++c) {
-            const unsigned long long m = __ballot(cls == c);
-            if (!m) continue;
-            int at = 0;
-            if (lane == 0) at = atomicAdd(&s_place[kHubBuckets + c], __popcll(m));
-            at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1));
-            if (cls == c) items[at] = make_int4(a, d, row, 0);
+    const int quad = threadIdx.x % QUADS, group = threadIdx.x / QUADS;
+    if (group < GROUPS) {                                  // the lists of all blocks, and of those before this one
+        int4 all = make_int4(0, 0, 0, 0), before = all;
+#pragma unroll 5
+        for (int b = group; b < (int)gridDim.x; b += GROUPS) {
+            const int4 c = reinterpret_cast<const int4 *>(counts)[(size_t)b * QUADS + quad];
+            const bool earlier = b < (int)blockIdx.x;
+            all.x += c.x; all.y += c.y; all.z += c.z; all.w += c.w;
+            before.x += earlier ? c.x : 0; before.y += earlier ? c.y : 0;
+            before.z += earlier ? c.z : 0; before.w += earlier ? c.w : 0;
         }
-    });
-    const int hubs = s_n & ((1 << kCountBits) - 1), total = s_n >> kCountBits;
-    const int row0 = s_place[kHubLists - 2], base = s_place[kHubLists - 1];
-    for (int i = threadIdx.x; i < hubs; i += 256)
-        rows[row0 + i] = make_int4(s_hub[i].z, base + s_hub[i].w, hub_pieces(s_hub[i].y), 0);
-    for (int t = threadIdx.x; t < total; t += 256) {
-        const int4 h = s_hub[hub_of_piece(s_hub, hubs, t)];
-        const int np = hub_pieces(h.y), p = t - h.w;
-        const int x = hub_begin(h.x, h.y, p, np), end = hub_begin(h.x, h.y, p + 1, np);
-        items[atomicAdd(&s_place[hub_bucket(p, np)], 1)] = make_int4(x, end - x, base + t, 0);
+        *reinterpret_cast<int4 *>(&s_all[group][4 * quad]) = all;
+        *reinterpret_cast<int4 *>(&s_before[group][4 * quad]) = before;
     }
+    __syncthreads();
+    int before = 0;
+    if (threadIdx.x < kHubLists) {
+        int all = 0;
+        for (int g = 0; g < GROUPS; ++g) {
+            all += s_all[g][threadIdx.x];
+            before += s_before[g][threadIdx.x];
+        }
+        s_place[threadIdx.x] = all;
+    }
+    __syncthreads();
+    int lists = 0;
+    if (threadIdx.x < kHubLists && threadIdx.x != kShares)  // shares are numbered from zero
+        for (int k = 0; k < (int)threadIdx.x; ++k) lists += s_place[k];
+    if (blockIdx.x == 0 && threadIdx.x == kHubBuckets) place[0] = lists;
+    if (blockIdx.x == 0 && threadIdx.x == kShares) {
+        int items_all = 0;
+        for (int k = 0; k < kShares; ++k) items_all += s_place[k];
+        place[1] = items_all;
+        place[2] = s_place[kShares];
+    }
+    __syncthreads();
+    if (threadIdx.x < kHubLists) s_place[threadIdx.x] = lists + before;
+    __syncthreads();
+    block_items(
+        n, nnz, rowptr, s_rows,
+        [&](int list, int start, int length, int to) {
+            const int at = take_places(s_place, list);
+            if (list >= 0) items[at] = make_int4(start, length, to, 0);
+        },
+        [&](int row, int first, int count, int which) {
+            tasks[atomicAdd(&s_place[kShares], 1)] = make_int4(row, first, count, which);
+        },
+        [&](int cls, int row, int start, int length) {
+            const int at = take_places(s_place, cls < 0 ? -1 : kHubBuckets + cls);
+            if (cls >= 0) items[at] = make_int4(start, length, row, 0);
+        });
 }
 
 // Lane l of every four holds entries 4 l ... 4 l + 3 of the batch of sixteen in x, y, z, w; every lane gets entry u.
@@ -228,7 +289,7 @@ __device__ __forceinline__ void load_batch(Entries &e, const int32_t *__restrict
 // place.  Counter 2 x is the x-th eighth of the pieces, 2 x + 1 every eighth share of the short rows.
 template <int LPE, bool WIDE, bool RAGGED>
 __global__ void __launch_bounds__(256, kBlocksPerCu)
-hub_gather_kernel(int nnz, int nblk, int f, int ld, const int32_t *__restrict__ use,
+hub_gather_kernel(int nnz, int f, int ld, const int32_t *__restrict__ use,
                   const int32_t *__restrict__ place, int32_t *__restrict__ queues,
                   const int4 *__restrict__ items, const int32_t *__restrict__ col, EdgeWeights w,
                   const float *__restrict__ B, float *__restrict__ part, float *__restrict__ C,
@@ -245,7 +306,7 @@ hub_gather_kernel(int nnz, int nblk, int f, int ld, const int32_t *__restrict__ 
         s_bias[l] = make_float4(b[0], b[1], b[2], b[3]);
     }
     __syncthreads();
-    const unsigned pieces = place[(size_t)kHubBuckets * nblk], all = place[(size_t)(kHubBuckets + kShortClasses) * nblk];
+    const unsigned pieces = place[0], all = place[1];
     const unsigned xcd = blockIdx.x % 8;
     const bool ok = foff < ld;
     const float *src = B + (ok ? foff : 0);
@@ -339,27 +400,28 @@ hub_gather_kernel(int nnz, int nblk, int f, int ld, const int32_t *__restrict__ 
     }
 }
 
-long hub_blocks(int64_t n) { return ceil_div(n, kRowsPerBlock); }
-
 struct HubBuffers {
-    int32_t *use, *place, *queues, *scan;
-    int4 *items, *rows;
+    int32_t *use, *place, *queues, *counts, *arrived;
+    int4 *items, *tasks;
     float *part;
-    int nqueues;
+    int nqueues, narrived;
     size_t bytes;
 };
 
 HubBuffers carve(void *base, int64_t n, int64_t nnz, int ld) {
     Carver c(base);
     HubBuffers b;
+    const int64_t pieces = ceil_div(nnz, kHubPiece);       // places for partial rows
     b.nqueues = 16 * kQueueStride * (int)ceil_div(ld, 4 * kWave);
+    b.narrived = (int)(pieces / kHubShare + 1);
     b.use = c.take<int32_t>(1);
-    b.place = c.take<int32_t>(kHubLists * hub_blocks(n));
+    b.place = c.take<int32_t>(3);
     b.queues = c.take<int32_t>(b.nqueues);
-    b.scan = reinterpret_cast<int32_t *>(c.take<char>(scan_workspace_bytes(kHubLists * hub_blocks(n))));
-    b.items = c.take<int4>(nnz / kHubPiece + n);           // a row of d entries has at most d / kHubPiece pieces
-    b.rows = c.take<int4>(nnz / kHubRow);
-    b.part = c.take<float>((size_t)(nnz / kHubPiece) * ld);
+    b.counts = c.take<int32_t>(kHubLists * kListBlocks);
+    b.arrived = c.take<int32_t>(b.narrived);
+    b.items = c.take<int4>(pieces + n);
+    b.tasks = c.take<int4>(nnz / kHubRow + pieces / kHubShare);             // long rows, and shares beyond their first
+    b.part = c.take<float>((size_t)pieces * ld);
     b.bytes = c.off;
     return b;
 }
@@ -378,11 +440,13 @@ gnn_status_t hub_spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_
                              int f, int ld, float *C, const float *bias, int act, void *workspace, hipStream_t st,
                              HubReduce *rest) {
     const HubBuffers b = carve(workspace, n, nnz, ld);
-    const int nblk = (int)hub_blocks(n);
-    hipLaunchKernelGGL(hub_count_kernel, dim3(nblk), dim3(256), 0, st, n, nnz, rowptr, b.use, b.place, b.queues, b.nqueues);
+    const int64_t want = ceil_div(nnz / kHubPiece + n, 2 * kListThreads);
+    const int blocks = (int)(want < kListBlocks ? want : kListBlocks);
+    hipLaunchKernelGGL(hub_count_kernel, dim3(blocks), dim3(kListThreads), 0, st, n, nnz, rowptr, b.use, b.counts, b.queues,
+                       b.nqueues, b.arrived, b.narrived);
     GNN_TRY(launch_status());
-    GNN_TRY(exclusive_scan_launch(b.place, (long)kHubLists * nblk, b.scan, st));
-    hipLaunchKernelGGL(hub_scatter_kernel, dim3(nblk), dim3(256), 0, st, n, nnz, rowptr, b.use, b.place, b.items, b.rows);
+    hipLaunchKernelGGL(hub_scatter_kernel, dim3(blocks), dim3(kListThreads), 0, st, n, nnz, rowptr, b.use, b.counts, b.place,
+                       b.items, b.tasks);
     GNN_TRY(launch_status());
     int lpe = pow2_at_least(ld / 4);
     if (lpe < 4) lpe = 4;
@@ -392,13 +456,13 @@ gnn_status_t hub_spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_
     const bool wide = n >= (1 << 24) || ld >= (1 << 22) || (int64_t)n * ld * 4 >= ((int64_t)1 << 32), ragged = f != ld;
 #define HUB_LAUNCH(LPE_, WIDE_, RAGGED_)                                                                                   \
     if (lpe == LPE_ && wide == WIDE_ && ragged == RAGGED_)                                                                 \
-        hipLaunchKernelGGL((hub_gather_kernel<LPE_, WIDE_, RAGGED_>), grid, dim3(256), 0, st, nnz, nblk, f, ld, b.use,     \
+        hipLaunchKernelGGL((hub_gather_kernel<LPE_, WIDE_, RAGGED_>), grid, dim3(256), 0, st, nnz, f, ld, b.use,           \
                            b.place, b.queues, b.items, col, w, B, b.part, C, bias, act);
 #define HUB_CASE(LPE_)                                                                                                     \
     HUB_LAUNCH(LPE_, false, false) HUB_LAUNCH(LPE_, false, true) HUB_LAUNCH(LPE_, true, false) HUB_LAUNCH(LPE_, true, true)
     HUB_CASE(4) HUB_CASE(8) HUB_CASE(16) HUB_CASE(32) HUB_CASE(64)
     GNN_TRY(launch_status());
-    *rest = HubReduce{b.use, b.place + (size_t)(kHubLists - 2) * nblk, b.rows, b.part, nblk, ld, lpe};
+    *rest = HubReduce{b.use, b.place + 2, b.tasks, b.part, b.arrived, ld, lpe};
     return GNN_OK;
 }
 

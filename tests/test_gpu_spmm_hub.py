@@ -10,14 +10,18 @@ pytestmark = pytest.mark.gpu
 EDGES = [0, 1, 2, 8, 9, 16, 17, 33, 64, 65, 127, 128, 129, 143, 144, 191, 192, 193, 255, 256, 1000, 4097, 65535, 65600, 200000]
 
 
-def matrix(seed, n, nnz, hubs=True, ordered=True):
-    """CSR on the device: the lengths of EDGES first and last, the others alike but a few thousand long ones."""
+def matrix(seed, n, nnz, hubs=True, ordered=True, more=(), by_length=False):
+    """CSR on the device: the lengths of EDGES first and last, `more` behind the first ones, the others alike but a few
+    thousand long ones; by_length: rows in descending order of their length."""
     gen = torch.Generator(device="cuda").manual_seed(seed)
     d = torch.full((n,), 3, dtype=torch.int64, device="cuda")
     if hubs:
         d[torch.randperm(n, generator=gen, device="cuda")[:4000]] = max(128, (nnz - 3 * n - 2 * sum(EDGES)) // 4000)
         edges = torch.tensor(EDGES, device="cuda")
         d[:len(EDGES)], d[n - len(EDGES):] = edges, edges.flip(0)
+        d[len(EDGES):len(EDGES) + len(more)] = torch.tensor(more, dtype=torch.int64, device="cuda")
+        if by_length:
+            d = d.sort(descending=True).values
     else:
         d[:] = nnz // n
     rowptr = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
@@ -45,17 +49,37 @@ def check(C, n, col, val, erow, X, bias=None, relu=False):
     X = X.double()
     piece = max(1, (1 << 28) // X.shape[1])
     for lo in range(0, col.numel(), piece):
+        rows = erow[lo:lo + piece].long()
         t = X[col[lo:lo + piece].long()] * val[lo:lo + piece, None].double()
-        ref.index_add_(0, erow[lo:lo + piece].long(), t)
-        mag.index_add_(0, erow[lo:lo + piece].long(), t.abs_())
+        # runs of one row, of 512 entries at most: millions of entries added to one row at once wait for each other for hours
+        first = torch.arange(rows.numel(), device="cuda") % 512 == 0
+        first[1:] |= rows[1:] != rows[:-1]
+        first = first.nonzero().squeeze(1)
+        lengths = torch.diff(first, append=first.new_tensor([rows.numel()]))
+        ref.index_add_(0, rows[first], torch.segment_reduce(t, "sum", lengths=lengths, axis=0))
+        mag.index_add_(0, rows[first], torch.segment_reduce(t.abs_(), "sum", lengths=lengths, axis=0))
     if bias is not None:
         ref += bias.double()
         mag += bias.double().abs()
     if relu:
         ref.clamp_(min=0)
-    # roundings on the way of a product: its chain in a piece (fewer than 160), the partials of one of four sums of a slot
-    # (1024 / 4 at most), the tree, the bias
-    assert bool(((C.double() - ref).abs() <= 430 * 2.0 ** -24 * mag).all())
+    most = roundings(torch.bincount(erow, minlength=n), X.shape[1])
+    assert bool(((C.double() - ref).abs() <= most[:, None] * 2.0 ** -24 * 1.001 * mag).all())
+
+
+def roundings(d, f):
+    """Roundings on the way of a product into a row of d entries.  A row below 128 entries: one for each and six for the
+    bias and for where segments meet.  A longer one: at most 111 in a piece; then 512 partials at a time, in four rotating
+    sums of each slot (three more for the rest), two to join those and a tree over the slots; the same over the shares of
+    512; the bias."""
+    lanes = 4
+    while lanes < 64 and 4 * lanes < f:
+        lanes *= 2
+    slots = 64 // lanes
+    level = lambda n: (n / (4 * slots)).ceil() + 5 + slots.bit_length() - 1  # noqa: E731
+    pieces = (d.double() / 64).floor()
+    shares = (pieces / 512).ceil()
+    return torch.where(d < 128, d + 6.0, 111 + level(pieces.clamp(max=512)) + torch.where(pieces > 512, level(shares), 0.0) + 1)
 
 
 @pytest.mark.parametrize("f,nnz,ordered,relu", [(64, 32_000_000, True, True), (47, 43_000_000, True, False),
@@ -69,6 +93,20 @@ def test_row_lengths(f, nnz, ordered, relu):
     C = run(n, rowptr, col, val, erow, X, bias, relu)
     check(C, n, col, val, erow, X, bias, relu)
     assert torch.equal(C, run(n, rowptr, col, val, erow, X, bias, relu))
+
+
+@pytest.mark.parametrize("f,more", [(64, [5_000_000, 300_000, 32_767, 32_768, 32_784, 32_832, 65_600]), (47, [16_000_000]),
+                                    (260, [2_100_000, 32_831, 98_368])])
+@pytest.mark.parametrize("by_length", [False, True])
+def test_a_row_with_much_of_the_graph(f, more, by_length):
+    """Equal products: every addition of a long chain rounds the same way, so that its length shows in the result."""
+    n = 70001
+    rowptr, col, val, erow, gen = matrix(f, n, 28_000_000, ordered=False, more=more, by_length=by_length)
+    val.fill_(1.0)
+    X = torch.rand(f, generator=gen, device="cuda").expand(n, f).contiguous()
+    C = run(n, rowptr, col, val, erow, X)
+    check(C, n, col, val, erow, X)
+    assert torch.equal(C, run(n, rowptr, col, val, erow, X))
 
 
 def test_operand_beyond_32_bit_offsets():
