@@ -51,9 +51,11 @@ constexpr int BK = 32;
 // the blocks of the first tile row alone: the gradient of a bias, and the mask for the product that reads B next, cost no
 // pass over B (2^17 rows, 128 x 512 with a mask: 350 -> 406 us under the profiler, the pass they replace 184).
 // words per LDS row of `cols` columns: the lanes of one k-row read 16 * T consecutive words.  T odd: word by word, the 16
-// lanes of a row T banks apart, four rows in 64 banks at a row length of 16 mod 64; T = 2: two rows per pass, 32 mod 64;
-// T = 4: one row per pass
-constexpr int tn_row_words(int cols, int T) { return cols + (T % 2 ? (80 - cols % 64) % 64 : T == 2 ? (96 - cols % 64) % 64 : 4); }
+// lanes of a row T banks apart, four rows in 64 banks at a row length of 16 or 48 mod 64; T = 2: two rows per pass, 32 mod
+// 64; T = 4: one row per pass
+constexpr int tn_row_words(int cols, int T) {
+    return cols + (T % 2 ? (cols % 64 == 48 ? 0 : (80 - cols % 64) % 64) : T == 2 ? (96 - cols % 64) % 64 : 4);
+}
 
 template <int WM, int WN, int TM, int TN, bool MASK, bool SUMS>
 __global__ void __launch_bounds__(256, 2)
@@ -727,7 +729,7 @@ Tiling pick_tiling(int64_t M, int64_t N) {
 // double partials are written and read once.  Rates are measured, at 2^17 to 2^22 rows, old tile and chunks / new, us:
 // 512 x 512 over 2048 290 / 38, 128 x 128 over 2048 49 / 9, over 16384 50 / 22, over 2^17 93 / 92; 300 x 300 over 8192
 // 411 / 46; 256 x 256 over 20000 315 / 61, over 2^17 322 / 302; 70 x 75 over 2^18 195 / 105; 96 x 64 over 50021 36 / 27;
-// 256 x 47 over 2^20 665 / 490, 100 x 256 1150 / 1094; 64 x 256 over 2^22 2230 / 2240.  Outputs of a few tiles fill the
+// 256 x 47 over 2^20 665 / 513, 100 x 256 1150 / 1094; 64 x 256 over 2^22 2230 / 2240.  Outputs of a few tiles fill the
 // chip only with many short chunks, whatever their partials come to beside the operands.
 struct TnTile {
     Tiling tile;
@@ -737,6 +739,15 @@ struct TnTile {
 
 constexpr TnTile kTnTiles[] = {{{4, 1, 1, 1}, 6, 1.7}, {{4, 1, 1, 2}, 5, 1.5}, {{4, 1, 2, 3}, 3, 1.15}, {{2, 2, 2, 2}, 3, 1.08},
                                {{2, 2, 3, 3}, 2, 1.13}, {{4, 1, 2, 5}, 2, 1.12}, {{4, 1, 2, 7}, 2, 1.1}, {{2, 2, 4, 4}, 2, 1.03}};
+constexpr int tn_lds_bytes(const Tiling &t) {              // two tiles of both operands
+    return 2 * BK * (tn_row_words(t.wm * t.tm * 16, t.tm) + tn_row_words(t.wn * t.tn * 16, t.tn)) * (int)sizeof(float);
+}
+constexpr bool tn_blocks_fit() {
+    for (const TnTile &c : kTnTiles)
+        if (c.resident * tn_lds_bytes(c.tile) > 160 * 1024) return false;
+    return true;
+}
+static_assert(tn_blocks_fit(), "resident blocks by LDS");
 constexpr double kTnWait = 0.4, kTnTurn = 0.15;            // us a k-tile: a block on its own, any number of them
 constexpr int kTnBlocks = 8;                               // blocks a CU at most, over the whole launch
 
@@ -879,9 +890,7 @@ bool gemm_takes_bits(int tb, int64_t M, int64_t N, int64_t K, const float *A, co
     }
 #define GEMM_F64_CASE(WM_, WN_, TM_, TN_)                                                                        \
     if (tl.wm == WM_ && tl.wn == WN_ && tl.tm == TM_ && tl.tn == TN_) {                                          \
-        constexpr int BM_ = WM_ * TM_ * 16, BN_ = WN_ * TN_ * 16;                                                \
-        constexpr int LA_ = tn_row_words(BM_, TM_), LB_ = tn_row_words(BN_, TN_);                                \
-        const size_t lds = (size_t)2 * BK * (LA_ + LB_) * sizeof(float);                                         \
+        const size_t lds = tn_lds_bytes(tl);                                                                     \
         constexpr bool SIDE_ = TM_ * TN_ < 16;                                                                   \
         auto kernel = b_mask ? (side ? gemm_tn_f64_kernel<WM_, WN_, TM_, TN_, true, SIDE_>                       \
                                      : gemm_tn_f64_kernel<WM_, WN_, TM_, TN_, true, false>)                      \
