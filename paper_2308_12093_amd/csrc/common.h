@@ -92,8 +92,17 @@ float *spmm_padded_operand(void *workspace, const int32_t *erow, int64_t b_rows,
 
 // ---- dense products (gemm.hip) ----------------------------------------------------
 size_t gemm_workspace_bytes(int ta, int tb, int64_t M, int64_t N, int64_t K);
-// the transposed-A form over exactly K indices: no more than the above
-size_t gemm_tn_workspace_bytes(int64_t M, int64_t N, int64_t K);
+// Tile and chunks of a transposed-A product over exactly K indices, on its own and with sums or bits beside it.  Choosing
+// takes over a microsecond: who runs the same product on each call keeps them.
+struct TnPlan {
+    int tile, splits;
+};
+struct TnPlans {
+    TnPlan plain, side;
+};
+TnPlans gemm_tn_plans(int64_t M, int64_t N, int64_t K);
+size_t gemm_tn_workspace_bytes(const TnPlans &tn, int64_t M, int64_t N);   // no more than gemm_workspace_bytes
+size_t gemm_sums_bytes(const TnPlans &tn, int64_t N);
 // b_mask (transposed-A form only): B is used as B .* act'(b_mask), the derivative of the activation
 // b_mask_act (kActRelu, kActElu) taken from its output b_mask, an array of B's shape.
 // ldc (plain products only): rows of C are ldc >= N floats apart, the columns in between written as zeros.
@@ -103,12 +112,12 @@ size_t gemm_tn_workspace_bytes(int64_t M, int64_t N, int64_t K);
 // extras: what a product does on the side, or a mask it takes (see GemmExtras).
 struct GemmExtras {
     float *sums;            // transposed-A form: the column sums of B as used, or NULL
-    void *workspace;        //   gemm_sums_bytes(M, N, K) of scratch for them
+    void *workspace;        //   gemm_sums_bytes of scratch for them
     uint16_t *bits;         //   and which elements of it are not zero, or NULL: [K][ceil(N / 16)], 16 columns to a word
     const uint16_t *a_bits; // plain products of one operand pair that gemm_takes_bits: such words for A
                             //   [M][ceil(K / 16)], zero = used as 0
+    const TnPlans *tn;      // transposed-A form: gemm_tn_plans(M, N, K), or NULL
 };
-size_t gemm_sums_bytes(int64_t M, int64_t N, int64_t K);
 bool gemm_takes_bits(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B);
 gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B,
                          float *C, const float *bias, int relu, void *workspace, hipStream_t st,

@@ -38,7 +38,7 @@ gnn_status_t gat_forward(Plan &p, const gnn_graph_t &g, const float *X, const fl
     const gnn_plan_desc_t &d = p.desc;
     const int n = d.n, q = d.nnz, m = d.f_in, h = d.heads, k = d.f_out, f = h * k;
     if (!g.csr_erow && q > 0) return GNN_ERR_BAD_GRAPH;
-    const GatLayout L = gat_layout(p);
+    const GatLayout &L = p.gat;
     const Buffers B = pick_buffers(L, cache, workspace);
 
     // M = X Theta; s, d per node and head (App. B)
@@ -71,7 +71,7 @@ gnn_status_t gat_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
     const gnn_plan_desc_t &d = p.desc;
     const int n = d.n, q = d.nnz, m = d.f_in, h = d.heads, k = d.f_out, f = h * k;
     if ((!g.csr_erow || !g.csc_ecol) && q > 0) return GNN_ERR_BAD_GRAPH;
-    const GatLayout L = gat_layout(p);
+    const GatLayout &L = p.gat;
     const Buffers B = pick_buffers(L, cache, workspace);
     const gnn_cache_t variant = p.info.cache;
 
@@ -125,7 +125,9 @@ gnn_status_t gat_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
     // da_src = M^T ds, da_dst = M^T dd, one pass over M
     GNN_TRY(gat_attention_grad2_launch(n, h, k, ds, dd, B.M, da_src, da_dst, at<char>(workspace, L.w_red), st));
     // dTheta = X^T dM, dX = dM Theta^T
-    GNN_TRY(gemm_launch(1, 0, m, f, n, X, dM, dW, nullptr, 0, at<char>(workspace, L.w_gemm_tn), st));
+    const GemmExtras keep{nullptr, nullptr, nullptr, nullptr, &p.tn};
+    GNN_TRY(gemm_launch(1, 0, m, f, n, X, dM, dW, nullptr, 0, at<char>(workspace, L.w_gemm_tn), st, nullptr, 0, 0, nullptr,
+                        nullptr, &keep));
     if (d.need_input_grad) GNN_TRY(gemm_launch(0, 1, n, m, f, dM, W, dX, nullptr, 0, at<char>(workspace, L.w_gemm_tn), st));
     return GNN_OK;
 }

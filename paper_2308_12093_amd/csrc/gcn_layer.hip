@@ -54,22 +54,27 @@ bool overlap(const float *a, size_t count_a, const float *b, size_t count_b) {
 // shares memory with it, and in the fused-propagate scheme, whose gather would fetch Y beside dY, one pass makes G and db.
 struct BiasAndMask {
     const float *G = nullptr, *mask_y = nullptr;       // G, or dY and what the products mask it by
-    GemmExtras side{}, masked{};                       // for the first weight-gradient product; for those with the weights
+    GemmExtras side{}, plain{}, masked{};              // for the first weight-gradient product, others, those with the weights
 
     // W, W2: the weights behind G; dX: where the input gradient goes if dY is read once more behind it, or NULL
-    gnn_status_t start(const gnn_plan_desc_t &d, gnn_bwd_t bwd, const float *W, const float *W2, const float *Y,
-                       const float *dY, const float *dX, float *db, Carver &ws, hipStream_t st) {
+    gnn_status_t start(const Plan &p, const float *W, const float *W2, const float *Y, const float *dY, const float *dX,
+                       float *db, Carver &ws, hipStream_t st) {
+        const gnn_plan_desc_t &d = p.desc;
         const int n = d.n, m = d.f_in, k = d.f_out;
-        const bool dx = d.need_input_grad != 0, split = bwd == GNN_BWD_SPLIT_PROPAGATE;
+        const bool dx = d.need_input_grad != 0, split = p.info.bwd == GNN_BWD_SPLIT_PROPAGATE;
         // carved either way: the layout is the plan's
         float *Gm = d.fuse_relu ? ws.take<float>((size_t)n * k) : nullptr;
-        void *red = d.has_bias ? ws.take<char>(bias_gradient_bytes(n, m, k)) : nullptr;
+        void *red = d.has_bias ? ws.take<char>(bias_gradient_bytes(p)) : nullptr;
         const bool in_products = split && (!d.fuse_relu || !dx ||
                                            (!overlap(dX, (size_t)n * m, dY, (size_t)n * k) &&
                                             gemm_takes_bits(1, n, m, k, dY, W) && gemm_takes_bits(1, n, m, k, dY, W2)));
         G = dY;
+        side.tn = plain.tn = &p.tn;
         if (in_products) {
-            if (d.has_bias) side = GemmExtras{db, red, nullptr, nullptr};
+            if (d.has_bias) {
+                side.sums = db;
+                side.workspace = red;
+            }
             if (d.fuse_relu) {
                 mask_y = Y;
                 // a word holds 16 columns in the place of 16 floats
@@ -88,10 +93,16 @@ struct BiasAndMask {
     }
 };
 
+// A weight gradient X^T G.
+gnn_status_t weight_gradient(int m, int k, int n, const float *X, const float *G, float *dW, void *ws, hipStream_t st,
+                             const float *mask_y, const GemmExtras &extras) {
+    return gemm_launch(1, 0, m, k, n, X, G, dW, nullptr, 0, ws, st, mask_y, kActRelu, 0, nullptr, nullptr, &extras);
+}
+
 }  // namespace
 
-size_t bias_gradient_bytes(int64_t n, int64_t m, int64_t k) {
-    const size_t pass = colsum_workspace_bytes(n, (int)k), side = gemm_sums_bytes(m, k, n);
+size_t bias_gradient_bytes(const Plan &p) {
+    const size_t pass = colsum_workspace_bytes(p.desc.n, p.desc.f_out), side = gemm_sums_bytes(p.tn, p.desc.f_out);
     return pass > side ? pass : side;
 }
 
@@ -136,16 +147,16 @@ gnn_status_t gcn_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
     Carver ws(workspace);
 
     BiasAndMask bm;
-    GNN_TRY(bm.start(d, p.info.bwd, W, W, Y, dY, nullptr, db, ws, st));
+    GNN_TRY(bm.start(p, W, W, Y, dY, nullptr, db, ws, st));
     const float *G = bm.G;
-    void *gemm_ws = ws.take<char>(backward_gemm_bytes(n, m, k, dx, 1));   // one product at a time
+    void *gemm_ws = ws.take<char>(backward_gemm_bytes(p, 1));   // one product at a time
 
     if (p.info.bwd == GNN_BWD_FUSED_PROPAGATE) {
         // H = A'^T G once; dW = X^T H; dX = H W^T
         float *H = ws.take<float>((size_t)n * k);
         void *sp = ws.take<char>(spmm_workspace_bytes(n, d.nnz, k));
         GNN_TRY(spmm(g, transposed_view(g, k), G, k, H, nullptr, 0, sp, st));
-        GNN_TRY(gemm_launch(1, 0, m, k, n, X, H, dW, nullptr, 0, gemm_ws, st));
+        GNN_TRY(weight_gradient(m, k, n, X, H, dW, gemm_ws, st, nullptr, bm.plain));
         if (dx) GNN_TRY(gemm_launch(0, 1, n, m, k, H, W, dX, nullptr, 0, gemm_ws, st));
     } else {
         // dW = (A'X)^T G with A'X from the cache or recomputed; dX = A'^T (G W^T)
@@ -158,7 +169,7 @@ gnn_status_t gcn_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
             GNN_TRY(spmm(g, forward_view(g, m), X, m, Pw, nullptr, 0, sp, st));
             P = Pw;
         }
-        GNN_TRY(gemm_launch(1, 0, m, k, n, P, G, dW, nullptr, 0, gemm_ws, st, bm.mask_y, kActRelu, 0, nullptr, nullptr, &bm.side));
+        GNN_TRY(weight_gradient(m, k, n, P, G, dW, gemm_ws, st, bm.mask_y, bm.side));
         if (dx) {
             const SparseView tv = transposed_view(g, m);
             int ldu = m;                                    // as in the forward pass: U written where the SpMM pads
@@ -211,18 +222,17 @@ gnn_status_t sage_backward(Plan &p, const gnn_graph_t &g, const float *X, const 
     Carver ws(workspace);
 
     BiasAndMask bm;
-    GNN_TRY(bm.start(d, p.info.bwd, Ws, Wn, Y, dY, dX, db, ws, st));
+    GNN_TRY(bm.start(p, Ws, Wn, Y, dY, dX, db, ws, st));
     const float *G = bm.G;
-    void *gemm_ws = ws.take<char>(backward_gemm_bytes(n, m, k, dx, 2));
-    GNN_TRY(gemm_launch(1, 0, m, k, n, X, G, dWs, nullptr, 0, gemm_ws, st, bm.mask_y, kActRelu, 0, nullptr, nullptr,
-                        &bm.side));                                                                // dWs = X^T G
+    void *gemm_ws = ws.take<char>(backward_gemm_bytes(p, 2));
+    GNN_TRY(weight_gradient(m, k, n, X, G, dWs, gemm_ws, st, bm.mask_y, bm.side));
 
     if (p.info.bwd == GNN_BWD_FUSED_PROPAGATE) {
         // H = A'^T G once; dWn = X^T H; dX = G Ws^T + H Wn^T
         float *H = ws.take<float>((size_t)n * k);
         void *sp = ws.take<char>(spmm_workspace_bytes(n, d.nnz, k));
         GNN_TRY(spmm(g, transposed_view(g, k), G, k, H, nullptr, 0, sp, st));
-        GNN_TRY(gemm_launch(1, 0, m, k, n, X, H, dWn, nullptr, 0, gemm_ws, st));
+        GNN_TRY(weight_gradient(m, k, n, X, H, dWn, gemm_ws, st, nullptr, bm.plain));
         if (dx) {
             GNN_TRY(gemm_launch(0, 1, n, m, k, G, Ws, dX, nullptr, 0, gemm_ws, st, nullptr, 0, 0, H, Wn));
         }
@@ -237,7 +247,7 @@ gnn_status_t sage_backward(Plan &p, const gnn_graph_t &g, const float *X, const 
             GNN_TRY(spmm(g, forward_view(g, m), X, m, Pw, nullptr, 0, sp, st));
             P = Pw;
         }
-        GNN_TRY(gemm_launch(1, 0, m, k, n, P, G, dWn, nullptr, 0, gemm_ws, st, bm.mask_y, kActRelu));
+        GNN_TRY(weight_gradient(m, k, n, P, G, dWn, gemm_ws, st, bm.mask_y, bm.plain));
         if (dx) {
             const SparseView tv = transposed_view(g, m);
             int ldu = m;

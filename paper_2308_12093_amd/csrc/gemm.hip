@@ -751,14 +751,9 @@ static_assert(tn_blocks_fit(), "resident blocks by LDS");
 constexpr double kTnWait = 0.4, kTnTurn = 0.15;            // us a k-tile: a block on its own, any number of them
 constexpr int kTnBlocks = 8;                               // blocks a CU at most, over the whole launch
 
-struct TnPlan {
-    Tiling tile;
-    int splits;
-};
-
 // side: with sums or bits beside it (128 x 128 outputs leave no registers for those)
 TnPlan pick_tn(int64_t M, int64_t N, int64_t K, bool side) {
-    TnPlan best{kTnTiles[0].tile, 1};
+    TnPlan best{0, 1};
     double least = 1e300;
     const int64_t ktiles = ceil_div(K > 0 ? K : 1, BK);
     for (const TnTile &c : kTnTiles) {
@@ -784,7 +779,7 @@ TnPlan pick_tn(int64_t M, int64_t N, int64_t K, bool side) {
                              0.4 * per_cu + (double)(splits * M * N) * (16 / 4.5e6);
             if (t < least) {
                 least = t;
-                best = TnPlan{c.tile, (int)splits};
+                best = TnPlan{(int)(&c - kTnTiles), (int)splits};
             }
         }
     }
@@ -851,13 +846,14 @@ size_t gemm_workspace_bytes(int ta, int tb, int64_t M, int64_t N, int64_t K) {
     return align_up((size_t)most_chunks(M, N, K) * M * N * sizeof(double));
 }
 
-size_t gemm_tn_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-    const int a = pick_tn(M, N, K, false).splits, b = pick_tn(M, N, K, true).splits;
-    return align_up((size_t)(a > b ? a : b) * M * N * sizeof(double));
+TnPlans gemm_tn_plans(int64_t M, int64_t N, int64_t K) { return TnPlans{pick_tn(M, N, K, false), pick_tn(M, N, K, true)}; }
+
+size_t gemm_tn_workspace_bytes(const TnPlans &tn, int64_t M, int64_t N) {
+    return align_up((size_t)(tn.plain.splits > tn.side.splits ? tn.plain.splits : tn.side.splits) * M * N * sizeof(double));
 }
 
-size_t gemm_sums_bytes(int64_t M, int64_t N, int64_t K) {
-    return align_up((size_t)pick_tn(M, N, K, true).splits * (N > 0 ? N : 1) * sizeof(double));
+size_t gemm_sums_bytes(const TnPlans &tn, int64_t N) {
+    return align_up((size_t)tn.side.splits * (N > 0 ? N : 1) * sizeof(double));
 }
 
 bool gemm_takes_bits(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B) {
@@ -922,8 +918,9 @@ gnn_status_t gemm_launch(int ta, int tb, int64_t M, int64_t N, int64_t K, const 
     if (M > INT32_MAX / 2 || N > INT32_MAX / 2 || (!ta && K > INT32_MAX / 2)) return GNN_ERR_UNSUPPORTED;
     const bool f64 = ta != 0;
     const bool side = extras && (extras->sums || extras->bits);
-    const TnPlan plan = f64 ? pick_tn(M, N, K, side) : TnPlan{pick_tiling(M, N), 1};
-    const Tiling tl = plan.tile;
+    TnPlan plan{0, 1};
+    if (f64) plan = !extras || !extras->tn ? pick_tn(M, N, K, side) : side ? extras->tn->side : extras->tn->plain;
+    const Tiling tl = f64 ? kTnTiles[plan.tile].tile : pick_tiling(M, N);
     const int tiles_m = (int)ceil_div(M, tile_m(f64, tl)), tiles_n = (int)ceil_div(N, tile_n(f64, tl));
     bool launched = false;
     if (!f64) {

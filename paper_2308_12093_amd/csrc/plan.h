@@ -4,15 +4,7 @@
 
 #include "common.h"
 
-struct gnn_plan {
-    gnn_plan_desc_t desc;
-    gnn_plan_info_t info;
-    bool cache_filled = false;
-};
-
 namespace gnn {
-
-using Plan = ::gnn_plan;
 
 // Byte offsets of the GAT cache blocks (in `cache`) and scratch blocks (in `workspace`).
 // (size_t)-1 marks a block that does not exist in this variant.
@@ -24,11 +16,24 @@ struct GatLayout {
     size_t workspace_bytes;
 };
 
+}  // namespace gnn
+
+struct gnn_plan {
+    gnn_plan_desc_t desc;
+    gnn_plan_info_t info;
+    gnn::TnPlans tn;               // of the weight-gradient products
+    gnn::GatLayout gat;
+    bool cache_filled = false;
+};
+
+namespace gnn {
+
+using Plan = ::gnn_plan;
+
 // scratch of the products of a backward pass, one at a time: X^T H, and (dx) up to `pairs` pairs of G W^T
-size_t backward_gemm_bytes(int64_t n, int64_t m, int64_t k, bool dx, int pairs);
+size_t backward_gemm_bytes(const Plan &p, int pairs);
 // scratch of the bias gradient, in a pass of its own or beside X^T H
-size_t bias_gradient_bytes(int64_t n, int64_t m, int64_t k);
-GatLayout gat_layout(const Plan &p);
+size_t bias_gradient_bytes(const Plan &p);
 gnn_status_t plan_create(const gnn_plan_desc_t *desc, Plan **out);
 
 gnn_status_t gcn_forward(Plan &p, const gnn_graph_t &g, const float *X, const float *W, const float *b, float *Y,

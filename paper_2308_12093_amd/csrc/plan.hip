@@ -92,8 +92,8 @@ void size_gcn(Plan &p) {
     // backward
     size_t bwd = 0;
     if (d.fuse_relu) bwd += align_up((size_t)n * k * fl);
-    if (d.has_bias) bwd += bias_gradient_bytes(n, m, k);
-    bwd += align_up(backward_gemm_bytes(n, m, k, dx, d.layer == GNN_LAYER_SAGE ? 2 : 1));
+    if (d.has_bias) bwd += bias_gradient_bytes(p);
+    bwd += align_up(backward_gemm_bytes(p, d.layer == GNN_LAYER_SAGE ? 2 : 1));
     if (fp) {
         bwd += align_up((size_t)n * k * fl) + spmm_workspace_bytes(n, q, (int)k);
         p.info.transient_bwd = n * k;
@@ -144,13 +144,14 @@ double spmm_time_model_us(int64_t n, int64_t nnz, int f) {
     return 12.0 + (double)nnz * per_entry_ps * 1e-6;
 }
 
-size_t backward_gemm_bytes(int64_t n, int64_t m, int64_t k, bool dx, int pairs) {
-    const size_t tn = gemm_tn_workspace_bytes(m, k, n);
-    const size_t nt = dx ? pairs * gemm_workspace_bytes(0, 1, n, m, k) : 0;
+size_t backward_gemm_bytes(const Plan &p, int pairs) {
+    const int64_t n = p.desc.n, m = p.desc.f_in, k = (int64_t)p.desc.heads * p.desc.f_out;
+    const size_t tn = gemm_tn_workspace_bytes(p.tn, m, k);
+    const size_t nt = p.desc.need_input_grad ? pairs * gemm_workspace_bytes(0, 1, n, m, k) : 0;
     return tn > nt ? tn : nt;
 }
 
-GatLayout gat_layout(const Plan &p) {
+static GatLayout gat_layout(const Plan &p) {
     const gnn_plan_desc_t &d = p.desc;
     const size_t n = d.n, q = d.nnz, h = d.heads, k = d.f_out, f = h * k, m = d.f_in, fl = sizeof(float);
     GatLayout L{};
@@ -180,7 +181,7 @@ GatLayout gat_layout(const Plan &p) {
     L.w_spmm_h = take(spmm_segments_bytes(0, q, (int)h));        // its dense operand has q rows: never padded
     L.w_dM = take(n * f * fl);
     L.w_red = take(2 * colsum_workspace_bytes(n, (int)f));
-    L.w_gemm_tn = take(backward_gemm_bytes(n, m, f, d.need_input_grad != 0, 1));
+    L.w_gemm_tn = take(backward_gemm_bytes(p, 1));
     L.w_G = d.fuse_elu ? take(n * f * fl) : (size_t)-1;
     L.w_fused = take(gat_fused_workspace_bytes(q, (int)h, (int)k));
     L.w_node = take(n * h * 4 * fl);
@@ -205,6 +206,7 @@ gnn_status_t plan_create(const gnn_plan_desc_t *desc, Plan **out) {
     gnn_status_t s;
     if (d.layer != GNN_LAYER_GAT) {                       // GCN and SAGE: same schemes, same buffers
         p->desc.heads = 1;
+        p->tn = gemm_tn_plans(d.f_in, d.f_out, d.n);
         s = resolve_gcn(*p);
         if (s == GNN_OK) size_gcn(*p);
     } else {
@@ -212,10 +214,11 @@ gnn_status_t plan_create(const gnn_plan_desc_t *desc, Plan **out) {
         if ((int64_t)d.heads * d.f_out > (1 << 20)) { delete p; return GNN_ERR_UNSUPPORTED; }
         s = resolve_gat(*p);
         if (s == GNN_OK) {
-            const GatLayout L = gat_layout(*p);
-            p->info.cache_bytes = L.cache_bytes;
-            p->info.workspace_bytes = L.workspace_bytes;
             const int64_t f = (int64_t)d.heads * d.f_out;
+            p->tn = gemm_tn_plans(d.f_in, f, d.n);
+            p->gat = gat_layout(*p);
+            p->info.cache_bytes = p->gat.cache_bytes;
+            p->info.workspace_bytes = p->gat.workspace_bytes;
             p->info.transient_fwd = (int64_t)d.n * f;
             p->info.transient_bwd = (int64_t)d.n * f;
             p->info.spmm_width_fwd = f;

@@ -287,7 +287,7 @@ def test_a_mask_beside_a_second_operand_pair_is_refused():
     launch = getattr(B.lib, "_ZN3gnn11gemm_launchEiilllPKfS1_PfS1_iPvP12ihipStream_tS1_ilS1_S1_PKNS_10GemmExtrasE")
     launch.restype, i64, ptr = ctypes.c_int, ctypes.c_int64, ctypes.c_void_p
     launch.argtypes = [ctypes.c_int] * 2 + [i64] * 3 + [ptr] * 4 + [ctypes.c_int, ptr, ptr, ptr, ctypes.c_int, i64] + [ptr] * 3
-    extras = (ptr * 4)(None, None, None, 256)              # sums, workspace, bits, a_bits
+    extras = (ptr * 5)(None, None, None, 256, None)        # sums, workspace, bits, a_bits, tn
     one, (M, N, K) = ptr(256), (200000, 128, 64)
     call = lambda a2: launch(0, 1, M, N, K, one, one, one, None, 0, one, None, None, 0, 0, a2, a2, extras)  # noqa: E731
     assert call(one) == B.GNN_ERR_UNSUPPORTED
