@@ -31,12 +31,19 @@ gnn_status_t spmm(const gnn_graph_t &g, const SparseView &v, const float *B, int
     return spmm_launch(g.n, g.nnz, v.ptr, v.idx, v.eidx, v.w, B, g.n, f, C, bias, relu, ws, st, pieces);
 }
 
-// A pre-activation within rounding of zero changes a row of dX by its full size: the sums before it stay as they are
-// whatever the size of the graph.  Without dX such an entry is one of n in the sums of dW.
+// Layers whose sums before a ReLU keep the order they have had: those with dX, where a pre-activation that falls on the other
+// side of zero changes a row of dX by its full size.  That is a choice, not a bound: the other sums are the more exact ones
+// (see relu_flags).
 bool sums_decide_signs(const gnn_plan_desc_t &d) { return d.fuse_relu && d.need_input_grad; }
 
-// Flags of the product before a fused ReLU.  From 2^16 nodes on, one of n is below what the float sums of dW are worth, and
-// the product may run on the faster split parts (2^20 x 100 -> 256: 726 -> 543 us).
+// Flags of the product before a fused ReLU.  Without dX it may run on split parts, whose sums lie closer to 64 bits than those
+// of the fp32 instruction, so that fewer pre-activations fall on the wrong side of zero.  fp32 instruction / split parts, a
+// forward pass in us, relative error of Y, wrong signs in three runs:
+//   2^17 nodes, 128 -> 512 240 / 195, 1.5e-7 / 5.9e-8, 4 / 2; 512 -> 128 289 / 254, 3.0e-7 / 1.1e-7, 3 / 2;
+//   2^19, 100 -> 256 508 / 419, 1.4e-7 / 5.9e-8, 15 / 5; 65536, 128 -> 512 121 / 95, 1.5e-7 / 5.9e-8, 4 / 1.
+// A wrong sign puts one term too many or too few into the sums of dW and db, 1e-4 of them at these sizes (else 2.5e-8).  The
+// same holds below 2^16 nodes (50021, 100 -> 256 76 / 54, 1.3e-7 / 5.7e-8): the line is where layers have been moved so far,
+// not one of accuracy.
 int relu_flags(const gnn_plan_desc_t &d, int with_relu) {
     return !d.fuse_relu ? 0 : sums_decide_signs(d) || d.n < 1 << 16 ? with_relu : with_relu | kActAnySign;
 }

@@ -1,4 +1,5 @@
-"""Backward of layers with bias and ReLU in the split-propagate scheme: bias gradient and mask formed beside X^T G, the mask
+"""Layers with bias and ReLU in the split-propagate scheme: the forward product on both sides of the node count from which it
+runs on split parts (without dX), and backward: bias gradient and mask formed beside X^T G, the mask
 taken by the products with the weights.  A' is the identity, so that every gradient is a dense product."""
 import pytest
 import torch
@@ -14,6 +15,32 @@ def normal(gen, *shape):
 
 def close(got, want, most):
     assert bool(((got.double() - want).abs() <= most).all())
+
+
+# ragged and whole tiles of one, two and four times 32 columns, reductions that end inside a step, outputs beyond 64 MB
+@pytest.mark.parametrize("sage", [False, True])
+@pytest.mark.parametrize("order", [B.GNN_ORDER_PROPAGATE_FIRST, B.GNN_ORDER_TRANSFORM_FIRST])
+@pytest.mark.parametrize("n", [65535, 65536, 70001])
+@pytest.mark.parametrize("m,k", [(64, 64), (16, 5), (100, 33), (130, 47), (70, 200), (128, 512), (33, 96), (4, 17), (40, 259)])
+def test_forward(n, m, k, order, sage):
+    gen = torch.Generator(device="cuda").manual_seed(n + m + k)
+    ids = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+    g = B.Graph(n, ids, ids[:n].clone(), torch.ones(n, device="cuda"), ids[:n].clone(), symmetric=True)
+    plan = B.Plan(B.GNN_LAYER_SAGE if sage else B.GNN_LAYER_GCN, n, n, m, k, need_input_grad=False, has_bias=True,
+                  fuse_relu=True, order=order)
+    X, Ws, Wn, b = normal(gen, n, m), normal(gen, m, k) * 0.1, normal(gen, m, k) * 0.1, normal(gen, k)
+    X[::7] *= 2.0 ** -100                                   # rows that are taken times a power of two
+    Y, cache, ws = torch.empty(n, k, device="cuda"), B.alloc(plan.info.cache_bytes), B.alloc(plan.info.workspace_bytes)
+    if sage:
+        B.sage_layer_fwd(plan, g, X, Ws, Wn, b, Y, cache, ws)
+    else:
+        B.gcn_layer_fwd(plan, g, X, Wn, b, Y, cache, ws)
+    W, Wabs = (Ws.double() + Wn.double(), Ws.abs().double() + Wn.abs().double()) if sage else (Wn.double(), Wn.abs().double())
+    ref, mag = X.double() @ W + b.double(), X.abs().double() @ Wabs + b.abs().double()
+    # sums in float: at most eight roundings per 16 indices of each operand pair, then those of the aggregation, the
+    # accumulated product and the bias
+    close(Y, ref.clamp(min=0), (8 * ((m + 15) // 16) * (2 if sage else 1) + 8) * 2.0 ** -24 * mag)
+    assert bool((Y >= 0).all())
 
 
 # widths at the edges of tiles and of 16-column words; 2100 columns and few rows take the mask no product's way
