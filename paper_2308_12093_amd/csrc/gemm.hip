@@ -46,10 +46,12 @@ constexpr int BK = 32;
 // of k-step s+1 are read and widened before the instructions of step s.
 // MASK: B is used as B .* act'(Ymask), the derivative of a fused activation taken from the layer's output
 // Ymask (same shape as B): ReLU 1 / 0, ELU 1 / y + 1.  The gradient through the activation then needs no
-// pass of its own: the second operand stream costs nothing while the matrix cores are the bound.
-// SUMS: the column sums of B (as used), and which of its elements are not zero, on the side, from the tile in LDS and by
-// the blocks of the first tile row alone: the gradient of a bias, and the mask for the product that reads B next, cost no
-// pass over B (2^17 rows, 128 x 512 with a mask: 350 -> 406 us under the profiler, the pass they replace 184).
+// pass of its own.
+// SUMS: the column sums of B (as used), and which of its elements are not zero, on the side, by the blocks of the first tile
+// row alone: the gradient of a bias, and the mask for the product that reads B next, cost no pass over B (2^17 rows, 128 x
+// 512: 302 us plain, 417 with mask, sums and bits, on tiles of 64 x 64, which ask for B and Ymask twice and for A eight times,
+// 1.6 GB in all; the pass they replace 184).
+// LDS:
 // words per LDS row of `cols` columns: the lanes of one k-row read 16 * T consecutive words.  T odd: word by word, the 16
 // lanes of a row T banks apart, four rows in 64 banks at a row length of 16 or 48 mod 64; T = 2: two rows per pass, 32 mod
 // 64; T = 4: one row per pass
