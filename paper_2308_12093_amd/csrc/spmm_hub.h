@@ -38,7 +38,9 @@ struct HubReduce {
 __device__ __forceinline__ void hub_add(const float *part, int ld, int lpf, size_t x, size_t by, int n, int c, float (&t)[4]) {
     const int slots = kWave / lpf, slot = threadIdx.x % kWave / lpf;
     const float *src = part + x * ld + c;
-    float a[4][4] = {};
+    float a[4][4];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) a[j / 4][j % 4] = -0.f;   // x + -0 is x: sums that underflow to -0 stay that
     if (c < ld) {
         int i = slot;
         for (; i + 3 * slots < n; i += 4 * slots)

@@ -127,6 +127,17 @@ def test_not_finite_only_where_it_is_stored():
     assert torch.equal(~torch.isfinite(C).all(1), held)
 
 
+def test_sums_that_underflow_keep_the_sign_of_zero():
+    n, d, f = 110_000, 300, 64
+    rowptr = torch.arange(0, n * d + 1, d, dtype=torch.int32, device="cuda")
+    erow = torch.arange(n, dtype=torch.int32, device="cuda").repeat_interleave(d)
+    col = torch.randint(0, n, (n * d,), dtype=torch.int32, device="cuda")
+    X = torch.full((n, f), 1e-30, device="cuda")
+    X[:, ::2] = -1e-30
+    C = run(n, rowptr, col, torch.full((n * d,), 1e-30, device="cuda"), erow, X)
+    assert bool((C == 0).all()) and bool(torch.signbit(C[:, ::2]).all()) and not bool(torch.signbit(C[:, 1::2]).any())
+
+
 def test_without_long_rows_the_segments_do_it():
     n, f = 300_000, 100
     rowptr, col, val, erow, gen = matrix(3, n, 21_000_000, hubs=False)
