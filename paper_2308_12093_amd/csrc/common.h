@@ -103,6 +103,7 @@ struct TnPlans {
 TnPlans gemm_tn_plans(int64_t M, int64_t N, int64_t K);
 size_t gemm_tn_workspace_bytes(const TnPlans &tn, int64_t M, int64_t N);   // no more than gemm_workspace_bytes
 size_t gemm_sums_bytes(const TnPlans &tn, int64_t N);
+double gemm_side_us(const TnPlans &tn, int64_t M, int64_t N, int64_t K);   // what mask, sums and bits add to its time, about
 // b_mask (transposed-A form only): B is used as B .* act'(b_mask), the derivative of the activation
 // b_mask_act (kActRelu, kActElu) taken from its output b_mask, an array of B's shape.
 // ldc (plain products only): rows of C are ldc >= N floats apart, the columns in between written as zeros.

@@ -57,8 +57,12 @@ bool overlap(const float *a, size_t count_a, const float *b, size_t count_b) {
 // Split-propagate scheme: G is read by the weight-gradient products, which mask dY as they load it and add up db on the
 // side, and with dX by the products with the weights, which take the mask as bits from the first of those: G is never
 // written, nothing but products reads dY or Y (2^17 nodes, 128 -> 512, a step: 930 -> 828 us; GraphSAGE 128 -> 128:
-// 588 -> 573).  Where those products run on a kernel that takes no bits, where dY is read again after dX was written and
-// shares memory with it, and in the fused-propagate scheme, whose gather would fetch Y beside dY, one pass makes G and db.
+// 588 -> 573).  One pass makes G and db where those products run on a kernel that takes no bits, where dY is read again after
+// dX was written and shares memory with it, in the fused-propagate scheme, whose gather would fetch Y beside dY, and with dX
+// where the weight gradients would read Y too often (`pass_us`): products / pass, us of a backward pass without aggregation,
+// GraphSAGE 58450 x 403 -> 293 without bias 1207 / 1030, 131072 x 512 -> 256 with bias 1866 / 1725, GCN 58450 x 403 -> 293
+// without 649 / 549, 124552 x 480 -> 16 without 259 / 235; the other way round GCN 307451 x 43 -> 45 with bias 145 / 206,
+// 131072 x 64 -> 16 48 / 63.
 struct BiasAndMask {
     const float *G = nullptr, *mask_y = nullptr;       // G, or dY and what the products mask it by
     GemmExtras side{}, plain{}, masked{};              // for the first weight-gradient product, others, those with the weights
@@ -72,8 +76,11 @@ struct BiasAndMask {
         // carved either way: the layout is the plan's
         float *Gm = d.fuse_relu ? ws.take<float>((size_t)n * k) : nullptr;
         void *red = d.has_bias ? ws.take<char>(bias_gradient_bytes(p)) : nullptr;
+        // what the pass takes, about: with the bias gradient two launches, and the sums in double
+        const double pass_us = d.has_bias ? 7 + 2.6e-6 * n * k : 1.5e-6 * n * k;
+        const double products_us = (d.layer == GNN_LAYER_SAGE ? 2 : 1) * gemm_side_us(p.tn, m, k, n);
         const bool in_products = split && (!d.fuse_relu || !dx ||
-                                           (!overlap(dX, (size_t)n * m, dY, (size_t)n * k) &&
+                                           (products_us < pass_us && !overlap(dX, (size_t)n * m, dY, (size_t)n * k) &&
                                             gemm_takes_bits(1, n, m, k, dY, W) && gemm_takes_bits(1, n, m, k, dY, W2)));
         G = dY;
         side.tn = plain.tn = &p.tn;

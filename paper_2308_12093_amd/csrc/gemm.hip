@@ -858,6 +858,13 @@ size_t gemm_sums_bytes(const TnPlans &tn, int64_t N) {
     return align_up((size_t)tn.side.splits * (N > 0 ? N : 1) * sizeof(double));
 }
 
+// Each row of tiles reads the mask once more; tiles beyond 64 x 64 pay more, with few blocks to hide it.  Fitted to backward
+// passes of 370 layers of 33 000 to 10^6 nodes, 16 to 512 features.
+double gemm_side_us(const TnPlans &tn, int64_t M, int64_t N, int64_t K) {
+    const Tiling &t = kTnTiles[tn.side.tile].tile;
+    return (t.tm * t.tn > 4 ? 0.85e-6 : 0.5e-6) * (double)ceil_div(M, tile_m(true, t)) * (double)N * (double)K;
+}
+
 bool gemm_takes_bits(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B) {
     const bool rows16 = K % 4 == 0 && aligned16(A) && (!tb || aligned16(B));
     return M > 0 && N > 0 && K >= 4 && K <= 2048 && !few_rows(tb, M, N, K) &&

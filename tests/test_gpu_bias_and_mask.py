@@ -43,12 +43,14 @@ def test_forward(n, m, k, order, sage):
     assert bool((Y >= 0).all())
 
 
-# widths at the edges of tiles and of 16-column words; 2100 columns and few rows take the mask no product's way
+# widths at the edges of tiles and of 16-column words; 2100 columns, few rows and long input features take the mask no
+# product's way
 @pytest.mark.parametrize("sage", [False, True])
 @pytest.mark.parametrize("relu,dx", [(True, True), (True, False), (False, True)])
 @pytest.mark.parametrize("n,m,k", [(40007, 64, 64), (33000, 100, 33), (40000, 130, 47), (36000, 70, 200), (65536, 128, 512),
                                    (35001, 96, 80), (34000, 300, 17), (3000, 40, 50), (40000, 40, 2100), (70001, 16, 5),
-                                   (33000, 64, 1000), (33000, 40, 2048), (33001, 130, 519)])
+                                   (33000, 64, 1000), (33000, 40, 2048), (33001, 130, 519),
+                                   (33000, 515, 300), (35000, 200, 130)])
 def test_gradients(n, m, k, relu, dx, sage):
     gen = torch.Generator(device="cuda").manual_seed(n + m + k)
     ids = torch.arange(n + 1, dtype=torch.int32, device="cuda")
