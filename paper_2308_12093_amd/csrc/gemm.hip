@@ -753,35 +753,52 @@ static_assert(tn_blocks_fit(), "resident blocks by LDS");
 constexpr double kTnWait = 0.4, kTnTurn = 0.15;            // us a k-tile: a block on its own, any number of them
 constexpr int kTnBlocks = 8;                               // blocks a CU at most, over the whole launch
 
-// side: with sums or bits beside it (128 x 128 outputs leave no registers for those)
+// side: with sums or bits beside it (128 x 128 outputs leave no registers for those).  gnn_gemm chooses on each call: 0.2 us for
+// outputs of a tile, where a call takes 12, and 1.2 for large ones; without the tiles that are left out, and with divisions of
+// 64 bits, 1.4 and 1.9.
 TnPlan pick_tn(int64_t M, int64_t N, int64_t K, bool side) {
+    constexpr int TILES = sizeof(kTnTiles) / sizeof(kTnTiles[0]);
     TnPlan best{0, 1};
     double least = 1e300;
-    const int64_t ktiles = ceil_div(K > 0 ? K : 1, BK);
-    for (const TnTile &c : kTnTiles) {
+    const int64_t ktiles = ceil_div(K > 0 ? K : 1, BK), most = ktiles / 3 > 1 ? ktiles / 3 : 1;
+    const double partials = (double)M * (double)N * (16 / 4.5e6);
+    struct { int64_t tiles; double step; } seen[TILES];
+    int nseen = 0;
+    for (int i = 0; i < TILES; ++i) {
+        const TnTile &c = kTnTiles[i];
         if (side && c.tile.tm * c.tile.tn == 16) continue;
         const int bm = tile_m(true, c.tile), bn = tile_n(true, c.tile);
         const int64_t tiles = ceil_div(M, bm) * ceil_div(N, bn);
         const double step = c.rate / 4096 * bm * bn;
+        bool worse = false;                                // than a tile of less work that covers the outputs as well
+        for (int j = 0; j < nseen; ++j) worse |= seen[j].tiles <= tiles && seen[j].step <= step;
+        if (worse) continue;
+        seen[nseen].tiles = tiles;
+        seen[nseen++].step = step;
+        double turn[8];                                    // one k-tile of each of so many blocks on a CU
+        for (int blocks = 0; blocks <= c.resident; ++blocks) {
+            const double busy = blocks * step + kTnTurn, alone = step + kTnWait;
+            turn[blocks] = blocks == 0 ? 0.0 : busy > alone ? busy : alone;
+        }
         int64_t before = 0;
         for (int want = -7; want <= kTnBlocks; ++want) {   // blocks a CU; below one, fractions of the chip
-            int64_t splits = (want > 0 ? 256 * want : 256 >> -want) / tiles;
-            if (splits > ktiles / 3) splits = ktiles / 3;
+            const uint32_t blocks = want > 0 ? 256 * want : 256 >> -want;
+            int64_t splits = tiles > blocks ? 0 : blocks / (uint32_t)tiles;
+            if (splits > most) splits = most;
             if (splits < 1) splits = 1;
             if (splits == before) continue;
             before = splits;
-            const int64_t per_cu = ceil_div(tiles * splits, 256), rest = per_cu % c.resident;
-            auto turn = [&](int64_t blocks) {              // one k-tile of each of `blocks` on a CU
-                const double busy = blocks * step + kTnTurn, alone = step + kTnWait;
-                return blocks == 0 ? 0.0 : busy > alone ? busy : alone;
-            };
-            const double chunk = (double)ceil_div(ktiles, splits), last = turn(per_cu < c.resident ? per_cu : c.resident);
+            const int64_t per_cu = ceil_div(tiles * splits, 256);
+            const uint32_t rounds = (uint32_t)per_cu / c.resident, rest = (uint32_t)per_cu % c.resident;
+            const int64_t chunk = ktiles <= INT32_MAX ? ((uint32_t)ktiles + (uint32_t)splits - 1) / (uint32_t)splits
+                                                      : ceil_div(ktiles, splits);
             // blocks do not end together: a few hundredths of the time of the last
-            const double t = ((double)(per_cu / c.resident) * turn(c.resident) + turn(rest) + 0.03 * last) * chunk +
-                             0.4 * per_cu + (double)(splits * M * N) * (16 / 4.5e6);
+            const double last = turn[per_cu < c.resident ? per_cu : c.resident];
+            const double t = (rounds * turn[c.resident] + turn[rest] + 0.03 * last) * (double)chunk + 0.4 * per_cu +
+                             splits * partials;
             if (t < least) {
                 least = t;
-                best = TnPlan{(int)(&c - kTnTiles), (int)splits};
+                best = TnPlan{i, (int)splits};
             }
         }
     }
