@@ -77,7 +77,7 @@ struct BiasAndMask {
         float *Gm = d.fuse_relu ? ws.take<float>((size_t)n * k) : nullptr;
         void *red = d.has_bias ? ws.take<char>(bias_gradient_bytes(p)) : nullptr;
         // what the pass takes, about: with the bias gradient two launches, and the sums in double
-        const double pass_us = d.has_bias ? 7 + 2.6e-6 * n * k : 1.5e-6 * n * k;
+        const double pass_us = d.has_bias ? 5 + 2.5e-6 * n * k : 1.6e-6 * n * k;
         const double products_us = (d.layer == GNN_LAYER_SAGE ? 2 : 1) * gemm_side_us(p.tn, m, k, n);
         const bool in_products = split && (!d.fuse_relu || !dx ||
                                            (products_us < pass_us && !overlap(dX, (size_t)n * m, dY, (size_t)n * k) &&

@@ -875,11 +875,13 @@ size_t gemm_sums_bytes(const TnPlans &tn, int64_t N) {
     return align_up((size_t)tn.side.splits * (N > 0 ? N : 1) * sizeof(double));
 }
 
-// Each row of tiles reads the mask once more; tiles beyond 64 x 64 pay more, with few blocks to hide it.  Fitted to backward
-// passes of 370 layers of 33 000 to 10^6 nodes, 16 to 512 features.
+// Each row of tiles reads the mask once more, padding columns count, and tiles beyond 64 x 64 pay more, with few blocks to hide
+// it.  Fitted, with what it is weighed against in gcn_layer.hip, to backward passes of 570 layers of 33 000 to 10^6 nodes, 16 to
+// 512 features: ten are more than 2 % slower than on the other way, up to 4 %.
 double gemm_side_us(const TnPlans &tn, int64_t M, int64_t N, int64_t K) {
     const Tiling &t = kTnTiles[tn.side.tile].tile;
-    return (t.tm * t.tn > 4 ? 0.85e-6 : 0.5e-6) * (double)ceil_div(M, tile_m(true, t)) * (double)N * (double)K;
+    const int64_t reads = ceil_div(M, tile_m(true, t)), cols = ceil_div(N, tile_n(true, t)) * tile_n(true, t);
+    return (t.tm * t.tn > 4 ? 0.9e-6 : 0.6e-6) * (double)reads * (double)cols * (double)K;
 }
 
 bool gemm_takes_bits(int tb, int64_t M, int64_t N, int64_t K, const float *A, const float *B) {
