@@ -188,7 +188,8 @@ gnn_status_t gcn_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
             const SparseView tv = transposed_view(g, m);
             int ldu = m;                                    // as in the forward pass: U written where the SpMM pads
             if (float *Up = spmm_padded_operand(sp, tv.eidx, n, d.nnz, m, &ldu)) U = Up;
-            GNN_TRY(gemm_launch(0, 1, n, m, k, G, W, U, nullptr, 0, gemm_ws, st, nullptr, 0, ldu, nullptr, nullptr, &bm.masked));
+            GNN_TRY(gemm_launch(0, 1, n, m, k, G, W, U, nullptr, 0, gemm_ws, st, nullptr, 0, ldu, nullptr, nullptr,
+                                &bm.masked));
             GNN_TRY(spmm(g, tv, U, m, dX, nullptr, 0, sp, st));
         }
     }
@@ -266,7 +267,8 @@ gnn_status_t sage_backward(Plan &p, const gnn_graph_t &g, const float *X, const 
             const SparseView tv = transposed_view(g, m);
             int ldu = m;
             if (float *Up = spmm_padded_operand(sp, tv.eidx, n, d.nnz, m, &ldu)) U = Up;
-            GNN_TRY(gemm_launch(0, 1, n, m, k, G, Wn, U, nullptr, 0, gemm_ws, st, nullptr, 0, ldu, nullptr, nullptr, &bm.masked));
+            GNN_TRY(gemm_launch(0, 1, n, m, k, G, Wn, U, nullptr, 0, gemm_ws, st, nullptr, 0, ldu, nullptr, nullptr,
+                                &bm.masked));
             GNN_TRY(spmm(g, tv, U, m, dX, nullptr, 0, sp, st));
             GNN_TRY(gemm_launch(0, 1, n, m, k, G, Ws, dX, nullptr, kActAccumulate, gemm_ws, st, nullptr, 0, 0, nullptr,
                                 nullptr, &bm.masked));

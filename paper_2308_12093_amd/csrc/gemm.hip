@@ -753,9 +753,9 @@ static_assert(tn_blocks_fit(), "resident blocks by LDS");
 constexpr double kTnWait = 0.4, kTnTurn = 0.15;            // us a k-tile: a block on its own, any number of them
 constexpr int kTnBlocks = 8;                               // blocks a CU at most, over the whole launch
 
-// side: with sums or bits beside it (128 x 128 outputs leave no registers for those).  gnn_gemm chooses on each call: 0.2 us for
-// outputs of a tile, where a call takes 12, and 1.2 for large ones; without the tiles that are left out, and with divisions of
-// 64 bits, 1.4 and 1.9.
+// side: with sums or bits beside it (128 x 128 outputs leave no registers for those).  gnn_gemm chooses on each call: 0.2 us on
+// the host for outputs of a tile, whose call takes 8 to 15, and 1.2 for large ones; with the tiles that are left out, and with
+// divisions of 64 bits, 1.4 and 1.9.
 TnPlan pick_tn(int64_t M, int64_t N, int64_t K, bool side) {
     constexpr int TILES = sizeof(kTnTiles) / sizeof(kTnTiles[0]);
     TnPlan best{0, 1};
@@ -876,8 +876,8 @@ size_t gemm_sums_bytes(const TnPlans &tn, int64_t N) {
 }
 
 // Each row of tiles reads the mask once more, padding columns count, and tiles beyond 64 x 64 pay more, with few blocks to hide
-// it.  Fitted, with what it is weighed against in gcn_layer.hip, to backward passes of 570 layers of 33 000 to 10^6 nodes, 16 to
-// 512 features: ten are more than 2 % slower than on the other way, up to 4 %.
+// it.  Fitted, with what it is weighed against in gcn_layer.hip, to backward passes of 570 layers of 33 000 to 10^6 nodes, 16
+// to 512 features: ten are more than 2 % slower than on the other way, up to 4 %.
 double gemm_side_us(const TnPlans &tn, int64_t M, int64_t N, int64_t K) {
     const Tiling &t = kTnTiles[tn.side.tile].tile;
     const int64_t reads = ceil_div(M, tile_m(true, t)), cols = ceil_div(N, tile_n(true, t)) * tile_n(true, t);

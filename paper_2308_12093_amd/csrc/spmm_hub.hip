@@ -40,7 +40,7 @@ constexpr int kShortClasses = 6;
 // per block: pieces by position, short rows by length, then the shares of long rows; padded to whole int4
 constexpr int kShares = kHubBuckets + kShortClasses, kHubLists = (kShares + 1 + 3) / 4 * 4;
 constexpr int kListBlocks = 512;           // blocks that make the lists: each reads the counts of all
-constexpr int kListThreads = 1024;         // of these: chains of three loads an item, so as many wavefronts as there is room for
+constexpr int kListThreads = 1024;         // in each: chains of loads for every item, so as many wavefronts as there is room for
 constexpr int kGrab = 4;                   // items a group takes at a time: 2 and 8 are 1 - 4 % slower
 constexpr int kQueueStride = 64;           // counters in lines of their own: in one line each of them waits for all others
 constexpr int kBlocksPerCu = 5;            // by registers

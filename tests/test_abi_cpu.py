@@ -265,10 +265,12 @@ def test_transposed_product_has_room_for_a_chunk_of_every_shape(M, N, K):
 
 
 @pytest.mark.parametrize("trans_a,trans_b", [(1, 0), (0, 0), (0, 1)])
-@pytest.mark.parametrize("M,N", [(100, 256), (512, 512), (512, 16), (300, 300), (128, 512), (47, 256), (2100, 2050), (1, 1), (7, 600)])
+@pytest.mark.parametrize("M,N", [(100, 256), (512, 512), (512, 16), (300, 300), (128, 512), (47, 256), (2100, 2050), (1, 1),
+                                 (7, 600)])
 def test_a_workspace_for_the_most_rows_serves_fewer(M, N, trans_a, trans_b):
     """The sizes that K = 33 to 5 million (transposed A: the rows of a mini-batch) ask for never fall."""
-    rows = sorted({int(33 * 1.05 ** i) for i in range(245)} | {1, 2, 31, 32, 96, 97, 1614731, 2018413, 14895, 18618, 4882, 6102})
+    edges = {1, 2, 31, 32, 96, 97, 1614731, 2018413, 14895, 18618, 4882, 6102}
+    rows = sorted({int(33 * 1.05 ** i) for i in range(245)} | edges)
     sizes = [B.gnn_gemm_workspace_bytes(trans_a, trans_b, M, N, K) for K in rows]
     if not trans_a:                                        # the rows are M there
         sizes = [B.gnn_gemm_workspace_bytes(0, trans_b, K, N, M) for K in rows]
