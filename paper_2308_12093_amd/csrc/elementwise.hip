@@ -31,7 +31,9 @@ activation_grad_kernel(long count4, long count, const float *__restrict__ G, con
 // row of f sums.  Four rows are in flight per thread (rotating accumulators, added in a
 // fixed order).  VEC = 4 needs f and head_dim to be multiples of 4 and 16-byte aligned rows.
 // DUAL: two sums of the same G in one pass, columns [0, fo / 2) with wgt and the others with wgt2 (2^17 x 256: 80 -> 53 us
-// against a second read of every row for the second sum); fo = 2f then.
+// against a second read of every row for the second sum); fo = 2f then.  What is asked of every row must be known to the
+// compiler: a branch on wgt between the loads of one row and those of the next kept them from being under way together (38 us
+// without it, 3.6 TB/s; 2^17 x 64 17.3 -> 12.2).
 // masked: the masked gradient is written as well, where others read it later: one pass over G and Y instead of two
 // over G (2^17 x 512: 131 + 66 -> 178 us).
 template <int VEC, bool DUAL>
@@ -56,14 +58,14 @@ colsum_partial_kernel(long n, int f, int fo, int fp, long rows_per_block, const 
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) a[d][j][v] = 0.0;
         if (c < f) {
-            const int hd = wgt ? c / head_dim : 0;
+            const int hd = DUAL || wgt ? c / head_dim : 0;
             auto row = [&](long i, int j) __attribute__((always_inline)) {
                 // with mask_y: G times the derivative of the fused activation, taken from its output
                 auto dact = [mask_act](float g, float y) { return y > 0.f ? g : (mask_act == kActElu ? g * (y + 1.f) : 0.f); };
                 float g[VEC];
                 if constexpr (VEC == 4) {
                     float4 q = *reinterpret_cast<const float4 *>(G + (size_t)i * f + c);
-                    if (mask_y) {
+                    if (!DUAL && mask_y) {
                         const float4 y = *reinterpret_cast<const float4 *>(mask_y + (size_t)i * f + c);
                         q = make_float4(dact(q.x, y.x), dact(q.y, y.y), dact(q.z, y.z), dact(q.w, y.w));
                         if (masked) *reinterpret_cast<float4 *>(masked + (size_t)i * f + c) = q;
@@ -71,12 +73,12 @@ colsum_partial_kernel(long n, int f, int fo, int fp, long rows_per_block, const 
                     g[0] = q.x; g[1] = q.y; g[2] = q.z; g[3] = q.w;
                 } else {
                     g[0] = G[(size_t)i * f + c];
-                    if (mask_y) {
+                    if (!DUAL && mask_y) {
                         g[0] = dact(g[0], mask_y[(size_t)i * f + c]);
                         if (masked) masked[(size_t)i * f + c] = g[0];
                     }
                 }
-                const double w = wgt ? (double)wgt[(size_t)i * heads + hd] : 1.0;
+                const double w = DUAL || wgt ? (double)wgt[(size_t)i * heads + hd] : 1.0;
                 const double w2 = DUAL ? (double)wgt2[(size_t)i * heads + hd] : 0.0;
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) {
