@@ -40,12 +40,16 @@ bool sums_decide_signs(const gnn_plan_desc_t &d) { return d.fuse_relu && d.need_
 // of the fp32 instruction, so that fewer pre-activations fall on the wrong side of zero.  fp32 instruction / split parts, a
 // forward pass in us, relative error of Y, wrong signs in three runs:
 //   2^17 nodes, 128 -> 512 240 / 195, 1.5e-7 / 5.9e-8, 4 / 2; 512 -> 128 289 / 254, 3.0e-7 / 1.1e-7, 3 / 2;
-//   2^19, 100 -> 256 508 / 419, 1.4e-7 / 5.9e-8, 15 / 5; 65536, 128 -> 512 121 / 95, 1.5e-7 / 5.9e-8, 4 / 1.
-// A wrong sign puts one term too many or too few into the sums of dW and db, 1e-4 of them at these sizes (else 2.5e-8).  The
-// same holds below 2^16 nodes (50021, 100 -> 256 76 / 54, 1.3e-7 / 5.7e-8): the line is where layers have been moved so far,
-// not one of accuracy.
+//   2^19, 100 -> 256 508 / 419, 1.4e-7 / 5.9e-8, 15 / 5; 65536, 128 -> 512 121 / 95, 1.5e-7 / 5.9e-8, 4 / 1;
+//   50021, 100 -> 256 76 / 54, 1.3e-7 / 5.7e-8.
+// A wrong sign puts one term too many or too few into the sums of dW and db, 1e-4 of them at these sizes (else 2.5e-8).
+// With dX a sign that falls differently shows in full, so only outputs of so few elements that it hardly ever does (one in
+// 10^7 changes sides) go the other way, four wavefronts to a tile: 3001 nodes, 203 -> 7, forward, 23.7 / 19.3 us, 1.1e-7 /
+// 6.9e-8.
+constexpr int64_t kFewSigns = 1 << 17;
 int relu_flags(const gnn_plan_desc_t &d, int with_relu) {
-    return !d.fuse_relu ? 0 : sums_decide_signs(d) || d.n < 1 << 16 ? with_relu : with_relu | kActAnySign;
+    if (!d.fuse_relu) return 0;
+    return sums_decide_signs(d) && (int64_t)d.n * d.f_out > kFewSigns ? with_relu : with_relu | kActAnySign;
 }
 
 bool overlap(const float *a, size_t count_a, const float *b, size_t count_b) {
