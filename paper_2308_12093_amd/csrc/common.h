@@ -81,7 +81,8 @@ size_t spmm_workspace_bytes(int64_t n, int64_t nnz, int f);
 size_t spmm_segments_bytes(int64_t n, int64_t nnz, int f);
 // b_rows: rows of B (n when the column indices are node numbers), or 0 = unknown: then a width that is
 // not a multiple of 4 is not run on a padded copy of B.  workspace: spmm_segments_bytes(b_rows, nnz, f).
-// pieces: long rows of a large product may be summed in another order (spmm_hub.hip); workspace: spmm_workspace_bytes
+// pieces: the rows of small and of large products may be summed in other orders (a wavefront per row; spmm_hub.hip);
+// workspace: spmm_workspace_bytes
 gnn_status_t spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_t *col, const int32_t *erow,
                          EdgeWeights w, const float *B, long b_rows, int f, float *C, const float *bias, int relu,
                          void *workspace, hipStream_t st, bool pieces = false);

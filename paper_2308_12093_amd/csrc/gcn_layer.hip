@@ -33,8 +33,11 @@ gnn_status_t spmm(const gnn_graph_t &g, const SparseView &v, const float *B, int
 
 // Layers whose sums before a ReLU keep the order they have had: those with dX, where a pre-activation that falls on the other
 // side of zero changes a row of dX by its full size.  That is a choice, not a bound: the other sums are the more exact ones
-// (see relu_flags).
-bool sums_decide_signs(const gnn_plan_desc_t &d) { return d.fuse_relu && d.need_input_grad; }
+// (see relu_flags).  Outputs of few elements take the other sums as well: one pre-activation in 10^7 changes sides.
+constexpr int64_t kFewSigns = 1 << 17;
+bool sums_decide_signs(const gnn_plan_desc_t &d) {
+    return d.fuse_relu && d.need_input_grad && (int64_t)d.n * d.f_out > kFewSigns;
+}
 
 // Flags of the product before a fused ReLU.  Without dX it may run on split parts, whose sums lie closer to 64 bits than those
 // of the fp32 instruction, so that fewer pre-activations fall on the wrong side of zero.  fp32 instruction / split parts, a
@@ -43,13 +46,9 @@ bool sums_decide_signs(const gnn_plan_desc_t &d) { return d.fuse_relu && d.need_
 //   2^19, 100 -> 256 508 / 419, 1.4e-7 / 5.9e-8, 15 / 5; 65536, 128 -> 512 121 / 95, 1.5e-7 / 5.9e-8, 4 / 1;
 //   50021, 100 -> 256 76 / 54, 1.3e-7 / 5.7e-8.
 // A wrong sign puts one term too many or too few into the sums of dW and db, 1e-4 of them at these sizes (else 2.5e-8).
-// With dX a sign that falls differently shows in full, so only outputs of so few elements that it hardly ever does (one in
-// 10^7 changes sides) go the other way, four wavefronts to a tile: 3001 nodes, 203 -> 7, forward, 23.7 / 19.3 us, 1.1e-7 /
-// 6.9e-8.
-constexpr int64_t kFewSigns = 1 << 17;
+// Few outputs, four wavefronts to a tile: 3001 nodes, 203 -> 7, forward, 23.7 / 19.2 us, 1.4e-7 / 8.6e-8.
 int relu_flags(const gnn_plan_desc_t &d, int with_relu) {
-    if (!d.fuse_relu) return 0;
-    return sums_decide_signs(d) && (int64_t)d.n * d.f_out > kFewSigns ? with_relu : with_relu | kActAnySign;
+    return !d.fuse_relu ? 0 : sums_decide_signs(d) ? with_relu : with_relu | kActAnySign;
 }
 
 bool overlap(const float *a, size_t count_a, const float *b, size_t count_b) {

@@ -27,7 +27,7 @@
 //
 // Large products with many long rows go to spmm_hub.hip instead.
 //
-// Row kernel (no `erow`): one wavefront per row; same results, no balancing.
+// Row kernel (small products, and those without `erow`): a wavefront per row, or several.
 #include "spmm_hub.h"
 
 namespace gnn {
@@ -375,23 +375,87 @@ spmm_fixup_kernel(int n, int nnz, int f, int span, long nspan, int lpf, const in
     }
 }
 
-// One wavefront per row, lanes stride over the features.
-__global__ void __launch_bounds__(256)
-spmm_row_kernel(int n, int f, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col, EdgeWeights w,
+// Eight rows a block, one wavefront each: 64 / LPE slots of LPE lanes (VEC features a lane, blockIdx.y picks which of them a
+// block has) take the entries of the row in turn, U at a time, and are added by a fixed shuffle tree.  A row of more than
+// kRowShare entries a slot is shared by the wavefronts of the block.  Everything follows from the row pointers, in one launch:
+// what bounds a small product is the chain of pointers, indices and rows of B, and the launches (2048 nodes, 18 432 entries,
+// f = 16, call by call: 11.0 us and 12.3 with hubs in segments, 8.8 and 8.3 here, where the calls bound it).  Shared by four
+// wavefronts or sixteen, and from 8 or 32 entries on, hubs take longer: 16384 nodes, 409 600 entries, f = 16, 4 / 8 / 16
+// wavefronts 16.6 / 14.1 / 24.2 us.
+constexpr int kRowWaves = 8, kRowShare = 16;
+
+template <int VEC, int LPE, int U>
+__global__ void __launch_bounds__(64 * kRowWaves)
+spmm_row_kernel(int n, int f, int ldb, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col, EdgeWeights w,
                 const float *__restrict__ B, float *__restrict__ C, const float *__restrict__ bias, int relu) {
-    const int row = blockIdx.x * 4 + threadIdx.x / kWave;
-    const int lane = threadIdx.x % kWave;
-    if (row >= n) return;
-    const int s = rowptr[row], e = rowptr[row + 1];
-    for (int c = lane; c < f; c += kWave) {
-        const int hd = w.heads > 1 ? c / w.head_dim : 0;
-        float acc = 0.f;
-        for (int x = s; x < e; ++x) {
-            const int slot = w.perm ? w.perm[x] : x;
-            const float v = w.val ? w.val[(size_t)slot * w.heads + hd] : 1.f;
-            acc = fmaf(v, B[(size_t)col[x] * f + c], acc);
+    constexpr int SLOTS = kWave / LPE, WAVES = kRowWaves;
+    __shared__ float s_part[WAVES][LPE * VEC];
+    __shared__ int32_t s_ptr[WAVES + 1];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, l = lane % LPE, slot = lane / LPE;
+    const int row0 = blockIdx.x * WAVES, c = (blockIdx.y * LPE + l) * VEC;
+    if (threadIdx.x <= WAVES) s_ptr[threadIdx.x] = rowptr[min(row0 + (int)threadIdx.x, n)];
+    __syncthreads();
+    const bool ok = c < f;
+    const int hd = w.heads > 1 && ok ? c / w.head_dim : 0;
+    float acc[VEC];
+    auto gather = [&](int first, int end, int step) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = slot == 0 || first < end ? 0.f : -0.f;   // x + -0 is x, also for -0
+        uint32_t x = first;
+        for (int left = end - first; left > 0; left -= U * step, x += U * step) {
+            int cj[U];
+            float v[U], b[U][VEC];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t e = u * step < left ? x + u * step : x;   // past the end: the first again, not added
+                cj[u] = col[e];
+                v[u] = w.val ? w.val[(size_t)(w.perm ? w.perm[e] : e) * w.heads + hd] : 1.f;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float *src = B + (size_t)cj[u] * ldb + (ok ? c : 0);
+                if constexpr (VEC == 4) {
+                    const float4 q = *reinterpret_cast<const float4 *>(src);
+                    b[u][0] = q.x; b[u][1] = q.y; b[u][2] = q.z; b[u][3] = q.w;
+                } else b[u][0] = *src;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u * step < left)
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) acc[i] = fmaf(v[u], b[u][i], acc[i]);
         }
-        C[(size_t)row * f + c] = epilogue(acc, bias, c, relu);
+#pragma unroll
+        for (int d = LPE; d < kWave; d <<= 1)
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], d, kWave);
+    };
+    auto store = [&](int row) __attribute__((always_inline)) {
+        if (slot != 0) return;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i)
+            if (c + i < f) C[(size_t)row * f + c + i] = epilogue(acc[i], bias, c + i, relu);
+    };
+    if (row0 + wave < n && s_ptr[wave + 1] - s_ptr[wave] <= kRowShare * SLOTS) {
+        gather(s_ptr[wave] + slot, s_ptr[wave + 1], SLOTS);
+        store(row0 + wave);
+    }
+    for (int r = 0; r < WAVES; ++r) {
+        if (row0 + r >= n || s_ptr[r + 1] - s_ptr[r] <= kRowShare * SLOTS) continue;      // the same for the whole block
+        gather(s_ptr[r] + wave * SLOTS + slot, s_ptr[r + 1], WAVES * SLOTS);
+        if (slot == 0)
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) s_part[wave][l * VEC + i] = acc[i];
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                acc[i] = s_part[0][l * VEC + i];
+                for (int k = 1; k < WAVES; ++k) acc[i] += s_part[k][l * VEC + i];
+            }
+            store(row0 + r);
+        }
+        __syncthreads();
     }
 }
 
@@ -494,6 +558,15 @@ float *spmm_padded_operand(void *workspace, const int32_t *erow, int64_t b_rows,
     return reinterpret_cast<float *>(static_cast<char *>(workspace) + partials_bytes(nnz, f));
 }
 
+// Products that a wavefront per row is faster at: few rows, and so few entries that hubs among them stay short.  Segments /
+// rows, us, call by call (8.3 to 8.8: the calls themselves), uniform; R-MAT: 3001 nodes, 30 009 entries, f = 7 16.1 / 8.8;
+// 19.3 / 8.4, 64 11.6 / 8.9; 11.2 / 8.4, 128 11.4 / 8.8; 11.1 / 11.6; 4096, 208 896, 32 11.2 / 8.9; 13.0 / 12.1, 64 11.3 /
+// 10.8; 11.8 / 18.6; 8192, 73 728, 32 11.4 / 8.9; 14.1 / 9.7, 64 11.4 / 8.8; 12.1 / 14.5; 16384, 409 600, 16 11.3 / 9.0; 18.4 /
+// 14.1, 32 11.5 / 9.8; 14.6 / 18.5; 32768, 360 448, 16 11.6 / 15.0; 19.0 / 19.4.
+static bool rows_pay(int64_t n, int64_t nnz, int f) {
+    return n <= 16384 && f <= 128 && nnz * (f < 16 ? 16 : f) <= (f <= 32 ? 6600000 : 2500000);
+}
+
 #define SPMM_CASE(VEC_, LPE_, NT_, U_)                                                                       \
     if (sh.vec == VEC_ && sh.lpe == LPE_ && sh.nt == NT_) {                                                  \
         constexpr int GPB_ = 256 / LPE_;                                                                     \
@@ -528,9 +601,19 @@ gnn_status_t spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_t *c
     if (w.heads == 1) w.head_dim = f;
     const bool heads = w.heads > 1 && w.val != nullptr;
 
-    if (!erow || nnz == 0) {
-        hipLaunchKernelGGL(spmm_row_kernel, dim3((unsigned)ceil_div(n, 4)), dim3(256), 0, st, n, f, rowptr, col, w,
-                           B, C, bias, relu);
+    if (!erow || nnz == 0 || (pieces && !heads && rows_pay(n, nnz, f))) {
+        int ldb = f;                                       // unless the caller has written the padded operand
+        if (!pieces || heads || B != spmm_padded_operand(workspace, erow, b_rows, nnz, f, &ldb)) ldb = f;
+        const bool vec4 = ldb % 4 == 0 && aligned16(B) && (!heads || w.head_dim % 4 == 0);
+        const int lanes = pow2_at_least(vec4 ? (f + 3) / 4 : f), lpe = lanes < kWave ? lanes : kWave;
+        const dim3 grid((unsigned)ceil_div(n, kRowWaves), (unsigned)ceil_div(f, lpe * (vec4 ? 4 : 1)));
+#define ROW_CASE(VEC_, LPE_)                                                                                 \
+        if (vec4 == (VEC_ == 4) && lpe == LPE_)                                                              \
+            hipLaunchKernelGGL((spmm_row_kernel<VEC_, LPE_, LPE_ < 16 ? 4 : 8>), grid, dim3(64 * kRowWaves), \
+                               0, st, n, f, ldb, rowptr, col, w, B, C, bias, relu);
+        ROW_CASE(4, 1) ROW_CASE(4, 2) ROW_CASE(4, 4) ROW_CASE(4, 8) ROW_CASE(4, 16) ROW_CASE(4, 32) ROW_CASE(4, 64)
+        ROW_CASE(1, 1) ROW_CASE(1, 2) ROW_CASE(1, 4) ROW_CASE(1, 8) ROW_CASE(1, 16) ROW_CASE(1, 32) ROW_CASE(1, 64)
+#undef ROW_CASE
         return launch_status();
     }
 

@@ -49,5 +49,6 @@ extern "C" gnn_status_t gnn_spmm_csr_static(int32_t n, int32_t nnz, const int32_
         GNN_TRY(scratch_of_current_device(&ws));
     }
     return gnn::spmm_launch(n, nnz, rowptr, col, erow, gnn::EdgeWeights{val, nullptr, 1, f}, B, n, f, C, bias, relu,
-                            ws, static_cast<hipStream_t>(hip_stream));
+                            ws, static_cast<hipStream_t>(hip_stream),
+                            gnn::spmm_segments_bytes(n, nnz, f) == gnn::spmm_workspace_bytes(n, nnz, f));
 }
