@@ -145,6 +145,8 @@ __device__ __forceinline__ void put(const Product &g, float *at, float o, float 
     else *at = o;
 }
 
+__host__ __device__ constexpr int kept_waves(int nt) { return nt == 1 ? 16 : 12; }   // wavefronts of a CU, by registers
+
 // ---- the product ------------------------------------------------------------------------------------------
 // A block of four wavefronts owns 4 x 32 rows and 32 NT columns.  A lane reads its 16 consecutive floats of a row
 // straight into registers (the two lane halves take a row's whole 128-byte line, in one go, one step ahead) and splits
@@ -158,22 +160,40 @@ __device__ __forceinline__ void put(const Product &g, float *at, float o, float 
 // 1162 (4.6 TB/s: what a copy reaches).  Matrix cores busy 27 % (512 -> 128, 128 -> 128) and 34 % (128 -> 512): matrix
 // instructions, stores and loads add up more than they overlap; without the stores 128 -> 512 took 115 of then 167 us,
 // with a sixth of the matrix instructions 117.
+// The columns of a row are stored one after the other: a row's lines reach memory together (column tile by column tile
+// 128 -> 128 over 2^17 rows 40.8 -> 38.9 us, 512 -> 128 140.5 -> 137.7, 64 -> 256 over 2^22 1397 -> 1342).
+// KEPT: KEPT wavefronts a block keep the parts of their columns in LDS, split by themselves, and go through the rows in
+// tiles of 32 each without a barrier, so that one stores while another multiplies, and without the launch before.
+// kept_waves_per_block says where.
 // BITS: A is used where its bit is set; a lane's 16 floats have one word, from the block's copy in LDS (held in registers a
 // step ahead it spills).
-template <int NT, bool BITS>
-__global__ void __launch_bounds__(256, (NT == 4 ? 3 : 4) - (BITS && NT > 1))
+template <int NT, bool BITS, int KEPT>
+__global__ void __launch_bounds__(KEPT ? 64 * KEPT : 256, (NT == 4 || (KEPT && NT == 2) ? 3 : 4) - (BITS && NT > 1))
 gemm_split_kernel(Product g) {
     extern __shared__ __align__(16) char lds[];
     constexpr int STAGE = NT * kStepBytes;
-    const long tile = xcd_tile((long)g.tiles_m * g.tiles_n);
-    if (tile >= (long)g.tiles_m * g.tiles_n) return;
-    const int t = threadIdx.x, lane = t % 64, wave = __builtin_amdgcn_readfirstlane(t / 64);
-    const int l = lane % 32, half = lane / 32;
-    const int row0 = (int)(tile / g.tiles_n) * 128 + wave * 32;
-    const int ct0 = (int)(tile % g.tiles_n) * NT;           // first 32-column tile
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t / 64);
+    int lane = t % 64, l = lane % 32, half = lane / 32;
     const int total = g.A2 ? 2 * g.steps : g.steps;
-
-    const size_t ro = (size_t)min(row0 + l, g.M - 1) * g.K;   // rows past the end re-read the last one
+    int rt, rt_end, rt_by, ct0;                             // the wavefront's tiles of 32 rows; first 32-column tile
+    if constexpr (KEPT) {                                   // XCD x: the x-th eighth of the rows, all columns of them
+        const int tiles = (g.M + 31) / 32, per = (tiles + 7) / 8, x = blockIdx.x % 8, i = blockIdx.x / 8;
+        ct0 = i % g.tiles_n * NT;
+        rt = x * per + i / g.tiles_n * KEPT + wave;
+        rt_end = min(tiles, (x + 1) * per);
+        rt_by = (int)gridDim.x / 8 / g.tiles_n * KEPT;
+    } else {
+        const long tile = xcd_tile((long)g.tiles_m * g.tiles_n);
+        if (tile >= (long)g.tiles_m * g.tiles_n) return;
+        ct0 = (int)(tile % g.tiles_n) * NT;
+        rt = (int)(tile / g.tiles_n) * 4 + wave;
+        rt_end = rt + 1;
+        rt_by = 1;
+    }
+    int row0 = rt * 32;
+    // rows past the end re-read the last one
+    auto row_offset = [&](int r) __attribute__((always_inline)) { return (size_t)min(r * 32 + l, g.M - 1) * g.K; };
+    size_t ro = row_offset(rt);
 
     // Four indices at a time, at any 4-byte aligned address; the ones that would run over the row's end are read from
     // its last four floats instead (K >= 4) and put in place by `settle`, so no load stands behind a branch.
@@ -216,7 +236,7 @@ gemm_split_kernel(Product g) {
     // Rows that begin with tiny values (a saturated node's gradient) are taken times a power of two and their results
     // back, in a wavefront that has one.  Formed again, one such row in 32 costs four times the product: 128 -> 512 over
     // 2^17 rows 606 us, 512 -> 128 717, with the power of two 152 and 136 (without such rows 152 and 133).
-    __shared__ float s_scale[128];                           // of the block's rows; a wavefront reads its own alone
+    __shared__ float s_scale[KEPT ? 32 * KEPT : 128];        // of the block's rows; a wavefront reads its own alone
     float *scale = s_scale + wave * 32;
     bool scaled = false;                                     // uniform
     auto fit = [&]() __attribute__((always_inline)) {       // from the first step, once it is settled
@@ -260,16 +280,69 @@ gemm_split_kernel(Product g) {
     clear();
     unsigned least = ~0u;                                   // of this lane's half of the row
 
-    stage(0, 0);
-    load(0);
-    for (int step = 0; step < total; ++step) {
-        // this wavefront's copies of the step have arrived; after the barrier everyone's have, and the other buffer,
-        // read in the step before, is free
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __shared__ unsigned s_least[NT], s_top[NT];              // KEPT: of the column tiles
+    if constexpr (KEPT) {
+        load(0);
+        if (t < NT) { s_least[t] = ~0u; s_top[t] = 0; }
         __syncthreads();
+        for (int f = wave; f < 2 * NT * total; f += KEPT) {  // a fragment at a time, as in split_weights_kernel
+            const int c = f / (2 * total), step = f / 2 % total, ins = f % 2;
+            const bool second = step >= g.steps;
+            const Operand b = second ? g.B2 : g.B;
+            const int k0 = (second ? step - g.steps : step) * KB + 16 * half + 8 * ins, n = (ct0 + c) * 32 + l;
+            floatx4 x[2];
+            unsigned low = ~0u, top = 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                x[j / 4][j % 4] = n < g.N && k0 + j < g.K ? b.p[(k0 + j) * b.sk + n * b.sn] : 0.f;
+                top = max(top, __float_as_uint(x[j / 4][j % 4]) & 0x7fffffffu);
+            }
+            bf16x8 part[3];
+            split8(x[0], x[1], part, low);
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                *reinterpret_cast<bf16x8 *>(lds + (size_t)(c * total + step) * kStepBytes + (ins * 3 + p) * kFragBytes + lane * 16) = part[p];
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) {
+                low = min(low, (unsigned)__shfl_xor((int)low, d, 64));
+                top = max(top, (unsigned)__shfl_xor((int)top, d, 64));
+            }
+            if (lane == 0) { atomicMin(&s_least[c], low); atomicMax(&s_top[c], top); }
+        }
+        __syncthreads();
+    } else {
+        stage(0, 0);
+        load(0);
+    }
+    auto range = [&](int c) __attribute__((always_inline)) {
+        Range b;
+        if constexpr (KEPT) {
+            b.least = s_least[c];
+            b.top = __uint_as_float(s_top[c]);
+        } else {
+            b = g.range[ct0 + c];
+            if (g.A2) {
+                const Range b2 = g.range2[ct0 + c];
+                b.least = min(b.least, b2.least);
+                b.top = fmaxf(b.top, b2.top);
+            }
+        }
+        return b;
+    };
+  if (KEPT && rt >= rt_end) return;
+  do {
+    row0 = rt * 32;
+    // addresses are formed for each tile again: kept for all of them they spill
+    if constexpr (KEPT) asm volatile("" : "+v"(half), "+v"(l), "+v"(lane));
+    for (int step = 0; step < total; ++step) {
         const int buf = step & 1;
-        const bool more = step + 1 < total;
-        if (more) stage(step + 1, buf ^ 1);
+        if constexpr (!KEPT) {
+            // this wavefront's copies of the step have arrived; after the barrier everyone's have, and the other buffer,
+            // read in the step before, is free
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (step + 1 < total) stage(step + 1, buf ^ 1);
+        }
         bf16x8 a[2][3];
         settle(step);
         if (step == 0) fit();
@@ -282,7 +355,9 @@ gemm_split_kernel(Product g) {
             bf16x8 b[2][3];
 #pragma unroll
             for (int i = 0; i < 6; ++i)
-                b[i / 3][i % 3] = *reinterpret_cast<const bf16x8 *>(lds + buf * STAGE + c * kStepBytes + i * kFragBytes + lane * 16);
+                b[i / 3][i % 3] = *reinterpret_cast<const bf16x8 *>(
+                    lds + (KEPT ? (size_t)(c * total + step) * kStepBytes : (size_t)buf * STAGE + c * kStepBytes) + i * kFragBytes +
+                    lane * 16);
             floatx16 small;
 #pragma unroll
             for (int v = 0; v < 16; ++v) small[v] = 0.f;
@@ -306,10 +381,7 @@ gemm_split_kernel(Product g) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) finite = fmaf(acc[c][v], 0.f, finite);
 #pragma unroll
-    for (int c = 0; c < NT; ++c) {
-        least_b = min(least_b, g.range[ct0 + c].least);
-        if (g.A2) least_b = min(least_b, g.range2[ct0 + c].least);
-    }
+    for (int c = 0; c < NT; ++c) least_b = min(least_b, range(c).least);
     bool bad = finite != 0.f;                                // 0 x (inf or NaN) is NaN
     if (!__any(bad) && __any(min(least, least_b) < kTinyCode)) {
         // Some operand lost up to 2^-134: a result is off by at most K 2^-134 times the largest magnitude it met (the
@@ -334,11 +406,7 @@ gemm_split_kernel(Product g) {
         for (int d = 32; d >= 1; d >>= 1) top = fmaxf(top, __shfl_xor(top, d, 64));
 #pragma unroll
         for (int c = 0; c < NT; ++c) {
-            Range b = g.range[ct0 + c];
-            if (g.A2) {
-                const Range b2 = g.range2[ct0 + c];
-                b = Range{min(b.least, b2.least), fmaxf(b.top, b2.top)};
-            }
+            const Range b = range(c);
             const float of_b = lost * b.top, of_a = b.least < kTinyCode ? lost * top : 0.f;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -368,6 +436,10 @@ gemm_split_kernel(Product g) {
         }
     }
 
+    if constexpr (KEPT) {                                   // the next tile's first step, ahead of this one's stores
+        ro = row_offset(rt + rt_by);
+        load(0);
+    }
     // accumulator register v of lane (half, l): row 8 (v / 4) + 4 half + v % 4, column l of its 32 x 32 tile
     if (scaled) {
 #pragma unroll
@@ -377,6 +449,17 @@ gemm_split_kernel(Product g) {
             for (int c = 0; c < NT; ++c) acc[c][v] *= back;
         }
     }
+    if (row0 + 32 <= g.M && (ct0 + NT) * 32 <= g.N && !(g.act & kActAccumulate)) {
+        // whole tiles, the columns of a row one after the other
+        float bias[NT];
+#pragma unroll
+        for (int c = 0; c < NT; ++c) bias[c] = g.bias ? g.bias[(ct0 + c) * 32 + l] : 0.f;
+        float *at = g.C + (size_t)(row0 + 4 * half) * g.ldc + ct0 * 32 + l;
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+            for (int c = 0; c < NT; ++c) put(g, at + (size_t)(8 * (v / 4) + v % 4) * g.ldc + 32 * c, acc[c][v], bias[c]);
+    } else
 #pragma unroll
     for (int c = 0; c < NT; ++c) {
         const int n = (ct0 + c) * 32 + l;
@@ -408,6 +491,11 @@ gemm_split_kernel(Product g) {
             }
         }
     }
+    if constexpr (KEPT) {
+        clear();
+        least = ~0u;
+    }
+  } while (KEPT && (rt += rt_by) < rt_end);
 }
 
 // 32-column tiles per block: as wide as the output allows (a row of A is split once per tile)
@@ -416,6 +504,24 @@ int tiles_wide(int64_t N) { return N <= 32 ? 1 : N <= 64 ? 2 : 4; }
 size_t parts_bytes(int64_t N, int64_t K) {
     const int64_t w = tiles_wide(N);
     return align_up((size_t)(ceil_div(N, 32 * w) * w) * ceil_div(K, KB) * kStepBytes);
+}
+
+// Wavefronts of a block that keeps the parts of its columns, or 0 where blocks pass them through LDS step by step.  Those
+// start their tiles as slots come free, which counts while there are few rows: 2^17 rows, B transposed, 128 -> 128 39 us
+// against 49 with the parts kept, 256 -> 64 36 / 44 (B as it is); 262144 68 / 71, 79 / 78; from 2^19 rows on keeping them is the
+// faster: 146.4 / 146.5, 157 / 153; 2^20 284 / 270, 303 / 284, 16 -> 128 139 / 130, 100 -> 256 527 / 493, 47 -> 256 303 / 285,
+// 40 -> 512 623 / 587; 2^22 64 -> 256 1342 / 1289, 256 -> 64 1166 / 1095; up to 32 columns the same (100 -> 16 135 / 135; 524288
+// 53 / 56).  One or two steps of few columns cost a block nothing to split: 60000 rows 16 -> 128 14.2 / 12.6, 64 -> 64 12.7 / 11.0,
+// 30 -> 30 9.9 / 7.3; 2^17 21.5 / 18.7, 16.9 / 16.7, 10.6 / 10.1.
+int kept_waves_per_block(int64_t M, int64_t N, int w, int steps) {
+    if (!(w * steps <= 4 && steps <= 2) && (w == 1 || M < 1 << 19)) return 0;
+    const size_t room = 160 * 1024, own = 4096;            // a block's scales and ranges: at most 2 KB
+    const int64_t tiles_n = ceil_div(N, 32 * w);
+    for (int kept = 4; kept <= kept_waves(w); kept = w > 1 && kept == 4 ? 6 : 2 * kept) {
+        const int on_cu = kept_waves(w) / kept;
+        if (((size_t)w * steps * kStepBytes + own) * on_cu <= room && tiles_n <= 32 * on_cu) return kept;
+    }
+    return 0;
 }
 
 int64_t split_blocks(int64_t M, int64_t N) { return 8 * ceil_div(ceil_div(M, 128) * ceil_div(N, 32 * tiles_wide(N)), 8); }
@@ -450,14 +556,30 @@ gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const fl
     g.parts = ws; g.parts2 = ws2;
     Range *range = reinterpret_cast<Range *>(ws + words), *range2 = reinterpret_cast<Range *>(ws2 + words);
     g.range = range; g.range2 = range2;
+    const int steps = A2 ? 2 * g.steps : g.steps, kept = a_bits ? 0 : kept_waves_per_block(M, N, w, steps);
+    if (kept) {
+        const int64_t per_xcd = ceil_div(ceil_div(M, 32), 8);
+        int64_t groups = 32 * (kept_waves(w) / kept) / g.tiles_n;      // blocks of an XCD that share a column tile
+        if (groups > ceil_div(per_xcd, kept)) groups = ceil_div(per_xcd, kept);
+        const dim3 grid((unsigned)(8 * groups * g.tiles_n));
+        const size_t lds = (size_t)w * steps * kStepBytes;
+#define KEPT_CASE(NT_, KEPT_)                                                                              \
+        if (w == NT_ && kept == KEPT_)                                                                     \
+            hipLaunchKernelGGL((gemm_split_kernel<NT_, false, KEPT_>), grid, dim3(64 * KEPT_), lds, st, g);
+        KEPT_CASE(1, 4)
+        KEPT_CASE(2, 4) KEPT_CASE(2, 6) KEPT_CASE(2, 12)
+        KEPT_CASE(4, 4) KEPT_CASE(4, 6) KEPT_CASE(4, 12)
+#undef KEPT_CASE
+        return launch_status();
+    }
     hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)(g.tiles_n * w), A2 ? 2 : 1), dim3(1024), 0, st, (int)N,
                        (int)K, g.steps, g.B, g.B2, ws, ws2, range, range2);
     GNN_TRY(launch_status());
     const dim3 grid((unsigned)split_blocks(M, N));
     const size_t lds = (size_t)2 * w * kStepBytes + (a_bits ? (size_t)128 * g.bit_stride * sizeof(uint16_t) : 0);
-    auto kernel = w == 1   ? (a_bits ? gemm_split_kernel<1, true> : gemm_split_kernel<1, false>)
-                  : w == 2 ? (a_bits ? gemm_split_kernel<2, true> : gemm_split_kernel<2, false>)
-                           : (a_bits ? gemm_split_kernel<4, true> : gemm_split_kernel<4, false>);
+    auto kernel = w == 1   ? (a_bits ? gemm_split_kernel<1, true, 0> : gemm_split_kernel<1, false, 0>)
+                  : w == 2 ? (a_bits ? gemm_split_kernel<2, true, 0> : gemm_split_kernel<2, false, 0>)
+                           : (a_bits ? gemm_split_kernel<4, true, 0> : gemm_split_kernel<4, false, 0>);
     hipLaunchKernelGGL(kernel, grid, dim3(256), lds, st, g);
     return launch_status();
 }
