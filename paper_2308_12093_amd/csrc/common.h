@@ -212,13 +212,14 @@ gnn_status_t gat_fused_forward_launch(int n, int nnz, int h, int k, const int32_
                                       float slope, const float *bias, int act, float *Y, float *stat, void *workspace,
                                       hipStream_t st);
 // alpha / mask [q][h] in CSR order, or NULL: rebuilt from s, d.
-// node: 4 n h floats of scratch.  Writes ds, dd [n][h] and the complete dM [n][h k].
+// node: 4 n h floats of scratch; edge: q h floats, used with alpha.  Writes ds, dd [n][h] and the complete dM [n][h k].
 gnn_status_t gat_fused_backward_launch(int n, int nnz, int h, int k, const int32_t *rowptr, const int32_t *erow,
                                        const int32_t *col, const int32_t *colptr, const int32_t *ecol,
                                        const int32_t *row, const int32_t *perm, const float *G, const float *M,
                                        const float *alpha, const uint8_t *mask, const float *s,
                                        const float *d, float slope, const float *a_src, const float *a_dst,
-                                       float *node, float *ds, float *dd, float *dM, void *workspace, hipStream_t st);
+                                       float *node, float *edge, float *ds, float *dd, float *dM, void *workspace,
+                                       hipStream_t st);
 // da_src[p][c] = sum_i ds[i][p] M[i][p][c] and da_dst likewise with dd, in one pass over M;
 // workspace 2 * colsum_workspace_bytes(n, h*k)
 gnn_status_t gat_attention_grad2_launch(int n, int h, int k, const float *ds, const float *dd, const float *M,

@@ -21,9 +21,10 @@
 //                       dd_j = sum g_y and dM_j = sum alpha_e G_i; the rank-one terms ds_j a_src +
 //                       dd_j a_dst are added when the row is written.
 //
-// alpha and the LeakyReLU sign come from the cache when the variant keeps them (read in entry order by the
-// row pass, through perm by the column pass; having the row pass leave them as one signed value per entry
-// and head, to halve the column pass's gathers, cost more in scattered writes than it saved).
+// alpha and the LeakyReLU sign come from the cache when the variant keeps them.  The row pass reads them in entry
+// order and leaves them as one signed value per entry and head, in the same order; the column pass gathers that
+// through perm, one line an entry instead of two (2^17 nodes, 8 heads of 8 features: row pass 74 -> 95 us, column pass
+// 145 -> 112; written in the column pass's own order, scattered, 67 -> 108 for 136 -> 107).
 // Otherwise they are rebuilt per entry from per-node values: s_i, d_j and the row statistics - the same
 // arithmetic on the same bits in every pass, so all passes see the same logit and take the same LeakyReLU
 // decision.  (Forming d_j = <a_dst, m_j> from the feature row that a lane has loaded anyway, instead of
@@ -40,6 +41,8 @@
 // arrays too large for that run the unfused kernels.
 #include "common.h"
 
+#include <type_traits>
+
 namespace gnn {
 namespace {
 
@@ -51,6 +54,7 @@ struct Lane {
     int hd;          // head of those features
     bool ok;         // the lane has features (the tile may be narrower than the group)
     bool leader;     // first lane of its head: writes the per-head results
+    int sub;         // which lane of its head
 };
 
 struct Geo {
@@ -64,7 +68,8 @@ struct Geo {
         ln.ok = in_tile < tile_heads * k && hd < h;
         ln.hd = ln.ok ? hd : 0;
         ln.foff = ln.ok ? tile * tile_heads * k + in_tile : 0;
-        ln.leader = ln.ok && (l % lh) == 0;
+        ln.sub = l % lh;
+        ln.leader = ln.ok && ln.sub == 0;
         return ln;
     }
 };
@@ -213,15 +218,34 @@ struct BwdRowCachedOp {
     float slope;
     float *ds;                // [n][h]
     float *node;              // t [n][h]
-    struct Ent { float4 m, g; float al, pos, ga; };
+    float *edge;              // [q][h]: alpha with the mask in its sign, for the column pass, or NULL
+    struct Ent { float4 m, g; float al, pos, ga; uint32_t at; };
     __device__ void init(A &a) const { a.d[0] = a.d[1] = a.d[2] = 0.0; }
     __device__ void load(Ent &e, int row, int col, int slot, const LaneOff &lo) const {
         e.m = ldb<float4>(M, off24(col, geo.f * 4u, lo.feat));
         e.g = ldb<float4>(G, off24(row, geo.f * 4u, lo.feat));
-        e.al = ldb<float>(alpha, off32(slot, geo.h * 4u, lo.head4));
+        e.at = off32(slot, geo.h * 4u, lo.head4);
+        e.al = ldb<float>(alpha, e.at);
         e.pos = ldb<uint8_t>(mask, off32(slot, geo.h, lo.head1)) ? 1.f : 0.f;
     }
     __device__ void prepare(Ent &e, const Lane &ln) const { e.ga = head_sum(ln.ok ? dot4(e.m, e.g) : 0.f, geo.lh); }
+    // Entry u of a batch is written by lane u of each head, so that one instruction writes a batch (two lanes a head or
+    // more; 16 lanes an entry, 8 heads: an instruction an entry 99 us, one for both 95).  Filler past the list's end is
+    // entry 0 again, the same value.
+    template <int U> __device__ void leave(const Ent (&e)[U], const Lane &ln) const {
+        auto put = [&](const Ent &x) { *reinterpret_cast<float *>(reinterpret_cast<char *>(edge) + x.at) = copysignf(x.al, x.pos - 0.5f); };
+        if (!edge || !ln.ok) return;
+        if (geo.lh >= U) {
+            Ent x = e[0];
+#pragma unroll
+            for (int u = 1; u < U; ++u)
+                if (ln.sub == u) { x.at = e[u].at; x.al = e[u].al; x.pos = e[u].pos; }
+            if (ln.sub < U) put(x);
+        } else if (ln.leader) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) put(e[u]);
+        }
+    }
     __device__ void fold(A &a, const Ent &e) const {
         const double x = (double)e.al * (double)e.ga, pos = (double)e.pos;
         a.d[0] += x;
@@ -302,15 +326,17 @@ struct BwdRowOnlineOp {
 // ---- backward, column pass: dd and dM = A^T G + ds a_src + dd a_dst ----------------------------------
 // Here "row" is the column j of the matrix (the pass walks the CSC arrays), "col" the row i of the entry.
 // f = (a0..a3: sum alpha_e G_i, dd)
-template <bool CACHED>
+// KIND: alpha and its sign from the cache (kColCached), from the row pass in one value (kColSigned), or rebuilt.
+enum { kColRebuilt, kColCached, kColSigned };
+template <int KIND>
 struct BwdColOp {
     typedef Acc<5, 0> A;
     Geo geo;
     const float *G, *M;
-    const float *alpha;            // CACHED: [q][h] and the mask, in CSR order
-    const uint8_t *mask;
-    const float *node;             // CACHED: t [n][h]; else (s, m, 1 / l, t) [n][h][4], as written by the row pass
-    const float *d;                // !CACHED: [n][h]
+    const float *alpha;            // [q][h] in CSR order: the cache's, or as written by the row pass
+    const uint8_t *mask;           // kColCached: [q][h]
+    const float *node;             // t [n][h]; rebuilt: (s, m, 1 / l, t) [n][h][4], as written by the row pass
+    const float *d;                // rebuilt: [n][h]
     float slope;
     const float *ds, *a_src, *a_dst;
     float *dd, *dM;
@@ -319,9 +345,9 @@ struct BwdColOp {
     __device__ void load(Ent &e, int j, int i, int slot, const LaneOff &lo) const {
         e.g = ldb<float4>(G, off24(i, geo.f * 4u, lo.feat));
         e.m = ldb<float4>(M, off24(j, geo.f * 4u, lo.feat));
-        if constexpr (CACHED) {
+        if constexpr (KIND != kColRebuilt) {
             e.al = ldb<float>(alpha, off32(slot, geo.h * 4u, lo.head4));   // through perm: the slot in CSR order
-            e.pos = ldb<uint8_t>(mask, off32(slot, geo.h, lo.head1)) ? 1.f : 0.f;
+            if constexpr (KIND == kColCached) e.pos = ldb<uint8_t>(mask, off32(slot, geo.h, lo.head1)) ? 1.f : 0.f;
             e.t = ldb<float>(node, off24(i, geo.h * 4u, lo.head4));
         } else {
             e.nd = ldb<float4>(node, off24(i, geo.h * 16u, lo.head16));     // s_i, m_i, 1 / l_i, t_i
@@ -329,11 +355,14 @@ struct BwdColOp {
         }
     }
     __device__ void prepare(Ent &e, const Lane &ln) const {
-        if constexpr (!CACHED) {
+        if constexpr (KIND == kColRebuilt) {
             const float y = e.nd.x + e.dv;                                  // the row pass's logit, bit for bit
             e.pos = y > 0.f ? 1.f : 0.f;
             e.al = __expf(leaky(y, slope) - e.nd.y) * e.nd.z;
             e.t = e.nd.w;
+        } else if constexpr (KIND == kColSigned) {
+            e.pos = signbit(e.al) ? 0.f : 1.f;
+            e.al = fabsf(e.al);
         }
         e.ga = head_sum(ln.ok ? dot4(e.g, e.m) : 0.f, geo.lh);
     }
@@ -453,6 +482,7 @@ seg_walk_kernel(int nnz, int seg, long nseg, const int32_t *__restrict__ rowidx,
         auto consume = [&](int x, const int (&r)[U], Ent (&ent)[U]) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < U; ++u) op.prepare(ent[u], ln);
+            if constexpr (std::is_same<Op, BwdRowCachedOp>::value) op.leave(ent, ln);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (x + u < cnt) {
@@ -665,29 +695,39 @@ gnn_status_t gat_fused_backward_launch(int n, int nnz, int h, int k, const int32
                                        const int32_t *row, const int32_t *perm, const float *G, const float *M,
                                        const float *alpha, const uint8_t *mask, const float *s,
                                        const float *d, float slope, const float *a_src, const float *a_dst,
-                                       float *node, float *ds, float *dd, float *dM, void *workspace, hipStream_t st) {
+                                       float *node, float *edge, float *ds, float *dd, float *dM, void *workspace,
+                                       hipStream_t st) {
     if (n <= 0) return GNN_OK;
     const Shape sh = pick_shape(nnz > 0 ? nnz : 1, h, k);
     float *part = static_cast<float *>(workspace);
     if (nnz <= 0) {
         const dim3 fgrid((unsigned)ceil_div(ceil_div(n, kWave), 4), 1);
-        BwdRowCachedOp ra{sh.geo, G, M, alpha, mask, slope, ds, node};
+        BwdRowCachedOp ra{sh.geo, G, M, alpha, mask, slope, ds, node, edge};
         hipLaunchKernelGGL((seg_fixup_kernel<BwdRowCachedOp, 16>), fgrid, dim3(256), 0, st, n, 0, 1, 0L, erow, rowptr, ra, part);
         GNN_TRY(launch_status());
-        BwdColOp<true> cb{sh.geo, G, M, alpha, mask, node, nullptr, slope, ds, a_src, a_dst, dd, dM};
-        hipLaunchKernelGGL((seg_fixup_kernel<BwdColOp<true>, 16>), fgrid, dim3(256), 0, st, n, 0, 1, 0L, ecol, colptr, cb, part);
+        BwdColOp<kColCached> cb{sh.geo, G, M, alpha, mask, node, nullptr, slope, ds, a_src, a_dst, dd, dM};
+        hipLaunchKernelGGL((seg_fixup_kernel<BwdColOp<kColCached>, 16>), fgrid, dim3(256), 0, st, n, 0, 1, 0L, ecol, colptr, cb, part);
         return launch_status();
     }
     if (alpha) {
-        BwdRowCachedOp ra{sh.geo, G, M, alpha, mask, slope, ds, node};
+        // Arrays that the L2s hold are read through perm twice as well; the row pass is spared its writes.  Backward calls from
+        // the cache / with one signed value, us: 5000 nodes, 55 000 entries, 8 heads of 8 48.5 / 50.1; 20000, 620 000, 8 of 16
+        // 139 / 134; 2^17, 2.0 M, 8 of 8 302 / 292, 8 of 32 802 / 795, 1 of 16 175 / 154, uniform 8 of 8 357 / 336; 2^19, 11 M,
+        // 8 of 8 1510 / 1428, 4 of 8 1120 / 1007, uniform 2 of 16 1245 / 1121.
+        const bool leave = (int64_t)nnz * h * 5 > 4 << 20;
+        BwdRowCachedOp ra{sh.geo, G, M, alpha, mask, slope, ds, node, leave ? edge : nullptr};
         GNN_TRY((run_pass<BwdRowCachedOp, 2>(sh, n, nnz, rowptr, erow, col, nullptr, ra, part, st)));
-        BwdColOp<true> cb{sh.geo, G, M, alpha, mask, node, nullptr, slope, ds, a_src, a_dst, dd, dM};
-        return run_pass<BwdColOp<true>, 2>(sh, n, nnz, colptr, ecol, row, perm, cb, part, st);
+        if (leave) {
+            BwdColOp<kColSigned> cb{sh.geo, G, M, edge, nullptr, node, nullptr, slope, ds, a_src, a_dst, dd, dM};
+            return run_pass<BwdColOp<kColSigned>, 2>(sh, n, nnz, colptr, ecol, row, perm, cb, part, st);
+        }
+        BwdColOp<kColCached> cb{sh.geo, G, M, alpha, mask, node, nullptr, slope, ds, a_src, a_dst, dd, dM};
+        return run_pass<BwdColOp<kColCached>, 2>(sh, n, nnz, colptr, ecol, row, perm, cb, part, st);
     }
     BwdRowOnlineOp ra{sh.geo, G, M, s, d, slope, ds, node};
     GNN_TRY((run_pass<BwdRowOnlineOp, 2>(sh, n, nnz, rowptr, erow, col, nullptr, ra, part, st)));
-    BwdColOp<false> cb{sh.geo, G, M, nullptr, nullptr, node, d, slope, ds, a_src, a_dst, dd, dM};
-    return run_pass<BwdColOp<false>, 2>(sh, n, nnz, colptr, ecol, row, perm, cb, part, st);
+    BwdColOp<kColRebuilt> cb{sh.geo, G, M, nullptr, nullptr, node, d, slope, ds, a_src, a_dst, dd, dM};
+    return run_pass<BwdColOp<kColRebuilt>, 2>(sh, n, nnz, colptr, ecol, row, perm, cb, part, st);
 }
 
 }  // namespace gnn

@@ -107,7 +107,7 @@ gnn_status_t gat_backward(Plan &p, const gnn_graph_t &g, const float *X, const f
         GNN_TRY(gat_fused_backward_launch(n, q, h, k, g.csr_rowptr, g.csr_erow, g.csr_col, g.csc_colptr, g.csc_ecol,
                                           g.csc_row, g.csc_perm, dY, B.M, cached ? B.alpha : nullptr,
                                           cached ? B.mask : nullptr, B.s, B.d, d.leaky_slope, a_src, a_dst,
-                                          at<float>(workspace, L.w_node), ds, dd, dM, at<char>(workspace, L.w_fused), st));
+                                          at<float>(workspace, L.w_node), gy, ds, dd, dM, at<char>(workspace, L.w_fused), st));
     } else {
         // dL/dalpha on the pattern: g_alpha_e = <G_i, M_j> per head (SDDMM)
         GNN_TRY(sddmm_launch(n, q, g.csr_erow, g.csr_col, nullptr, dY, B.M, h, k, gy, st));
