@@ -382,6 +382,10 @@ spmm_fixup_kernel(int n, int nnz, int f, int span, long nspan, int lpf, const in
 // f = 16, call by call: 11.0 us and 12.3 with hubs in segments, 8.8 and 8.3 here, where the calls bound it).  Shared by four
 // wavefronts or sixteen, and from 8 or 32 entries on, hubs take longer: 16384 nodes, 409 600 entries, f = 16, 4 / 8 / 16
 // wavefronts 16.6 / 14.1 / 24.2 us.
+// Four features a lane at any 4-byte aligned address: the last lane of a ragged width takes the row's last four, some of them
+// for the second time, with the same result.  With one feature a lane a width has an eighth to a half of the slots: 1024
+// nodes, 17 336 entries, eight of the rows 1024 long, f = 23 86 us against 37, which f = 32 takes; 8192 nodes, 196 303 entries,
+// f = 23 11.8 / 6.2 (widths of 5 to 7 with rows of nine entries 3.6 / 4.0: more slots to add up).
 constexpr int kRowWaves = 8, kRowShare = 16;
 
 template <int VEC, int LPE, int U>
@@ -392,11 +396,13 @@ spmm_row_kernel(int n, int f, int ldb, const int32_t *__restrict__ rowptr, const
     __shared__ float s_part[WAVES][LPE * VEC];
     __shared__ int32_t s_ptr[WAVES + 1];
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, l = lane % LPE, slot = lane / LPE;
-    const int row0 = blockIdx.x * WAVES, c = (blockIdx.y * LPE + l) * VEC;
+    const int row0 = blockIdx.x * WAVES;
+    int c = (blockIdx.y * LPE + l) * VEC;
     if (threadIdx.x <= WAVES) s_ptr[threadIdx.x] = rowptr[min(row0 + (int)threadIdx.x, n)];
     __syncthreads();
     const bool ok = c < f;
-    const int hd = w.heads > 1 && ok ? c / w.head_dim : 0;
+    c = ok ? min(c, f - VEC) : 0;
+    const int hd = w.heads > 1 ? c / w.head_dim : 0;
     float acc[VEC];
     auto gather = [&](int first, int end, int step) __attribute__((always_inline)) {
 #pragma unroll
@@ -413,9 +419,9 @@ spmm_row_kernel(int n, int f, int ldb, const int32_t *__restrict__ rowptr, const
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const float *src = B + (size_t)cj[u] * ldb + (ok ? c : 0);
+                const float *src = B + (size_t)cj[u] * ldb + c;
                 if constexpr (VEC == 4) {
-                    const float4 q = *reinterpret_cast<const float4 *>(src);
+                    const float4u q = *reinterpret_cast<const float4u *>(src);
                     b[u][0] = q.x; b[u][1] = q.y; b[u][2] = q.z; b[u][3] = q.w;
                 } else b[u][0] = *src;
             }
@@ -431,10 +437,9 @@ spmm_row_kernel(int n, int f, int ldb, const int32_t *__restrict__ rowptr, const
             for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], d, kWave);
     };
     auto store = [&](int row) __attribute__((always_inline)) {
-        if (slot != 0) return;
+        if (slot != 0 || !ok) return;
 #pragma unroll
-        for (int i = 0; i < VEC; ++i)
-            if (c + i < f) C[(size_t)row * f + c + i] = epilogue(acc[i], bias, c + i, relu);
+        for (int i = 0; i < VEC; ++i) C[(size_t)row * f + c + i] = epilogue(acc[i], bias, c + i, relu);
     };
     if (row0 + wave < n && s_ptr[wave + 1] - s_ptr[wave] <= kRowShare * SLOTS) {
         gather(s_ptr[wave] + slot, s_ptr[wave + 1], SLOTS);
@@ -604,7 +609,7 @@ gnn_status_t spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_t *c
     if (!erow || nnz == 0 || (pieces && !heads && rows_pay(n, nnz, f))) {
         int ldb = f;                                       // unless the caller has written the padded operand
         if (!pieces || heads || B != spmm_padded_operand(workspace, erow, b_rows, nnz, f, &ldb)) ldb = f;
-        const bool vec4 = ldb % 4 == 0 && aligned16(B) && (!heads || w.head_dim % 4 == 0);
+        const bool vec4 = f >= 4 && (!heads || w.head_dim % 4 == 0);
         const int lanes = pow2_at_least(vec4 ? (f + 3) / 4 : f), lpe = lanes < kWave ? lanes : kWave;
         const dim3 grid((unsigned)ceil_div(n, kRowWaves), (unsigned)ceil_div(f, lpe * (vec4 ? 4 : 1)));
 #define ROW_CASE(VEC_, LPE_)                                                                                 \
