@@ -378,30 +378,34 @@ spmm_fixup_kernel(int n, int nnz, int f, int span, long nspan, int lpf, const in
 // Eight rows a block, one wavefront each: 64 / LPE slots of LPE lanes (VEC features a lane, blockIdx.y picks which of them a
 // block has) take the entries of the row in turn, U at a time, and are added by a fixed shuffle tree.  A row of more than
 // kRowShare entries a slot is shared by the wavefronts of the block.  Everything follows from the row pointers, in one launch:
-// what bounds a small product is the chain of pointers, indices and rows of B, and the launches (2048 nodes, 18 432 entries,
-// f = 16, call by call: 11.0 us and 12.3 with hubs in segments, 8.8 and 8.3 here, where the calls bound it).  Shared by four
-// wavefronts or sixteen, and from 8 or 32 entries on, hubs take longer: 16384 nodes, 409 600 entries, f = 16, 4 / 8 / 16
-// wavefronts 16.6 / 14.1 / 24.2 us.
+// what bounds a small product is the chain of pointers, indices and rows of B, and the launches (2048 nodes, 18 390 entries,
+// f = 16: 10.9 us in segments, 3.9 here).  Shared by four wavefronts or sixteen, and from 8 or 32 entries on, hubs take longer:
+// 16384 nodes, 409 600 entries, f = 16, 4 / 8 / 16 wavefronts 16.6 / 14.1 / 24.2 us.
+// Up to kDealtRows rows, row i goes to block i % blocks: hubs next to each other (nodes numbered by degree) go to different
+// blocks, where one block would take them one after the other: 2048 nodes, eight of them joined to all, f = 16 37 us / 7.9,
+// f = 32 65 / 11.4; without hubs 3.86 / 3.87.  Beyond, a block has eight consecutive rows, whose indices share lines (2^17 nodes,
+// 2 M entries, f = 1 53 us against 61 dealt).
 // Four features a lane at any 4-byte aligned address: the last lane of a ragged width takes the row's last four, some of them
 // for the second time, with the same result.  With one feature a lane a width has an eighth to a half of the slots: 1024
 // nodes, 17 336 entries, eight of the rows 1024 long, f = 23 86 us against 37, which f = 32 takes; 8192 nodes, 196 303 entries,
 // f = 23 11.8 / 6.2 (widths of 5 to 7 with rows of nine entries 3.6 / 4.0: more slots to add up).
-constexpr int kRowWaves = 8, kRowShare = 16;
+constexpr int kRowWaves = 8, kRowShare = 16, kDealtRows = 8192;
 
 template <int VEC, int LPE, int U>
 __global__ void __launch_bounds__(64 * kRowWaves)
-spmm_row_kernel(int n, int f, int ldb, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col, EdgeWeights w,
-                const float *__restrict__ B, float *__restrict__ C, const float *__restrict__ bias, int relu) {
+spmm_row_kernel(int n, uint32_t by, uint32_t apart, const int32_t *__restrict__ rowptr, int f, int ldb,
+                const int32_t *__restrict__ col, EdgeWeights w, const float *__restrict__ B, float *__restrict__ C,
+                const float *__restrict__ bias, int relu) {
     constexpr int SLOTS = kWave / LPE, WAVES = kRowWaves;
     __shared__ float s_part[WAVES][LPE * VEC];
-    __shared__ int32_t s_ptr[WAVES + 1];
+    __shared__ int32_t s_ptr[2 * WAVES];                   // first and last entry of the block's rows
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, l = lane % LPE, slot = lane / LPE;
-    const int row0 = blockIdx.x * WAVES;
-    int c = (blockIdx.y * LPE + l) * VEC;
-    if (threadIdx.x <= WAVES) s_ptr[threadIdx.x] = rowptr[min(row0 + (int)threadIdx.x, n)];
+    auto row_of = [&](int i) __attribute__((always_inline)) { return blockIdx.x * by + i * apart; };
+    if (threadIdx.x < 2 * WAVES) s_ptr[threadIdx.x] = rowptr[min(row_of(threadIdx.x / 2) + threadIdx.x % 2, (uint32_t)n)];
     __syncthreads();
+    int c = (blockIdx.y * LPE + l) * VEC;
     const bool ok = c < f;
-    c = ok ? min(c, f - VEC) : 0;
+    c = ok ? min(c, f - VEC) : 0;                          // the last lane of a ragged width has features of the one before too
     const int hd = w.heads > 1 ? c / w.head_dim : 0;
     float acc[VEC];
     auto gather = [&](int first, int end, int step) __attribute__((always_inline)) {
@@ -436,18 +440,19 @@ spmm_row_kernel(int n, int f, int ldb, const int32_t *__restrict__ rowptr, const
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], d, kWave);
     };
-    auto store = [&](int row) __attribute__((always_inline)) {
+    auto store = [&](uint32_t row) __attribute__((always_inline)) {
         if (slot != 0 || !ok) return;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) C[(size_t)row * f + c + i] = epilogue(acc[i], bias, c + i, relu);
     };
-    if (row0 + wave < n && s_ptr[wave + 1] - s_ptr[wave] <= kRowShare * SLOTS) {
-        gather(s_ptr[wave] + slot, s_ptr[wave + 1], SLOTS);
-        store(row0 + wave);
+    if (row_of(wave) < (uint32_t)n && s_ptr[2 * wave + 1] - s_ptr[2 * wave] <= kRowShare * SLOTS) {
+        gather(s_ptr[2 * wave] + slot, s_ptr[2 * wave + 1], SLOTS);
+        store(row_of(wave));
     }
     for (int r = 0; r < WAVES; ++r) {
-        if (row0 + r >= n || s_ptr[r + 1] - s_ptr[r] <= kRowShare * SLOTS) continue;      // the same for the whole block
-        gather(s_ptr[r] + wave * SLOTS + slot, s_ptr[r + 1], WAVES * SLOTS);
+        const int first = s_ptr[2 * r], end = s_ptr[2 * r + 1];
+        if (row_of(r) >= (uint32_t)n || end - first <= kRowShare * SLOTS) continue;                 // the same for the whole block
+        gather(first + wave * SLOTS + slot, end, WAVES * SLOTS);
         if (slot == 0)
 #pragma unroll
             for (int i = 0; i < VEC; ++i) s_part[wave][l * VEC + i] = acc[i];
@@ -458,7 +463,7 @@ spmm_row_kernel(int n, int f, int ldb, const int32_t *__restrict__ rowptr, const
                 acc[i] = s_part[0][l * VEC + i];
                 for (int k = 1; k < WAVES; ++k) acc[i] += s_part[k][l * VEC + i];
             }
-            store(row0 + r);
+            store(row_of(r));
         }
         __syncthreads();
     }
@@ -563,13 +568,17 @@ float *spmm_padded_operand(void *workspace, const int32_t *erow, int64_t b_rows,
     return reinterpret_cast<float *>(static_cast<char *>(workspace) + partials_bytes(nnz, f));
 }
 
-// Products that a wavefront per row is faster at: few rows, and so few entries that hubs among them stay short.  Segments /
-// rows, us, call by call (8.3 to 8.8: the calls themselves), uniform; R-MAT: 3001 nodes, 30 009 entries, f = 7 16.1 / 8.8;
-// 19.3 / 8.4, 64 11.6 / 8.9; 11.2 / 8.4, 128 11.4 / 8.8; 11.1 / 11.6; 4096, 208 896, 32 11.2 / 8.9; 13.0 / 12.1, 64 11.3 /
-// 10.8; 11.8 / 18.6; 8192, 73 728, 32 11.4 / 8.9; 14.1 / 9.7, 64 11.4 / 8.8; 12.1 / 14.5; 16384, 409 600, 16 11.3 / 9.0; 18.4 /
-// 14.1, 32 11.5 / 9.8; 14.6 / 18.5; 32768, 360 448, 16 11.6 / 15.0; 19.0 / 19.4.
+// Products that a wavefront per row is faster at, whatever the lengths of the rows, which the host does not know: a row of n
+// entries is the work of one block, and so are eight rows of a graph in which all are long.  A block takes 3.5 us and 1.1 us for
+// every 10 000 entries x features (the features its lanes cover), 64 lines under way as on any CU; segments take 8 to 11 us, with
+// a copy of a ragged operand 11 to 16.  Segments / rows, us: a row of n entries, the others of three, 2048 nodes, f = 16 15.7 /
+// 7.6, 32 10.8 / 11.2; 4096, 7 28 / 8.0, 16 15.7 / 11.2, 32 11.0 / 18.2; 512, 64 9.8 / 7.7; 1024, 64 9.9 / 11.0; eight such rows
+// 2048, 32 12.0 / 11.7; 4096, 16 16.8 / 11.6; 512, 64 9.5 / 8.1; 256, 128 8.3 / 9.3; 64 of them 2048, 32 12.9 / 13.1; rows of 450
+// entries and no others, 32 13.1 / 22.9; no long rows, 4096, 16 10.9 / 4.3; 2048, 32 10.1 / 3.9.  Rows that name nodes many times
+// over, so that one has several times n entries, are the exception that this does not bound.
 static bool rows_pay(int64_t n, int64_t nnz, int f) {
-    return n <= 16384 && f <= 128 && nnz * (f < 16 ? 16 : f) <= (f <= 32 ? 6600000 : 2500000);
+    const int64_t work = 4 * pow2_at_least(f >= 4 ? (f + 3) / 4 : f);      // a slot of one lane has the loads of four features
+    return n <= kDealtRows && work <= 64 && n * work <= (work <= 32 ? 65536 : 32768) && nnz * work <= 3072 * n;
 }
 
 #define SPMM_CASE(VEC_, LPE_, NT_, U_)                                                                       \
@@ -611,11 +620,13 @@ gnn_status_t spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_t *c
         if (!pieces || heads || B != spmm_padded_operand(workspace, erow, b_rows, nnz, f, &ldb)) ldb = f;
         const bool vec4 = f >= 4 && (!heads || w.head_dim % 4 == 0);
         const int lanes = pow2_at_least(vec4 ? (f + 3) / 4 : f), lpe = lanes < kWave ? lanes : kWave;
-        const dim3 grid((unsigned)ceil_div(n, kRowWaves), (unsigned)ceil_div(f, lpe * (vec4 ? 4 : 1)));
+        const uint32_t blocks = (uint32_t)ceil_div(n, kRowWaves);
+        const uint32_t by = n <= kDealtRows ? 1 : kRowWaves, apart = n <= kDealtRows ? blocks : 1;
+        const dim3 grid(blocks, (unsigned)ceil_div(f, lpe * (vec4 ? 4 : 1)));
 #define ROW_CASE(VEC_, LPE_)                                                                                 \
         if (vec4 == (VEC_ == 4) && lpe == LPE_)                                                              \
             hipLaunchKernelGGL((spmm_row_kernel<VEC_, LPE_, LPE_ < 16 ? 4 : 8>), grid, dim3(64 * kRowWaves), \
-                               0, st, n, f, ldb, rowptr, col, w, B, C, bias, relu);
+                               0, st, n, by, apart, rowptr, f, ldb, col, w, B, C, bias, relu);
         ROW_CASE(4, 1) ROW_CASE(4, 2) ROW_CASE(4, 4) ROW_CASE(4, 8) ROW_CASE(4, 16) ROW_CASE(4, 32) ROW_CASE(4, 64)
         ROW_CASE(1, 1) ROW_CASE(1, 2) ROW_CASE(1, 4) ROW_CASE(1, 8) ROW_CASE(1, 16) ROW_CASE(1, 32) ROW_CASE(1, 64)
 #undef ROW_CASE

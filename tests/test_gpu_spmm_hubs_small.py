@@ -1,5 +1,6 @@
-"""Small products with long rows side by side: the time of a call does not hang on a ragged width.  Times of a graph of twenty
-calls, the least of several replays, against another call of the same kernel: the bounds leave a factor of about two."""
+"""Small products with long rows side by side: sums against float64 on both sides of the lines between the kernels, and the
+time of a call, which hangs neither on a ragged width nor on where the long rows are.  Times of a graph of twenty calls, the least
+of several replays, against another call of the same size: the bounds leave a factor of about two."""
 import pytest
 import torch
 
@@ -22,13 +23,35 @@ def csr(n, key):
     return rowptr, col.int(), row.int()
 
 
-def call(n, f, graph, seed=1):
+def uniform_graph(n, q, seed=1):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    return csr(n, torch.randint(0, n * n, (q,), generator=gen, device="cuda").sort().values)
+
+
+def operands(n, f, q, seed=1):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.randn(q, generator=gen, device="cuda"), torch.randn(n, f, generator=gen, device="cuda")
+
+
+def call(n, f, graph):
     rowptr, col, erow = graph
     q = col.numel()
-    gen = torch.Generator(device="cuda").manual_seed(seed)
-    val, X = torch.randn(q, generator=gen, device="cuda"), torch.randn(n, f, generator=gen, device="cuda")
+    val, X = operands(n, f, q)
     C, ws = torch.empty(n, f, device="cuda"), B.alloc(B.gnn_spmm_workspace_bytes(n, q, f))
     return lambda: B.gnn_spmm_csr(n, q, rowptr, col, val, erow, X, f, C, workspace=ws)
+
+
+def check(n, f, graph, expanded=True):
+    rowptr, col, erow = graph
+    q = col.numel()
+    val, X = operands(n, f, q)
+    C, ws = torch.full((n, f), float("nan"), device="cuda"), B.alloc(B.gnn_spmm_workspace_bytes(n, q, f))
+    B.gnn_spmm_csr(n, q, rowptr, col, val, erow if expanded else None, X, f, C, workspace=ws)
+    A = torch.zeros(n, n, dtype=torch.float64, device="cuda").index_put_((erow.long(), col.long()), val.double(), accumulate=True)
+    size = torch.zeros_like(A).index_put_((erow.long(), col.long()), val.double().abs(), accumulate=True) @ X.double().abs()
+    length = (rowptr[1:] - rowptr[:-1]).double()[:, None]
+    # a rounding per entry at the most, and a few for the sums of the slots
+    assert bool(((C.double() - A @ X.double()).abs() <= (length + 16) * 2.0 ** -24 * size).all())
 
 
 def least_us(run, calls=20, replays=8):
@@ -57,3 +80,22 @@ def test_ragged_width(n, f, aligned):
     """Takes about what the next aligned width takes (1024 x 23: 2.3 times that with one feature a lane)."""
     graph = hub_graph(n, 8)
     assert least_us(call(n, f, graph)) <= 1.6 * least_us(call(n, aligned, graph))
+
+
+@pytest.mark.parametrize("n,f", [(1024, 16), (4096, 32), (2048, 23), (8192, 16)])
+def test_hubs_side_by_side(n, f):
+    """Eight rows of n entries take about what as many entries take in rows of one length (one block for the eight: 6 to 30 times)."""
+    graph = hub_graph(n, 8)
+    assert least_us(call(n, f, graph)) <= 4 * least_us(call(n, f, uniform_graph(n, graph[1].numel())))
+
+
+@pytest.mark.parametrize("n,f", [(2048, 32), (2049, 32), (2047, 17), (4096, 16), (4097, 13), (8191, 8), (8192, 5), (8193, 8), (512, 64),
+                                 (513, 64), (511, 33), (512, 65), (16, 64), (9, 3), (8193, 3)])
+@pytest.mark.parametrize("expanded", [True, False])
+def test_hubs_against_float64(n, f, expanded):
+    check(n, f, hub_graph(n, 8), expanded)
+
+
+@pytest.mark.parametrize("n,f,q", [(512, 16, 98304), (512, 16, 98305), (512, 64, 24576), (512, 64, 24577)])
+def test_entries_against_float64(n, f, q):
+    check(n, f, uniform_graph(n, q))
