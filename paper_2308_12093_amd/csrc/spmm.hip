@@ -375,8 +375,8 @@ spmm_fixup_kernel(int n, int nnz, int f, int span, long nspan, int lpf, const in
     }
 }
 
-// Eight rows a block, one wavefront each: 64 / LPE slots of LPE lanes (VEC features a lane, blockIdx.y picks which of them a
-// block has) take the entries of the row in turn, U at a time, and are added by a fixed shuffle tree.  A row of more than
+// Eight rows a block, one wavefront each: 64 / LPE slots of LPE lanes (VEC features a lane, tile0 + blockIdx.y picks which of them
+// a block has) take the entries of the row in turn, U at a time, and are added by a fixed shuffle tree.  A row of more than
 // kRowShare entries a slot is shared by the wavefronts of the block.  Everything follows from the row pointers, in one launch:
 // what bounds a small product is the chain of pointers, indices and rows of B, and the launches (2048 nodes, 18 390 entries,
 // f = 16: 10.9 us in segments, 3.9 here).  Shared by four wavefronts or sixteen, and from 8 or 32 entries on, hubs take longer:
@@ -393,7 +393,7 @@ constexpr int kRowWaves = 8, kRowShare = 16, kDealtRows = 8192;
 
 template <int VEC, int LPE, int U>
 __global__ void __launch_bounds__(64 * kRowWaves)
-spmm_row_kernel(int n, uint32_t by, uint32_t apart, const int32_t *__restrict__ rowptr, int f, int ldb,
+spmm_row_kernel(int n, uint32_t by, uint32_t apart, const int32_t *__restrict__ rowptr, int f, int ldb, uint32_t tile0,
                 const int32_t *__restrict__ col, EdgeWeights w, const float *__restrict__ B, float *__restrict__ C,
                 const float *__restrict__ bias, int relu) {
     constexpr int SLOTS = kWave / LPE, WAVES = kRowWaves;
@@ -403,8 +403,8 @@ spmm_row_kernel(int n, uint32_t by, uint32_t apart, const int32_t *__restrict__ 
     auto row_of = [&](int i) __attribute__((always_inline)) { return blockIdx.x * by + i * apart; };
     if (threadIdx.x < 2 * WAVES) s_ptr[threadIdx.x] = rowptr[min(row_of(threadIdx.x / 2) + threadIdx.x % 2, (uint32_t)n)];
     __syncthreads();
-    int c = (blockIdx.y * LPE + l) * VEC;
-    const bool ok = c < f;
+    int c = ((tile0 + blockIdx.y) * LPE + l) * VEC;
+    const bool ok = (uint32_t)c < (uint32_t)f;
     c = ok ? min(c, f - VEC) : 0;                          // the last lane of a ragged width has features of the one before too
     const int hd = w.heads > 1 ? c / w.head_dim : 0;
     float acc[VEC];
@@ -622,14 +622,17 @@ gnn_status_t spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_t *c
         const int lanes = pow2_at_least(vec4 ? (f + 3) / 4 : f), lpe = lanes < kWave ? lanes : kWave;
         const uint32_t blocks = (uint32_t)ceil_div(n, kRowWaves);
         const uint32_t by = n <= kDealtRows ? 1 : kRowWaves, apart = n <= kDealtRows ? blocks : 1;
-        const dim3 grid(blocks, (unsigned)ceil_div(f, lpe * (vec4 ? 4 : 1)));
+        const long tiles = ceil_div(f, lpe * (vec4 ? 4 : 1));
+        for (long tile0 = 0; tile0 < tiles; tile0 += 65535) {                   // blocks in y that any device takes
+            const dim3 grid(blocks, (unsigned)(tiles - tile0 < 65535 ? tiles - tile0 : 65535));
 #define ROW_CASE(VEC_, LPE_)                                                                                 \
-        if (vec4 == (VEC_ == 4) && lpe == LPE_)                                                              \
-            hipLaunchKernelGGL((spmm_row_kernel<VEC_, LPE_, LPE_ < 16 ? 4 : 8>), grid, dim3(64 * kRowWaves), \
-                               0, st, n, by, apart, rowptr, f, ldb, col, w, B, C, bias, relu);
-        ROW_CASE(4, 1) ROW_CASE(4, 2) ROW_CASE(4, 4) ROW_CASE(4, 8) ROW_CASE(4, 16) ROW_CASE(4, 32) ROW_CASE(4, 64)
-        ROW_CASE(1, 1) ROW_CASE(1, 2) ROW_CASE(1, 4) ROW_CASE(1, 8) ROW_CASE(1, 16) ROW_CASE(1, 32) ROW_CASE(1, 64)
+            if (vec4 == (VEC_ == 4) && lpe == LPE_)                                                              \
+                hipLaunchKernelGGL((spmm_row_kernel<VEC_, LPE_, LPE_ < 16 ? 4 : 8>), grid, dim3(64 * kRowWaves), \
+                                   0, st, n, by, apart, rowptr, f, ldb, (uint32_t)tile0, col, w, B, C, bias, relu);
+            ROW_CASE(4, 1) ROW_CASE(4, 2) ROW_CASE(4, 4) ROW_CASE(4, 8) ROW_CASE(4, 16) ROW_CASE(4, 32) ROW_CASE(4, 64)
+            ROW_CASE(1, 1) ROW_CASE(1, 2) ROW_CASE(1, 4) ROW_CASE(1, 8) ROW_CASE(1, 16) ROW_CASE(1, 32) ROW_CASE(1, 64)
 #undef ROW_CASE
+        }
         return launch_status();
     }
 

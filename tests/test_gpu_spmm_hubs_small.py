@@ -99,3 +99,13 @@ def test_hubs_against_float64(n, f, expanded):
 @pytest.mark.parametrize("n,f,q", [(512, 16, 98304), (512, 16, 98305), (512, 64, 24576), (512, 64, 24577)])
 def test_entries_against_float64(n, f, q):
     check(n, f, uniform_graph(n, q))
+
+
+@pytest.mark.parametrize("f", [256 * 65535, 256 * 65535 + 5])
+def test_more_feature_tiles_than_a_grid_has(f):
+    rowptr, col = (torch.tensor(x, dtype=torch.int32, device="cuda") for x in ([0, 2, 3], [0, 1, 1]))
+    val, X = torch.tensor([1.5, -2.0, 0.5], device="cuda"), torch.randn(2, f, device="cuda")
+    C = torch.full((2, f), float("nan"), device="cuda")
+    B.gnn_spmm_csr(2, 3, rowptr, col, val, None, X, f, C)
+    assert torch.equal(C[1], 0.5 * X[1])
+    assert bool(((C[0] - (1.5 * X[0] - 2.0 * X[1])).abs() <= 2.0 ** -22 * (1.5 * X[0].abs() + 2.0 * X[1].abs())).all())
