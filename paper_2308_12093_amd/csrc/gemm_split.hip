@@ -164,7 +164,7 @@ __host__ __device__ constexpr int kept_waves(int nt) { return nt == 1 ? 16 : 12;
 // 128 -> 128 over 2^17 rows 40.8 -> 38.9 us, 512 -> 128 140.5 -> 137.7, 64 -> 256 over 2^22 1397 -> 1342).
 // KEPT: KEPT wavefronts a block keep the parts of their columns in LDS, split by themselves, and go through the rows in
 // tiles of 32 each without a barrier, so that one stores while another multiplies, and without the launch before.
-// kept_waves_per_block says where.
+// kept_pays says where.
 // BITS: A is used where its bit is set; a lane's 16 floats have one word, from the block's copy in LDS (held in registers a
 // step ahead it spills).
 template <int NT, bool BITS, int KEPT>
@@ -506,18 +506,39 @@ size_t parts_bytes(int64_t N, int64_t K) {
     return align_up((size_t)(ceil_div(N, 32 * w) * w) * ceil_div(K, KB) * kStepBytes);
 }
 
-// Wavefronts of a block that keeps the parts of its columns, or 0 where blocks pass them through LDS step by step.  Those
-// start their tiles as slots come free, which counts while there are few rows: 2^17 rows, B transposed, 128 -> 128 39 us
-// against 49 with the parts kept, 256 -> 64 36 / 44 (B as it is); 262144 68 / 71, 79 / 78; from 2^19 rows on keeping them is the
-// faster: 146.4 / 146.5, 157 / 153; 2^20 284 / 270, 303 / 284, 16 -> 128 139 / 130, 100 -> 256 527 / 493, 47 -> 256 303 / 285,
-// 40 -> 512 623 / 587; 2^22 64 -> 256 1342 / 1289, 256 -> 64 1166 / 1095; up to 32 columns the same (100 -> 16 135 / 135; 524288
-// 53 / 56).  One or two steps of few columns cost a block nothing to split: 60000 rows 16 -> 128 14.2 / 12.6, 64 -> 64 12.7 / 11.0,
-// 30 -> 30 9.9 / 7.3; 2^17 21.5 / 18.7, 16.9 / 16.7, 10.6 / 10.1.
-int kept_waves_per_block(int64_t M, int64_t N, int w, int steps) {
-    if (!(w * steps <= 4 && steps <= 2) && (w == 1 || M < 1 << 19)) return 0;
+// Whether blocks that keep the parts of their columns are the faster.  Those that pass them through LDS start their tiles as
+// slots come free, and the blocks of one row's columns run side by side; where a block has its columns for good, these drift
+// apart, which costs where they share lines of C.  Fitted to 7300 shapes; step by step / kept in us, t: B transposed.
+//   One step, up to 2^19 rows: 60000 x 16 -> 128 14.3 / 12.3, 2^17 22.6 / 19.4; not rows of C that begin within a line where C
+//     is larger than the memory-side cache (2^18 x 4 -> 400 106 / 113, 2^19 x 4 -> 300 160 / 208), nor B in rows of 32 floats,
+//     which a block reads a line per lane (t 90000 x 32 -> 128 19.5 / 21.2, 2^17 x 32 -> 16 10.3 / 10.6).
+//   One step, more rows: short reductions, 2^20 x 16 -> 96 137 / 110, 2^22 x 10 -> 47 285 / 241; 2^22 x 16 -> 64 264 / 266, 2^20 x
+//     32 -> 128 133 / 145; rows of C that begin within a line as above (2^22 x 4 -> 259 1128 / 1747, x 32 -> 100 529 / 756).
+//   Two steps: 60000 x 64 -> 64 12.6 / 11.5, x 48 -> 16 9.2 / 7.5; t 2^17 x 48 -> 64 18.6 / 20.1, 2^20 x 48 -> 30 73.7 / 80.4;
+//     several whole lines of C a row 2^20 x 48 -> 192 288 / 282, 2^22 1118 / 1146, 2^22 x 64 -> 256 1364 / 1342.
+//   More, from 2^19 rows on: 2^17 x 128 -> 128 39 / 49, 2^19 147 / 148, 2^20 281 / 262, 100 -> 256 540 / 501, 128 -> 64 179 / 164;
+//     not a third step into more than 64 columns (2^20 x 96 -> 352 620 / 716), a fifth and sixth into fewer (2^20 x 160 -> 64
+//     210 / 240), last tiles of a few columns (2^22 x 128 -> 130 1769 / 2023), nor four steps into one nearly whole, ragged tile
+//     (2 588 361 x 112 -> 117 751 / 804).
+bool kept_pays(int tb, int64_t M, int64_t N, int64_t K, int w, int steps) {
+    const bool lines = N % 32 == 0, near = M * N <= 5 << 24, fewer = M <= 1 << 20;      // near: 335 MB of C
+    if (steps == 1 && M <= 1 << 19) return (w < 4 || lines || near) && !(tb && K == 32 && (w == 4 || M > 1 << 16));
+    if (steps == 1 && w == 1) return K <= (N <= 16 ? 31 : 16);
+    if (steps == 1 && w == 2) return N == 64 ? K <= (fewer ? 20 : 16) : fewer ? K < 32 : K <= 20 && N <= 48;
+    if (steps == 1) return !lines ? near && K <= 16 : K <= (fewer ? (N % 128 ? 32 : 24) : N == 128 ? 16 : 24);
+    if (steps == 2 && w == 4) return lines && N > 128 && M >= 1 << 19 && (M <= 1 << 21 || K % 32 == 0);
+    if (steps == 2) return M <= 1 << 16 || (w == 1 && K < 48 && fewer);
+    if (M < 1 << 19 || w == 1) return false;
+    if (w == 2) return (steps != 3 || lines || N <= 48) && steps != 5 && steps != 6;
+    return steps >= 4 && (lines || (N % 128 >= 32 && (steps > 4 || N < 96 || N > 128)));
+}
+
+// Wavefronts of a block that keeps the parts of its columns, or 0 where blocks pass them through LDS.
+int kept_waves_per_block(int tb, int64_t M, int64_t N, int64_t K, int w, int steps) {
+    if (!kept_pays(tb, M, N, K, w, steps)) return 0;
     const size_t room = 160 * 1024, own = 4096;            // a block's scales and ranges: at most 2 KB
     const int64_t tiles_n = ceil_div(N, 32 * w);
-    for (int kept = 4; kept <= kept_waves(w); kept = w > 1 && kept == 4 ? 6 : 2 * kept) {
+    for (int kept : {4, kept_waves(w)}) {
         const int on_cu = kept_waves(w) / kept;
         if (((size_t)w * steps * kStepBytes + own) * on_cu <= room && tiles_n <= 32 * on_cu) return kept;
     }
@@ -556,7 +577,7 @@ gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const fl
     g.parts = ws; g.parts2 = ws2;
     Range *range = reinterpret_cast<Range *>(ws + words), *range2 = reinterpret_cast<Range *>(ws2 + words);
     g.range = range; g.range2 = range2;
-    const int steps = A2 ? 2 * g.steps : g.steps, kept = a_bits ? 0 : kept_waves_per_block(M, N, w, steps);
+    const int steps = A2 ? 2 * g.steps : g.steps, kept = a_bits ? 0 : kept_waves_per_block(tb, M, N, K, w, steps);
     if (kept) {
         const int64_t per_xcd = ceil_div(ceil_div(M, 32), 8);
         int64_t groups = 32 * (kept_waves(w) / kept) / g.tiles_n;      // blocks of an XCD that share a column tile
@@ -566,9 +587,7 @@ gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const fl
 #define KEPT_CASE(NT_, KEPT_)                                                                              \
         if (w == NT_ && kept == KEPT_)                                                                     \
             hipLaunchKernelGGL((gemm_split_kernel<NT_, false, KEPT_>), grid, dim3(64 * KEPT_), lds, st, g);
-        KEPT_CASE(1, 4)
-        KEPT_CASE(2, 4) KEPT_CASE(2, 6) KEPT_CASE(2, 12)
-        KEPT_CASE(4, 4) KEPT_CASE(4, 6) KEPT_CASE(4, 12)
+        KEPT_CASE(1, 4) KEPT_CASE(2, 4) KEPT_CASE(2, 12) KEPT_CASE(4, 4) KEPT_CASE(4, 12)
 #undef KEPT_CASE
         return launch_status();
     }
