@@ -1,5 +1,6 @@
-"""Products whose blocks keep the parts of their columns: from 2^19 rows on, and one or two steps of few columns; several tiles
-a wavefront, ragged ends, several column tiles, values that the parts cannot hold, two operand pairs."""
+"""Products on split parts around the lines between blocks that keep the parts of their columns and blocks that do not (which is which
+is tested in test_gpu_gemm_routes.py): several tiles a wavefront, ragged ends, several column tiles, values that the parts cannot
+hold, two operand pairs."""
 import pytest
 import torch
 
@@ -27,11 +28,12 @@ def test_against_float64(M, N, K, tb):
     bound = (8 * ((K + 15) // 16) + 4) * 2.0 ** -24 * (A.abs().double() @ Bm.abs().double())
     assert bool(((product(M, N, K, A, Bm, tb).double() - ref).abs() <= bound).all())
     bound += 2.0 ** -22 * (ref.abs() + bias.abs() + held.abs())
+    # a ReLU decides signs: the same shape on the fp32 instruction
     assert bool(((product(M, N, K, A, Bm, tb, bias, 1).double() - torch.relu(ref + bias)).abs() <= bound).all())
     assert bool(((product(M, N, K, A, Bm, tb, bias, 4, held.clone()).double() - (ref + bias + held)).abs() <= bound).all())
 
 
-@pytest.mark.parametrize("M,N,K", [(BIG, 64, 70), (BIG, 130, 40), (70000, 40, 60)])
+@pytest.mark.parametrize("M,N,K", [(BIG, 64, 70), (BIG, 130, 40), (70000, 40, 60), (60000, 40, 60), (BIG, 160, 100), (BIG, 47, 300)])
 def test_values_the_parts_cannot_hold(M, N, K):
     gen = torch.Generator(device="cuda").manual_seed(N)
     A, Bm = torch.randn(M, K, generator=gen, device="cuda"), torch.randn(K, N, generator=gen, device="cuda").abs() + 0.5

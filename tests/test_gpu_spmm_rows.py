@@ -1,5 +1,5 @@
 """The product with a wavefront per row: widths that fill lanes or not, rows around what wavefronts share, counts of rows around
-a block's, both sides of the lines to the segments, with and without expanded rows, against float64."""
+a block's, many entries, with and without expanded rows, against float64.  (The lines to the segments: test_gpu_spmm_hubs_small.py.)"""
 import pytest
 import torch
 
