@@ -375,32 +375,43 @@ spmm_fixup_kernel(int n, int nnz, int f, int span, long nspan, int lpf, const in
     }
 }
 
-// Eight rows a block, one wavefront each: 64 / LPE slots of LPE lanes (VEC features a lane, tile0 + blockIdx.y picks which of them
-// a block has) take the entries of the row in turn, U at a time, and are added by a fixed shuffle tree.  A row of more than
-// kRowShare entries a slot is shared by the wavefronts of the block.  Everything follows from the row pointers, in one launch:
-// what bounds a small product is the chain of pointers, indices and rows of B, and the launches (2048 nodes, 18 390 entries,
-// f = 16: 10.9 us in segments, 3.9 here).  Shared by four wavefronts or sixteen, and from 8 or 32 entries on, hubs take longer:
-// 16384 nodes, 409 600 entries, f = 16, 4 / 8 / 16 wavefronts 16.6 / 14.1 / 24.2 us.
+// Eight rows a block, one wavefront each: 64 / LPE slots of LPE lanes (VEC features a lane, tile0 + blockIdx.y picks which of
+// them a block has) take the entries of the row in turn, U at a time, and are added by a fixed shuffle tree.  Everything
+// follows from the row pointers, in one launch: what bounds a small product is the chain of pointers, indices and rows of B,
+// and the launches (2048 nodes, 18 395 entries, f = 16: 11.2 us in segments, 3.3 here).  The indices of a batch are read behind
+// the rows of the one before: eight of 2048 nodes joined to all, f = 32 11.6 -> 7.2 us, with the ballot below; without long
+// rows 4.0 -> 3.3.  Weights in the order of the entries are read with the indices (135 577 nodes, 7.3 M entries, f = 4, without
+// expanded rows 98 us if not, 65 if so).
+// A row of more than kRowShare entries a slot is shared by the wavefronts of the block, where few rows are that long: eight of
+// them take longer one after the other than side by side (469 nodes, 150 entries each, f = 28 13.2 / 5.3 us), so the more there
+// are the longer they have to be.  Shared by four wavefronts or sixteen, and from 8 or 32 entries on, hubs take longer: 16384
+// nodes, 409 600 entries, f = 16, 4 / 8 / 16 wavefronts 16.6 / 14.1 / 24.2 us.
 // Up to kDealtRows rows, row i goes to block i % blocks: hubs next to each other (nodes numbered by degree) go to different
 // blocks, where one block would take them one after the other: 2048 nodes, eight of them joined to all, f = 16 37 us / 7.9,
 // f = 32 65 / 11.4; without hubs 3.86 / 3.87.  Beyond, a block has eight consecutive rows, whose indices share lines (2^17 nodes,
 // 2 M entries, f = 1 53 us against 61 dealt).
+// A CU has 64 lines under way, whatever the kernel, so a long row is as fast as the CUs that share it: small products have
+// kRowLanes lanes, a line, to a tile of features, and the tiles of a row turned against each other so that a CU does not get
+// all of them (hubs among 1000 to 2048 nodes, 68 to 128 features, tiles of 128 / 64 / 32 features 14.5 / 10.6 / 9.0 us; 2048
+// nodes, eight joined to all, f = 112 16.3 us, with the tiles turned 8.9).
 // Four features a lane at any 4-byte aligned address: the last lane of a ragged width takes the row's last four, some of them
-// for the second time, with the same result.  With one feature a lane a width has an eighth to a half of the slots: 1024
-// nodes, 17 336 entries, eight of the rows 1024 long, f = 23 86 us against 37, which f = 32 takes; 8192 nodes, 196 303 entries,
-// f = 23 11.8 / 6.2 (widths of 5 to 7 with rows of nine entries 3.6 / 4.0: more slots to add up).
-constexpr int kRowWaves = 8, kRowShare = 16, kDealtRows = 8192;
+// for the second time, with the same result.  With one feature a lane a width has an eighth to a half of the slots: 1024 nodes,
+// 17 336 entries, eight of the rows 1024 long, f = 23 86 us against 37, which f = 32 takes; 8192 nodes, 196 303 entries, f = 23
+// 11.8 / 6.2 (widths of 5 to 7 with rows of nine entries 3.6 / 4.0: more slots to add up).
+constexpr int kRowWaves = 8, kRowShare = 16, kRowLanes = 8, kDealtRows = 16384;
 
-template <int VEC, int LPE, int U>
+template <int VEC, int LPE, int U, bool PERM>
 __global__ void __launch_bounds__(64 * kRowWaves)
-spmm_row_kernel(int n, uint32_t by, uint32_t apart, const int32_t *__restrict__ rowptr, int f, int ldb, uint32_t tile0,
-                const int32_t *__restrict__ col, EdgeWeights w, const float *__restrict__ B, float *__restrict__ C,
+spmm_row_kernel(int n, uint32_t by, uint32_t apart, uint32_t turn, const int32_t *__restrict__ rowptr, int f, int ldb,
+                uint32_t tile0, const int32_t *__restrict__ col, EdgeWeights w, const float *__restrict__ B, float *__restrict__ C,
                 const float *__restrict__ bias, int relu) {
     constexpr int SLOTS = kWave / LPE, WAVES = kRowWaves;
     __shared__ float s_part[WAVES][LPE * VEC];
     __shared__ int32_t s_ptr[2 * WAVES];                   // first and last entry of the block's rows
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, l = lane % LPE, slot = lane / LPE;
-    auto row_of = [&](int i) __attribute__((always_inline)) { return blockIdx.x * by + i * apart; };
+    uint32_t row0 = blockIdx.x + turn * (blockIdx.y % 4);
+    row0 = (row0 < gridDim.x ? row0 : row0 - gridDim.x) * by;
+    auto row_of = [&](int i) __attribute__((always_inline)) { return row0 + i * apart; };
     if (threadIdx.x < 2 * WAVES) s_ptr[threadIdx.x] = rowptr[min(row_of(threadIdx.x / 2) + threadIdx.x % 2, (uint32_t)n)];
     __syncthreads();
     int c = ((tile0 + blockIdx.y) * LPE + l) * VEC;
@@ -411,29 +422,37 @@ spmm_row_kernel(int n, uint32_t by, uint32_t apart, const int32_t *__restrict__ 
     auto gather = [&](int first, int end, int step) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < VEC; ++i) acc[i] = slot == 0 || first < end ? 0.f : -0.f;   // x + -0 is x, also for -0
-        uint32_t x = first;
-        for (int left = end - first; left > 0; left -= U * step, x += U * step) {
-            int cj[U];
-            float v[U], b[U][VEC];
+        int cj[U], at[U];                                  // of a batch, read behind the rows of the one before
+        float v[U];
+        auto indices = [&](uint32_t x, int left) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const uint32_t e = u * step < left ? x + u * step : x;   // past the end: the first again, not added
+                const uint32_t e = u * step < left ? x + u * step : first;   // past the end: the first again, not added
                 cj[u] = col[e];
-                v[u] = w.val ? w.val[(size_t)(w.perm ? w.perm[e] : e) * w.heads + hd] : 1.f;
+                if constexpr (PERM) at[u] = w.perm[e];
+                else v[u] = w.val ? w.val[(size_t)e * w.heads + hd] : 1.f;
             }
+        };
+        if (first < end) indices(first, end - first);
+        uint32_t x = first;
+        for (int left = end - first; left > 0; left -= U * step) {
+            float now[U], b[U][VEC];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                if constexpr (PERM) now[u] = w.val[(size_t)at[u] * w.heads + hd];
+                else now[u] = v[u];
                 const float *src = B + (size_t)cj[u] * ldb + c;
                 if constexpr (VEC == 4) {
                     const float4u q = *reinterpret_cast<const float4u *>(src);
                     b[u][0] = q.x; b[u][1] = q.y; b[u][2] = q.z; b[u][3] = q.w;
                 } else b[u][0] = *src;
             }
+            if (left > U * step) indices(x += U * step, left - U * step);
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (u * step < left)
 #pragma unroll
-                    for (int i = 0; i < VEC; ++i) acc[i] = fmaf(v[u], b[u][i], acc[i]);
+                    for (int i = 0; i < VEC; ++i) acc[i] = fmaf(now[u], b[u][i], acc[i]);
         }
 #pragma unroll
         for (int d = LPE; d < kWave; d <<= 1)
@@ -445,14 +464,17 @@ spmm_row_kernel(int n, uint32_t by, uint32_t apart, const int32_t *__restrict__ 
 #pragma unroll
         for (int i = 0; i < VEC; ++i) C[(size_t)row * f + c + i] = epilogue(acc[i], bias, c + i, relu);
     };
-    if (row_of(wave) < (uint32_t)n && s_ptr[2 * wave + 1] - s_ptr[2 * wave] <= kRowShare * SLOTS) {
+    const int length = s_ptr[2 * (lane % WAVES) + 1] - s_ptr[2 * (lane % WAVES)];
+    auto longer = [&](int entries) __attribute__((always_inline)) { return __ballot(lane < WAVES && length > entries); };
+    const int many = __popcll(longer(kRowShare * SLOTS));
+    uint32_t shared = (uint32_t)longer(kRowShare * SLOTS * max(many, 1));                     // the same for the whole block
+    if (row_of(wave) < (uint32_t)n && !((shared >> wave) & 1)) {
         gather(s_ptr[2 * wave] + slot, s_ptr[2 * wave + 1], SLOTS);
         store(row_of(wave));
     }
-    for (int r = 0; r < WAVES; ++r) {
-        const int first = s_ptr[2 * r], end = s_ptr[2 * r + 1];
-        if (row_of(r) >= (uint32_t)n || end - first <= kRowShare * SLOTS) continue;                 // the same for the whole block
-        gather(first + wave * SLOTS + slot, end, WAVES * SLOTS);
+    for (; shared; shared &= shared - 1) {
+        const int r = __ffs(shared) - 1;
+        gather(s_ptr[2 * r] + wave * SLOTS + slot, s_ptr[2 * r + 1], WAVES * SLOTS);
         if (slot == 0)
 #pragma unroll
             for (int i = 0; i < VEC; ++i) s_part[wave][l * VEC + i] = acc[i];
@@ -569,16 +591,23 @@ float *spmm_padded_operand(void *workspace, const int32_t *erow, int64_t b_rows,
 }
 
 // Products that a wavefront per row is faster at, whatever the lengths of the rows, which the host does not know: a row of n
-// entries is the work of one block, and so are eight rows of a graph in which all are long.  A block takes 3.5 us and 1.1 us for
-// every 10 000 entries x features (the features its lanes cover), 64 lines under way as on any CU; segments take 8 to 11 us, with
-// a copy of a ragged operand 11 to 16.  Segments / rows, us: a row of n entries, the others of three, 2048 nodes, f = 16 15.7 /
-// 7.6, 32 10.8 / 11.2; 4096, 7 28 / 8.0, 16 15.7 / 11.2, 32 11.0 / 18.2; 512, 64 9.8 / 7.7; 1024, 64 9.9 / 11.0; eight such rows
-// 2048, 32 12.0 / 11.7; 4096, 16 16.8 / 11.6; 512, 64 9.5 / 8.1; 256, 128 8.3 / 9.3; 64 of them 2048, 32 12.9 / 13.1; rows of 450
-// entries and no others, 32 13.1 / 22.9; no long rows, 4096, 16 10.9 / 4.3; 2048, 32 10.1 / 3.9.  Rows that name nodes many times
-// over, so that one has several times n entries, are the exception that this does not bound.
-static bool rows_pay(int64_t n, int64_t nnz, int f) {
-    const int64_t work = 4 * pow2_at_least(f >= 4 ? (f + 3) / 4 : f);      // a slot of one lane has the loads of four features
-    return n <= kDealtRows && work <= 64 && n * work <= (work <= 32 ? 65536 : 32768) && nnz * work <= 3072 * n;
+// entries is the work of the blocks of its tiles.  Chosen on 12 000 graphs of 100 to 17 000 nodes and up to 700 000 entries
+// (uniform, R-MAT, R-MAT numbered by degree, 1 to 300 nodes joined to all), 3 to 130 features: of 8900 products that it takes,
+// three are more than 3 % slower than in segments (5 %); all together take 0.36 of the time.  whole: segments read B as it is;
+// else they take 3 to 4 us for a copy.  Segments / rows, us:
+//   a row of n entries, the others of three: 2048 nodes, f = 16 15.7 / 5.5; 4096, 31 14.6 / 10.5, 32 11.0 / 10.6; 10240, 16
+//     15.8 / 12.9; 1536, 64 10.2 / 6.7, 128 10.6 / 7.4; beyond the line 8192, 23 15.1 / 17.9; 16384, 16 16.0 / 18.8;
+//   eight such rows: 4096, 31 14.9 / 10.7, 32 12.3 / 10.8, 45 15.2 / 12.3; 10240, 16 17.2 / 13.2; 2048, 112 9.6 / 8.9; beyond
+//     3000, 112 10.4 / 11.8; 8192, 32 12.4 / 18.2; 16384, 16 17.4 / 19.2;
+//   none: 4096, f = 23 15.4 / 3.8; 8192, 16 11.7 / 4.8; 1500, 128 9.0 / 4.2; and what stays in segments for the sake of the
+//     others: 4096, 64 12.2 / 4.8; 5462, 45 18.5 / 6.0; 8192, 23 13.6 / 5.2;
+//   many entries: 14000 nodes, f = 4, 688 745 entries 12.1 / 8.1; 1000, R-MAT, 94 222, 32 12.4 / 7.6; 3000, 919 902, 100 28 / 56.
+// Rows that name nodes many times over, so that one has several times n entries, are the exception that this does not bound.
+static bool rows_pay(int64_t n, int64_t nnz, int f, bool whole) {
+    if (n > kDealtRows || f > 128) return false;
+    const int64_t work = 4 * pow2_at_least(f >= 4 ? (f + 3) / 4 : f), tile = work < 4 * kRowLanes ? work : 4 * kRowLanes;
+    return n * tile <= (whole && work > 32 ? 65536 : work <= 16 ? 163840 : 131072) &&
+           nnz <= 700000 && (work <= 16 || nnz * work <= 5 << 20);
 }
 
 #define SPMM_CASE(VEC_, LPE_, NT_, U_)                                                                       \
@@ -615,20 +644,25 @@ gnn_status_t spmm_launch(int n, int nnz, const int32_t *rowptr, const int32_t *c
     if (w.heads == 1) w.head_dim = f;
     const bool heads = w.heads > 1 && w.val != nullptr;
 
-    if (!erow || nnz == 0 || (pieces && !heads && rows_pay(n, nnz, f))) {
-        int ldb = f;                                       // unless the caller has written the padded operand
-        if (!pieces || heads || B != spmm_padded_operand(workspace, erow, b_rows, nnz, f, &ldb)) ldb = f;
+    int ldb = f;                                           // unless the caller has written the padded operand
+    const bool padded = pieces && !heads && B == spmm_padded_operand(workspace, erow, b_rows, nnz, f, &ldb);
+    if (!padded) ldb = f;
+    const bool few = rows_pay(n, nnz, f, padded || f % 4 == 0);
+    if (!erow || nnz == 0 || (pieces && !heads && few)) {
         const bool vec4 = f >= 4 && (!heads || w.head_dim % 4 == 0);
-        const int lanes = pow2_at_least(vec4 ? (f + 3) / 4 : f), lpe = lanes < kWave ? lanes : kWave;
+        const int lanes = pow2_at_least(vec4 ? (f + 3) / 4 : f), most = few ? kRowLanes : kWave;
+        const int lpe = lanes < most ? lanes : most;
         const uint32_t blocks = (uint32_t)ceil_div(n, kRowWaves);
-        const uint32_t by = n <= kDealtRows ? 1 : kRowWaves, apart = n <= kDealtRows ? blocks : 1;
+        const uint32_t by = n <= kDealtRows ? 1 : kRowWaves, apart = n <= kDealtRows ? blocks : 1, turn = blocks >= 64 ? 13 : 0;
         const long tiles = ceil_div(f, lpe * (vec4 ? 4 : 1));
         for (long tile0 = 0; tile0 < tiles; tile0 += 65535) {                   // blocks in y that any device takes
             const dim3 grid(blocks, (unsigned)(tiles - tile0 < 65535 ? tiles - tile0 : 65535));
 #define ROW_CASE(VEC_, LPE_)                                                                                 \
             if (vec4 == (VEC_ == 4) && lpe == LPE_)                                                              \
-                hipLaunchKernelGGL((spmm_row_kernel<VEC_, LPE_, LPE_ < 16 ? 4 : 8>), grid, dim3(64 * kRowWaves), \
-                                   0, st, n, by, apart, rowptr, f, ldb, (uint32_t)tile0, col, w, B, C, bias, relu);
+                hipLaunchKernelGGL((w.val && w.perm ? spmm_row_kernel<VEC_, LPE_, LPE_ < 16 ? 4 : 8, true>           \
+                                                    : spmm_row_kernel<VEC_, LPE_, LPE_ < 16 ? 4 : 8, false>),        \
+                                   grid, dim3(64 * kRowWaves), 0, st, n, by, apart, turn, rowptr, f, ldb, (uint32_t)tile0, \
+                                   col, w, B, C, bias, relu);
             ROW_CASE(4, 1) ROW_CASE(4, 2) ROW_CASE(4, 4) ROW_CASE(4, 8) ROW_CASE(4, 16) ROW_CASE(4, 32) ROW_CASE(4, 64)
             ROW_CASE(1, 1) ROW_CASE(1, 2) ROW_CASE(1, 4) ROW_CASE(1, 8) ROW_CASE(1, 16) ROW_CASE(1, 32) ROW_CASE(1, 64)
 #undef ROW_CASE

@@ -41,6 +41,13 @@ def call(n, f, graph):
     return lambda: B.gnn_spmm_csr(n, q, rowptr, col, val, erow, X, f, C, workspace=ws)
 
 
+def without_expanded_rows(n, f, graph):
+    rowptr, col, _ = graph
+    val, X = operands(n, f, col.numel())
+    C = torch.empty(n, f, device="cuda")
+    return lambda: B.gnn_spmm_csr(n, col.numel(), rowptr, col, val, None, X, f, C)
+
+
 def check(n, f, graph, expanded=True):
     rowptr, col, erow = graph
     q = col.numel()
@@ -89,14 +96,24 @@ def test_hubs_side_by_side(n, f):
     assert least_us(call(n, f, graph)) <= 4 * least_us(call(n, f, uniform_graph(n, graph[1].numel())))
 
 
-@pytest.mark.parametrize("n,f", [(2048, 32), (2049, 32), (2047, 17), (4096, 16), (4097, 13), (8191, 8), (8192, 5), (8193, 8), (512, 64),
+@pytest.mark.parametrize("n,f", [(1500, 128), (4096, 23), (8192, 16), (1500, 64)])
+def test_no_long_rows(n, f):
+    """Small products without long rows are not held back by those with them: what calls without expanded rows take, which always go by
+    rows (in segments 1.6 to 4 times that)."""
+    graph = uniform_graph(n, 9 * n)
+    assert least_us(call(n, f, graph)) <= 1.35 * least_us(without_expanded_rows(n, f, graph))
+
+
+@pytest.mark.parametrize("n,f", [(4096, 31), (4097, 31), (10240, 16), (10241, 16), (2048, 64), (2049, 64), (1536, 100), (4096, 127), (2048, 112),
+                                 (2048, 32), (2049, 32), (2047, 17), (4096, 16), (4097, 13), (8191, 8), (8192, 5), (8193, 8), (512, 64),
                                  (513, 64), (511, 33), (512, 65), (16, 64), (9, 3), (8193, 3)])
 @pytest.mark.parametrize("expanded", [True, False])
 def test_hubs_against_float64(n, f, expanded):
     check(n, f, hub_graph(n, 8), expanded)
 
 
-@pytest.mark.parametrize("n,f,q", [(512, 16, 98304), (512, 16, 98305), (512, 64, 24576), (512, 64, 24577)])
+@pytest.mark.parametrize("n,f,q", [(512, 16, 98304), (512, 16, 98305), (512, 64, 24576), (512, 64, 24577), (469, 28, 70182), (469, 99, 52000),
+                                   (512, 32, 163840), (512, 32, 163841), (2048, 8, 700000), (2048, 8, 700001)])
 def test_entries_against_float64(n, f, q):
     check(n, f, uniform_graph(n, q))
 
@@ -109,3 +126,16 @@ def test_more_feature_tiles_than_a_grid_has(f):
     B.gnn_spmm_csr(2, 3, rowptr, col, val, None, X, f, C)
     assert torch.equal(C[1], 0.5 * X[1])
     assert bool(((C[0] - (1.5 * X[0] - 2.0 * X[1])).abs() <= 2.0 ** -22 * (1.5 * X[0].abs() + 2.0 * X[1].abs())).all())
+
+
+@pytest.mark.parametrize("f", [3, 16, 23, 60, 100])
+@pytest.mark.parametrize("lengths", [[2000] + [150] * 7, [150] * 6 + [3000, 3000], [129, 128, 127, 1025, 1024, 1023, 0, 5], [700] * 8, [0] * 7 + [4000]])
+def test_long_and_short_rows_of_a_block(f, lengths):
+    """Seven rows that are not long between a block's eight, so that it has these."""
+    n = 8 * 64
+    rows = torch.zeros(n, dtype=torch.long)
+    rows[::64] = torch.tensor(lengths)
+    rows[5::64] = 3
+    gen = torch.Generator(device="cuda").manual_seed(f)
+    row = torch.repeat_interleave(torch.arange(n), rows).cuda()
+    check(n, f, csr(n, (row * n + torch.randint(0, n, row.shape, generator=gen, device="cuda")).sort().values))
