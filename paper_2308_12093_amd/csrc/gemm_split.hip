@@ -508,29 +508,31 @@ size_t parts_bytes(int64_t N, int64_t K) {
 
 // Whether blocks that keep the parts of their columns are the faster.  Those that pass them through LDS start their tiles as
 // slots come free, and the blocks of one row's columns run side by side; where a block has its columns for good, these drift
-// apart, which costs where they share lines of C.  Fitted to 7300 shapes; step by step / kept in us, t: B transposed.
-//   One step, up to 2^19 rows: 60000 x 16 -> 128 14.3 / 12.3, 2^17 22.6 / 19.4; not rows of C that begin within a line where C
-//     is larger than the memory-side cache (2^18 x 4 -> 400 106 / 113, 2^19 x 4 -> 300 160 / 208), nor B in rows of 32 floats,
-//     which a block reads a line per lane (t 90000 x 32 -> 128 19.5 / 21.2, 2^17 x 32 -> 16 10.3 / 10.6).
-//   One step, more rows: short reductions, 2^20 x 16 -> 96 137 / 110, 2^22 x 10 -> 47 285 / 241; 2^22 x 16 -> 64 264 / 266, 2^20 x
-//     32 -> 128 133 / 145; rows of C that begin within a line as above (2^22 x 4 -> 259 1128 / 1747, x 32 -> 100 529 / 756).
-//   Two steps: 60000 x 64 -> 64 12.6 / 11.5, x 48 -> 16 9.2 / 7.5; t 2^17 x 48 -> 64 18.6 / 20.1, 2^20 x 48 -> 30 73.7 / 80.4;
-//     several whole lines of C a row 2^20 x 48 -> 192 288 / 282, 2^22 1118 / 1146, 2^22 x 64 -> 256 1364 / 1342.
-//   More, from 2^19 rows on: 2^17 x 128 -> 128 39 / 49, 2^19 147 / 148, 2^20 281 / 262, 100 -> 256 540 / 501, 128 -> 64 179 / 164;
-//     not a third step into more than 64 columns (2^20 x 96 -> 352 620 / 716), a fifth and sixth into fewer (2^20 x 160 -> 64
-//     210 / 240), last tiles of a few columns (2^22 x 128 -> 130 1769 / 2023), nor four steps into one nearly whole, ragged tile
-//     (2 588 361 x 112 -> 117 751 / 804).
+// apart, which costs where they share lines of C and the caches no longer hold what was written of them.  Chosen on 18 000
+// shapes, into buffers that the caches hold and into others: the time is 1.01 of the better of the two, 0.93 of that of blocks
+// that pass the parts on and store column tile by column tile.  Step by step / kept, us, other buffers each time; t: B
+// transposed.
+//   One step, C up to 134 MB: 60000 x 16 -> 128 14.9 / 13.1, 2^17 33 / 22; not B in rows of 32 floats, which a block reads a line
+//     per lane, for 128 columns (t 90000 x 32 -> 128 21.5 / 22.7).
+//   More of C: few columns, 2^22 x 10 -> 47 288 / 244, x 16 -> 64 265 / 269, 2^22 x 20 -> 30 176 / 193, 2^21 x 32 -> 64 153 / 168;
+//     rows that begin with a line, 2^20 x 16 -> 96 137 / 109, x 24 -> 128 135 / 137, x 32 135 / 149, or with half a line, up to
+//     335 MB, 2^19 x 16 -> 80 67 / 61; others 2^19 x 16 -> 83 71 / 83, x 4 -> 300 161 / 209, 2^22 x 4 -> 259 1132 / 1749.
+//   Two steps: 60000 x 64 -> 64 14.5 / 13.4, x 48 -> 16 10.1 / 8.5; t 2^17 x 48 -> 64 21.8 / 23.9, 2^20 x 48 -> 30 77.5 / 82.7;
+//     several whole lines of C a row 2^20 x 48 -> 192 296 / 278, 2^22 x 64 -> 256 1365 / 1321; -> 100 180 / 210.
+//   More, from 2^19 rows on: 2^17 x 128 -> 128 47 / 53, 2^19 150 / 148, 2^20 289 / 273, 100 -> 256 539 / 507, 128 -> 64 181 / 166,
+//     96 -> 96 225 / 208; not a third step into ragged rows (90 -> 100 261 / 268), nor last tiles of a few columns (2^22 x 128 ->
+//     130 1730 / 2006) or four steps into nearly whole ones (2 588 361 x 112 -> 117 759 / 801), nor up to 32 columns (2^20 x 300 ->
+//     30 331 / 333).
 bool kept_pays(int tb, int64_t M, int64_t N, int64_t K, int w, int steps) {
-    const bool lines = N % 32 == 0, near = M * N <= 5 << 24, fewer = M <= 1 << 20;      // near: 335 MB of C
-    if (steps == 1 && M <= 1 << 19) return (w < 4 || lines || near) && !(tb && K == 32 && (w == 4 || M > 1 << 16));
-    if (steps == 1 && w == 1) return K <= (N <= 16 ? 31 : 16);
-    if (steps == 1 && w == 2) return N == 64 ? K <= (fewer ? 20 : 16) : fewer ? K < 32 : K <= 20 && N <= 48;
-    if (steps == 1) return !lines ? near && K <= 16 : K <= (fewer ? (N % 128 ? 32 : 24) : N == 128 ? 16 : 24);
-    if (steps == 2 && w == 4) return lines && N > 128 && M >= 1 << 19 && (M <= 1 << 21 || K % 32 == 0);
-    if (steps == 2) return M <= 1 << 16 || (w == 1 && K < 48 && fewer);
-    if (M < 1 << 19 || w == 1) return false;
-    if (w == 2) return (steps != 3 || lines || N <= 48) && steps != 5 && steps != 6;
-    return steps >= 4 && (lines || (N % 128 >= 32 && (steps > 4 || N < 96 || N > 128)));
+    const bool line = N % 32 == 0, half = N % 16 == 0, many = M >= 1 << 19;
+    if (steps == 1) {
+        if (M * N <= 1 << 25) return !(tb && K == 32 && w == 4);
+        if (w < 4) return N <= 16 || K <= (half || w == 1 ? 16 : 12);
+        return K <= 24 && (line || (half && M * N <= 5 << 24));
+    }
+    if (steps == 2) return w == 4 ? line && N > 128 && many : M <= (w == 2 ? 1 << 16 : K > 48 ? 1 << 18 : 1 << 19);
+    if (w == 1 || !many) return false;
+    return line || (w == 2 ? steps > 3 : N % 128 >= 32 && steps > (N % 128 < 96 ? 3 : 4));
 }
 
 // Wavefronts of a block that keeps the parts of its columns, or 0 where blocks pass them through LDS.
@@ -538,7 +540,7 @@ int kept_waves_per_block(int tb, int64_t M, int64_t N, int64_t K, int w, int ste
     if (!kept_pays(tb, M, N, K, w, steps)) return 0;
     const size_t room = 160 * 1024, own = 4096;            // a block's scales and ranges: at most 2 KB
     const int64_t tiles_n = ceil_div(N, 32 * w);
-    for (int kept : {4, kept_waves(w)}) {
+    for (int kept : {4, w == 1 ? 4 : 12}) {                // what the launch has
         const int on_cu = kept_waves(w) / kept;
         if (((size_t)w * steps * kStepBytes + own) * on_cu <= room && tiles_n <= 32 * on_cu) return kept;
     }
@@ -584,12 +586,15 @@ gnn_status_t gemm_split_launch(int tb, int64_t M, int64_t N, int64_t K, const fl
         if (groups > ceil_div(per_xcd, kept)) groups = ceil_div(per_xcd, kept);
         const dim3 grid((unsigned)(8 * groups * g.tiles_n));
         const size_t lds = (size_t)w * steps * kStepBytes;
+        bool launched = false;
 #define KEPT_CASE(NT_, KEPT_)                                                                              \
-        if (w == NT_ && kept == KEPT_)                                                                     \
-            hipLaunchKernelGGL((gemm_split_kernel<NT_, false, KEPT_>), grid, dim3(64 * KEPT_), lds, st, g);
+        if (w == NT_ && kept == KEPT_) {                                                                   \
+            hipLaunchKernelGGL((gemm_split_kernel<NT_, false, KEPT_>), grid, dim3(64 * KEPT_), lds, st, g);  \
+            launched = true;                                                                               \
+        }
         KEPT_CASE(1, 4) KEPT_CASE(2, 4) KEPT_CASE(2, 12) KEPT_CASE(4, 4) KEPT_CASE(4, 12)
 #undef KEPT_CASE
-        return launch_status();
+        return launched ? launch_status() : GNN_ERR_UNSUPPORTED;
     }
     hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)(g.tiles_n * w), A2 ? 2 : 1), dim3(1024), 0, st, (int)N,
                        (int)K, g.steps, g.B, g.B2, ws, ws2, range, range2);

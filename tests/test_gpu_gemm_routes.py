@@ -30,23 +30,26 @@ def gemm(tb, M, N, K):
 
 @pytest.mark.parametrize("tb,M,N,K", [
     (0, 1 << 18, 400, 4), (1, 1 << 20, 300, 4), (0, 1 << 20, 336, 20), (1, 1 << 20, 200, 32), (0, 1 << 20, 100, 32),   # shared lines
-    (1, 1 << 17, 128, 32), (1, 90000, 16, 32),                                                # B in rows of 32 floats
-    (0, 1 << 20, 128, 32), (0, 1 << 21, 64, 20), (1, 1 << 21, 30, 20),                        # one step, many rows
+    (0, 420000, 83, 16), (1, 1 << 19, 176, 24), (1, 1 << 20, 47, 30), (0, 1 << 21, 30, 20), (0, 1 << 20, 60, 16),
+    (1, 1 << 17, 128, 32), (1, 90000, 100, 32),                                               # B in rows of 32 floats
+    (0, 1 << 20, 128, 32), (0, 1 << 21, 64, 20),                                              # one step, much of C
     (1, 1 << 17, 64, 48), (0, 1 << 20, 30, 48), (0, 1 << 20, 100, 48), (0, 1 << 19, 128, 64),  # two
-    (0, 1 << 20, 352, 96), (1, 1 << 20, 64, 160), (0, 1 << 20, 259, 128)])
+    (0, 1 << 20, 100, 90), (0, 1 << 20, 259, 128), (0, 1 << 20, 117, 112), (1, 1 << 20, 30, 301), (0, 1 << 18, 256, 100)])
 def test_step_by_step(tb, M, N, K):
     assert launches(gemm(tb, M, N, K)) == 2
 
 
 @pytest.mark.parametrize("tb,M,N,K", [
-    (0, 60000, 128, 16), (1, 60000, 336, 20), (0, 1 << 17, 128, 32), (1, 60000, 30, 48), (0, 60000, 64, 64), (0, 1 << 20, 96, 16),
-    (1, 1 << 20, 47, 30), (0, 1 << 20, 192, 48), (0, 1 << 20, 256, 100), (1, 1 << 20, 352, 190), (0, 1 << 19, 64, 400)])
+    (0, 60000, 128, 16), (1, 60000, 336, 20), (0, 1 << 17, 128, 32), (1, 60000, 30, 50), (0, 60000, 64, 64), (0, 1 << 20, 96, 16),
+    (0, 400000, 83, 16), (0, 1 << 19, 80, 16), (1, 1 << 20, 47, 10), (0, 1 << 22, 16, 30), (1, 1 << 21, 30, 15), (0, 1 << 18, 16, 48),
+    (0, 1 << 20, 192, 48), (0, 1 << 20, 256, 100), (1, 1 << 20, 352, 190), (0, 1 << 20, 352, 96), (0, 1 << 19, 64, 400),
+    (1, 1 << 20, 60, 160), (0, 1 << 20, 100, 160)])
 def test_kept(tb, M, N, K):
     assert launches(gemm(tb, M, N, K)) == 1
 
 
 # (BIG, 64, 80) and so on: all block shapes that keep parts, of every width
-SHAPES = [(66001, 24, 20), (60001, 30, 40), (BIG, 64, 80), (BIG, 47, 250), (131100, 128, 16), (BIG, 160, 48), (BIG, 256, 100),
+SHAPES = [(66001, 24, 20), (60001, 30, 42), (BIG, 64, 80), (BIG, 47, 250), (131100, 128, 16), (BIG, 160, 48), (BIG, 256, 100),
           (BIG, 100, 170), (70001, 130, 25)]
 
 
