@@ -836,19 +836,22 @@ bool few_share(int64_t M, int64_t N, int64_t K) { return K >= 64 && ceil_div(M, 
 
 // Where the fp32 instruction is faster than split parts all the same (K: indices of all operand pairs; aligned rows).  fp32 /
 // parts in us, other buffers each time, tb where B is [N][K] and the fp32 kernel needs no launch before it:
-//   32 columns, a whole tile: tb but for the shortest reductions (65536 x 16 6.8 / 7.6, x 64 10.1 / 11.6, x 128 13.2 / 17.5, 2^20
-//     x 16 47.6 / 50.9, x 128 139 / 149; up to 8 indices 1.08 over all shapes); else A from 64 MB on (2^18 x 100 41 / 45, 2^20 x 100
-//     136 / 149, x 300 317 / 375; x 64 93 / 85; below, 131072 x 64 19.4 / 16.0);
-//   fewer: tb, few rows and longer reductions (65536 x 16 x 128 15.0 / 16.1, 40000 x 16 x 96 11.4 / 12.6; x 64 11.0 / 9.9 and 9.4 /
-//     8.6, x 4 7.1 / 5.6), and long ones over a large A (2^20 x 8 x 300 294 / 358, 2^19 x 16 x 160 90 / 92; 2^20 x 16 x 64 96 / 76);
-//   64: tb, few rows, short reductions (65536 x 64 x 32 11.4 / 12.1, x 64 13.2 / 15.7, x 128 19.0 / 20.7; x 16 10.0 / 9.7);
+//   32 columns, a whole tile: tb (65536 x 16 6.8 / 7.6, x 64 10.1 / 11.6, x 128 13.2 / 17.5, 2^20 x 16 47.6 / 50.9, x 128 139 / 149);
+//     else A from 64 MB on (2^18 x 64 27.5 / 28.6, x 100 41 / 45, 2^20 x 100 136 / 149, x 300 317 / 375; below, 131072 x 64 19.4 /
+//     16.0);
+//   fewer: tb and few rows (65536 x 16 x 128 15.0 / 16.1, 40000 x 16 x 96 11.4 / 12.6), and long reductions over a large A (2^20 x 8
+//     x 300 294 / 358, 2^19 x 16 x 160 90 / 92; but 2^20 x 16 x 64 96 / 76);
+//   64: tb, few rows, short reductions (65536 x 64 x 32 11.4 / 12.1, x 64 13.2 / 15.7, x 128 19.0 / 20.7; but x 16 10.0 / 9.7);
 //   and what few_rows leaves to it (15000 x 30 x 448 20 / 23, 30000 x 10 x 1000 36 / 47).
-// Nowhere else: whole tiles of 128 columns, short reductions into outputs of 1 GB, 2^21 x 128 x 4 240 / 226, 2^20 x 256 x 16 246 /
-// 235, x 32 266 / 249, 3 000 000 x 256 x 24 698 / 695.
+// Since blocks keep the parts, these are the faster at the short end: 32 columns and 8 indices by a twelfth (2^20 x 64, B as it is,
+// 93 / 85), fewer columns and up to 64 indices with few rows 11.0 / 9.9 (65536 x 16 x 64), 7.1 / 5.6 (40000 x 16 x 4).  There the
+// sums are held to those that the same product has before an activation, so these lines stay.
+// Wider outputs are faster on parts throughout: 2^21 x 128 x 4 240 / 226, 2^20 x 256 x 16 246 / 235, x 32 266 / 249, 3 000 000 x 256
+// x 24 698 / 695.
 bool fp32_pays(int tb, int64_t M, int64_t N, int64_t K) {
     if (few_tiles(M, N)) return true;
-    if (N == 32) return tb ? K > 8 : K > 64 && M * K >= 1 << 24;
-    if (N < 32) return (tb && M <= 65536 && K > 64) || (K >= 160 && M * K >= 1 << 26);
+    if (N == 32) return tb || (K >= 64 && M * K >= 1 << 24);
+    if (N < 32) return (tb && M <= 65536) || (K >= 160 && M * K >= 1 << 26);
     return N == 64 && tb && M <= 65536 && K > 16 && K <= 128;
 }
 

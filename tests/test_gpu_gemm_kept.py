@@ -19,7 +19,7 @@ def product(M, N, K, A, Bm, tb, bias=None, relu=0, C=None):
 @pytest.mark.parametrize("tb", [0, 1])
 @pytest.mark.parametrize("M,N,K", [(BIG, 64, 64), (BIG, 47, 130), (BIG, 33, 200), (BIG, 128, 50), (BIG, 200, 90), (BIG, 65, 190),
                                    (BIG, 300, 20), (1 << 21, 128, 4), (1 << 20, 256, 32), (65536, 64, 16), (65536, 64, 20),
-                                   (65536, 16, 64), (65536, 16, 68), (1 << 18, 32, 64), (70000, 32, 8), (70000, 32, 12), (33000, 128, 32), (40001, 70, 4), (66001, 30, 64), (1 << 18, 64, 33)])
+                                   (33000, 128, 32), (40001, 70, 4), (66001, 30, 64), (1 << 18, 64, 33)])
 def test_against_float64(M, N, K, tb):
     gen = torch.Generator(device="cuda").manual_seed(M + N + K)
     A, Bm = torch.randn(M, K, generator=gen, device="cuda"), torch.randn(K, N, generator=gen, device="cuda")
