@@ -89,8 +89,9 @@ typedef enum {
  *   csr_erow   optional for GCN, required for GAT: row index of every stored entry (erow[e] = i for
  *              rowptr[i] <= e < rowptr[i+1]), as written by gnn_expand_ptr.  With it
  *              the sparse kernels split work by equal numbers of entries, which
- *              keeps hub rows from serialising; without it they fall back to one
- *              lane group per row (same results, slower on skewed graphs).
+ *              keeps hub rows from serialising (products of a few thousand rows go
+ *              by rows all the same); without it a row is the work of one or eight
+ *              wavefronts (sums in another order, slower on skewed graphs).
  *   csc_*      the same matrix by columns, i.e. the CSR arrays of its transpose:
  *              colptr[n+1], row[nnz] ascending inside a column, perm[nnz] mapping a
  *              CSC slot to the CSR slot of the same entry, val = csr_val[perm]
@@ -317,7 +318,8 @@ gnn_status_t gnn_gather_f32(int64_t count, const float *in, const int32_t *perm,
 
 /*
  * gnn_spmm_csr - C = A B (App. E.1).  B, C [n, f].  val NULL = all ones.
- *   erow: optional expanded row index (see gnn_graph_t); selects the entry-balanced kernel.
+ *   erow: optional expanded row index (see gnn_graph_t).  Products of more than a few thousand rows are then split by entries
+ *   instead of by rows; smaller ones go by rows with it or without.
  *   bias [f] or NULL, relu (0 or 1; anything else is GNN_ERR_INVALID_ARG): fused epilogue C = relu(A B + 1 b^T).
  *   workspace: gnn_spmm_workspace_bytes(n, nnz, f) bytes (only used with erow): partial rows of the
  *   blocks, when f is not a multiple of 4 a copy of B with rows padded to the next multiple of 4, and for

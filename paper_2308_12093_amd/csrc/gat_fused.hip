@@ -23,8 +23,8 @@
 //
 // alpha and the LeakyReLU sign come from the cache when the variant keeps them.  The row pass reads them in entry
 // order and leaves them as one signed value per entry and head, in the same order; the column pass gathers that
-// through perm, one line an entry instead of two (2^17 nodes, 8 heads of 8 features: row pass 74 -> 95 us, column pass
-// 145 -> 112; written in the column pass's own order, scattered, 67 -> 108 for 136 -> 107).
+// through perm, one line an entry instead of two (2^17 nodes, 1.8 M entries, 8 heads of 8 features: row pass 71 -> 88
+// us, column pass 136 -> 105; written in the column pass's own order, scattered, 67 -> 108 for 136 -> 107).
 // Otherwise they are rebuilt per entry from per-node values: s_i, d_j and the row statistics - the same
 // arithmetic on the same bits in every pass, so all passes see the same logit and take the same LeakyReLU
 // decision.  (Forming d_j = <a_dst, m_j> from the feature row that a lane has loaded anyway, instead of

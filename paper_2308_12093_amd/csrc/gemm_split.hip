@@ -154,10 +154,10 @@ __host__ __device__ constexpr int kept_waves(int nt) { return nt == 1 ? 16 : 12;
 // shared by the block: copied to LDS without touching registers, 6 NT KB per step, double-buffered, one barrier per
 // step.  Three to four wavefronts fit a SIMD: loads, splitting, matrix instructions and stores of a block hardly overlap,
 // those of different blocks do (64 rows a wavefront, two of them a SIMD: the same within 5 %, 24 % slower at 65536 rows
-// and 64 columns).  At 2^17 rows, against the fp32 instruction, B transposed (K -> N): 128 -> 512 165 -> 148 us,
-// 512 -> 128 142 -> 133, 256 -> 256 150 -> 115, 128 -> 128 48 -> 43, 256 -> 64 43 -> 39 (4.3 TB/s); at 2^20 rows
-// 100 -> 256 662 -> 543, 47 -> 256 571 -> 318, 256 -> 47 378 -> 296; at 2^22 64 -> 256 1460 -> 1420, 256 -> 64 1308 ->
-// 1162 (4.6 TB/s: what a copy reaches).  Matrix cores busy 27 % (512 -> 128, 128 -> 128) and 34 % (128 -> 512): matrix
+// and 64 columns).  Against the fp32 instruction, B transposed (K -> N), other buffers each time, us: 2^17 rows 128 -> 512 187
+// -> 146, 512 -> 128 157 -> 135, 256 -> 256 167 -> 127, 128 -> 128 51 -> 48, 256 -> 64 48 -> 51 (into buffers that the caches hold
+// 47 -> 42); 2^20 100 -> 256 732 -> 521, 47 -> 256 335 -> 328, 256 -> 47 417 -> 292; 2^22 64 -> 256 1552 -> 1341, 256 -> 64 1397 ->
+// 1123 (4.8 TB/s: what a copy reaches).  Matrix cores busy 30 % (512 -> 128, 128 -> 128) and 36 % (128 -> 512): matrix
 // instructions, stores and loads add up more than they overlap; without the stores 128 -> 512 took 115 of then 167 us,
 // with a sixth of the matrix instructions 117.
 // The columns of a row are stored one after the other: a row's lines reach memory together (column tile by column tile
